@@ -14,6 +14,19 @@ constexpr int TM = 64;    // d rows per workgroup
 constexpr int TN = 128;   // (g,e) columns per workgroup
 constexpr int TK = 32;    // contraction rows per LDS round
 
+// Workgroup i runs on XCD i % 8.  The (head, K slice, output tile) triples, tiles fastest, are dealt out in eight equal runs, one
+// per XCD: the tiles of one (head, K slice) share their operand rows and mostly re-read them from one L2, and the XCDs are
+// loaded alike however few (head, K slice) pairs there are.  (Whole pairs per XCD, as it was, left seven XCDs idle for one head
+// without K slices: 1 x 2048, 4096 rows, 1363 us.)
+__device__ __forceinline__ bool tile_of_block(int tiles, int combos, int& combo, int& tile) {
+    const int total = tiles * combos, per_xcd = (total + 7) / 8;
+    const int slot = blockIdx.x >> 3, id = (blockIdx.x & 7) * per_xcd + slot;
+    if (slot >= per_xcd || id >= total) return false;
+    combo = id / tiles;
+    tile = id % tiles;
+    return true;
+}
+
 // LDS tiles hold the operands transposed: [row or column][k], bf16 pairs packed along k (BF16) or floats.
 template <bool BF16>
 __global__ __launch_bounds__(256) void dr_gemm_kernel(const float* __restrict__ states, const void* __restrict__ dWx,
@@ -25,11 +38,8 @@ __global__ __launch_bounds__(256) void dr_gemm_kernel(const float* __restrict__ 
     __shared__ __align__(16) char ldsB[TN * PITCH * ESZ];
     const int GD = G * D;
     const int tiles_n = (GD + TN - 1) / TN, tiles_m = (D + TM - 1) / TM;
-    // Workgroup i runs on XCD i % 8.  All tiles of one (head, K slice) share their operand rows, so they
-    // get block indices that are equal modulo 8 and re-read those rows from one L2.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, tiles = tiles_n * tiles_m;
-    const int combo = (slot / tiles) * 8 + xcd, tile = slot % tiles;
-    if (combo >= SK * NH) return;
+    int combo, tile;   // (head, K slice) and output tile of this workgroup
+    if (!tile_of_block(tiles_n * tiles_m, SK * NH, combo, tile)) return;
     const int tn = tile % tiles_n, tm = tile / tiles_n;
     const int sk = combo % SK;
     const int n = combo / SK;
@@ -199,11 +209,8 @@ __global__ __launch_bounds__(WM * WN * 64) void dr_gemm_tr_kernel(const float* _
     __shared__ __align__(16) uint16_t ldsB[2][TK * PB];
     const int GD = G * D;
     const int tiles_n = (GD + TNW - 1) / TNW, tiles_m = (D + TMW - 1) / TMW;
-    // Workgroup i runs on XCD i % 8.  All tiles of one (head, K slice) share their operand rows, so they get block indices
-    // that are equal modulo 8 and re-read those rows from one L2.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, tiles = tiles_n * tiles_m;
-    const int combo = (slot / tiles) * 8 + xcd, tile = slot % tiles;
-    if (combo >= SK * NH) return;
+    int combo, tile;   // (head, K slice) and output tile of this workgroup
+    if (!tile_of_block(tiles_n * tiles_m, SK * NH, combo, tile)) return;
     const int tn = tile % tiles_n, tm = tile / tiles_n;
     const int sk = combo % SK, n = combo / SK;
     const int K = T * B;
@@ -477,7 +484,19 @@ int dr_split_k(bool bf16, int T, int B, int NH, int D, int G) {
     const int K = T * B;
     int sk = 1;
     const DrTile t = dr_tile(bf16, NH, D, G);
-    const int tiles = dr_tiles(t, NH, D, G), want = t == kDrSquare ? 256 : 512;   // (the square tile's workgroups fill a CU each)
+    const int tiles = dr_tiles(t, NH, D, G), want = 512;
+    if (t == kDrSquare) {
+        // The square tile's workgroups fill a CU each: the number of slices with the fewest rounds of 32 contraction rows over the
+        // 256 CUs (1.2 us a round), counting what writing and adding the partial results costs.  (Powers of two only, as it was,
+        // gave 1 x 768 eight slices of 36 tiles, 288 workgroups: a second wave of 32.)
+        double best = 0.0;
+        for (int k = 1; k <= 64 && (k == 1 || K / k >= 4 * TK); ++k) {
+            const double rounds = (double)((tiles * k + 255) / 256) * ((K / k + TK - 1) / TK + 8);
+            const double cost = 1.2 * rounds + (k > 1 ? (double)k * NH * D * G * D * 8 / 4e6 : 0.0);
+            if (k == 1 || cost < best) { best = cost; sk = k; }
+        }
+        return sk;
+    }
     while (tiles * sk < want && K / (sk * 2) >= 4 * TK && sk < 64) sk *= 2;
     return sk;
 }
@@ -490,7 +509,7 @@ hipError_t launch_dr_gemm(bool bf16, const float* states, const void* dWx, const
     const int GD = G * D;
     float* target = SK == 1 ? dR : part;
     const DrTile t = dr_tile(bf16, NH, D, G);
-    const int grid = (NH * SK + 7) / 8 * 8 * (dr_tiles(t, NH, D, G) / NH);   // (head, K slice) padded to the 8 XCDs
+    const int grid = (dr_tiles(t, NH, D, G) * SK + 7) / 8 * 8;
     if (db_from_gemm && (!bf16 || t == kDrSquare)) return hipErrorInvalidValue;
     if (t == kDrSquare)
         hipLaunchKernelGGL((dr_gemm_tr_kernel<4, 8, 4, 2, false, 1>), dim3(grid), dim3(512), 0, stream, states, dWx, dgn, target, db_part, T, B, NH, D, G, S, SK, gru ? 1 : 0);

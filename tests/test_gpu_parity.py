@@ -490,3 +490,11 @@ def test_forward_backward_replay_from_a_hip_graph(D):
         api.flashrnn_check(desc, ws)
         for a, r in zip(eager, replayed):
             assert torch.equal(a, r), f"replay {rep} differs from the eager result"
+
+
+@pytest.mark.parametrize("cell,NH,D,T,B", [(CELL_LSTM, 1, 768, 21, 16), (CELL_GRU, 1, 1024, 40, 16), (CELL_ELMAN, 1, 2048, 9, 15), (CELL_LSTM, 3, 272, 9, 15)])
+def test_weight_gradient_gemm_with_few_heads(cell, NH, D, T, B):
+    """Fewer (head, contraction slice) pairs than XCDs, a number of slices that is no power of two, and a last slice that is
+    shorter than the others: the output tiles are dealt out over the XCDs in equal runs."""
+    w = Workload(f"fewheads_{cell}_NH{NH}_D{D}", cell, T, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + T)
+    _check(w, with_dlast=True)
