@@ -124,7 +124,6 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
     const int force_nwu = env_int("FLASHRNN_NWU", 0);
     const int force_ks = env_int("FLASHRNN_KS", 0);
     const int force_gpar = env_int("FLASHRNN_GPAR", 0);
-    const int force_ebk = env_int("FLASHRNN_EBK", 0);        // contraction slices of the backward tile kernel
     const int force_kind = env_int("FLASHRNN_KIND", -1);     // kernel family (KernelEntry::tile)
     const int force_eb = env_int("FLASHRNN_EB", 0);          // blocks of 16 units per wave (one workgroup per group)      // groups in flight when groups are split (testing the group loop)
     Plan pl;
@@ -150,11 +149,10 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             const KernelEntry& e = tab.entries[i];
             if (e.bwd != bwd || e.multi || e.KS != 1) continue;
             if (force_bt && e.BT != force_bt) continue;
-            if (e.KT * kstep < kdim || units16 % e.eb != 0 || e.maxw * (e.tile == 1 ? 1 : e.eb) < units16) continue;
+            if (e.KT * kstep < kdim || units16 % e.eb != 0 || e.maxw * e.eb < units16) continue;
             if (force_eb ? e.eb != force_eb : false) continue;
             if (force_kind >= 0 && e.tile != force_kind) continue;
-            if (force_ebk && bwd && e.tile == 1 && e.eb != force_ebk) continue;
-            const int dk = e.KT * kstep, nw = e.tile == 1 ? units16 : units16 / e.eb;
+            const int dk = e.KT * kstep, nw = units16 / e.eb;
             const bool exact_only = e.exact == 1 || e.exact == 2;
             if (exact_only && dk != kdim) continue;
             if (e.exact >= 2 && !deep) continue;
@@ -167,7 +165,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             size_t smem = (size_t)2 * e.BT * (dk + (bf ? 8 : 4)) * (bf ? 2 : 4);
             if (e.tile == 1 && bwd) {
                 const int nsb = d->cell == FLASHRNN_SLSTM ? 2 : d->cell == FLASHRNN_ELMAN ? 0 : 1, go = d->cell == FLASHRNN_GRU ? G + 1 : G;
-                smem = tile_lds_bwd(e.BT, go, nsb, d->D, dk * 2, e.eb, record_slots(d->cell) * 2).total;
+                smem = tile_lds_bwd(e.BT, go, nsb, d->D, dk * 2, record_slots(d->cell) * 2).total;
             } else if (e.tile == 1) {
                 smem = tile_lds(e.BT, G, num_states(d->cell), d->D, 64 * nw, dk * 2).total_fwd;
             }
@@ -184,9 +182,6 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             // sLSTM's forward step, whose point-wise function is the longest, 2.7)
             const double rel8 = bwd ? 1.3 : (d->cell == FLASHRNN_SLSTM ? 2.7 : (mode == 2 ? 1.25 : 1.65));
             double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? 1.8 : e.BT == 8 ? 3.0 : 6.0);
-            // the backward tile kernel splits the contraction over its waves only when the operand reads are
-            // many (k-steps x waves); otherwise the second barrier costs more than it saves
-            if (e.tile == 1 && bwd && ((e.eb > 1) != (e.KT * units16 >= 256))) rel *= 1.05;
             if (e.tile == 0) rel *= 1.0 + 0.05 * (e.eb - 1);       // thin waves overlap better
             rel *= 1.0 + 0.02 * (dk - kdim) / (double)kstep;       // padded k-steps are wasted MFMAs
             if (exact_only) rel *= 0.99;                           // compile-time LDS layout: fewer address instructions
@@ -196,7 +191,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
         }
         if (best) {
             pl.e = best;
-            pl.NWU = best->tile == 1 ? units16 : units16 / best->eb;   // the tile kernels run one wave per block of 16 units
+            pl.NWU = units16 / best->eb;
             pl.P = 1;
             pl.NG = d->NH * ((d->B + best->BT - 1) / best->BT);
             pl.GPAR = pl.NG;

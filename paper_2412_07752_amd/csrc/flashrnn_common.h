@@ -84,21 +84,17 @@ __host__ __device__ inline TileLds tile_lds(int BT, int G, int S, int D, int NT,
 struct TileLdsBwd {
     uint32_t hp;                 // operand (gate-gradient) row pitch, buf = BT * hp, two buffers
     uint32_t rp_io;              // row pitch of the output image (bf16 rows)
-    uint32_t red_off;            // partial sums of the contraction slices
     uint32_t in_off, in_pitch;   // two input images: records | state rows | dh rows
     uint32_t st_off, dh_off;     // ... offsets of the state rows and the dh rows inside an input image
     uint32_t out_off, out_pitch; // two output images: BT * GO bf16 rows
     uint32_t total;
 };
 __host__ __device__ inline uint32_t round_up(uint32_t a, uint32_t b) { return (a + b - 1) / b * b; }
-__host__ __device__ inline TileLdsBwd tile_lds_bwd(int BT, int GO, int NSB, int D, int k_bytes, int EBK, int rec_bytes) {
+__host__ __device__ inline TileLdsBwd tile_lds_bwd(int BT, int GO, int NSB, int D, int k_bytes, int rec_bytes) {
     TileLdsBwd L;
-    const uint32_t NT = 4u * (uint32_t)D, PP = (uint32_t)BT / 4u;
     L.hp = lds_row_pitch((uint32_t)k_bytes);
     L.rp_io = lds_row_pitch((uint32_t)D * 2);
-    L.red_off = 2u * BT * L.hp;
-    const uint32_t red_bytes = EBK > 1 ? (NT / 64u) * EBK * 64u * PP * 4u : 0u;
-    L.in_off = L.red_off + red_bytes;
+    L.in_off = 2u * BT * L.hp;
     L.st_off = round_up((uint32_t)BT * D * (uint32_t)rec_bytes, 1024u);
     L.dh_off = L.st_off + round_up((uint32_t)BT * NSB * D * 4u, 1024u);
     L.in_pitch = L.dh_off + round_up((uint32_t)BT * D * 2u, 1024u);
@@ -419,6 +415,52 @@ template <> struct Operand<false> {
     }
 };
 
+// The recurrent product of small batch tiles (bf16, 4 or 8 rows) on the 4:2-sparse matrix instruction.
+// A dense [16 x 32] tile product spends three quarters (half) of its 16 batch columns on nothing.  v_smfmac_f32_16x16x64_bf16
+// takes the same 16 clocks (measured: 16.6 per instruction and SIMD, both) for a contraction of 64: its first operand holds, per
+// row and group of four contraction indices, two values and their positions.  Here that operand is h_{t-1} (or dg_t), two rows
+// per batch slot: the even row carries positions 0 and 1 of every group, the odd row positions 2 and 3.  Their results add up to the
+// full, exact product over 64 indices -- nothing is dropped, every product is formed once -- in half the instructions, and
+// a batch tile of 8 rows fills all 16 rows of the operand.  R is the dense second operand, 16 units wide.
+//   operand row i = 4 qq + 2 j + hf: batch slot qq + 4 j, half hf (BT = 4: j = 0 only, the rows of j = 1 repeat it)
+//   result: lane (c, quad) holds unit c; registers 0 + 1 add up to slot quad, 2 + 3 to slot quad + 4 (BT = 8 only)
+// so that every lane has its (unit, slot) pairs without moving anything between lanes.  The instruction adds to its result
+// in place: the registers start from what is to be added anyway (inputs, bias).
+// Contraction order: a lane of the first operand (row i, quad q) reads eight consecutive elements 16 q + 8 hf .. + 7 of its
+// slot's row; the dense operand is laid out to match (sparse_k).
+typedef __attribute__((__vector_size__(16 * sizeof(__bf16)))) __bf16 bf16x16;
+typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
+template <int BT> struct SparseLane {
+    static constexpr int PP = BT / 4;   // (unit, batch slot) pairs per lane: slots quad + 4 i of unit c
+    int c, quad, rslot, idx;
+    uint32_t rbyte;                     // byte offset of this lane's elements inside 64 contraction elements of its slot's row
+    __device__ __forceinline__ SparseLane(int lane) {
+        c = lane & 15;
+        quad = lane >> 4;
+        const int hf = c & 1;
+        rslot = (c >> 2) + (BT == 8 ? 4 * ((c >> 1) & 1) : 0);
+        idx = hf ? 0xEEEE : 0x4444;
+        rbyte = (uint32_t)(quad * 32 + hf * 16);
+    }
+    __device__ __forceinline__ int slot(int i) const { return quad + 4 * i; }
+    // the same where only 32 contraction elements are left: the quads of the other half re-read these (times weights of zero)
+    __device__ __forceinline__ uint32_t rbyte_half() const { return (uint32_t)((quad & 1) * 32 + (c & 1) * 16); }
+};
+// First contraction index of the four that make up the low half of 8-element piece m = quad (of 32 indices) of the dense operand; the
+// high half starts 8 further on; element order {lo0 lo1 hi0 hi1 lo2 lo3 hi2 hi3}.
+__device__ __forceinline__ int sparse_k(int quad) { return 16 * (quad >> 1) + 4 * (quad & 1); }
+__device__ __forceinline__ i32x4 sparse_piece(i32x2 lo, i32x2 hi) { return i32x4{lo[0], hi[0], lo[1], hi[1]}; }
+__device__ __forceinline__ bf16x16 sparse_dense(i32x4 a, i32x4 b) {
+    return __builtin_bit_cast(bf16x16, i32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]});
+}
+__device__ __forceinline__ f32x4 smfmac(bf16x8 a, bf16x16 b, f32x4 c, int idx) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, c, idx, 0, 0);
+#else
+    (void)a; (void)b; (void)idx;
+    return c;
+#endif
+}
 // Contraction index held by (k-step kt, lane quad q, element j) of a wave whose slice starts at k0.
 // The assignment is free as long as both MFMA operands use the same one; this one makes the KPL*KT
 // elements of a lane... (bf16) 8 consecutive per k-step, (f32) KT consecutive per lane.

@@ -23,18 +23,18 @@ namespace flashrnn {
 // small batch tiles (bf16, one workgroup per group): forward from the dedicated tile kernel
 #define FRNN_FT(KT, BT, MAXW) \
     {FRNN_CELL, FRNN_BF16, 0, KT, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&fwd_tile_kernel<FRNN_CELL, KT, BT, MAXW>},
-// ... backward with the contraction split over EBK waves per set of EBK unit blocks; one kernel for heads of exactly
-// KT * 32 units (compile-time LDS layout) and one for the sizes below (two kernels, not two paths in one: the backward
-// kernel sits at the register limit of its launch bound, and a spill in either path would disqualify both)
-#define FRNN_BTL(KT, EBK, BT, MAXW) \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, EBK, 1, 1, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G / (EBK), EBK, BT, MAXW, true>}, \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, EBK, 1, 0, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G / (EBK), EBK, BT, MAXW, false>},
+// ... backward: one kernel for heads of exactly KT * 32 units (compile-time LDS layout) and one for the sizes below (two
+// kernels, not two paths in one: the backward kernel sits near the register limit of its launch bound, and a spill in either
+// path would disqualify both)
+#define FRNN_BTL(KT, BT, MAXW) \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 1, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true>}, \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false>},
 // ... and, for heads of up to 128 units, two more that request their inputs six steps ahead through registers
 // (taken when they will come from HBM; KernelEntry::exact = 2: heads of exactly 32, 64 or 128 units, 3: the sizes below)
-#define FRNN_BTLD(KT, EBK, BT, MAXW) \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, EBK, 1, 2, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G / (EBK), EBK, BT, MAXW, true, true>}, \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, EBK, 1, 3, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G / (EBK), EBK, BT, MAXW, false, true>},
-#define FRNN_TILE(KT, EBK, BT, MAXW) FRNN_FT(KT, BT, MAXW) FRNN_B(KT, 1, BT, 0, MAXW, 1) FRNN_BTL(KT, EBK, BT, MAXW)
+#define FRNN_BTLD(KT, BT, MAXW) \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 2, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true, true>}, \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 3, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false, true>},
+#define FRNN_TILE(KT, BT, MAXW) FRNN_FT(KT, BT, MAXW) FRNN_B(KT, 1, BT, 0, MAXW, 1) FRNN_BTL(KT, BT, MAXW)
 // the largest heads: one block of 16 units per workgroup, 4 contraction slices, one wave per SIMD
 #define FRNN_FL(KT, BT) FRNN_F(KT, 4, BT, 1, 4, 1)
 #define FRNN_BL(KT, BT) FRNN_B(KT, 4, BT, 1, 4, 1)
@@ -43,10 +43,10 @@ namespace flashrnn {
 
 static const KernelEntry kEntries[] = {
 #if FRNN_BF16
-    FRNN_FB(1, 1, 16, 0, 4) FRNN_TILE(1, 1, 8, 4) FRNN_TILE(1, 1, 4, 4) FRNN_BTLD(1, 1, 8, 4) FRNN_BTLD(1, 1, 4, 4)
-    FRNN_FB(2, 1, 16, 0, 4) FRNN_TILE(2, 2, 8, 4) FRNN_TILE(2, 2, 4, 4) FRNN_BTL(2, 1, 8, 4) FRNN_BTL(2, 1, 4, 4) FRNN_BTLD(2, 1, 8, 4) FRNN_BTLD(2, 1, 4, 4)
-    FRNN_FB(4, 1, 16, 0, 8) FRNN_TILE(4, 2, 8, 8) FRNN_TILE(4, 2, 4, 8) FRNN_BTL(4, 1, 8, 8) FRNN_BTL(4, 1, 4, 8) FRNN_BTL(4, 4, 8, 8) FRNN_BTL(4, 4, 4, 8) FRNN_BTLD(4, 1, 8, 8) FRNN_BTLD(4, 1, 4, 8)
-    FRNN_FB(6, 1, 16, 0, 12) FRNN_TILE(6, 3, 8, 12) FRNN_TILE(6, 3, 4, 12) FRNN_BTL(6, 1, 8, 12) FRNN_BTL(6, 1, 4, 12)
+    FRNN_FB(1, 1, 16, 0, 4) FRNN_TILE(1, 8, 4) FRNN_TILE(1, 4, 4) FRNN_BTLD(1, 8, 4) FRNN_BTLD(1, 4, 4)
+    FRNN_FB(2, 1, 16, 0, 4) FRNN_TILE(2, 8, 4) FRNN_TILE(2, 4, 4) FRNN_BTLD(2, 8, 4) FRNN_BTLD(2, 4, 4)
+    FRNN_FB(4, 1, 16, 0, 8) FRNN_TILE(4, 8, 8) FRNN_TILE(4, 4, 8) FRNN_BTLD(4, 8, 8) FRNN_BTLD(4, 4, 8)
+    FRNN_FB(6, 1, 16, 0, 12) FRNN_TILE(6, 8, 12) FRNN_TILE(6, 4, 12)
     FRNN_FBE(4, 16, 4, 2) FRNN_FBE(4, 8, 4, 2) FRNN_FBE(4, 4, 4, 2)
     FRNN_FBE(6, 16, 4, 3) FRNN_FBE(6, 8, 4, 3) FRNN_FBE(6, 4, 4, 3)
 #define FRNN_MULTI_SHAPES(BT) \

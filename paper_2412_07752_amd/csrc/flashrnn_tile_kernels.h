@@ -1,8 +1,12 @@
 // Persistent kernels for the case that carries the headline workload: bf16 I/O, one workgroup per
 // group, batch tiles of 4 or 8 rows (BT < 16), one block of 16 units per wave.
 //
-// The matrix pipe of each SIMD is busy for about 1150 cycles per step here (three waves share it), the
-// point-wise function of a wave takes a few hundred.  Everything that is not on the dependency chain
+// The recurrent products run on the sparse matrix instruction (SparseLane): half the instructions and half the operand reads of
+// dense ones, and every lane ends up with its (unit, slot) pairs in place.  At 4 x 192 the matrix pipe of a SIMD, shared by
+// three waves, is then busy for 580 of 1450 clocks per step (sLSTM, 16 rows: forward 0.91 -> 0.67 us per step, backward
+// 1.01 -> 0.76; LSTM 12 x 64 forward 0.32 -> 0.25, backward 0.42 -> 0.355), and the issue of vector instructions bounds the step: 46
+// of them plus 10 transcendental ones (16 clocks each) per wave, 1100 clocks per SIMD.
+// Everything that is not on the dependency chain
 //     h_{t-1} in LDS -> MFMA chain -> point-wise -> h_t in LDS -> barrier
 // is issued between the MFMAs of a wave's chain:
 //   - global traffic goes through LDS images and moves as one 16-byte chunk per thread (a lane holds
@@ -32,11 +36,10 @@ __device__ __forceinline__ void pin_order() { __builtin_amdgcn_sched_barrier(0);
 template <int CELL, int KT, int BT, int MAXW, bool EXACT>
 __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     using CT = CellTraits<CELL>;
-    using OP = Operand<true>;
     constexpr int G = CT::G, S = CT::S, NC = CT::NC;
     constexpr int PP = BT / 4;
     constexpr int ESZ = 2;
-    constexpr int DK = KT * 32;
+    constexpr int DK = KT * 32, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64 (KT odd: the last one holds 32)
     constexpr int NCH_IN = (BT * G + 31) / 32, NCH_ST = (BT * S + 15) / 16;
     constexpr uint32_t kDrop = 0x80000000u;
     constexpr uint32_t REC = CT::RS * ESZ;
@@ -48,10 +51,10 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     const int D = EXACT ? DK : p.D;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, tid = threadIdx.x, NT = 4 * D;   // one wave per block of 16 units
     stagger_waves(w);
-    const LaneMap<BT> lm(lane);
+    const SparseLane<BT> lm(lane);
     const int T = p.T, B = p.B, NH = p.NH;
     const int n = gid % NH, q = gid / NH;
-    const int e_wave = w * 16, e0 = e_wave + lm.uoff;
+    const int e_wave = w * 16, e0 = e_wave + lm.c;   // this lane's unit
 
     const uint32_t HD = (uint32_t)NH * D;
     const size_t wx_step = (size_t)B * G * HD * ESZ, st_step = (size_t)S * B * HD * 4, c_step = (size_t)B * HD * REC;
@@ -65,23 +68,22 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
 
     // ---- R fragments and bias: resident for all T steps.  p.R is the caller's R[n][k][g][e] (no packed copy: a packing
     // kernel in front of this one costs its own run time plus a launch gap, together a few percent of a short sequence).
-    // The MFMA A operand of lane (c, quad) is R[k = kt*32 + quad*8 .. +7][g][e_wave + c]: eight values a row pitch apart in
-    // memory.  Each wave moves its [32 k] x [16 units] tile of a (gate, k-step) pair to LDS as it lies (two 16-byte
-    // pieces per row) and reads it back with the transposing LDS load, which hands every lane four consecutive rows of
-    // its column.  The error words of the call are cleared here as well (the kernels of this file never wait on another
+    // The dense operand of lane (c, quad) holds column e_wave + c of R[k][g][.], eight values of each 32 rows of k in the order
+    // of sparse_k, a row pitch apart in memory.  Each wave moves its [32 k] x [16 units] tile of a (gate, 32 rows) pair to LDS
+    // as it lies (two 16-byte pieces per row) and reads it back with the transposing LDS load, which hands every lane four
+    // consecutive rows of its column.  The error words of the call are cleared here as well (the kernels of this file never wait on another
     // workgroup, they never set them).
-    bf16x8 Rf[G][KT];
-    float bias[G][PP];
+    bf16x16 Rf[G][NK];
+    float bias[G];
     if (gid == 0 && tid == 0) { p.err[0] = 0; p.err[1] = 0; }
     {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         char* tile = smem + (uint32_t)w * 1024;                       // this wave's [32][16] bf16 tile
         const int row = lane >> 1, half = lane & 1;
         const char* src = (const char*)p.R + ((((size_t)n * D + row) * G) * D + e_wave + half * 8) * ESZ;
         const uint32_t wr = (uint32_t)row * 32 + half * 16;
-        const uint32_t rd = (uint32_t)(lm.quad * 8 + (lm.c >> 2)) * 32 + (lm.c & 3) * 8;
+        const uint32_t rd = (uint32_t)(sparse_k(lm.quad) + (lm.c >> 2)) * 32 + (lm.c & 3) * 8;
         i32x4 raw[G][KT];   // all loads in flight at once; a fragment takes the registers of the rows it was made from
 #pragma unroll
         for (int g = 0; g < G; ++g)
@@ -92,6 +94,8 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
             }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
+            i32x4 piece[2 * NK];
+            if constexpr (KT & 1) piece[KT] = i32x4{0, 0, 0, 0};
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
                 // (a wave's LDS operations run in the order it issues them and the tile is its own: no barrier, only the compiler is held)
@@ -99,21 +103,29 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
                 *(i32x4*)(tile + wr) = raw[g][kt];
                 asm volatile("" ::: "memory");
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rd));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rd + 4 * 32));
-                Rf[g][kt] = __builtin_bit_cast(bf16x8, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rd + 8 * 32));
+                piece[kt] = sparse_piece(__builtin_bit_cast(i32x2, lo), __builtin_bit_cast(i32x2, hi));
             }
-            load_io<true, PP>(p.bias, ((size_t)n * G + g) * D + e0, bias[g]);
+#pragma unroll
+            for (int kc = 0; kc < NK; ++kc) Rf[g][kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
+            float bv[1];
+            load_io<true, 1>(p.bias, ((size_t)n * G + g) * D + e0, bv);
+            bias[g] = bv[0];
         }
         __syncthreads();   // the tiles lie where the operand rows and images are set up next
     }
 
-    const int bb_raw = q * BT + lm.bslot;
-    const bool row_valid = bb_raw < B;
-    const int bb = row_valid ? bb_raw : B - 1;
     const char* wx_g = (const char*)p.Wx + (size_t)n * D * ESZ;
     char* st_g = (char*)p.states + (size_t)n * D * 4;
     char* c_g = (char*)p.cache + (size_t)n * D * REC;
-    const uint32_t voff_st = ((uint32_t)bb * HD + e0) * 4;
+    uint32_t voff_st[PP];   // this lane's pairs: batch rows q * BT + slot(i)
+    bool row_valid[PP];
+#pragma unroll
+    for (int i = 0; i < PP; ++i) {
+        const int brow = q * BT + lm.slot(i);
+        row_valid[i] = brow < B;
+        voff_st[i] = ((uint32_t)(row_valid[i] ? brow : B - 1) * HD + e0) * 4;
+    }
 
     // ---- chunk roles: global byte offset (out of range = nothing to move) and LDS offset inside the image
     uint32_t cin_g[NCH_IN], cin_l[NCH_IN], cst_g[NCH_ST], cst_l[NCH_ST];
@@ -138,34 +150,54 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     }
     // this lane's places: inputs row = g*BT + slot, states row = s*BT + slot; the saved-values records (16 bytes per
     // lane, 256 contiguous bytes per batch row and wave) go to HBM straight from the lanes
-    const uint32_t l_in = (uint32_t)lm.bslot * L.rp_io + e0 * ESZ;
-    const uint32_t l_st = (uint32_t)lm.bslot * L.rp_st + e0 * 4;
-    const uint32_t voff_c = (row_valid && p.cache != nullptr) ? ((uint32_t)bb * HD + e0) * REC : kDrop;
-    const uint32_t lds_row = (uint32_t)lm.bslot * L.hp;
+    // (pair i: slot quad + 4 i, i.e. four rows further on)
+    const uint32_t l_in = (uint32_t)lm.quad * L.rp_io + e0 * ESZ;
+    const uint32_t l_st = (uint32_t)lm.quad * L.rp_st + e0 * 4;
+    const uint32_t l_h = (uint32_t)lm.quad * L.hp + e0 * ESZ;
+    uint32_t voff_c[PP];
+#pragma unroll
+    for (int i = 0; i < PP; ++i) voff_c[i] = (row_valid[i] && p.cache != nullptr) ? (voff_st[i] / 4) * REC : kDrop;
+    const uint32_t lds_rd = (uint32_t)lm.rslot * L.hp;   // the row this lane reads as the recurrent product's operand
+    auto write_h = [&](char* buf, const float (&h)[PP]) {
+#pragma unroll
+        for (int i = 0; i < PP; ++i) *(uint16_t*)(buf + l_h + (uint32_t)(4 * i) * L.hp) = (uint16_t)f32_to_bf16_bits(h[i]);
+    };
+    auto write_states = [&](char* img, const float (&v)[S][PP]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int i = 0; i < PP; ++i) *(float*)(img + l_st + (uint32_t)(s * BT + 4 * i) * L.rp_st) = v[s][i];
+    };
 
     constexpr bool kLongChain = KT >= 6;   // (see below: how far ahead the inputs are fetched)
     // ---- initial states: slot 0 is written directly (once)
     float st[S][PP];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (p.states0 != nullptr) load_io_r<false, PP>(make_rsrc((const char*)p.states0 + (size_t)n * D * 4), voff_st, s * st_state, st[s]);
-        else
+    for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int i = 0; i < PP; ++i) st[s][i] = 0.0f;
-        store_io_r<false, PP>(make_rsrc(st_g), row_valid ? voff_st : kDrop, s * st_state, st[s]);
-    }
+        for (int i = 0; i < PP; ++i) {
+            float v[1] = {0.0f};
+            if (p.states0 != nullptr) load_io_r<false, 1>(make_rsrc((const char*)p.states0 + (size_t)n * D * 4), voff_st[i], s * st_state, v);
+            store_io_r<false, 1>(make_rsrc(st_g), row_valid[i] ? voff_st[i] : kDrop, s * st_state, v);
+            st[s][i] = v[0];
+        }
     for (uint32_t j = tid; j < 2 * BUF / 4; j += NT) ((uint32_t*)hbuf)[j] = 0u;
     __syncthreads();
-    write_operand_lds<true, PP>(hbuf + lds_row, e0, st[0]);
+    write_h(hbuf, st[0]);
+    // (Wx_j waits in image j & 1, from where its values are read during step j - 1: they start the accumulators of step j)
     if (T > 0) {
-        const rsrc_t rs1 = make_rsrc(wx_g);
+        const rsrc_t rs1 = make_rsrc(wx_g), rs2 = make_rsrc(wx_g + (size_t)(T > 1 ? 1 : 0) * wx_step);
 #pragma unroll
-        for (int k2 = 0; k2 < NCH_IN; ++k2) *(i32x4*)(in_img + L.in_pitch + cin_l[k2]) = __builtin_amdgcn_raw_buffer_load_b128(rs1, cin_g[k2], 0, 0);
+        for (int k2 = 0; k2 < NCH_IN; ++k2) {
+            const i32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(rs1, cin_g[k2], 0, 0), v2 = __builtin_amdgcn_raw_buffer_load_b128(rs2, cin_g[k2], 0, 0);
+            *(i32x4*)(in_img + L.in_pitch + cin_l[k2]) = v1;
+            *(i32x4*)(in_img + cin_l[k2]) = v2;
+        }
     }
     __syncthreads();
     // With a short chain a step is shorter than the HBM latency under load (0.4 us against 1 us and more once most CUs
-    // stream): the inputs are fetched four steps ahead there, in four register sets of one chunk per thread (Wx_j travels
-    // in set j mod 4: requested at the top of step j - 4, parked in its image at the end of step j - 1), one step ahead with a
+    // stream): the inputs are fetched five steps ahead there, in four register sets of one chunk per thread (Wx_j travels
+    // in set j mod 4: requested at the top of step j - 5, parked in its image at the end of step j - 2), two to three steps ahead with a
     // long chain.  Requests beyond the last step fetch the last step's inputs again.
     i32x4 pre[4][NCH_IN];
     if constexpr (!kLongChain) {
@@ -175,7 +207,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
             for (int k2 = 0; k2 < NCH_IN; ++k2) pre[j][k2] = i32x4{0, 0, 0, 0};
         if (T > 0) {   // (with T = 0 there is no Wx to touch)
 #pragma unroll
-            for (int j = 2; j <= 4; ++j) {   // Wx_2, Wx_3, Wx_4: slots 1, 2, 3
+            for (int j = 3; j <= 5; ++j) {   // Wx_3, Wx_4, Wx_5: slots 2, 3, 4
                 const rsrc_t rsj = make_rsrc(wx_g + (size_t)(j - 1 < T ? j - 1 : T - 1) * wx_step);
 #pragma unroll
                 for (int k2 = 0; k2 < NCH_IN; ++k2) pre[j & 3][k2] = __builtin_amdgcn_raw_buffer_load_b128(rsj, cin_g[k2], 0, 0);
@@ -198,14 +230,14 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     };
     // The three streams of a step advance by whole time steps: their bases are carried as pointers (a product of the
     // step index and a 64-bit stride per stream and step is a dozen scalar instructions).
-    // Long chain: one register set, Wx_{t+2} requested at the tail of step t and parked a third into step t+1 -- or, with the
-    // step's parity a compile-time constant (EXACT), two sets that alternate: Wx_{t+3} requested at the tail of step t into the
-    // set that Wx_{t+1} has just left, parked a third into step t+2 (1.6 steps of lead instead of 0.6: with a hundred and more
+    // Long chain: one register set, Wx_{t+3} requested at the tail of step t and parked a third into step t+1 -- or, with the
+    // step's parity a compile-time constant (EXACT), two sets that alternate: Wx_{t+4} requested at the tail of step t into the
+    // set that Wx_{t+2} has just left, parked a third into step t+2 (1.6 steps of lead instead of 0.6: with a hundred and more
     // CUs streaming the latency of HBM exceeds a step).
     constexpr bool kTwoSets = kLongChain && EXACT;
-    constexpr int kFirstAhead = kLongChain ? (kTwoSets ? 3 : 2) : 4;   // slot of the first request made inside the time loop (slot 2 = Wx_3)
+    constexpr int kFirstAhead = kLongChain ? (kTwoSets ? 4 : 3) : 5;   // slot of the first request made inside the time loop (slot 2 = Wx_3)
     const char* wx_ptr = wx_g + (size_t)(kFirstAhead < T ? kFirstAhead : (T > 0 ? T - 1 : 0)) * wx_step;   // Wx of the step fetched next
-    // Long chain: Wx_{t+1} is requested at the end of step t-1, AHEAD of that step's stores in the wave's memory queue.  A
+    // Long chain: Wx is requested at the end of a step, AHEAD of that step's stores in the wave's memory queue.  A
     // wave's vector memory operations retire in order: a load issued behind the stores of the step before could not be
     // waited for without waiting for their acknowledgements as well, which tied the step to the write latency of the
     // memory system (sequences whose buffers outgrow the last-level cache ran 15 % slower per step, the LSTM 25 %).
@@ -218,19 +250,19 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
 #pragma unroll
         for (int k2 = 0; k2 < NCH_IN; ++k2) pre_next[k2] = pre[0][k2] = pre[1][k2] = i32x4{0, 0, 0, 0};
         if (T > 0) {
-            const rsrc_t rs2 = make_rsrc(wx_g + (size_t)(T > 1 ? 1 : 0) * wx_step);
-            if constexpr (kTwoSets) {   // Wx_2 travels in set 0, Wx_3 in set 1
-                const rsrc_t rs3 = make_rsrc(wx_g + (size_t)(T > 2 ? 2 : T - 1) * wx_step);
-#pragma unroll
-                for (int k2 = 0; k2 < NCH_IN; ++k2) pre[0][k2] = __builtin_amdgcn_raw_buffer_load_b128(rs2, cin_g[k2], 0, 0);
-                dropped_stores(rs2, 2 * PP + NCH_ST);
+            const rsrc_t rs3 = make_rsrc(wx_g + (size_t)(T > 2 ? 2 : T - 1) * wx_step);
+            if constexpr (kTwoSets) {   // Wx_3 travels in set 1, Wx_4 in set 0
+                const rsrc_t rs4 = make_rsrc(wx_g + (size_t)(T > 3 ? 3 : T - 1) * wx_step);
 #pragma unroll
                 for (int k2 = 0; k2 < NCH_IN; ++k2) pre[1][k2] = __builtin_amdgcn_raw_buffer_load_b128(rs3, cin_g[k2], 0, 0);
-                dropped_stores(rs3, 2 * PP);
+                dropped_stores(rs3, 2 * PP + NCH_ST);
+#pragma unroll
+                for (int k2 = 0; k2 < NCH_IN; ++k2) pre[0][k2] = __builtin_amdgcn_raw_buffer_load_b128(rs4, cin_g[k2], 0, 0);
+                dropped_stores(rs4, 2 * PP);
             } else {
 #pragma unroll
-                for (int k2 = 0; k2 < NCH_IN; ++k2) pre_next[k2] = __builtin_amdgcn_raw_buffer_load_b128(rs2, cin_g[k2], 0, 0);
-                dropped_stores(rs2, 2 * PP);
+                for (int k2 = 0; k2 < NCH_IN; ++k2) pre_next[k2] = __builtin_amdgcn_raw_buffer_load_b128(rs3, cin_g[k2], 0, 0);
+                dropped_stores(rs3, 2 * PP);
             }
         }
     }
@@ -256,6 +288,42 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
 #pragma unroll
         for (int k2 = 0; k2 < NCH_ST; ++k2) __builtin_amdgcn_raw_buffer_store_b128(vs[k2], rs_st, cst_g[k2] | none, 0, 0);
     };
+    // The sparse instruction adds to its result registers in place: they start from bias and input, set ahead of the barrier
+    // that ends the step before, where the wave waits for its LDS write anyway.  (The GRU's candidate input meets the recurrent
+    // term behind sig(r): it stays apart.)
+    f32x4 acc[G];
+    uint32_t wxb[G][PP];   // this lane's inputs of the next step (bf16 bits)
+    float wx_cand[PP];
+    auto read_inputs = [&](int parity) {
+        const char* im = in_img + parity * L.in_pitch + l_in;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < PP; ++i) wxb[g][i] = *(const uint16_t*)(im + (uint32_t)(g * BT + 4 * i) * L.rp_io);
+    };
+    auto start_acc = [&]() {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int i = 0; i < PP; ++i) {
+                const float x = bf16_bits_to_f32(wxb[g][i]);
+                if (CELL == CELL_GRU && g == 2) wx_cand[i] = x;
+                acc[g][2 * i] = bias[g];
+                acc[g][2 * i + 1] = (CELL == CELL_GRU && g == 2) ? 0.0f : x;
+            }
+            asm volatile("" : "+v"(acc[g]));
+        }
+    };
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};   // (4-row tiles: registers 2 and 3 are never used)
+    if (T > 0) read_inputs(1);
+    else
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < PP; ++i) wxb[g][i] = 0u;
+    start_acc();
+    __syncthreads();   // step 1 parks Wx_3 where Wx_1 has been read
     // (trace builds: clocks per wave between 0 the barrier and the top of a step | 2 the top and the issue of the chain's
     // last MFMA | 3 that and the barrier: compaction, point-wise function, LDS writes)
     FRNN_TRACE_BEGIN();
@@ -273,93 +341,79 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
         // (the sched barriers keep the compiler from bunching it all up in front).  With a long chain (KT >= 6) that
         // work sits between the k-steps; with a short one all LDS reads go out together at the top of the step (one
         // latency) and the next inputs are parked at its end, where they have had time to arrive (measured both ways).
-        bf16x8 hB[KT];
-        const char* hrow = hbuf + (par ^ 1) * BUF + lds_row;
+        bf16x8 hB[NK];
+        const char* hrow = hbuf + (par ^ 1) * BUF + lds_rd;
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) hB[kt] = *(const bf16x8*)(hrow + (size_t)(kt * 32 + lm.quad * 8) * 2);
+        for (int kc = 0; kc < NK; ++kc) hB[kc] = *(const bf16x8*)(hrow + kc * 128 + ((KT & 1) && kc == NK - 1 ? lm.rbyte_half() : lm.rbyte));
         i32x4 vs[NCH_ST];
-        float wx[G][PP];
         auto side_reads = [&]() {
-            const char* im = in_img + par * L.in_pitch + l_in;
-#pragma unroll
-            for (int g = 0; g < G; ++g) load_io<true, PP>(im + (uint32_t)g * BT * L.rp_io, 0, wx[g]);
+            read_inputs(par ^ 1);   // Wx_{t+1}
             if constexpr (kDefer) {
                 if constexpr (kDeferRec) {   // the saved values of step t-1 leave here as well: packing and storing them is off the tail too
                     const rsrc_t rs_prev = make_rsrc(c_ptr);
                     c_ptr += t >= 2 ? c_step : 0;
 #pragma unroll
-                    for (int i = 0; i < PP; ++i) store_record<true, CT::RS, NC>(rs_prev, (voff_c + i * REC) | (t < 2 ? kDrop : 0u), 0, cv_keep[i]);
+                    for (int i = 0; i < PP; ++i) store_record<true, CT::RS, NC>(rs_prev, voff_c[i] | (t < 2 ? kDrop : 0u), 0, cv_keep[i]);
                 }
-#pragma unroll
-                for (int s = 0; s < S; ++s) store_io<false, PP>(out_img + (par ^ 1) * OUT_PITCH + l_st + (uint32_t)s * BT * L.rp_st, 0, st[s]);   // states after step t-1
-                copy_out_load(par, vs);                                                                                                       // states after step t-2
+                write_states(out_img + (par ^ 1) * OUT_PITCH, st);   // states after step t-1
+                copy_out_load(par, vs);                              // states after step t-2
             } else {
                 copy_out_load(par ^ 1, vs);   // states after step t-1
             }
-#pragma unroll
-            for (int g = 0; g < G; ++g)     // the bias joins the inputs here, off the step's tail (GRU's candidate bias
-#pragma unroll                      // belongs to the recurrent term that sig(r) multiplies: it stays with y)
-                for (int i = 0; i < PP; ++i)
-                    if (!(CELL == CELL_GRU && g == 2)) wx[g][i] += bias[g][i];
         };
         if constexpr (!kLongChain) side_reads();
         if constexpr (!kLongChain) {
-            const int ahead = t + 3;   // slot of Wx_{t+4} (the last steps fetch the last slot again)
+            const int ahead = t + 4;   // slot of Wx_{t+5} (the last steps fetch the last slot again)
             const rsrc_t rsn = make_rsrc(wx_ptr);
             wx_ptr += ahead < T - 1 ? wx_step : 0;
 #pragma unroll
-            for (int k2 = 0; k2 < NCH_IN; ++k2) pre[PH][k2] = __builtin_amdgcn_raw_buffer_load_b128(rsn, cin_g[k2], 0, 0);
+            for (int k2 = 0; k2 < NCH_IN; ++k2) pre[(PH + 1) & 3][k2] = __builtin_amdgcn_raw_buffer_load_b128(rsn, cin_g[k2], 0, 0);
         }
         pin_order();
-        f32x4 acc[G];
+        auto product = [&](int kc) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[g][0], hB[0], f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int g = 0; g < G; ++g) acc[g] = smfmac(hB[kc], Rf[g][kc], acc[g], lm.idx);
+        };
+        product(0);
         pin_order();
         if constexpr (!kLongChain) {
             copy_out_store(kDefer ? t - 2 : t - 1, vs);
             pin_order();
-#pragma unroll
-            for (int kt = 1; kt < (KT < 3 ? KT : 3); ++kt)
-#pragma unroll
-                for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[g][kt], hB[kt], acc[g]);
         } else {
-#pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[g][1], hB[1], acc[g]);
-            pin_order();
             side_reads();
             pin_order();
-#pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[g][2], hB[2], acc[g]);
+            product(1);
             pin_order();
             copy_out_store(kDefer ? t - 2 : t - 1, vs);
             pin_order();
-            char* im = in_img + (par ^ 1) * L.in_pitch;
+            char* im = in_img + par * L.in_pitch;   // Wx_{t+2}
 #pragma unroll
-            for (int k2 = 0; k2 < NCH_IN; ++k2) *(i32x4*)(im + cin_l[k2]) = kTwoSets ? pre[PAR ^ 1][k2] : pre_next[k2];
+            for (int k2 = 0; k2 < NCH_IN; ++k2) *(i32x4*)(im + cin_l[k2]) = kTwoSets ? pre[PAR][k2] : pre_next[k2];
         }
         pin_order();
 #pragma unroll
-        for (int kt = 3; kt < KT; ++kt)
-#pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[g][kt], hB[kt], acc[g]);
+        for (int kc = kLongChain ? 2 : 1; kc < NK; ++kc) product(kc);
         FRNN_TRACE_MARK(2);
-        // (short chain: Wx_{t+1}, requested three steps ago, goes to its image here, in the shadow of the last MFMAs, not behind the
-        // point-wise function, where every instruction is on the step's tail; Wx_{t+2} .. Wx_{t+4} stay in flight)
+        // (short chain: Wx_{t+2}, requested three steps ago, goes to its image here, in the shadow of the last MFMAs, not behind the
+        // point-wise function, where every instruction is on the step's tail; Wx_{t+3} .. Wx_{t+5} stay in flight)
         if constexpr (!kLongChain) {
-            char* im = in_img + (par ^ 1) * L.in_pitch;
+            char* im = in_img + par * L.in_pitch;
 #pragma unroll
-            for (int k2 = 0; k2 < NCH_IN; ++k2) *(i32x4*)(im + cin_l[k2]) = pre[(PH + 1) & 3][k2];
+            for (int k2 = 0; k2 < NCH_IN; ++k2) *(i32x4*)(im + cin_l[k2]) = pre[(PH + 2) & 3][k2];
         }
         pin_order();
         // ---- point-wise function; the step's outputs go to their image (they leave for HBM during the next step)
+        float y[G][PP];   // complete pre-activations (GRU: the candidate's recurrent term with its bias, without the input)
 #pragma unroll
-        for (int g = 0; g < G; ++g) compact_tile<BT>(acc[g]);
-        if constexpr (kLongChain) {   // Wx_{t+2}: slot t + 1, or with two sets Wx_{t+3} (the last steps fetch the last slot again)
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < PP; ++i) y[g][i] = acc[g][2 * i] + acc[g][2 * i + 1];
+        if constexpr (kLongChain) {   // Wx_{t+3}: slot t + 2, or with two sets Wx_{t+4} (the last steps fetch the last slot again)
             const rsrc_t rsn = make_rsrc(wx_ptr);
-            wx_ptr += t + (kTwoSets ? 2 : 1) < T - 1 ? wx_step : 0;
+            wx_ptr += t + (kTwoSets ? 3 : 2) < T - 1 ? wx_step : 0;
 #pragma unroll
             for (int k2 = 0; k2 < NCH_IN; ++k2) {
-                if constexpr (kTwoSets) pre[PAR ^ 1][k2] = __builtin_amdgcn_raw_buffer_load_b128(rsn, cin_g[k2], 0, 0);
+                if constexpr (kTwoSets) pre[PAR][k2] = __builtin_amdgcn_raw_buffer_load_b128(rsn, cin_g[k2], 0, 0);
                 else pre_next[k2] = __builtin_amdgcn_raw_buffer_load_b128(rsn, cin_g[k2], 0, 0);
             }
         }
@@ -370,7 +424,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
         for (int i = 0; i < PP; ++i) {
             float wxi[G], ybi[G], sti[S], cvi[NC];
 #pragma unroll
-            for (int g = 0; g < G; ++g) { wxi[g] = wx[g][i]; ybi[g] = (CELL == CELL_GRU && g == 2) ? acc[g][i] + bias[g][i] : acc[g][i]; }
+            for (int g = 0; g < G; ++g) { wxi[g] = (CELL == CELL_GRU && g == 2) ? wx_cand[i] : 0.0f; ybi[g] = y[g][i]; }
 #pragma unroll
             for (int s = 0; s < S; ++s) sti[s] = st[s][i];
             Cell<CELL, true>::fwd(wxi, ybi, sti, cvi);
@@ -380,14 +434,12 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
 #pragma unroll
                 for (int c2 = 0; c2 < NC; ++c2) cv_keep[i][c2] = cvi[c2];
             } else {
-                store_record<true, CT::RS, NC>(rs_c, voff_c + i * REC, 0, cvi);
+                store_record<true, CT::RS, NC>(rs_c, voff_c[i], 0, cvi);
             }
         }
-        write_operand_lds<true, PP>(hbuf + par * BUF + lds_row, e0, st[0]);
-        if constexpr (!kDefer) {
-#pragma unroll
-            for (int s = 0; s < S; ++s) store_io<false, PP>(out_img + par * OUT_PITCH + l_st + (uint32_t)s * BT * L.rp_st, 0, st[s]);
-        }
+        write_h(hbuf + par * BUF, st[0]);
+        if constexpr (!kDefer) write_states(out_img + par * OUT_PITCH, st);
+        start_acc();
 #ifdef FLASHRNN_TRACE
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #endif
@@ -426,10 +478,9 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
             if constexpr (kDeferRec) {
                 const rsrc_t rs_last = make_rsrc(c_g + (size_t)(T - 1) * c_step);   // the saved values of step T
 #pragma unroll
-                for (int i = 0; i < PP; ++i) store_record<true, CT::RS, NC>(rs_last, voff_c + i * REC, 0, cv_keep[i]);
+                for (int i = 0; i < PP; ++i) store_record<true, CT::RS, NC>(rs_last, voff_c[i], 0, cv_keep[i]);
             }
-#pragma unroll
-            for (int s = 0; s < S; ++s) store_io<false, PP>(out_img + (T & 1) * OUT_PITCH + l_st + (uint32_t)s * BT * L.rp_st, 0, st[s]);
+            write_states(out_img + (T & 1) * OUT_PITCH, st);
             st_ptr = st_g + (size_t)(T - 1) * st_step;
             copy_out_load((T & 1) ^ 1, vs);
             copy_out_store(T - 1, vs);
@@ -449,20 +500,19 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_tile_kernel(const KernelParams 
 }
 
 // =============================================================================================
-// backward, one block of 16 units per wave, contraction split over EBK waves
+// backward, one block of 16 units per wave
 // =============================================================================================
 // A step of the backward pass is the chain
 //     point-wise Jacobians of step t -> dg_t in LDS -> barrier -> MFMA chain R dg_t -> dh_{t-1}.
-// The contraction axis (G * D gate gradients) is G times longer than in the forward pass; if every wave
-// read all of it from LDS, the LDS would bound the step.  Here waves come in sets of EBK: a set owns EBK
-// blocks of units, and each of its waves contracts all of the set's blocks over one of EBK slices of the
-// axis (the same number of MFMAs and R registers per wave, 1/EBK of the operand reads).  The partial sums
-// go through LDS; wave w then runs the point-wise function of block w.
+// The contraction axis (G * D gate gradients) is G times longer than in the forward pass and every wave reads all of it from
+// LDS.  (With dense matrix instructions, twice the operand reads, heads of 192 units split it over sets of three waves and added
+// partial sums behind a second barrier; with the sparse ones that is 12 to 20 % slower than the one chain: 4 x 192, 16 rows,
+// sLSTM 0.926 us per step against 0.753, LSTM 0.884 / 0.767, GRU 0.806 / 0.665.)
 // Global traffic moves as 16-byte chunks through LDS images, off the chain: the inputs of step t-2 are
 // fetched while step t's MFMAs run, by loads that write their image in LDS directly (no registers are
 // held across the HBM latency), and are read into registers during step t-1's MFMAs; dWx_t leaves
 // during step t's MFMAs.
-// EXACT: as in the forward kernel (the head has exactly KTW * EBK * 32 / G units: compile-time LDS pitches, and a
+// EXACT: as in the forward kernel (the head has exactly KT * 32 / G units: compile-time LDS pitches, and a
 // compile-time step parity with the time loop unrolled by two).
 // 1 KB pieces of an input image of the backward kernel (records | state rows | dh rows, each part rounded up to whole
 // pieces as in tile_lds_bwd) per wave of a head of D units
@@ -471,21 +521,19 @@ constexpr int deep_pieces_per_wave(int BT, int D, int rec_bytes, int nsb) {
     return (pieces + D / 16 - 1) / (D / 16);
 }
 
-template <int CELL, int KTW, int EBK, int BT, int MAXW, bool EXACT, bool DEEP = false>
+template <int CELL, int KT, int BT, int MAXW, bool EXACT, bool DEEP = false>
 __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams p) {
     using CT = CellTraits<CELL>;
-    using OP = Operand<true>;
     constexpr int G = CT::G, S = CT::S, NC = CT::NC;
     constexpr int PP = BT / 4;
     constexpr int ESZ = 2;
-    constexpr int KT = KTW * EBK, DK = KT * 32;
+    constexpr int DK = KT * 32, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64 (KT odd: the last one holds 32)
     constexpr int NSB = CELL == CELL_SLSTM ? 2 : CELL == CELL_ELMAN ? 0 : 1;   // state rows the Jacobian needs per time level ...
     constexpr int SB0 = cell_uses_h_prev(CELL) ? 0 : 1;   // ... starting at this state
     constexpr int GO = CELL == CELL_GRU ? G + 1 : G;  // output rows per batch row: dWx (+ the recurrent-side candidate gradient)
-    // accumulators per block: independent MFMAs in flight.  A wave that has its SIMD to itself (heads of up to 64 units) issues
-    // an MFMA every 16 clocks, so two chains keep dependent ones 32 apart, which a 4-pass MFMA allows; four chains cost eight
-    // more additions and eight more register moves per step there (12 x 64 backward: -6 %).  With two waves per SIMD four measured 1 % better.
-    constexpr int NA = EBK == 1 ? (MAXW <= 4 ? 2 : 4) : (EBK == 2 ? 2 : 1);
+    // accumulators: independent matrix instructions in flight.  One is issued every 16 clocks and takes 20 when it depends on the
+    // one before (measured): two chains do.
+    constexpr int NA = 2;
     constexpr uint32_t kDrop = 0x80000000u;
     constexpr uint32_t REC = CT::RS * ESZ;
     static_assert(BT == 4 || BT == 8, "batch tiles of 4 or 8 rows");
@@ -495,43 +543,48 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     const int gid = blockIdx.x;
     if (gid >= p.NG) return;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tid = threadIdx.x;
-    const int tg = w / EBK, ks = w % EBK;
-    const LaneMap<BT> lm(lane);
+    const SparseLane<BT> lm(lane);
     const int D = EXACT ? DK / G : p.D;
     const int T = p.T, B = p.B, NH = p.NH;
     const int NT = 4 * D;
     const int n = gid % NH, q = gid / NH;
-    const int e0 = w * 16 + lm.uoff;                 // this lane's units in the point-wise phase: block w
+    const int e0 = w * 16 + lm.c;                    // this lane's unit in the point-wise phase: block w
 
     const uint32_t HD = (uint32_t)NH * D;
     const size_t wx_step = (size_t)B * G * HD * ESZ, st_step = (size_t)S * B * HD * 4, c_step = (size_t)B * HD * REC;
     const size_t dh_step = (size_t)B * HD * ESZ;
     const uint32_t st_state = (uint32_t)B * HD * 4;
-    const TileLdsBwd L = tile_lds_bwd(BT, GO, NSB, D, DK * 2, EBK, REC);
+    const TileLdsBwd L = tile_lds_bwd(BT, GO, NSB, D, DK * 2, REC);
     const uint32_t BUF = BT * L.hp;
     char* gbuf = smem;
-    float* red = (float*)(smem + L.red_off);
     char* in_img = smem + L.in_off;
     char* out_img = smem + L.out_off;
 
-    // ---- R fragments: blocks tg*EBK + j, contraction slice ks
-    bf16x8 Rf[EBK][KTW];
+    // ---- R: row d = w * 16 + c, all of the contraction axis
+    bf16x16 Rf[NK];
+    {
+        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK + sparse_k(lm.quad);
+        i32x4 piece[2 * NK];
+        if constexpr (KT & 1) piece[KT] = i32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < EBK; ++j) {
-        const size_t rrow = ((size_t)n * D + (tg * EBK + j) * 16 + lm.c) * DK + (size_t)ks * KTW * 32;
+        for (int kt = 0; kt < KT; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32), *(const i32x2*)(rrow + kt * 32 + 8));
 #pragma unroll
-        for (int kt = 0; kt < KTW; ++kt) Rf[j][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + kt * 32 + lm.quad * 8);
+        for (int kc = 0; kc < NK; ++kc) Rf[kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
     }
 
-    const int bb_raw = q * BT + lm.bslot;
-    const bool row_valid = bb_raw < B;
-    const int bb = row_valid ? bb_raw : B - 1;
     const char* c_g = (const char*)p.cache + (size_t)n * D * REC;
     const char* st_g = (const char*)p.states + (size_t)n * D * 4;
     const char* dh_g = (const char*)p.dH + (size_t)n * D * ESZ;
     char* dwx_g = (char*)p.dWx + (size_t)n * D * ESZ;
     char* dgn_g = (char*)p.dgn + (size_t)n * D * ESZ;
-    const uint32_t voff_st = ((uint32_t)bb * HD + e0) * 4;
+    uint32_t voff_st[PP];   // this lane's pairs: batch rows q * BT + slot(i)
+    bool row_valid[PP];
+#pragma unroll
+    for (int i = 0; i < PP; ++i) {
+        const int brow = q * BT + lm.slot(i);
+        row_valid[i] = brow < B;
+        voff_st[i] = ((uint32_t)(row_valid[i] ? brow : B - 1) * HD + e0) * 4;
+    }
 
     // ---- chunk roles: global byte offsets (out of range = nothing to move)
     constexpr int NCC = (BT * (int)REC + 63) / 64;   // record chunks per thread: BT rows of D records, NT = 4 D threads
@@ -610,27 +663,29 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
         }
     }
     // this lane's places in the images
-    // (byte o of slot r's row lies in the chunk at row position rotated(o / 16); a lane's PP values of a state or of dh share
-    // a chunk, its PP records need not)
-    auto in_row = [&](uint32_t o, uint32_t cpr) { return rotated(o / 16, (uint32_t)lm.bslot, cpr) * 16 + o % 16; };
-    uint32_t l_c[PP];
+    // (byte o of slot r's row lies in the chunk at row position rotated(o / 16))
+    auto in_row = [&](uint32_t o, uint32_t slot, uint32_t cpr) { return rotated(o / 16, slot, cpr) * 16 + o % 16; };
+    uint32_t l_c[PP], l_st[PP], l_dh[PP];
 #pragma unroll
-    for (int i = 0; i < PP; ++i) l_c[i] = (uint32_t)lm.bslot * D * REC + in_row((e0 + i) * REC, cpr_c);
-    const uint32_t l_st = L.st_off + (uint32_t)lm.bslot * D * 4 + in_row(e0 * 4, cpr_st);
-    const uint32_t l_dh = L.dh_off + (uint32_t)lm.bslot * D * ESZ + in_row(e0 * ESZ, cpr_io);
-    const uint32_t l_out = (uint32_t)lm.bslot * L.rp_io + e0 * ESZ;
-    const uint32_t lds_row = (uint32_t)lm.bslot * L.hp;
+    for (int i = 0; i < PP; ++i) {
+        const uint32_t sl = (uint32_t)lm.slot(i);
+        l_c[i] = sl * D * REC + in_row(e0 * REC, sl, cpr_c);
+        l_st[i] = L.st_off + sl * D * 4 + in_row(e0 * 4, sl, cpr_st);
+        l_dh[i] = L.dh_off + sl * D * ESZ + in_row(e0 * ESZ, sl, cpr_io);
+    }
+    const uint32_t l_out = (uint32_t)lm.quad * L.rp_io + e0 * ESZ;   // (pair i: four rows further on)
+    const uint32_t l_dg = (uint32_t)lm.quad * L.hp + e0 * ESZ;
 
     // carried state gradients; ds[0] is the part of dh_t that came through R and the direct path
     float ds[S][PP];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3))
-            load_io_r<false, PP>(make_rsrc((const char*)p.dlast + (size_t)n * D * 4), voff_st, s * st_state, ds[s]);
-        else
+    for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int i = 0; i < PP; ++i) ds[s][i] = 0.0f;
-    }
+        for (int i = 0; i < PP; ++i) {
+            float v[1] = {0.0f};
+            if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3)) load_io_r<false, 1>(make_rsrc((const char*)p.dlast + (size_t)n * D * 4), voff_st[i], s * st_state, v);
+            ds[s][i] = v[0];
+        }
 
     for (uint32_t j = tid; j < 2 * BUF / 4; j += NT) ((uint32_t*)gbuf)[j] = 0u;
 
@@ -727,13 +782,11 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             for (int c2 = 0; c2 < NC; ++c2) cv[c2][i] = rec[c2];
         }
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            if (s >= SB0 && s < SB0 + NSB) load_io<false, PP>(img + l_st + (uint32_t)(s - SB0) * BT * D * 4, 0, sp[s]);
-            else
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-                for (int i = 0; i < PP; ++i) sp[s][i] = 1.0f;
-        }
-        load_io<true, PP>(img + l_dh, 0, dh_ext);
+            for (int i = 0; i < PP; ++i) sp[s][i] = s >= SB0 && s < SB0 + NSB ? *(const float*)(img + l_st[i] + (uint32_t)(s - SB0) * BT * D * 4) : 1.0f;
+#pragma unroll
+        for (int i = 0; i < PP; ++i) dh_ext[i] = bf16_bits_to_f32(*(const uint16_t*)(img + l_dh[i]));
     };
 
     // The factors of the Jacobian that do not depend on dh_t are formed as soon as the step's saved values and states
@@ -772,13 +825,13 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     };
     // ---- prologue: images of steps T and T-1, this lane's inputs of step T, the states after step T
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        if (!cell_uses_h_prev(CELL) && s >= SB0 && s < SB0 + NSB && T > 0)
-            load_io_r<false, PP>(make_rsrc(st_g + (size_t)T * st_step), voff_st, s * st_state, sc[s]);
-        else
+    for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int i = 0; i < PP; ++i) sc[s][i] = 1.0f;
-    }
+        for (int i = 0; i < PP; ++i) {
+            float v[1] = {1.0f};
+            if (!cell_uses_h_prev(CELL) && s >= SB0 && s < SB0 + NSB && T > 0) load_io_r<false, 1>(make_rsrc(st_g + (size_t)T * st_step), voff_st[i], s * st_state, v);
+            sc[s][i] = v[0];
+        }
     // (DEEP: images and register sets take turns by the distance T - t from the first step, not by t: the first step
     // then has phase 0 whatever T is, and the time loop needs no steps peeled off in front of it)
     auto par_of = [&](const int t) { return DEEP ? ((T - t) & 1) : (t & 1); };
@@ -804,6 +857,9 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
 
     // (the bias gradient, the sum of dg over time and batch rows, is formed by the dR GEMM, which reads every dg anyway:
     // this kernel has neither the registers to keep the sums while its MFMAs run nor LDS bandwidth to spare for them)
+    f32x4 acc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
     // one time step; PH = (T - t) & 3 (DEEP) or t & 1 as a compile-time constant where the loop is unrolled by four or two
     constexpr bool kUnroll = true;
     auto step = [&](auto ph_c, const int t) {
@@ -856,10 +912,13 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
                 }
             }
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                write_operand_lds<true, PP>(gbuf + par * BUF + lds_row, g * D + e0, dg[g]);
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < PP; ++i) *(uint16_t*)(gbuf + par * BUF + l_dg + (uint32_t)(4 * i) * L.hp + (uint32_t)g * D * ESZ) = (uint16_t)f32_to_bf16_bits(dg[g][i]);
+            if constexpr (CELL == CELL_GRU) {
+#pragma unroll
+                for (int i = 0; i < PP; ++i) *(uint16_t*)(out_img + par * L.out_pitch + l_out + (uint32_t)(4 * i) * L.rp_io) = (uint16_t)f32_to_bf16_bits(dwx[2][i]);
             }
-            if constexpr (CELL == CELL_GRU) store_io<true, PP>(out_img + par * L.out_pitch + l_out, 0, dwx[2]);
             if constexpr (!cell_uses_h_prev(CELL)) {
 #pragma unroll
                 for (int s = SB0; s < SB0 + NSB; ++s)
@@ -867,28 +926,35 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
                     for (int i = 0; i < PP; ++i) sc[s][i] = sp[s][i];
             }
         }
+        // (the sparse instruction adds to its result register in place: the accumulators are cleared ahead of the barrier, where
+        // the wave waits for its LDS writes anyway)
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+#pragma unroll
+            for (int r = 0; r < BT / 2; ++r) acc[a][r] = 0.0f;   // (4-row tiles: registers 2 and 3 are never used)
+            asm volatile("" : "+v"(acc[a]));
+        }
         // the chunks fetched during the previous step are in LDS once only that step's stores are younger;
         // they are read after this barrier
         if constexpr (!kRegFetch) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CELL == CELL_GRU ? 2 : 1) : "memory");
         __syncthreads();
         // ---- dh_{t-1} += R dg_t; in the shadow of the chain: fetch step t-2, dWx_t out, step t-1's values
-        // The operand is read in chunks of KC k-steps, one chunk ahead of the MFMAs that use it.
-        constexpr int KC = 4, NCK = (KTW + KC - 1) / KC;
+        // The operand is read in chunks of KC sparse steps, one chunk ahead of the MFMAs that use it.
+        constexpr int KC = 4, NCK = (NK + KC - 1) / KC;
         bf16x8 gB[NCK][KC];
-        const char* grow = gbuf + par * BUF + lds_row + (size_t)(ks * KTW * 32 + lm.quad * 8) * 2;
-        // Only the lanes of the BT valid batch columns read: the backward step is bound by the LDS (busy 62 % of the
-        // step, nearly half of it these reads), and an LDS read costs bandwidth per active lane.  The other lanes' registers
-        // keep whatever they held -- a column of the B operand only reaches the same column of the result, and the
-        // columns c >= BT of a result are never used; the empty asm statements stand for "any value" (without them
-        // the compiler would give the idle lanes a defined value, one move per register and chunk).
+        const char* grow = gbuf + par * BUF + (uint32_t)lm.rslot * L.hp;
+        // Only the lanes of the 2 BT operand rows in use read: the backward step is bound by the LDS, and an LDS read costs
+        // bandwidth per active lane.  The other lanes' registers keep whatever they held -- a row of this operand only reaches
+        // the same row of the result, and the others are never used; the empty asm statements stand for "any
+        // value" (without them the compiler would give the idle lanes a defined value, one move per register and chunk).
         auto read_chunk = [&](int c) {
             i32x4 raw[KC];
 #pragma unroll
             for (int k = 0; k < KC; ++k) asm volatile("" : "=v"(raw[k]));
-            if (lm.c < BT) {
+            if (BT == 8 || (lm.c & 2) == 0) {
 #pragma unroll
                 for (int k = 0; k < KC; ++k)
-                    if (c * KC + k < KTW) raw[k] = *(const i32x4*)(grow + (size_t)(c * KC + k) * 64);
+                    if (c * KC + k < NK) raw[k] = *(const i32x4*)(grow + (c * KC + k) * 128 + ((KT & 1) && c * KC + k == NK - 1 ? lm.rbyte_half() : lm.rbyte));
             }
 #pragma unroll
             for (int k = 0; k < KC; ++k) gB[c][k] = __builtin_bit_cast(bf16x8, raw[k]);
@@ -904,19 +970,11 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             if (t > 2) fetch(par);
         }
         pin_order();
-        f32x4 acc[EBK][NA];
-#pragma unroll
-        for (int j = 0; j < EBK; ++j)
-#pragma unroll
-            for (int a = 0; a < NA; ++a) acc[j][a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < NCK; ++c) {
 #pragma unroll
             for (int k = 0; k < KC; ++k)
-                if (c * KC + k < KTW) {
-#pragma unroll
-                    for (int j = 0; j < EBK; ++j) acc[j][(c * KC + k) % NA] = OP::mfma(Rf[j][c * KC + k], gB[c][k], acc[j][(c * KC + k) % NA]);
-                }
+                if (c * KC + k < NK) acc[(c * KC + k) % NA] = smfmac(gB[c][k], Rf[c * KC + k], acc[(c * KC + k) % NA], lm.idx);
             pin_order();
             if (c + 1 < NCK) read_chunk(c + 1);
             if (c == 0) {   // dWx_t out of its image and on its way, step t-1's values out of theirs
@@ -933,36 +991,12 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             }
             pin_order();
         }
-        float part[EBK][PP];
 #pragma unroll
-        for (int j = 0; j < EBK; ++j) {
-            f32x4 a = acc[j][0];
+        for (int i = 0; i < PP; ++i) {
+            float rec = acc[0][2 * i] + acc[0][2 * i + 1];   // R dg_t
 #pragma unroll
-            for (int x = 1; x < NA; ++x) a += acc[j][x];
-            compact_tile<BT>(a);
-#pragma unroll
-            for (int i = 0; i < PP; ++i) part[j][i] = a[i];
-        }
-        if constexpr (EBK > 1) {
-#pragma unroll
-            for (int j = 0; j < EBK; ++j)   // partial sum of block tg*EBK + j from slice ks
-                store_io<false, PP>(red, ((size_t)((tg * EBK + j) * EBK + ks) * 64 + lane) * PP, part[j]);
-            __syncthreads();
-            float rec[PP];   // R dg_t of this lane's pairs, summed over the slices
-#pragma unroll
-            for (int i = 0; i < PP; ++i) rec[i] = 0.0f;
-#pragma unroll
-            for (int x = 0; x < EBK; ++x) {
-                float v[PP];
-                load_io<false, PP>(red, ((size_t)(w * EBK + x) * 64 + lane) * PP, v);
-#pragma unroll
-                for (int i = 0; i < PP; ++i) rec[i] += v[i];
-            }
-#pragma unroll
-            for (int i = 0; i < PP; ++i) ds[0][i] += fminf(fmaxf(rec[i], -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
-        } else {
-#pragma unroll
-            for (int i = 0; i < PP; ++i) ds[0][i] += fminf(fmaxf(part[0][i], -p.clip), p.clip);
+            for (int x = 1; x < NA; ++x) rec += acc[x][2 * i] + acc[x][2 * i + 1];
+            ds[0][i] += fminf(fmaxf(rec, -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
         }
     };
     using ph0 = std::integral_constant<int, 0>;
@@ -991,11 +1025,15 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
         for (int t = T; t >= 1; --t) step(ph0{}, t);
     }
     // ---- gradients w.r.t. the initial states
-    if (row_valid) {
 #pragma unroll
-        for (int s = 0; s < S; ++s)
-            store_io_r<false, PP>(make_rsrc((char*)p.dstates0 + (size_t)n * D * 4), voff_st, s * st_state, ds[s]);
-    }
+    for (int i = 0; i < PP; ++i)
+        if (row_valid[i]) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const float v[1] = {ds[s][i]};
+                store_io_r<false, 1>(make_rsrc((char*)p.dstates0 + (size_t)n * D * 4), voff_st[i], s * st_state, v);
+            }
+        }
 }
 
 }  // namespace flashrnn

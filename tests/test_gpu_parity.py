@@ -498,3 +498,13 @@ def test_weight_gradient_gemm_with_few_heads(cell, NH, D, T, B):
     shorter than the others: the output tiles are dealt out over the XCDs in equal runs."""
     w = Workload(f"fewheads_{cell}_NH{NH}_D{D}", cell, T, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + T)
     _check(w, with_dlast=True)
+
+
+@pytest.mark.parametrize("cell", [CELL_LSTM, CELL_GRU])
+@pytest.mark.parametrize("D,bt", [(192, 4), (160, 4), (192, 8), (128, 8), (32, 4), (16, 8)])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 6, 7, 9])
+def test_staged_forward_kernels_at_every_pipeline_length(cell, D, bt, T):
+    """The staged kernels fetch their inputs up to five steps ahead and park them two ahead: sequences around those distances, a
+    ragged last batch tile, contraction lengths that fill the last sparse step of 64 and that leave half of it."""
+    w = Workload(f"pipe_{cell}_D{D}_bt{bt}_T{T}", cell, T, bt + 3, 2, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=T + D + bt)
+    _check(w, {"FLASHRNN_BT": str(bt)}, with_dlast=True)
