@@ -181,7 +181,11 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             // 1.25 when the call saves nothing and writes a third of the bytes: 1.48 in one round, 1.12 per round in two --, the
             // sLSTM's forward step, whose point-wise function is the longest, 2.7)
             const double rel8 = bwd ? 1.3 : (d->cell == FLASHRNN_SLSTM ? 2.7 : (mode == 2 ? 1.25 : 1.65));
-            double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? 1.8 : e.BT == 8 ? 3.0 : 6.0);
+            // (float32: the 4-row kernels run on the 4 x 4 matrix instruction.  Two workgroups of 4 rows on a CU beat one of 8 -- LSTM 16 x 64
+            // with 128 rows 283 us per 64 steps against 349, GRU 8 x 96 with 256 rows 452 against 600 --, four of 4 rows lose to one of 16: LSTM
+            // 16 x 64 with 256 rows 565 against 522, Elman 16 x 128 438 against 391)
+            const double rel4 = bf ? 1.8 : 1.45, rel16 = bf ? 6.0 : 5.5;
+            double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? rel4 : e.BT == 8 ? 3.0 : rel16);
             if (e.tile == 0) rel *= 1.0 + 0.05 * (e.eb - 1);       // thin waves overlap better
             rel *= 1.0 + 0.02 * (dk - kdim) / (double)kstep;       // padded k-steps are wasted MFMAs
             if (exact_only) rel *= 0.99;                           // compile-time LDS layout: fewer address instructions

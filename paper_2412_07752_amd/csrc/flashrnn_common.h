@@ -196,6 +196,29 @@ template <int BT> __device__ __forceinline__ void compact_tile(f32x4& a) {
     }
 }
 
+// Recurrent product of a 4-row batch tile in float32.  v_mfma_f32_16x16x4 would spend 32 clocks on a [16 x 4] x [4 x 16] product of
+// which four columns are rows of the tile.  v_mfma_f32_4x4x1 forms 16 independent [4 x 1] x [1 x 4] products in 8 clocks, all
+// of them used here: block b = lane / 4 takes units 4 (b / 4) .. + 3 of the wave and contraction slice b % 4, so that one
+// instruction still covers 16 units and 4 contraction steps.  (GRU 4 x 96, 12 rows: the step was 80 % matrix pipe;
+// forward 3.15 -> 1.19 us, backward 2.99 -> 0.92.  LSTM 1 x 64 forward 1.51 -> 0.96.)  The four slices of a unit quad meet across the lanes
+// of a row (sum_quad_slices), which also leaves lane (c, quad) with unit 4 quad + c / 4 of batch slot c % 4: the
+// places of compact_tile<4>.
+template <bool BF16, int BT> constexpr bool kQuadTiles = !BF16 && BT == 4;
+__device__ __forceinline__ f32x4 mfma_quads(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ float sum_quad_slices(const f32x4& a, int c) {
+    auto ror = [](float x, auto n) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + decltype(n)::value, 0xF, 0xF, false));
+    };
+    // lane bits 3 and 2 (the slice) select the unit that the lane ends up with: halve the register set twice
+    const bool hi = (c & 8) != 0, odd = (c & 4) != 0;
+    const float k0 = hi ? a[2] : a[0], k1 = hi ? a[3] : a[1], s0 = hi ? a[0] : a[2], s1 = hi ? a[1] : a[3];
+    const float f0 = k0 + ror(s0, std::integral_constant<int, 8>{}), f1 = k1 + ror(s1, std::integral_constant<int, 8>{});
+    // (an even slice takes from the lane 4 up, an odd one from the lane 4 down: rotations by 12 and by 4
+    // -- both with all lanes active, a lane outside the execution mask gives nothing)
+    const float up = f0 + ror(f0, std::integral_constant<int, 12>{}), down = f1 + ror(f1, std::integral_constant<int, 4>{});
+    return odd ? down : up;
+}
+
 // The inverse of compact_tile for one value per pair: the lanes c < BT of a row collect the four consecutive
 // units 4q..4q+3 of their batch slot from the lanes that computed them (valid in those lanes only).
 template <int BT, int PP> __device__ __forceinline__ void expand_tile(const float (&v)[PP], float (&out)[4]) {

@@ -416,8 +416,21 @@ __device__ __forceinline__ void read_operand_lds(const char* row, int k0, int qu
         for (int kt = 0; kt < KT; ++kt) hB[kt] = *(const bf16x8*)(row + (size_t)(k0 + kt * 32 + quad * 8) * 2);
     } else {
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) hB[kt] = *(const float*)(row + (size_t)(k0 + quad * KT + kt) * 4);
+        for (int kt = 0; kt < KT; kt += 4) {   // (KT is a multiple of 4, rows and quarters are aligned to 16 bytes)
+            const f32x4 v = *(const f32x4*)(row + (size_t)(k0 + quad * KT + kt) * 4);
+            hB[kt] = v[0]; hB[kt + 1] = v[1]; hB[kt + 2] = v[2]; hB[kt + 3] = v[3];
+        }
     }
+}
+
+// one k-step of a tile product, and the tile's (unit, batch slot) pairs from its accumulators
+template <bool BF16, int BT> __device__ __forceinline__ f32x4 mfma_step(typename Operand<BF16>::type a, typename Operand<BF16>::type b, f32x4 c) {
+    if constexpr (kQuadTiles<BF16, BT>) return mfma_quads(a, b, c);
+    else return Operand<BF16>::mfma(a, b, c);
+}
+template <bool BF16, int BT> __device__ __forceinline__ void finish_tile(f32x4& a, int c) {
+    if constexpr (kQuadTiles<BF16, BT>) a[0] = sum_quad_slices(a, c);
+    else compact_tile<BT>(a);
 }
 
 template <bool BF16, int PP> __device__ __forceinline__ void write_operand_lds(char* row, int k, const float (&v)[PP]) {
@@ -491,6 +504,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
+    static_assert(KS == 1 || !kQuadTiles<BF16, BT>, "the sums of contraction slices assume 16 x 16 tiles");
 
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, MULTI);
@@ -503,6 +517,8 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;  // first unit of this wave
     const int e0 = e_wave + lm.uoff;                    // first unit of this lane's pairs
     const int k0 = ks * KT * OP::KSTEP;
+    constexpr bool QT = kQuadTiles<BF16, BT>;
+    const int kq = QT ? lm.c >> 2 : lm.quad, arow = QT ? 4 * lm.quad + (lm.c & 3) : lm.c;   // contraction quarter, row of R that this lane holds
 
     char* hbuf = smem;                                          // !MULTI: [2][BT][HP] operand rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));            // MULTI: one operand buffer [BT][HP], then (KS > 1) the partial sums
@@ -537,11 +553,11 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
         for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const size_t rrow = (((size_t)n * G + g) * D + e_wave + 16 * eb + lm.c) * DK;
+            const size_t rrow = (((size_t)n * G + g) * D + e_wave + 16 * eb + arow) * DK;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
-                if constexpr (BF16) Rf[eb][g][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0));
-                else Rf[eb][g][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0)];
+                if constexpr (BF16) Rf[eb][g][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
+                else Rf[eb][g][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
             }
             load_io<BF16, PP>(p.bias, ((size_t)n * G + g) * D + e0 + 16 * eb, bias[eb][g]);
         }
@@ -622,13 +638,13 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
             f32x4 (&acc)[G] = accs[0];
             if constexpr (!MULTI) {
                 op_t hB[KT];
-                read_operand_lds<BF16, KT>(hbuf + ((t - 1) & 1) * BUF + lds_rd, k0, lm.quad, hB);
+                read_operand_lds<BF16, KT>(hbuf + ((t - 1) & 1) * BUF + lds_rd, k0, kq, hB);
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int g = 0; g < G; ++g) accs[eb][g] = OP::mfma(Rf[eb][g][kt], hB[kt], accs[eb][g]);
+                    for (int g = 0; g < G; ++g) accs[eb][g] = mfma_step<BF16, BT>(Rf[eb][g][kt], hB[kt], accs[eb][g]);
             } else {
                 // h_{t-1} of the whole group: polled once per workgroup into LDS, then read like in the one-workgroup case
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(t - 1);
@@ -648,12 +664,12 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                         lds_operand_chunk<BT, KC, (KT >= 8)>(hbuf + lds_rd + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, lm.c, hB);
                     } else {
 #pragma unroll
-                        for (int j = 0; j < KC; ++j) hB[j] = *(const float*)(hbuf + lds_rd + (size_t)(k0 + lm.quad * KT + kc + j) * 4);
+                        for (int j = 0; j < KC; ++j) hB[j] = *(const float*)(hbuf + lds_rd + (size_t)(k0 + kq * KT + kc + j) * 4);
                     }
 #pragma unroll
                     for (int j = 0; j < KC; ++j)
 #pragma unroll
-                        for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[0][g][kc + j], hB[j], acc[g]);
+                        for (int g = 0; g < G; ++g) acc[g] = mfma_step<BF16, BT>(Rf[0][g][kc + j], hB[j], acc[g]);
                 }
             }
             reduce_slices<G, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, acc);
@@ -666,7 +682,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb) {
 #pragma unroll
-                    for (int g = 0; g < G; ++g) compact_tile<BT>(accs[eb][g]);
+                    for (int g = 0; g < G; ++g) finish_tile<BF16, BT>(accs[eb][g], lm.c);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) {
                         float wxi[G], ybi[G], sti[S], cvi[NC];
@@ -749,6 +765,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
+    static_assert(KS == 1 || !kQuadTiles<BF16, BT>, "the sums of contraction slices assume 16 x 16 tiles");
 
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, MULTI);
@@ -761,6 +778,8 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;
     const int e0 = e_wave + lm.uoff;
     const int k0 = ks * KT * OP::KSTEP;
+    constexpr bool QT = kQuadTiles<BF16, BT>;
+    const int kq = QT ? lm.c >> 2 : lm.quad, arow = QT ? 4 * lm.quad + (lm.c & 3) : lm.c;   // (as in the forward kernel)
 
     char* gbuf = smem;          // !MULTI: [2][BT][HP] gate-gradient rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));  // MULTI: one operand buffer [16][HP], then (KS > 1) the partial sums
@@ -789,11 +808,11 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
         op_t Rf[EB][KT];
 #pragma unroll
         for (int eb = 0; eb < EB; ++eb) {
-            const size_t rrow = ((size_t)n * D + e_wave + 16 * eb + lm.c) * DK;
+            const size_t rrow = ((size_t)n * D + e_wave + 16 * eb + arow) * DK;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
-                if constexpr (BF16) Rf[eb][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0));
-                else Rf[eb][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0)];
+                if constexpr (BF16) Rf[eb][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
+                else Rf[eb][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
             }
         }
         const int bb_raw = q * BT + lm.bslot;
@@ -963,11 +982,11 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             if constexpr (!MULTI) {
                 __syncthreads();
                 op_t gB[KT];
-                read_operand_lds<BF16, KT>(gbuf + (t & 1) * BUF + lds_row, k0, lm.quad, gB);
+                read_operand_lds<BF16, KT>(gbuf + (t & 1) * BUF + lds_row, k0, kq, gB);
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int eb = 0; eb < EB; ++eb) a4[eb][kt % NA] = OP::mfma(Rf[eb][kt], gB[kt], a4[eb][kt % NA]);
+                    for (int eb = 0; eb < EB; ++eb) a4[eb][kt % NA] = mfma_step<BF16, BT>(Rf[eb][kt], gB[kt], a4[eb][kt % NA]);
             } else {
                 // dg_t of the whole group: polled once per workgroup into LDS, then read like in the one-workgroup case
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(T - t);
@@ -991,10 +1010,10 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                         lds_operand_chunk<BT, KC, true>(gbuf + lds_row + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, lm.c, gB);
                     } else {
 #pragma unroll
-                        for (int j = 0; j < KC; ++j) gB[j] = *(const float*)(gbuf + lds_row + (size_t)(k0 + lm.quad * KT + kc + j) * 4);
+                        for (int j = 0; j < KC; ++j) gB[j] = *(const float*)(gbuf + lds_row + (size_t)(k0 + kq * KT + kc + j) * 4);
                     }
 #pragma unroll
-                    for (int j = 0; j < KC; ++j) a4[0][(kc + j) % NA] = OP::mfma(Rf[0][kc + j], gB[j], a4[0][(kc + j) % NA]);
+                    for (int j = 0; j < KC; ++j) a4[0][(kc + j) % NA] = mfma_step<BF16, BT>(Rf[0][kc + j], gB[j], a4[0][(kc + j) % NA]);
                 }
                 if constexpr (kOutRows) {
                     const rsrc_t dwx_rows = make_rsrc(kRunning ? dwx_run : dwx_g + (size_t)(t - 1) * wx_step);
@@ -1015,7 +1034,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             if (KS == 1 || ks == 0) {
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb) {
-                    compact_tile<BT>(accs[eb][0]);
+                    finish_tile<BF16, BT>(accs[eb][0], lm.c);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) ds[eb][0][i] += fminf(fmaxf(accs[eb][0][i], -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
                 }

@@ -97,6 +97,17 @@ def test_batch_tiles_with_f32_io(cell, bt, D):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("D", [16, 32, 80, 96, 128, 144, 192, 256])
+def test_four_row_tiles_with_f32_io(cell, D):
+    """4-row float32 tiles on the 4 x 4 matrix instruction: full and padded contraction quarters, one workgroup per group (up to 128
+    units) and split groups (beyond); 7 rows = ragged last tile."""
+    w = Workload(f"f32_quads_{cell}_D{D}", cell, 6, 7, 2, D, "f32", True, bias="uniform0.1", init="uniform0.1", seed=D + 5)
+    _check(w, {"FLASHRNN_BT": "4"}, with_dlast=True)
+    d = api.make_desc(cell, 6, 7, 2, D, api.FLASHRNN_F32)
+    assert all(api.flashrnn_plan_kernel(d, x)[1] == 4 for x in (0, 1))
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("D,bt", [(32, 4), (32, 8), (64, 4), (64, 8), (16, 4), (48, 8), (48, 4)])
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 13])
 def test_backward_kernels_that_fetch_deep(cell, D, bt, T):
