@@ -102,7 +102,7 @@ int flashrnn_fwd(const flashrnn_desc_t* desc, const void* Wx, const void* R, con
  *   - A problem whose forward scratch does not fit returns FLASHRNN_ERR_SCRATCH (nothing is launched); every one of
  *     the five benchmark shapes fits (the largest, one head of 768 units, needs 4.6 MiB + exchange buffers).
  *   - All calls on one GPU share that GPU's array, on whatever stream: calls that overlap in time race.  The array
- *     keeps the last call's content; what a call needs cleared (exchange stamps, error words) it clears itself.
+ *     keeps the last call's content; what a call needs cleared (exchange words, error words) it clears itself.
  *   - Timeouts of split plans: flashrnn_check(desc, FLASHRNN_STATIC_SCRATCH, stream).
  */
 #define FLASHRNN_STATIC_SCRATCH_BYTES (16u << 20)

@@ -284,7 +284,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
                     const int nt = bwd ? 1 : G;
                     // one buffer of BT operand rows (polled once per workgroup and step), then the partial sums of the slices
                     pl.smem = (size_t)BT * (pl.DK + (bf ? 8 : 4)) * (bf ? 2 : 4) + (best->KS > 1 ? (size_t)2 * (best->KS - 1) * chosen * nt * 4 * 64 * 4 : 16);
-                    pl.exch_bytes = (size_t)2 * gpar * BT * pl.DK * (bf ? 4 : 8);
+                    pl.exch_bytes = (size_t)4 * gpar * BT * pl.DK * (bf ? 2 : 4);   // four buffers
                 }
             }
         }
@@ -325,7 +325,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             pl.block = 64 * 4;
             pl.DK = dk;
             pl.smem = smem;
-            pl.exch_bytes = (size_t)2 * gpar * BT * dk * 4;
+            pl.exch_bytes = (size_t)4 * gpar * BT * dk * 2;
             pl.spread = 1;
         }
     }
@@ -487,9 +487,9 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     hipStream_t stream = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     const int G = num_gates(d->cell);
-    // the exchange words start from zero stamps (a fill kernel, not a memset: the call may be captured into a graph);
+    // the exchange buffers start empty (a fill kernel, not a memset: the call may be captured into a graph);
     // both error words are cleared by the packing kernel
-    if (pf.exch_bytes && launch_fill_zero(ws + w.exch_off, align_up(pf.exch_bytes), stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
+    if (pf.exch_bytes && launch_fill(ws + w.exch_off, align_up(pf.exch_bytes), kNoWord, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
     // (the staged forward kernels read R as it is and clear the error words themselves)
     const bool r_in_place = pf.e->tile != 0;
     if (!r_in_place && launch_pack_r(d->io_dtype == FLASHRNN_BF16, false, R, ws + w.rpack_off, d->NH, d->D, G, pf.DK, (int*)(ws + w.err_off), stream) != hipSuccess)
@@ -579,7 +579,7 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
         } else if (!recompute) {
             cache = gate_cache;
         }
-        if (pb.exch_bytes && launch_fill_zero(ws + w.exch_off, align_up(pb.exch_bytes), stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
+        if (pb.exch_bytes && launch_fill(ws + w.exch_off, align_up(pb.exch_bytes), kNoWord, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
         KernelParams kp;
         memset(&kp, 0, sizeof(kp));
         kp.R = r_in_place ? R : (const void*)(ws + w.rpack_off);

@@ -107,6 +107,9 @@ __host__ __device__ inline TileLdsBwd tile_lds_bwd(int BT, int GO, int NSB, int 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// a word of the cross-CU exchange buffers that nobody has written yet (a NaN pattern, never published)
+constexpr uint32_t kNoWord = 0xFFFFFFFFu;
+
 // Cache policy bits of the raw buffer intrinsics on gfx942/gfx950.
 constexpr int kAuxAgent = 16;  // sc1: coherent at agent scope (misses the CU's vector L1)
 
@@ -126,7 +129,7 @@ struct KernelParams {
     void* dgn;             // bwd, GRU: recurrent-side gradient of gate n, [T,B,NH,D] io
     float* dstates0;       // bwd: [S,B,NH,D]
     float* db_part;        // bwd: [B,NH,G,D] per-batch-row partial sums of db
-    uint32_t* exch;        // cross-CU exchange buffer (stamped words)
+    uint32_t* exch;        // cross-CU exchange buffers (words of kNoWord until written)
     int* err;              // error word
     int T, B, NH, D;
     int P;                 // workgroups per group

@@ -2,7 +2,7 @@
 //
 // Forward (paper Sec. 3 eq. (1)-(2), Alg. 1): per step  y = R^T h_{t-1}  on the matrix cores, then
 // g = Wx_t + y + b and the cell's point-wise function in registers; states and the values the
-// backward pass needs go to HBM; the new h goes to LDS (one CU per group) or to a stamped exchange
+// backward pass needs go to HBM; the new h goes to LDS (one CU per group) or to an exchange
 // buffer in global memory (several CUs per group) and is the next step's MFMA operand.
 // Backward (paper Sec. 4 eq. (3)-(4)): per step the point-wise Jacobians give the gate gradients dg_t,
 // which are streamed out as dWx, handed to the other waves like h in the forward pass, and contracted
@@ -254,15 +254,19 @@ __device__ __forceinline__ void stagger_waves(int w) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// operand hand-over between waves: LDS (one workgroup per group) or stamped words in global memory
+// operand hand-over between waves: LDS (one workgroup per group) or words in global memory
 // ---------------------------------------------------------------------------------------------
-// Exchange word = 8 bytes {payload, stamp}: payload is two bf16 or one float.  A consumer polls the
-// words it needs until every stamp equals the one it expects; a word is written by one aligned
-// 8- or 16-byte store, so payload and stamp always arrive together and no fence is needed.  Stores and
-// loads carry the agent-scope cache policy.  Two buffers alternate; writing round r+1 requires having
-// read round r from every member, which implies every member has finished reading round r-1.
-// The operand rows of a group (`rows` of them, cpr chunks of 16 bytes = two stamped
-// words per row, rows xrow bytes apart from byte offset goff of rs) are polled once, NT threads taking consecutive
+// Exchange word = 4 bytes: two bf16 or one float.  A word that is not there yet holds kNoWord, a NaN pattern that a producer never
+// writes (a payload that happened to be it is published as another NaN), so presence needs no stamps beside the payload, and each
+// word is checked by itself: no assumption about what arrives together beyond 4 bytes.  A consumer polls the words it
+// needs until none of them is kNoWord.  Four buffers alternate, round r in buffer r & 3, all of kNoWord at the launch.  A workgroup that
+// has received round r from every member knows that every member has finished reading round r-1 (each had all of it before it
+// published round r): it sets its own words of that buffer back to kNoWord (Clearer), for round r+3.  Those stores are complete
+// before the end of its next poll, where every wave waits for all it has in flight ahead of a barrier, hence before it publishes round r+2,
+// hence before anybody looks for round r+3.  Loads carry the agent-scope cache policy, and stores where the group spans XCDs.
+// (Against words of twice the size with a stamp beside each payload: LSTM 1 x 2048, 16 rows, 256 steps forward + backward 5170 -> 3413 us,
+// 1 x 768, 128 rows, 1024 steps 13168 -> 11000, 16 rows forward 1897 -> 1580; sLSTM 8 x 256, 32 rows, 2048 steps 7424 -> 7062.)
+// The operand rows of a group (`rows` of them, cpr chunks of 16 bytes per row, rows xrow bytes apart from byte offset goff of rs) are polled once, NT threads taking consecutive
 // chunks, and their payloads go to LDS rows (lds_pitch bytes apart, plain element order).  The waves then read
 // their MFMA operands from LDS like the one-workgroup kernels do (every wave polling every row in L2 itself
 // measured 1.2x to 1.5x slower at D = 256 and 768).  The loads are marked volatile: every round goes to memory again.
@@ -272,6 +276,7 @@ __device__ __forceinline__ void stagger_waves(int w) {
 // (uniform) offset of the buffer in use as the scalar offset of the loads.  Forming the offsets inside the time loop --
 // sixteen integer divisions and a hundred more instructions per thread and step -- cost more than the hand-over itself
 // (measured: 2000 of 7500 clocks per step at D = 256).
+__device__ __forceinline__ int exch_word(uint32_t w) { return (int)(w < kNoWord - 1u ? w : kNoWord - 1u); }
 struct Poller {
     static constexpr int NBP = 2;  // chunks per thread whose offsets are kept for the whole kernel (the usual shapes need no more)
     static constexpr int NB = 8;   // chunks per thread and round beyond those (a round costs one L2 round trip: few rounds)
@@ -291,15 +296,15 @@ struct Poller {
     // offsets of chunk idx (the running position is at idx) and the advance to chunk idx + NT
     __device__ __forceinline__ void place(uint32_t idx, uint32_t& vo, uint32_t& lo) {
         vo = idx < total ? row * xrow + c * 16u : kDrop;
-        lo = row * lds_pitch + c * 8u;
+        lo = row * lds_pitch + c * 16u;
         row += dq;
         c += dr;
         if (c >= cpr) { c -= cpr; ++row; }
     }
-    // one set of up to N chunks: poll until every stamp is there, then move the payloads to LDS
+    // one set of up to N chunks: poll until every word is there, then move the payloads to LDS
     template <int N>
     __device__ __forceinline__ bool round(__amdgpu_buffer_rsrc_t rs, uint32_t goff, const uint32_t (&vo)[N], const uint32_t (&lo)[N], int n, char* lds,
-                                          uint32_t stamp, int spin_limit, int* err, unsigned long long* first_round) const {
+                                          int spin_limit, int* err, unsigned long long* first_round) const {
         constexpr int kAuxPoll = (int)(0x80000000u | (unsigned)kAuxAgent);
         i32x4 raw[N];
         bool good = true;
@@ -308,10 +313,11 @@ struct Poller {
 #pragma unroll
             for (int j = 0; j < N; ++j)
                 if (j < n) raw[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[j], goff, kAuxPoll);
-            bool ok = true;
+            uint32_t top = 0u;   // (a chunk out of range reads as zeros)
 #pragma unroll
             for (int j = 0; j < N; ++j)
-                if (j < n) ok = ok && (vo[j] == kDrop || ((uint32_t)raw[j][1] == stamp && (uint32_t)raw[j][3] == stamp));
+                if (j < n) top = max(top, max(max((uint32_t)raw[j][0], (uint32_t)raw[j][1]), max((uint32_t)raw[j][2], (uint32_t)raw[j][3])));
+            const bool ok = top != kNoWord;
 #ifdef FLASHRNN_TRACE
             if (first_round != nullptr && spins == 0) { asm volatile("" : : "v"(ok) : "memory"); *first_round = __builtin_amdgcn_s_memtime(); }
 #else
@@ -327,64 +333,91 @@ struct Poller {
         }
 #pragma unroll
         for (int j = 0; j < N; ++j)
-            if (j < n && vo[j] != kDrop) *(i32x2*)(lds + lo[j]) = i32x2{raw[j][0], raw[j][2]};
+            if (j < n && vo[j] != kDrop) *(i32x4*)(lds + lo[j]) = raw[j];
         return good;
     }
     // goff: byte offset of the group's rows in the buffer in use (uniform).  Returns false on a timeout.
-    __device__ __forceinline__ bool poll(__amdgpu_buffer_rsrc_t rs, uint32_t goff, char* lds, uint32_t stamp, int spin_limit, int* err,
+    __device__ __forceinline__ bool poll(__amdgpu_buffer_rsrc_t rs, uint32_t goff, char* lds, int spin_limit, int* err,
                                          unsigned long long* first_round = nullptr) const {
         if (spin_limit < 0) {   // host-forced failure (tests of the error path): give up without looking
             __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
-        bool good = round<NBP>(rs, goff, voff, loff, nb, lds, stamp, spin_limit, err, first_round);
+        bool good = round<NBP>(rs, goff, voff, loff, nb, lds, spin_limit, err, first_round);
         if (total > NT * NBP) {   // long rows: further sets, their offsets formed on the way
             Poller run = *this;
             for (uint32_t base = NT * NBP; base < total && good; base += NT * NB) {
                 uint32_t vo[NB], lo[NB];
 #pragma unroll
                 for (int j = 0; j < NB; ++j) run.place(base + tid + (uint32_t)j * NT, vo[j], lo[j]);
-                good = round<NB>(rs, goff, vo, lo, NB, lds, stamp, spin_limit, err, nullptr);
+                good = round<NB>(rs, goff, vo, lo, NB, lds, spin_limit, err, nullptr);
             }
         }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): also for a wave without a chunk of its own (see above; free behind a poll's loads)
         return good;
     }
 };
 
-// write PP = 4 consecutive operand elements of one row as stamped words.  far = the group's workgroups sit on several
+// write 4 consecutive operand elements of one row as exchange words.  far = the group's workgroups sit on several
 // XCDs: the store must go through to memory (agent scope).  Inside one XCD the L2 is the point of coherence and an
 // ordinary store reaches it (the vector L1 writes through); it is acknowledged by the L2, not by memory, which matters
 // because a wave's memory operations retire in order: the next poll's first answer waits for this store's acknowledgement
 // (measured: 0.9 us per step with the write-through store).
-template <bool BF16>
-__device__ __forceinline__ void publish4(__amdgpu_buffer_rsrc_t rs, uint32_t row_off, int k, const float (&v)[4], uint32_t stamp, bool far) {
-    if constexpr (BF16) {
-        const i32x4 w = {(int)pack_bf16x2(v[0], v[1]), (int)stamp, (int)pack_bf16x2(v[2], v[3]), (int)stamp};
-        if (far) __builtin_amdgcn_raw_buffer_store_b128(w, rs, row_off + k * 4, 0, kAuxAgent);
-        else __builtin_amdgcn_raw_buffer_store_b128(w, rs, row_off + k * 4, 0, 0);
-    } else {
-        const i32x4 w0 = {__builtin_bit_cast(int, v[0]), (int)stamp, __builtin_bit_cast(int, v[1]), (int)stamp};
-        const i32x4 w1 = {__builtin_bit_cast(int, v[2]), (int)stamp, __builtin_bit_cast(int, v[3]), (int)stamp};
-        if (far) {
-            __builtin_amdgcn_raw_buffer_store_b128(w0, rs, row_off + k * 8, 0, kAuxAgent);
-            __builtin_amdgcn_raw_buffer_store_b128(w1, rs, row_off + k * 8 + 16, 0, kAuxAgent);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128(w0, rs, row_off + k * 8, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(w1, rs, row_off + k * 8 + 16, 0, 0);
-        }
-    }
+// The address is a lane offset that a kernel forms once (exch_lane_off) and a uniform offset: buffer, group and gate.
+__device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, i32x2 w, bool far) {
+    if (far) __builtin_amdgcn_raw_buffer_store_b64(w, rs, lane_off, off, kAuxAgent);
+    else __builtin_amdgcn_raw_buffer_store_b64(w, rs, lane_off, off, 0);
 }
-
-// A wave publishes its 16 units of the group's BT rows: with BT < 16 the lanes c < BT collect the four consecutive
+__device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, i32x4 w, bool far) {
+    if (far) __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, kAuxAgent);
+    else __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, 0);
+}
+// A wave publishes its 16 units (from k_wave on) of the group's BT rows: with BT < 16 the lanes c < BT collect the four consecutive
 // units 4q..4q+3 of their batch row first (every lane holds fewer values there), the other lanes' stores are dropped.
+template <bool BF16, int BT> __device__ __forceinline__ uint32_t exch_lane_off(const LaneMap<BT>& lm, uint32_t xrow, int k_wave) {
+    return lm.c < BT ? (uint32_t)lm.c * xrow + (uint32_t)(k_wave + 4 * lm.quad) * (BF16 ? 2 : 4) : 0x80000000u;
+}
 template <bool BF16, int BT, int PP>
-__device__ __forceinline__ void publish_tile(__amdgpu_buffer_rsrc_t rs, uint32_t group_off, uint32_t xrow, const LaneMap<BT>& lm, int k_wave,
-                                             const float (&v)[PP], uint32_t stamp, bool far) {
+__device__ __forceinline__ void publish_tile(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, const float (&v)[PP], bool far) {
     float v4[4];
     expand_tile<BT, PP>(v, v4);
-    const uint32_t row_off = lm.c < BT ? group_off + (uint32_t)lm.c * xrow : 0x80000000u;
-    publish4<BF16>(rs, row_off, k_wave + 4 * lm.quad, v4, stamp, far);
+    if constexpr (BF16) {
+        store_words(rs, lane_off, off, i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, far);
+    } else {
+        const i32x4 w = __builtin_bit_cast(i32x4, f32x4{v4[0], v4[1], v4[2], v4[3]});
+        store_words(rs, lane_off, off, i32x4{exch_word((uint32_t)w[0]), exch_word((uint32_t)w[1]), exch_word((uint32_t)w[2]), exch_word((uint32_t)w[3])}, far);
+    }
 }
+// ... and takes the same words back (off: as in publish_tile)
+template <bool BF16> __device__ __forceinline__ void clear_tile(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, bool far) {
+    constexpr int none = (int)kNoWord;
+    if constexpr (BF16) store_words(rs, lane_off, off, i32x2{none, none}, far);
+    else store_words(rs, lane_off, off, i32x4{none, none, none, none}, far);
+}
+// Backward without contraction slices: the workgroup's threads take its words back in 16-byte chunks, one store or two (each wave for
+// its own 16 units of every gate: G narrow ones: sLSTM 8 x 256, 32 rows, 2048 steps 7663 us instead of 7062; the kernels with slices have no register left for the offsets).  The member's
+// NWU waves publish NWU * 16 consecutive units, G times per row, D units apart.
+template <bool BF16, int BT, int G> struct Clearer {
+    static constexpr uint32_t kEsz = BF16 ? 2 : 4, kDrop = 0x80000000u;
+    static constexpr int N = (BT * G * (int)kEsz + 63) / 64;   // NWU * kEsz chunks per row and gate over 64 * NWU threads
+    uint32_t off[N];
+    bool some;   // this wave has a chunk
+    __device__ __forceinline__ Clearer(uint32_t tid, uint32_t NWU, uint32_t D, uint32_t member, uint32_t xrow) {
+        const uint32_t NT = NWU * 64, per = NWU * kEsz, total = BT * G * per;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t idx = tid + (uint32_t)j * NT, seg = idx / per, ch = idx % per;
+            off[j] = idx < total ? (seg / G) * xrow + ((seg % G) * D + member * NWU * 16) * kEsz + ch * 16 : kDrop;
+        }
+        some = (tid & ~63u) < total;
+    }
+    __device__ __forceinline__ void clear(__amdgpu_buffer_rsrc_t rs, uint32_t buf_off, bool far) const {
+        constexpr int none = (int)kNoWord;
+        if (!some) return;
+#pragma unroll
+        for (int j = 0; j < N; ++j) store_words(rs, off[j], buf_off, i32x4{none, none, none, none}, far);
+    }
+};
 
 // KC consecutive k-steps (64 bytes apart) of the B operand, read by the lanes of the valid batch columns only, under one
 // execution mask.  The other lanes' registers keep whatever they held: a column of the B operand only reaches the same
@@ -523,11 +556,12 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     char* hbuf = smem;                                          // !MULTI: [2][BT][HP] operand rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));            // MULTI: one operand buffer [BT][HP], then (KS > 1) the partial sums
     __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(p.exch, 0, 0x7FFFFFFF, 0x00020000);
-    constexpr uint32_t XROW = DK * (BF16 ? 4 : 8);             // bytes per exchange row
+    constexpr uint32_t XROW = DK * ESZ;                        // bytes per exchange row
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;     // this group's BT rows inside one buffer
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;        // bytes per buffer
+    const uint32_t xlane = exch_lane_off<BF16, BT>(lm, XROW, e_wave);
     bool failed = false;
-    const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)p.D * (BF16 ? 4 : 8) / 16, XROW, HP * ESZ);
+    const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)p.D * ESZ / 16, XROW, HP * ESZ);
     FRNN_TRACE_BEGIN();
 
     // uniform strides in bytes
@@ -602,7 +636,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
         } else {
             if (ks == 0 && T > 0) {
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T;
-                publish_tile<BF16, BT, PP>(xr, (cnt & 1u) * xbuf + xgroup, XROW, lm, e_wave, st[0][0], cnt + 1u, p.spread != 0);
+                publish_tile<BF16, BT, PP>(xr, xlane, (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
             }
         }
 
@@ -651,10 +685,11 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                 FRNN_TRACE_MARK(0);
                 __syncthreads();   // every wave has read the previous step's rows
                 FRNN_TRACE_MARK(1);
-                if (!failed) failed = !poller.poll(xr, (cnt & 1u) * xbuf + xgroup, hbuf, cnt + 1u, p.spin_limit, p.err, FRNN_TRACE_FIRST);
+                if (!failed) failed = !poller.poll(xr, (cnt & 3u) * xbuf + xgroup, hbuf, p.spin_limit, p.err, FRNN_TRACE_FIRST);
                 FRNN_TRACE_SPLIT(7, 2);
                 __syncthreads();
                 FRNN_TRACE_MARK(3);
+                if (KS == 1 || ks == 0) clear_tile<BF16>(xr, xlane, ((cnt + 3u) & 3u) * xbuf + xgroup, p.spread != 0);
                 prefetch_inputs();
 #pragma unroll
                 for (int kc = 0; kc < KT; kc += KC) {
@@ -704,7 +739,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                         // Under a condition the compiler could no longer count this store among the memory operations behind the
                         // input prefetch, and the wait for the prefetched inputs below would wait for its acknowledgement as well.)
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)t;
-                        publish_tile<BF16, BT, PP>(xr, t < T ? (cnt & 1u) * xbuf + xgroup : 0x80000000u, XROW, lm, e_wave, st[0][0], cnt + 1u, p.spread != 0);
+                        publish_tile<BF16, BT, PP>(xr, xlane | (t < T ? 0u : 0x80000000u), (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
                     }
                 }
                 if constexpr (MULTI) FRNN_TRACE_MARK(5);
@@ -784,11 +819,13 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     char* gbuf = smem;          // !MULTI: [2][BT][HP] gate-gradient rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));  // MULTI: one operand buffer [16][HP], then (KS > 1) the partial sums
     __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(p.exch, 0, 0x7FFFFFFF, 0x00020000);
-    constexpr uint32_t XROW = DK * (BF16 ? 4 : 8);
+    constexpr uint32_t XROW = DK * ESZ;
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;
+    const uint32_t xlane = exch_lane_off<BF16, BT>(lm, XROW, e_wave);
+    const Clearer<BF16, BT, G> clearer(threadIdx.x, (uint32_t)p.NWU, (uint32_t)D, (uint32_t)bm.member, XROW);
     bool failed = false;
-    const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)(G * p.D) * (BF16 ? 4 : 8) / 16, XROW, HP * ESZ);
+    const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)(G * p.D) * ESZ / 16, XROW, HP * ESZ);
     FRNN_TRACE_BEGIN();
 
     const uint32_t HD = (uint32_t)NH * D;
@@ -962,7 +999,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(T - t);
 #pragma unroll
                         for (int g2 = 0; g2 < G; ++g2)
-                            publish_tile<BF16, BT, PP>(xr, (cnt & 1u) * xbuf + xgroup, XROW, lm, g2 * D + e_wave, dg[g2], cnt + 1u, p.spread != 0);
+                            publish_tile<BF16, BT, PP>(xr, xlane, (cnt & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, dg[g2], p.spread != 0);
                     }
                     if constexpr (!kOutRows) {
 #pragma unroll
@@ -993,10 +1030,16 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                 FRNN_TRACE_MARK(0);
                 __syncthreads();   // every wave has read the previous step's rows
                 FRNN_TRACE_MARK(1);
-                if (!failed) failed = !poller.poll(xr, (cnt & 1u) * xbuf + xgroup, gbuf, cnt + 1u, p.spin_limit, p.err, FRNN_TRACE_FIRST);
+                if (!failed) failed = !poller.poll(xr, (cnt & 3u) * xbuf + xgroup, gbuf, p.spin_limit, p.err, FRNN_TRACE_FIRST);
                 FRNN_TRACE_SPLIT(7, 2);
                 __syncthreads();
                 FRNN_TRACE_MARK(3);
+                if constexpr (KS == 1) {
+                    clearer.clear(xr, ((cnt + 3u) & 3u) * xbuf + xgroup, p.spread != 0);
+                } else if (ks == 0) {
+#pragma unroll
+                    for (int g2 = 0; g2 < G; ++g2) clear_tile<BF16>(xr, xlane, ((cnt + 3u) & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, p.spread != 0);
+                }
                 if (KS == 1 || ks == 0) load_step(t > 1 ? t - 1 : 1, t > 2, cvn, scn, spn, dhn);
                 i32x4 out_v[NBO];
                 if constexpr (kOutRows) {

@@ -412,9 +412,9 @@ __global__ void sum_slices2_kernel(const float* __restrict__ part1, float* __res
     *(f32x4*)(out + j) = a;
 }
 
-__global__ void fill_zero_kernel(uint32_t* __restrict__ p, size_t count) {
+__global__ void fill_kernel(uint32_t* __restrict__ p, size_t count, uint32_t word) {
     const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < count) p[j] = 0u;
+    if (j < count) p[j] = word;
 }
 
 // Packed copies of R for the persistent kernels (made once per call, R is read once per launch):
@@ -538,10 +538,10 @@ hipError_t launch_sum_slices(const float* part, float* out, size_t count, int NS
     return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
+hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t stream) {
     const size_t count = bytes / 4;
     if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, (uint32_t*)p, count);
+    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, (uint32_t*)p, count, word);
     return hipGetLastError();
 }
 

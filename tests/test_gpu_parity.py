@@ -275,6 +275,29 @@ def test_split_groups_on_small_batch_tiles(cell, bt, dtype, D, env):
     _check(w, e, with_dlast=True)
 
 
+@pytest.mark.parametrize("dtype,D,env", [
+    ("bf16", 256, {}), ("bf16", 128, {"FLASHRNN_KS": "4"}), ("bf16", 64, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "8"}), ("f32", 192, {}),
+])
+def test_split_groups_pass_every_nan_pattern_on(dtype, D, env):
+    """The exchange buffers of a split head mark a missing word by the NaN of all ones: that value in a caller's data must reach the
+    other workgroups as a NaN (no wait that never ends), and leave the other batch rows as they are, bit for bit."""
+    e = {"FLASHRNN_MULTI": "1", "FLASHRNN_BT": "4"}
+    e.update(env)
+    os.environ.update(e)
+    w = Workload(f"nan_{dtype}_D{D}", CELL_LSTM, 9, 8, 1, D, dtype, True, bias="uniform0.1", init="uniform0.1", seed=D)
+    inp = synth.make_inputs(w)
+    ones = np.array([0xFFFFFFFF], dtype=np.uint32).view(np.float32)[0]
+    bad = {k: None if v is None else v.copy() for k, v in inp.items()}
+    bad["states0"][0, 2] = ones          # h_0 of row 2
+    bad["dH"][5, 5, 0] = ones            # a gradient of row 5
+    got, ref = pu.run_gpu(w, bad), pu.run_gpu(w, inp)   # (flashrnn_check after every call: no time-out)
+    assert np.isnan(got["states"][1:, :, 2]).all() and np.isnan(got["dWx"][:6, 5]).all()
+    rows = [r for r in range(8) if r != 2]
+    assert np.array_equal(got["states"][:, :, rows], ref["states"][:, :, rows])
+    rows.remove(5)
+    assert np.array_equal(got["dWx"][:, rows], ref["dWx"][:, rows]) and np.array_equal(got["dstates0"][:, rows], ref["dstates0"][:, rows])
+
+
 LARGE_CASES = [
     # (dtype, D, environment, batch): staged tile kernels, generic kernels, a head split over workgroups (with and
     # without contraction slices), f32 single and split

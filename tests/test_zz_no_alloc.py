@@ -1,7 +1,7 @@
 """The entry point that allocates nothing: flashrnn_fwd_static_scratch works in the library's static device array
 instead of a caller's workspace.  Same kernels as flashrnn_fwd, so the outputs must agree bit for bit (and with the
 oracle within the usual tolerance).  Two calls in a row, the second one smaller: the array keeps the first call's
-content, and everything the second call needs cleared (exchange stamps, error words) it must clear itself."""
+content, and everything the second call needs cleared (exchange words, error words) it must clear itself."""
 import ctypes
 
 import numpy as np
