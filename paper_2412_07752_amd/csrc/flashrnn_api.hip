@@ -283,7 +283,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
                     pl.DK = best->KT * best->KS * kstep;
                     const int nt = bwd ? 1 : G;
                     // one buffer of BT operand rows (polled once per workgroup and step), then the partial sums of the slices
-                    pl.smem = (size_t)BT * (pl.DK + (bf ? 8 : 4)) * (bf ? 2 : 4) + (best->KS > 1 ? (size_t)2 * (best->KS - 1) * chosen * nt * 4 * 64 * 4 : 16);
+                    pl.smem = (size_t)BT * (pl.DK + operand_pad(bf, bf && BT < 16)) * (bf ? 2 : 4) + (best->KS > 1 ? (size_t)2 * (best->KS - 1) * chosen * nt * 4 * 64 * 4 : 16);
                     pl.exch_bytes = (size_t)4 * gpar * BT * pl.DK * (bf ? 2 : 4);   // four buffers
                 }
             }
@@ -310,7 +310,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             }
             if (!best || units16 > budget) continue;
             const int dk = best->KT * best->KS * kstep, nt = bwd ? 1 : G;
-            const size_t smem = (size_t)BT * (dk + 8) * 2 + (size_t)2 * 3 * nt * 4 * 64 * 4;
+            const size_t smem = (size_t)BT * (dk + operand_pad(true, BT < 16)) * 2 + (size_t)2 * 3 * nt * 4 * 64 * 4;
             if (smem > kLdsBytes || (!spills_ok && kernel_spills(best->fn))) continue;
             const int NG = d->NH * ((d->B + BT - 1) / BT);
             int gpar = budget / units16;

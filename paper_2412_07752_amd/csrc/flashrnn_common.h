@@ -81,6 +81,9 @@ __host__ __device__ inline TileLds tile_lds(int BT, int G, int S, int D, int NT,
 // LDS layout of the backward tile kernel (bf16 I/O, one workgroup per group, BT < 16, NT = 4 * D threads).
 // The input images are filled by loads that write LDS directly: a wave's 64 chunks of 16 bytes land
 // back to back, so these images are plain arrays of chunks (no row padding), each rounded up to whole waves.
+// elements between the operand rows of the kernels with plain rows, beyond the contraction length: 16 bytes, or 32 where the sparse
+// instruction's lanes read two 16-byte pieces of each of 4 or 8 rows at once (all in different banks then)
+__host__ __device__ constexpr int operand_pad(bool bf16, bool sparse) { return sparse ? 16 : bf16 ? 8 : 4; }
 struct TileLdsBwd {
     uint32_t hp;                 // operand (gate-gradient) row pitch, buf = BT * hp, two buffers
     uint32_t rp_io;              // row pitch of the output image (bf16 rows)
@@ -224,7 +227,7 @@ __device__ __forceinline__ float sum_quad_slices(const f32x4& a, int c) {
 
 // The inverse of compact_tile for one value per pair: the lanes c < BT of a row collect the four consecutive
 // units 4q..4q+3 of their batch slot from the lanes that computed them (valid in those lanes only).
-template <int BT, int PP> __device__ __forceinline__ void expand_tile(const float (&v)[PP], float (&out)[4]) {
+template <int BT, int PP, bool SPARSE = false> __device__ __forceinline__ void expand_tile(const float (&v)[PP], float (&out)[4]) {
     auto shl = [](float x, auto n) {   // lane i takes the value of lane i + n of its row
         constexpr int N = decltype(n)::value;
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x100 + N, 0xF, 0xF, false));
@@ -232,6 +235,15 @@ template <int BT, int PP> __device__ __forceinline__ void expand_tile(const floa
     if constexpr (BT == 16) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) out[i] = v[i];
+    } else if constexpr (SPARSE && BT == 8) {   // (after the sparse instruction consecutive units lie in neighbouring lanes: see LaneMap)
+        out[0] = v[0]; out[1] = v[1];
+        out[2] = shl(v[0], std::integral_constant<int, 2>{});
+        out[3] = shl(v[1], std::integral_constant<int, 2>{});
+    } else if constexpr (SPARSE) {
+        out[0] = v[0];
+        out[1] = shl(v[0], std::integral_constant<int, 1>{});
+        out[2] = shl(v[0], std::integral_constant<int, 2>{});
+        out[3] = shl(v[0], std::integral_constant<int, 3>{});
     } else if constexpr (BT == 8) {
         out[0] = v[0]; out[1] = v[1];
         out[2] = shl(v[0], std::integral_constant<int, 8>{});

@@ -204,13 +204,16 @@ template <int N> __device__ __forceinline__ void pin(float (&v)[N]) {
 // ---------------------------------------------------------------------------------------------
 // common per-lane geometry
 // ---------------------------------------------------------------------------------------------
-template <int BT> struct LaneMap {
+// SPARSE: the places after the sparse matrix instruction (sparse_pairs below).
+template <int BT, bool SPARSE = false> struct LaneMap {
     static constexpr int PP = BT / 4;  // (unit, batch row) pairs per lane and tile
     int c, quad, bslot, uoff;
     __device__ __forceinline__ LaneMap(int lane) {
         c = lane & 15;
         quad = lane >> 4;
-        if constexpr (BT == 16) { bslot = c; uoff = 4 * quad; }
+        if constexpr (SPARSE && BT == 8) { bslot = quad + 4 * (c & 1); uoff = c & ~1; }
+        else if constexpr (SPARSE) { bslot = quad; uoff = c; }
+        else if constexpr (BT == 16) { bslot = c; uoff = 4 * quad; }
         else if constexpr (BT == 8) { bslot = c & 7; uoff = 4 * quad + 2 * (c >> 3); }
         else { bslot = c & 3; uoff = 4 * quad + (c >> 2); }
     }
@@ -372,15 +375,15 @@ __device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t rs, uint32_t 
     if (far) __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, kAuxAgent);
     else __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, 0);
 }
-// A wave publishes its 16 units (from k_wave on) of the group's BT rows: with BT < 16 the lanes c < BT collect the four consecutive
-// units 4q..4q+3 of their batch row first (every lane holds fewer values there), the other lanes' stores are dropped.
-template <bool BF16, int BT> __device__ __forceinline__ uint32_t exch_lane_off(const LaneMap<BT>& lm, uint32_t xrow, int k_wave) {
-    return lm.c < BT ? (uint32_t)lm.c * xrow + (uint32_t)(k_wave + 4 * lm.quad) * (BF16 ? 2 : 4) : 0x80000000u;
+// A wave publishes its 16 units (from k_wave on) of the group's BT rows: with BT < 16 the lanes whose first unit is a multiple of four
+// collect it and the three units behind it first (every lane holds fewer values there), the other lanes' stores are dropped.
+template <bool BF16, int BT, bool SP> __device__ __forceinline__ uint32_t exch_lane_off(const LaneMap<BT, SP>& lm, uint32_t xrow, int k_wave) {
+    return (lm.uoff & 3) == 0 ? (uint32_t)lm.bslot * xrow + (uint32_t)(k_wave + lm.uoff) * (BF16 ? 2 : 4) : 0x80000000u;
 }
-template <bool BF16, int BT, int PP>
+template <bool BF16, int BT, int PP, bool SP>
 __device__ __forceinline__ void publish_tile(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, const float (&v)[PP], bool far) {
     float v4[4];
-    expand_tile<BT, PP>(v, v4);
+    expand_tile<BT, PP, SP>(v, v4);
     if constexpr (BF16) {
         store_words(rs, lane_off, off, i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, far);
     } else {
@@ -438,6 +441,59 @@ template <int BT, int KC, bool MASKED> __device__ __forceinline__ void lds_opera
         }
 #pragma unroll
         for (int j = 0; j < KC; ++j) out[j] = __builtin_bit_cast(bf16x8, raw[j]);
+    }
+}
+
+// Split groups with bf16 batch tiles of 4 or 8 rows run the recurrent products on the sparse matrix instruction (SparseLane), like the
+// staged kernels: half the matrix instructions and half the operand reads, which were a third of a step.  (sLSTM 8 x 256, 32 rows, 2048 steps
+// forward + backward 7062 -> 6040 us, 3 x 256 with recompute 3400 -> 2962, LSTM 1 x 768, 16 rows, 1024 steps forward 1584 -> 1171.)
+template <bool BF16, int BT, bool MULTI> constexpr bool kSparseTiles = BF16 && MULTI && BT < 16;
+// dense operand of one 64-index step: R row of the lane's unit (contraction index contiguous), KT steps of 32 in all
+template <int KT> __device__ __forceinline__ bf16x16 load_sparse_dense(const uint16_t* row, int kc, int quad) {
+    i32x4 piece[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (2 * kc + h >= KT) { piece[h] = i32x4{0, 0, 0, 0}; continue; }
+        const uint16_t* q = row + (2 * kc + h) * 32 + sparse_k(quad);
+        piece[h] = sparse_piece(*(const i32x2*)q, *(const i32x2*)(q + 8));
+    }
+    return sparse_dense(piece[0], piece[1]);
+}
+// N consecutive 64-index steps (from kc on, of NK; the last one holds 32 indices if HALF) of the h / dg operand.  With 4 rows the
+// rows j = 1 of the operand need no values (their results are never used): their lanes read nothing, as in lds_operand_chunk.
+template <int BT, int N, int NK, bool HALF, bool MASKED>
+__device__ __forceinline__ void lds_sparse_chunk(const char* p, const SparseLane<BT>& sl, int kc, bf16x8 (&out)[N]) {
+    i32x4 raw[N];
+    auto read = [&]() {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (kc + j < NK) raw[j] = *(const i32x4*)(p + (kc + j) * 128 + (HALF && kc + j == NK - 1 ? sl.rbyte_half() : sl.rbyte));
+    };
+    if constexpr (BT == 4 && MASKED) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) asm volatile("" : "=v"(raw[j]));
+        if ((sl.c & 2) == 0) read();
+    } else {
+        read();
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        if (HALF && kc + j == NK - 1) raw[j] = sl.quad < 2 ? raw[j] : i32x4{0, 0, 0, 0};   // (the weights there are zero: whatever else is read must not turn that into a NaN)
+        out[j] = __builtin_bit_cast(bf16x8, raw[j]);
+    }
+}
+// The (unit, batch slot) pairs from the sparse instruction's accumulators: lane (c, quad) holds unit c of the slots quad (registers
+// 0 + 1) and, with 8 rows, quad + 4 (2 + 3).  There two neighbours trade, so that each lane has two consecutive units of one slot.
+template <int BT> __device__ __forceinline__ void sparse_pairs(f32x4& a, int c) {
+    const float y0 = a[0] + a[1];
+    if constexpr (BT == 4) {
+        a[0] = y0;
+    } else {
+        const float y1 = a[2] + a[3];
+        const bool odd = (c & 1) != 0;
+        const float got = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, odd ? y0 : y1), 0xB1, 0xF, 0xF, false));
+        a[0] = odd ? got : y0;
+        a[1] = odd ? y1 : got;
     }
 }
 
@@ -507,6 +563,36 @@ __device__ __forceinline__ void reduce_slices(float* red, int parity, int ks, in
     }
 }
 
+// the same for the pairs of the sparse tiles: NT * PP values per lane, all lanes valid
+template <int NT, int KS, int PP>
+__device__ __forceinline__ void reduce_pairs(float* red, int parity, int ks, int wu, int NWU, int lane, f32x4 (&acc)[NT]) {
+    if constexpr (KS > 1) {
+        constexpr int NV = NT * PP, V = NV % 4 == 0 ? 4 : NV % 2 == 0 ? 2 : 1;   // values per access
+        typedef __attribute__((__vector_size__(V * sizeof(float)))) float vec;
+        auto at = [&](int s, int j) { return (vec*)(red + ((((size_t)(parity * (KS - 1) + s - 1) * NWU + wu) * (NV / V) + j) * 64 + lane) * V); };
+        if (ks > 0) {
+#pragma unroll
+            for (int j = 0; j < NV / V; ++j) {
+                vec v;
+#pragma unroll
+                for (int x = 0; x < V; ++x) v[x] = acc[(j * V + x) / PP][(j * V + x) % PP];
+                *at(ks, j) = v;
+            }
+        }
+        __syncthreads();
+        if (ks == 0) {
+#pragma unroll
+            for (int s = 1; s < KS; ++s)
+#pragma unroll
+                for (int j = 0; j < NV / V; ++j) {
+                    const vec v = *at(s, j);
+#pragma unroll
+                    for (int x = 0; x < V; ++x) acc[(j * V + x) / PP][(j * V + x) % PP] += v[x];
+                }
+        }
+    }
+}
+
 // =============================================================================================
 // forward
 // =============================================================================================
@@ -531,7 +617,9 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     constexpr int PP = BT / 4;
     constexpr int ESZ = BF16 ? 2 : 4;               // element size of the I/O dtype and of LDS operand rows
     constexpr int DK = KT * KS * OP::KSTEP;         // padded contraction length
-    constexpr int HP = DK + (BF16 ? 8 : 4);         // LDS row pitch in elements
+    constexpr bool SP = kSparseTiles<BF16, BT, MULTI>;
+    constexpr int NKS = (KT + 1) / 2, KCS = NKS <= 6 ? NKS : NKS % 6 == 0 ? 6 : NKS % 4 == 0 ? 4 : NKS % 5 == 0 ? 5 : 6;  // sparse steps of 64 indices, and how many are read at a time
+    constexpr int HP = DK + operand_pad(BF16, SP);         // LDS row pitch in elements
     constexpr int BUF = BT * HP * ESZ;              // bytes of one LDS operand buffer
     constexpr int KC = poll_chunk<BF16>(KT);
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
@@ -545,7 +633,8 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wu = w % p.NWU, ks = w / p.NWU;
     stagger_waves(w);
-    const LaneMap<BT> lm(lane);
+    const LaneMap<BT, SP> lm(lane);
+    const SparseLane<BT == 8 ? 8 : 4> sl(lane);
     const int T = p.T, B = p.B, NH = p.NH, D = p.D;
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;  // first unit of this wave
     const int e0 = e_wave + lm.uoff;                    // first unit of this lane's pairs
@@ -559,7 +648,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     constexpr uint32_t XROW = DK * ESZ;                        // bytes per exchange row
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;     // this group's BT rows inside one buffer
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;        // bytes per buffer
-    const uint32_t xlane = exch_lane_off<BF16, BT>(lm, XROW, e_wave);
+    const uint32_t xlane = exch_lane_off<BF16, BT, SP>(lm, XROW, e_wave);
     bool failed = false;
     const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)p.D * ESZ / 16, XROW, HP * ESZ);
     FRNN_TRACE_BEGIN();
@@ -581,15 +670,20 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
         const int n = gid % NH, q = gid / NH;
         // ---- load once per group: R fragments (A operand: row = unit e_wave + c) and bias; they stay
         // in registers for all T steps
-        op_t Rf[EB][G][KT];
+        op_t Rf[EB][G][SP ? 1 : KT];
+        bf16x16 Rs[G][SP ? NKS : 1];
         float bias[EB][G][PP];
 #pragma unroll
         for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const size_t rrow = (((size_t)n * G + g) * D + e_wave + 16 * eb + arow) * DK;
+            if constexpr (SP) {
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
+                for (int kc = 0; kc < NKS; ++kc) Rs[g][kc] = load_sparse_dense<KT>((const uint16_t*)p.R + rrow + k0, kc, lm.quad);
+            }
+#pragma unroll
+            for (int kt = 0; kt < (SP ? 0 : KT); ++kt) {
                 if constexpr (BF16) Rf[eb][g][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
                 else Rf[eb][g][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
             }
@@ -636,7 +730,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
         } else {
             if (ks == 0 && T > 0) {
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T;
-                publish_tile<BF16, BT, PP>(xr, xlane, (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
+                publish_tile<BF16, BT, PP, SP>(xr, xlane, (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
             }
         }
 
@@ -691,8 +785,20 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                 FRNN_TRACE_MARK(3);
                 if (KS == 1 || ks == 0) clear_tile<BF16>(xr, xlane, ((cnt + 3u) & 3u) * xbuf + xgroup, p.spread != 0);
                 prefetch_inputs();
+                if constexpr (SP) {
 #pragma unroll
-                for (int kc = 0; kc < KT; kc += KC) {
+                    for (int kc = 0; kc < NKS; kc += KCS) {
+                        bf16x8 hS[KCS];
+                        lds_sparse_chunk<BT, KCS, NKS, (KT & 1) != 0, (KT >= 8)>(hbuf + (uint32_t)sl.rslot * HP * ESZ + (uint32_t)k0 * ESZ, sl, kc, hS);
+#pragma unroll
+                        for (int j = 0; j < KCS; ++j)
+#pragma unroll
+                            for (int g = 0; g < G; ++g)
+                                if (kc + j < NKS) acc[g] = smfmac(hS[j], Rs[g][kc + j], acc[g], sl.idx);
+                    }
+                }
+#pragma unroll
+                for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
                     op_t hB[KC];
                     if constexpr (BF16) {
                         // (forward: worth it from 8 k-steps per wave on; with shorter rows the LDS is not what bounds the step)
@@ -707,7 +813,13 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                         for (int g = 0; g < G; ++g) acc[g] = mfma_step<BF16, BT>(Rf[0][g][kc + j], hB[j], acc[g]);
                 }
             }
-            reduce_slices<G, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, acc);
+            if constexpr (SP) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) sparse_pairs<BT>(acc[g], lm.c);
+                reduce_pairs<G, KS, PP>(red, t & 1, ks, wu, p.NWU, lane, acc);
+            } else {
+                reduce_slices<G, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, acc);
+            }
 #ifdef FLASHRNN_TRACE
             if constexpr (MULTI) { asm volatile("" : "+v"(acc[0]), "+v"(acc[G - 1]) : : "memory"); FRNN_TRACE_MARK(4); }
 #endif
@@ -717,7 +829,8 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb) {
 #pragma unroll
-                    for (int g = 0; g < G; ++g) finish_tile<BF16, BT>(accs[eb][g], lm.c);
+                    for (int g = 0; g < G; ++g)
+                        if constexpr (!SP) finish_tile<BF16, BT>(accs[eb][g], lm.c);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) {
                         float wxi[G], ybi[G], sti[S], cvi[NC];
@@ -739,7 +852,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                         // Under a condition the compiler could no longer count this store among the memory operations behind the
                         // input prefetch, and the wait for the prefetched inputs below would wait for its acknowledgement as well.)
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)t;
-                        publish_tile<BF16, BT, PP>(xr, xlane | (t < T ? 0u : 0x80000000u), (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
+                        publish_tile<BF16, BT, PP, SP>(xr, xlane | (t < T ? 0u : 0x80000000u), (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
                     }
                 }
                 if constexpr (MULTI) FRNN_TRACE_MARK(5);
@@ -794,7 +907,9 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     constexpr int PP = BT / 4;
     constexpr int ESZ = BF16 ? 2 : 4;
     constexpr int DK = KT * KS * OP::KSTEP;
-    constexpr int HP = DK + (BF16 ? 8 : 4);
+    constexpr bool SP = kSparseTiles<BF16, BT, MULTI>;
+    constexpr int NKS = (KT + 1) / 2, KCS = NKS <= 6 ? NKS : NKS % 6 == 0 ? 6 : NKS % 4 == 0 ? 4 : NKS % 5 == 0 ? 5 : 6;  // sparse steps of 64 indices, and how many are read at a time
+    constexpr int HP = DK + operand_pad(BF16, SP);
     constexpr int BUF = BT * HP * ESZ;
     constexpr int KC = poll_chunk<BF16>(KT);
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
@@ -808,7 +923,8 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wu = w % p.NWU, ks = w / p.NWU;
     stagger_waves(w);
-    const LaneMap<BT> lm(lane);
+    const LaneMap<BT, SP> lm(lane);
+    const SparseLane<BT == 8 ? 8 : 4> sl(lane);
     const int T = p.T, B = p.B, NH = p.NH, D = p.D;
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;
     const int e0 = e_wave + lm.uoff;
@@ -822,7 +938,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     constexpr uint32_t XROW = DK * ESZ;
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;
-    const uint32_t xlane = exch_lane_off<BF16, BT>(lm, XROW, e_wave);
+    const uint32_t xlane = exch_lane_off<BF16, BT, SP>(lm, XROW, e_wave);
     const Clearer<BF16, BT, G> clearer(threadIdx.x, (uint32_t)p.NWU, (uint32_t)D, (uint32_t)bm.member, XROW);
     bool failed = false;
     const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)(G * p.D) * ESZ / 16, XROW, HP * ESZ);
@@ -842,12 +958,17 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
         const int n = gid % NH, q = gid / NH;
         // ---- load once per group: R fragments, A operand row = previous-state index d = e_wave + c
-        op_t Rf[EB][KT];
+        op_t Rf[EB][SP ? 1 : KT];
+        bf16x16 Rs[SP ? NKS : 1];
 #pragma unroll
         for (int eb = 0; eb < EB; ++eb) {
             const size_t rrow = ((size_t)n * D + e_wave + 16 * eb + arow) * DK;
+            if constexpr (SP) {
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
+                for (int kc = 0; kc < NKS; ++kc) Rs[kc] = load_sparse_dense<KT>((const uint16_t*)p.R + rrow + k0, kc, lm.quad);
+            }
+#pragma unroll
+            for (int kt = 0; kt < (SP ? 0 : KT); ++kt) {
                 if constexpr (BF16) Rf[eb][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
                 else Rf[eb][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
             }
@@ -999,7 +1120,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(T - t);
 #pragma unroll
                         for (int g2 = 0; g2 < G; ++g2)
-                            publish_tile<BF16, BT, PP>(xr, xlane, (cnt & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, dg[g2], p.spread != 0);
+                            publish_tile<BF16, BT, PP, SP>(xr, xlane, (cnt & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, dg[g2], p.spread != 0);
                     }
                     if constexpr (!kOutRows) {
 #pragma unroll
@@ -1046,8 +1167,18 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
 #pragma unroll
                     for (int j = 0; j < NBO; ++j) out_v[j] = *(const i32x4*)(gbuf + out_l[j]);
                 }
+                if constexpr (SP) {
 #pragma unroll
-                for (int kc = 0; kc < KT; kc += KC) {
+                    for (int kc = 0; kc < NKS; kc += KCS) {
+                        bf16x8 gS[KCS];
+                        lds_sparse_chunk<BT, KCS, NKS, (KT & 1) != 0, true>(gbuf + (uint32_t)sl.rslot * HP * ESZ + (uint32_t)k0 * ESZ, sl, kc, gS);
+#pragma unroll
+                        for (int j = 0; j < KCS; ++j)
+                            if (kc + j < NKS) a4[0][(kc + j) % NA] = smfmac(gS[j], Rs[kc + j], a4[0][(kc + j) % NA], sl.idx);
+                    }
+                }
+#pragma unroll
+                for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
                     op_t gB[KC];
                     if constexpr (BF16) {
                         lds_operand_chunk<BT, KC, true>(gbuf + lds_row + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, lm.c, gB);
@@ -1070,14 +1201,19 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                 if constexpr (NA == 4) accs[eb][0] = (a4[eb][0] + a4[eb][1]) + (a4[eb][2] + a4[eb][3]);
                 else accs[eb][0] = a4[eb][0] + a4[eb][1];
             }
-            reduce_slices<1, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
+            if constexpr (SP) {
+                sparse_pairs<BT>(accs[0][0], lm.c);
+                reduce_pairs<1, KS, PP>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
+            } else {
+                reduce_slices<1, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
+            }
 #ifdef FLASHRNN_TRACE
             if constexpr (MULTI) { asm volatile("" : "+v"(accs[0][0]) : : "memory"); FRNN_TRACE_MARK(4); }
 #endif
             if (KS == 1 || ks == 0) {
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb) {
-                    finish_tile<BF16, BT>(accs[eb][0], lm.c);
+                    if constexpr (!SP) finish_tile<BF16, BT>(accs[eb][0], lm.c);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) ds[eb][0][i] += fminf(fmaxf(accs[eb][0][i], -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
                 }

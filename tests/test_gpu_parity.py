@@ -291,7 +291,8 @@ def test_split_groups_pass_every_nan_pattern_on(dtype, D, env):
     bad["states0"][0, 2] = ones          # h_0 of row 2
     bad["dH"][5, 5, 0] = ones            # a gradient of row 5
     got, ref = pu.run_gpu(w, bad), pu.run_gpu(w, inp)   # (flashrnn_check after every call: no time-out)
-    assert np.isnan(got["states"][1:, :, 2]).all() and np.isnan(got["dWx"][:6, 5]).all()
+    assert np.isnan(got["states"][1:, :, 2]).all()
+    assert not np.isfinite(got["dWx"][:6, 5]).any()      # (an infinity where the NaN has passed the bound of the recurrent term)
     rows = [r for r in range(8) if r != 2]
     assert np.array_equal(got["states"][:, :, rows], ref["states"][:, :, rows])
     rows.remove(5)
