@@ -209,31 +209,52 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
     if (!pl.e && force_multi != 0 && force_multi != 2) {
         // Batch tiles of 16, 8 or 4 rows here too.  A smaller tile means more groups (each with its own workgroups, on its
         // own XCD when there are few) and proportionally less to exchange and less point-wise work per workgroup; the
-        // smallest tile whose groups all run at once is taken, else the largest (fewest rounds over the groups).
+        // smallest tile whose groups all run at once is taken, else the largest (fewest rounds over the groups) -- of those that come into question.
         const int want_ks = force_ks ? force_ks : (d->D >= 512 ? 4 : 1);
+        auto entry_of = [&](int BT) {
+            const KernelEntry* best = nullptr;
+            for (int spills_ok = 0; spills_ok < 2 && !best; ++spills_ok)   // a kernel that keeps registers in scratch memory only as a last resort
+            for (int i = 0; i < tab.count; ++i) {
+                const KernelEntry& e = tab.entries[i];
+                const int dk = e.KT * e.KS * kstep;
+                if (e.bwd != bwd || !e.multi || e.BT != BT || dk < kdim) continue;
+                if (e.maxw == 4 && e.KS == 4 && e.KT * (bwd ? 1 : G) >= 40) continue;   // the shapes of the spread placement
+                if (!spills_ok && kernel_spills(e.fn)) continue;
+                // least padding of the contraction axis first, then the wanted number of slices, then the most waves
+                const int bdk = best ? best->KT * best->KS * kstep : 0;
+                const bool want = e.KS == want_ks, bwant = best && best->KS == want_ks;
+                if (!best || dk < bdk || (dk == bdk && (want > bwant || (want == bwant && e.maxw > best->maxw)))) best = &e;
+            }
+            return best;
+        };
         const int bts[3] = {4, 8, 16};
+        // Only tiles whose kernels let a group run on the fewest workgroups: where the registers of a larger tile allow
+        // four waves per workgroup instead of eight, each group of it takes twice the CUs, and a smaller tile in more rounds is faster (heads of 256
+        // units: sLSTM 8 x 256, 256 steps backward, 128 rows 1618 us with 16-row tiles on 4 CUs, 1152 in two rounds of 4-row tiles on 2;
+        // LSTM 8 x 256, 128 steps, 256 rows 1485 and, with 8-row tiles, 885; sLSTM forward 1037 and 774).
+        // The sLSTM's backward pass holds the most values per row: one round of 16-row tiles is slower there than two of 8-row tiles at every size
+        // (128 steps, 4 x 384 with 256 rows 1912 and 1760 us, 4 x 512 with 128 rows 1100 and 977, 1 x 768 1448 and 1208, 2 x 1024 with 64 rows
+        // 2083 and 1833; LSTM 1 x 768 with 128 rows 1012 and 1186, GRU 3 x 640 with 80 rows 1280 and 1628, hence for this cell only).
+        int usable[3], fewest = 0;
+        for (int bi = 0; bi < 3; ++bi) {
+            const KernelEntry* e = entry_of(bts[bi]);
+            int nwu = e ? e->maxw / e->KS : 0;
+            while (nwu > 1 && units16 % nwu) --nwu;
+            usable[bi] = nwu > 0 ? units16 / nwu : 0;   // workgroups of a group
+            if (usable[bi] && (!fewest || usable[bi] < fewest)) fewest = usable[bi];
+        }
+        for (int bi = 0; bi < 3; ++bi) usable[bi] = usable[bi] && (!bf || usable[bi] == fewest);   // (float32: not measured)
+        if (bf && bwd && d->cell == FLASHRNN_SLSTM && (usable[0] || usable[1])) usable[2] = 0;
         for (int pass = 0; pass < 2 && !pl.e; ++pass) {
             for (int bi = 0; bi < 3 && !pl.e; ++bi) {
                 const int BT = pass == 0 ? bts[bi] : bts[2 - bi];
-                if (force_bt && BT != force_bt) continue;
+                if (force_bt ? BT != force_bt : !usable[pass == 0 ? bi : 2 - bi]) continue;
                 // workgroups of one launch per XCD: all members of a group must be resident at once, at most one per CU
                 // where a workgroup takes all registers of its CU.  (A head of 1024 units asks for every CU of an XCD, in both
                 // directions: with two CUs kept back the backward pass of such a head fell to one group of 16 rows at 13 us a step.)
                 int cap = cus / kXcds;
                 const int NG = d->NH * ((d->B + BT - 1) / BT);
-                const KernelEntry* best = nullptr;
-                for (int spills_ok = 0; spills_ok < 2 && !best; ++spills_ok)   // a kernel that keeps registers in scratch memory only as a last resort
-                for (int i = 0; i < tab.count; ++i) {
-                    const KernelEntry& e = tab.entries[i];
-                    const int dk = e.KT * e.KS * kstep;
-                    if (e.bwd != bwd || !e.multi || e.BT != BT || dk < kdim) continue;
-                    if (e.maxw == 4 && e.KS == 4 && e.KT * (bwd ? 1 : G) >= 40) continue;   // the shapes of the spread placement
-                    if (!spills_ok && kernel_spills(e.fn)) continue;
-                    // least padding of the contraction axis first, then the wanted number of slices, then the most waves
-                    const int bdk = best ? best->KT * best->KS * kstep : 0;
-                    const bool want = e.KS == want_ks, bwant = best && best->KS == want_ks;
-                    if (!best || dk < bdk || (dk == bdk && (want > bwant || (want == bwant && e.maxw > best->maxw)))) best = &e;
-                }
+                const KernelEntry* best = entry_of(BT);
                 if (!best) continue;
                 const int nwu_max = best->maxw / best->KS;
                 // most workgroups per group (shortest MFMA and point-wise phase per step) that still lets

@@ -240,6 +240,17 @@ def test_group_loop_when_groups_do_not_fit(cell):
     _check(w, {"FLASHRNN_MULTI": "1", "FLASHRNN_NWU": "2", "FLASHRNN_GPAR": "4"}, with_dlast=True)
 
 
+@pytest.mark.parametrize("cell,NH,D,B,bt,split", [
+    (CELL_SLSTM, 8, 256, 66, 4, 2), (CELL_SLSTM, 3, 224, 177, 4, 2), (CELL_LSTM, 8, 256, 130, 8, 2), (CELL_SLSTM, 1, 768, 65, 8, 24), (CELL_SLSTM, 2, 1024, 33, 8, 32),
+])
+def test_backward_groups_in_rounds_of_smaller_tiles(cell, NH, D, B, bt, split):
+    """Batches whose 16-row tiles would run at once, or in fewer rounds, in kernels that are slower all the same; ragged last tiles."""
+    w = Workload(f"rounds_{cell}_D{D}", cell, 5, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=B)
+    _check(w, with_dlast=True)
+    d = api.make_desc(cell, 5, B, NH, D, api.FLASHRNN_BF16)
+    assert api.flashrnn_plan_kernel(d, True)[1:] == (bt, split)
+
+
 @pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
