@@ -472,6 +472,7 @@ template <int BT> struct SparseLane {
     static constexpr int PP = BT / 4;   // (unit, batch slot) pairs per lane: slots quad + 4 i of unit c
     int c, quad, rslot, idx;
     uint32_t rbyte;                     // byte offset of this lane's elements inside 64 contraction elements of its slot's row
+    uint32_t rbyte32;                   // ... inside the 32 elements of a last half step (smfmac32)
     __device__ __forceinline__ SparseLane(int lane) {
         c = lane & 15;
         quad = lane >> 4;
@@ -479,6 +480,7 @@ template <int BT> struct SparseLane {
         rslot = (c >> 2) + (BT == 8 ? 4 * ((c >> 1) & 1) : 0);
         idx = hf ? 0xEEEE : 0x4444;
         rbyte = (uint32_t)(quad * 32 + hf * 16);
+        rbyte32 = (uint32_t)(quad * 16 + hf * 8);
     }
     __device__ __forceinline__ int slot(int i) const { return quad + 4 * i; }
     // the same where only 32 contraction elements are left: the quads of the other half re-read these (times weights of zero)
@@ -494,6 +496,20 @@ __device__ __forceinline__ bf16x16 sparse_dense(i32x4 a, i32x4 b) {
 __device__ __forceinline__ f32x4 smfmac(bf16x8 a, bf16x16 b, f32x4 c, int idx) {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a, b, c, idx, 0, 0);
+#else
+    (void)a; (void)b; (void)idx;
+    return c;
+#endif
+}
+// Where only 32 contraction elements are left (an odd number of 32-element blocks): the sparse instruction of that depth, in the staged kernels.  A
+// lane of the first operand reads the four elements 8 q + 4 hf .. + 3 of its slot's row, the dense operand's lane holds
+// sparse_piece(8 q .. + 3, 8 q + 4 .. + 7).  (Filling a step of 64 with elements that meet weights of zero makes a NaN of an infinite h or dg, and takes
+// twice the registers for R.)
+__device__ __forceinline__ f32x4 smfmac32(i32x2 a, i32x4 b, f32x4 c, int idx) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_smfmac_f32_16x16x32_bf16(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x8, b), c, idx, 0, 0);
 #else
     (void)a; (void)b; (void)idx;
     return c;

@@ -39,7 +39,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     constexpr int G = CT::G, S = CT::S, NC = CT::NC;
     constexpr int PP = BT / 4;
     constexpr int ESZ = 2;
-    constexpr int DK = KT * 32, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64 (KT odd: the last one holds 32)
+    constexpr int DK = KT * 32, NF = KT / 2, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64, and with the one of 32 that an odd KT ends with
     constexpr int NCH_IN = (BT * G + 31) / 32, NCH_ST = (BT * S + 15) / 16;
     constexpr uint32_t kDrop = 0x80000000u;
     constexpr uint32_t REC = CT::RS * ESZ;
@@ -73,7 +73,8 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
     // as it lies (two 16-byte pieces per row) and reads it back with the transposing LDS load, which hands every lane four
     // consecutive rows of its column.  The error words of the call are cleared here as well (the kernels of this file never wait on another
     // workgroup, they never set them).
-    bf16x16 Rf[G][NK];
+    bf16x16 Rf[G][NF > 0 ? NF : 1];
+    i32x4 Rh[G];   // (KT odd)
     float bias[G];
     if (gid == 0 && tid == 0) { p.err[0] = 0; p.err[1] = 0; }
     {
@@ -84,6 +85,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
         const char* src = (const char*)p.R + ((((size_t)n * D + row) * G) * D + e_wave + half * 8) * ESZ;
         const uint32_t wr = (uint32_t)row * 32 + half * 16;
         const uint32_t rd = (uint32_t)(sparse_k(lm.quad) + (lm.c >> 2)) * 32 + (lm.c & 3) * 8;
+        const uint32_t rd32 = (uint32_t)(8 * lm.quad + (lm.c >> 2)) * 32 + (lm.c & 3) * 8;
         i32x4 raw[G][KT];   // all loads in flight at once; a fragment takes the registers of the rows it was made from
 #pragma unroll
         for (int g = 0; g < G; ++g)
@@ -94,20 +96,21 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
             }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            i32x4 piece[2 * NK];
-            if constexpr (KT & 1) piece[KT] = i32x4{0, 0, 0, 0};
+            i32x4 piece[KT];
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
+                const bool half = kt == 2 * NF;   // the 32 elements of a last half step
                 // (a wave's LDS operations run in the order it issues them and the tile is its own: no barrier, only the compiler is held)
                 asm volatile("" ::: "memory");
                 *(i32x4*)(tile + wr) = raw[g][kt];
                 asm volatile("" ::: "memory");
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rd));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + rd + 8 * 32));
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (half ? rd32 : rd)));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (half ? rd32 + 4 * 32 : rd + 8 * 32)));
                 piece[kt] = sparse_piece(__builtin_bit_cast(i32x2, lo), __builtin_bit_cast(i32x2, hi));
             }
 #pragma unroll
-            for (int kc = 0; kc < NK; ++kc) Rf[g][kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
+            for (int kc = 0; kc < NF; ++kc) Rf[g][kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
+            if constexpr (KT & 1) Rh[g] = piece[KT - 1];
             float bv[1];
             load_io<true, 1>(p.bias, ((size_t)n * G + g) * D + e0, bv);
             bias[g] = bv[0];
@@ -341,10 +344,12 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
         // (the sched barriers keep the compiler from bunching it all up in front).  With a long chain (KT >= 6) that
         // work sits between the k-steps; with a short one all LDS reads go out together at the top of the step (one
         // latency) and the next inputs are parked at its end, where they have had time to arrive (measured both ways).
-        bf16x8 hB[NK];
+        bf16x8 hB[NF > 0 ? NF : 1];
+        i32x2 hH;
         const char* hrow = hbuf + (par ^ 1) * BUF + lds_rd;
 #pragma unroll
-        for (int kc = 0; kc < NK; ++kc) hB[kc] = *(const bf16x8*)(hrow + kc * 128 + ((KT & 1) && kc == NK - 1 ? lm.rbyte_half() : lm.rbyte));
+        for (int kc = 0; kc < NF; ++kc) hB[kc] = *(const bf16x8*)(hrow + kc * 128 + lm.rbyte);
+        if constexpr (KT & 1) hH = *(const i32x2*)(hrow + NF * 128 + lm.rbyte32);
         i32x4 vs[NCH_ST];
         auto side_reads = [&]() {
             read_inputs(par ^ 1);   // Wx_{t+1}
@@ -372,7 +377,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
         pin_order();
         auto product = [&](int kc) {
 #pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = smfmac(hB[kc], Rf[g][kc], acc[g], lm.idx);
+            for (int g = 0; g < G; ++g) acc[g] = kc < NF ? smfmac(hB[kc], Rf[g][kc], acc[g], lm.idx) : smfmac32(hH, Rh[g], acc[g], lm.idx);
         };
         product(0);
         pin_order();
@@ -527,7 +532,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     constexpr int G = CT::G, S = CT::S, NC = CT::NC;
     constexpr int PP = BT / 4;
     constexpr int ESZ = 2;
-    constexpr int DK = KT * 32, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64 (KT odd: the last one holds 32)
+    constexpr int DK = KT * 32, NF = KT / 2, NK = (KT + 1) / 2;   // contraction length, sparse steps of 64, and with the one of 32 that an odd KT ends with
     constexpr int NSB = CELL == CELL_SLSTM ? 2 : CELL == CELL_ELMAN ? 0 : 1;   // state rows the Jacobian needs per time level ...
     constexpr int SB0 = cell_uses_h_prev(CELL) ? 0 : 1;   // ... starting at this state
     constexpr int GO = CELL == CELL_GRU ? G + 1 : G;  // output rows per batch row: dWx (+ the recurrent-side candidate gradient)
@@ -561,15 +566,19 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     char* out_img = smem + L.out_off;
 
     // ---- R: row d = w * 16 + c, all of the contraction axis
-    bf16x16 Rf[NK];
+    bf16x16 Rf[NF > 0 ? NF : 1];
+    i32x4 Rh;   // (KT odd)
     {
-        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK + sparse_k(lm.quad);
-        i32x4 piece[2 * NK];
-        if constexpr (KT & 1) piece[KT] = i32x4{0, 0, 0, 0};
+        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK;
+        i32x4 piece[NF > 0 ? 2 * NF : 1];
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32), *(const i32x2*)(rrow + kt * 32 + 8));
+        for (int kt = 0; kt < 2 * NF; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32 + sparse_k(lm.quad)), *(const i32x2*)(rrow + kt * 32 + sparse_k(lm.quad) + 8));
+        if constexpr (KT & 1) {
+            const i32x4 v = *(const i32x4*)(rrow + 2 * NF * 32 + 8 * lm.quad);
+            Rh = sparse_piece(i32x2{v[0], v[1]}, i32x2{v[2], v[3]});
+        }
 #pragma unroll
-        for (int kc = 0; kc < NK; ++kc) Rf[kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
+        for (int kc = 0; kc < NF; ++kc) Rf[kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
     }
 
     const char* c_g = (const char*)p.cache + (size_t)n * D * REC;
@@ -954,7 +963,13 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             if (BT == 8 || (lm.c & 2) == 0) {
 #pragma unroll
                 for (int k = 0; k < KC; ++k)
-                    if (c * KC + k < NK) raw[k] = *(const i32x4*)(grow + (c * KC + k) * 128 + ((KT & 1) && c * KC + k == NK - 1 ? lm.rbyte_half() : lm.rbyte));
+                    if (c * KC + k < NF) {
+                        raw[k] = *(const i32x4*)(grow + (c * KC + k) * 128 + lm.rbyte);
+                    } else if (c * KC + k < NK) {
+                        const i32x2 v = *(const i32x2*)(grow + NF * 128 + lm.rbyte32);
+                        raw[k][0] = v[0];
+                        raw[k][1] = v[1];
+                    }
             }
 #pragma unroll
             for (int k = 0; k < KC; ++k) gB[c][k] = __builtin_bit_cast(bf16x8, raw[k]);
@@ -974,7 +989,12 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
         for (int c = 0; c < NCK; ++c) {
 #pragma unroll
             for (int k = 0; k < KC; ++k)
-                if (c * KC + k < NK) acc[(c * KC + k) % NA] = smfmac(gB[c][k], Rf[c * KC + k], acc[(c * KC + k) % NA], lm.idx);
+                if (c * KC + k < NF) {
+                    acc[(c * KC + k) % NA] = smfmac(gB[c][k], Rf[c * KC + k], acc[(c * KC + k) % NA], lm.idx);
+                } else if (c * KC + k < NK) {
+                    const i32x4 v = __builtin_bit_cast(i32x4, gB[c][k]);
+                    acc[NF % NA] = smfmac32(i32x2{v[0], v[1]}, Rh, acc[NF % NA], lm.idx);
+                }
             pin_order();
             if (c + 1 < NCK) read_chunk(c + 1);
             if (c == 0) {   // dWx_t out of its image and on its way, step t-1's values out of theirs

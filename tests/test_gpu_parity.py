@@ -554,3 +554,35 @@ def test_staged_forward_kernels_at_every_pipeline_length(cell, D, bt, T):
     ragged last batch tile, contraction lengths that fill the last sparse step of 64 and that leave half of it."""
     w = Workload(f"pipe_{cell}_D{D}_bt{bt}_T{T}", cell, T, bt + 3, 2, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=T + D + bt)
     _check(w, {"FLASHRNN_BT": str(bt)}, with_dlast=True)
+
+
+@pytest.mark.parametrize("cell", [CELL_LSTM, CELL_GRU, CELL_ELMAN, CELL_GRU4])
+@pytest.mark.parametrize("D", [16, 32, 64])
+@pytest.mark.parametrize("bt", [4, 8])
+def test_staged_forward_kernels_with_an_infinite_state(cell, D, bt):
+    """An overflowed h saturates the gates it reaches, with its sign: nothing of it may meet the zero weights behind a contraction of 32."""
+    os.environ["FLASHRNN_BT"] = str(bt)
+    w = Workload(f"infh_{cell}_D{D}_bt{bt}", cell, 1, bt + 3, 2, D, "bf16", False, bias="uniform0.1", init="uniform0.1", seed=D + bt)
+    inp = synth.make_inputs(w)
+    inp["states0"][0, 1, 0, 5], inp["states0"][0, w.B - 1, 1, D - 1] = np.inf, -np.inf
+    got, ref = pu.run_gpu(w, inp)["states"][1], pu.run_oracle(w, inp)["states"][1]
+    fin = np.isfinite(ref)
+    assert fin[0, 1, 0].sum() > D // 8      # (a GRU with r = 0 multiplies it by zero itself, and carries the infinite unit on)
+    assert np.isfinite(got[fin]).all() and np.abs(got[fin] - ref[fin]).max() <= pu.TOL_BF16_REL * np.abs(ref[fin]).max()
+
+
+@pytest.mark.parametrize("cell", [CELL_ELMAN, CELL_GRU, CELL_LSTM])
+@pytest.mark.parametrize("D", [16, 32, 64])
+@pytest.mark.parametrize("bt", [4, 8])
+@pytest.mark.parametrize("clip", [None, 0.5])
+def test_staged_backward_kernels_with_an_infinite_gradient(cell, D, bt, clip):
+    """An overflowed gate gradient: the recurrent term is an infinity with the sign of R, and the clip makes it plus or minus its bound."""
+    os.environ["FLASHRNN_BT"] = str(bt)
+    w = Workload(f"infdg_{cell}_D{D}_bt{bt}", cell, 2, bt + 3, 2, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + bt)
+    inp = synth.make_inputs(w)
+    inp["dH"][1, 1, 0, 5], inp["dH"][1, w.B - 1, 1, D - 1] = np.inf, -np.inf
+    got, ref = pu.run_gpu(w, inp, clip=clip), pu.run_oracle(w, inp, clip=clip)
+    for k in ("dWx", "dstates0"):
+        inf, fin = np.isinf(ref[k]), np.isfinite(ref[k])
+        assert np.array_equal(got[k][inf], ref[k][inf])
+        assert np.isfinite(got[k][fin]).all() and np.abs(got[k][fin] - ref[k][fin]).max() <= pu.TOL_BF16_REL * np.abs(ref[k][fin]).max()
