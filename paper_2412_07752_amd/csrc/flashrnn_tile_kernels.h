@@ -1045,15 +1045,22 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
         for (int t = T; t >= 1; --t) step(ph0{}, t);
     }
     // ---- gradients w.r.t. the initial states
+    // (kernels of twelve waves, 168 registers per lane: the lane's places are formed anew from the lane index of the hardware.  Kept from
+    // the prologue they hold registers through the time loop, and the 8-row kernel of the four-gate GRU's heads of 144 to 176 units
+    // spills: 16 x 144 with 256 rows, 128 steps backward 936 us in 4-row tiles instead of 760.)
+    constexpr bool kAnew = MAXW > 8;
+    const SparseLane<BT> lm_end(kAnew ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane);
 #pragma unroll
-    for (int i = 0; i < PP; ++i)
-        if (row_valid[i]) {
+    for (int i = 0; i < PP; ++i) {
+        const int brow = q * BT + lm_end.slot(i);
+        if (kAnew ? brow < B : row_valid[i]) {
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const float v[1] = {ds[s][i]};
-                store_io_r<false, 1>(make_rsrc((char*)p.dstates0 + (size_t)n * D * 4), voff_st[i], s * st_state, v);
+                store_io_r<false, 1>(make_rsrc((char*)p.dstates0 + (size_t)n * D * 4), kAnew ? ((uint32_t)brow * HD + w * 16 + lm_end.c) * 4 : voff_st[i], s * st_state, v);
             }
         }
+    }
 }
 
 }  // namespace flashrnn
