@@ -160,8 +160,11 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             // -6 %, LSTM 6 x 128 with 128 rows -5 %, with 16 rows +10 %)
             if (e.exact >= 2 && deep_mode != 2 && e.maxw > 4 && d->NH * ((d->B + e.BT - 1) / e.BT) < cus / 2) continue;
             // (three and more workgroups per CU: they hide each other's latency and the call runs at the bandwidth of HBM; the
-            // direct loads are then 4 to 9 % faster -- 12 x 64 with 512 rows, 24 x 32 with 256)
-            if (e.exact >= 2 && deep_mode != 2 && d->NH * ((d->B + e.BT - 1) / e.BT) > 2 * cus) continue;
+            // direct loads are then 4 to 9 % faster -- 12 x 64 with 512 rows.  Workgroups of one or two waves do so once a time step's saved
+            // values exceed 1 MB: LSTM 48 x 16, 512 steps backward with 42 / 85 / 128 rows 242 / 429 / 627 us deep and 406 / 545 / 630 direct, 48 x 32
+            // with 64 / 85 rows 428 / 622 and 525 / 562, sLSTM 48 x 32 with 32 / 53 rows 288 / 488 and 422 / 496)
+            const bool many = nw <= 2 ? (size_t)d->B * d->NH * d->D * record_slots(d->cell) * 2 > 1000000 : d->NH * ((d->B + e.BT - 1) / e.BT) > 2 * cus;
+            if (e.exact >= 2 && deep_mode != 2 && many) continue;
             size_t smem = (size_t)2 * e.BT * (dk + (bf ? 8 : 4)) * (bf ? 2 : 4);
             if (e.tile == 1 && bwd) {
                 const int nsb = d->cell == FLASHRNN_SLSTM ? 2 : d->cell == FLASHRNN_ELMAN ? 0 : 1, go = d->cell == FLASHRNN_GRU ? G + 1 : G;
@@ -176,11 +179,18 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             // time, and overlap each other's waits: with more groups than CUs their time grows by 0.62 per CU-load of groups, not by
             // whole rounds (forward 12 x 64: 1.38 of a single round's time at 1.125 groups per CU, 1.55 at 1.5, 2.6 at 3).
             const double per_cu = (double)ng / cus;
-            const double rounds = (e.tile == 1 && e.BT == 4 && nw <= 4 && ng > cus) ? 0.7 + 0.62 * per_cu : (double)((ng + cus - 1) / cus);
+            // With one or two waves each, several fit on the CU's four SIMDs and the time grows less, until the CU is full (LSTM 48 x 16, 512 steps
+            // without saved values with 16 / 32 / 42 / 64 / 85 / 128 rows 112 / 116 / 117 / 160 / 236 / 328 us, 48 x 32 126 / 162 / 165 / 211 / 313 / 424).
+            double rounds = (double)((ng + cus - 1) / cus);
+            if (e.tile == 1 && e.BT == 4 && nw <= 4 && ng > cus) {
+                rounds = nw > 2 ? 0.7 + 0.62 * per_cu : 0.8 + 0.4 * per_cu;
+                if (nw <= 2 && rounds < 0.77 * per_cu) rounds = 0.77 * per_cu;
+            }
             // (8-row staged tiles, measured at 12 x 64 with 96 to 256 rows: backward 1.3 of a 4-row step, forward 1.65 --
             // 1.25 when the call saves nothing and writes a third of the bytes: 1.48 in one round, 1.12 per round in two --, the
-            // sLSTM's forward step, whose point-wise function is the longest, 2.7)
-            const double rel8 = bwd ? 1.3 : (d->cell == FLASHRNN_SLSTM ? 2.7 : (mode == 2 ? 1.25 : 1.65));
+            // sLSTM's forward step, whose point-wise function is the longest, 2.7.  Heads of 16 and 32 units 1.5 without saved values
+            // and backward: 48 x 16 with 24 rows 175 and 258 us against 115 and 208 in 4-row tiles, 48 x 32 with 32 rows 181 and 293 against 162 and 270)
+            const double rel8 = nw <= 2 && mode != 0 && !(d->cell == FLASHRNN_SLSTM && !bwd) ? 1.5 : bwd ? 1.3 : (d->cell == FLASHRNN_SLSTM ? 2.7 : (mode == 2 ? 1.25 : 1.65));
             // (float32: the 4-row kernels run on the 4 x 4 matrix instruction.  Two workgroups of 4 rows on a CU beat one of 8 -- LSTM 16 x 64
             // with 128 rows 283 us per 64 steps against 349, GRU 8 x 96 with 256 rows 452 against 600 --, four of 4 rows lose to one of 16: LSTM
             // 16 x 64 with 256 rows 565 against 522, Elman 16 x 128 438 against 391)

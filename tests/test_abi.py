@@ -101,3 +101,15 @@ def test_sizes_and_plans_of_the_benchmark_configurations():
         for bwd in (False, True):
             assert api.flashrnn_plan(d, bwd)[0] % (D // 16) == 0 and api.flashrnn_plan_kernel(d, bwd)[2] == D // 16
     assert api.flashrnn_workspace_bytes(api.make_desc(0, 4, 2, 1, 2704, api.FLASHRNN_BF16)) == 0
+
+
+@pytest.mark.parametrize("cell,T,B,NH,D,mode,staged,bt", [
+    # more 4-row groups than CUs, one or two waves each: they share a CU, 4-row tiles (with three or four waves 8-row tiles backward)
+    (0, 512, 24, 48, 16, 2, 1, 4), (4, 512, 32, 48, 32, 2, 1, 4), (0, 512, 32, 48, 32, 1, 2, 4), (2, 128, 96, 12, 32, 1, 2, 4), (0, 512, 96, 12, 64, 1, 2, 8),
+    # ... until the CU is full
+    (0, 512, 128, 48, 16, 2, 1, 8), (1, 512, 128, 48, 32, 2, 1, 8),
+    # the deep fetch up to 1 MB of saved values per time step
+    (0, 512, 64, 48, 32, 1, 2, 4), (0, 512, 85, 48, 32, 1, 1, 4), (2, 512, 32, 48, 32, 1, 2, 4), (2, 512, 64, 48, 32, 1, 1, 4), (0, 512, 200, 12, 16, 1, 2, 4),
+])
+def test_plans_of_many_small_heads(cell, T, B, NH, D, mode, staged, bt):
+    assert api.flashrnn_plan_kernel(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16), mode) == (staged, bt, 1)
