@@ -16,14 +16,20 @@ constexpr int TK = 32;    // contraction rows per LDS round
 
 // Workgroup i runs on XCD i % 8.  The (head, K slice, output tile) triples, tiles fastest, are dealt out in eight equal runs, one
 // per XCD: the tiles of one (head, K slice) share their operand rows and mostly re-read them from one L2, and the XCDs are
-// loaded alike however few (head, K slice) pairs there are.  (Whole pairs per XCD, as it was, left seven XCDs idle for one head
-// without K slices: 1 x 2048, 4096 rows, 1363 us.)
-__device__ __forceinline__ bool tile_of_block(int tiles, int combos, int& combo, int& tile) {
-    const int total = tiles * combos, per_xcd = (total + 7) / 8;
-    const int slot = blockIdx.x >> 3, id = (blockIdx.x & 7) * per_xcd + slot;
-    if (slot >= per_xcd || id >= total) return false;
-    combo = id / tiles;
+// loaded alike however few (head, K slice) pairs there are.  (Whole pairs per XCD left seven XCDs idle for one head
+// without K slices: 1 x 2048, 4096 rows, 1363 us.)  Small tiles of heads whose rows share cache lines (`shared`: no multiple of 128 bytes) with eight slices and
+// more: XCD x takes slices x, x + 8, ... of every head, so that a line is fetched into one L2 (12 x 48 units, 12800 rows, 4 gates: 20 us, in runs 29).  Elsewhere
+// runs are the faster ones (12 x 64, 16384 rows 33.3 us against 34.5; backward pass and GEMM of the GRU's 12 x 176, 7040 rows 168 and 176).
+__device__ __forceinline__ bool tile_of_block(int tiles, int SK, int NH, bool shared, int& sk, int& n, int& tile) {
+    const int total = tiles * SK * NH, per_xcd = (total + 7) / 8;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    if (slot >= per_xcd) return false;
+    const int id = shared && SK % 8 == 0 ? (slot / tiles * 8 + xcd) * tiles + slot % tiles : xcd * per_xcd + slot;
+    if (id >= total) return false;
+    const int combo = id / tiles;
     tile = id % tiles;
+    sk = combo % SK;
+    n = combo / SK;
     return true;
 }
 
@@ -38,11 +44,9 @@ __global__ __launch_bounds__(256) void dr_gemm_kernel(const float* __restrict__ 
     __shared__ __align__(16) char ldsB[TN * PITCH * ESZ];
     const int GD = G * D;
     const int tiles_n = (GD + TN - 1) / TN, tiles_m = (D + TM - 1) / TM;
-    int combo, tile;   // (head, K slice) and output tile of this workgroup
-    if (!tile_of_block(tiles_n * tiles_m, SK * NH, combo, tile)) return;
+    int sk, n, tile;   // K slice, head and output tile of this workgroup
+    if (!tile_of_block(tiles_n * tiles_m, SK, NH, D * ESZ % 128 != 0, sk, n, tile)) return;
     const int tn = tile % tiles_n, tm = tile / tiles_n;
-    const int sk = combo % SK;
-    const int n = combo / SK;
     const int K = T * B;
     const int kchunk = ((K + SK - 1) / SK + TK - 1) / TK * TK;
     const int kbeg = sk * kchunk, kend = min(K, kbeg + kchunk);
@@ -209,10 +213,9 @@ __global__ __launch_bounds__(WM * WN * 64) void dr_gemm_tr_kernel(const float* _
     __shared__ __align__(16) uint16_t ldsB[2][TK * PB];
     const int GD = G * D;
     const int tiles_n = (GD + TNW - 1) / TNW, tiles_m = (D + TMW - 1) / TMW;
-    int combo, tile;   // (head, K slice) and output tile of this workgroup
-    if (!tile_of_block(tiles_n * tiles_m, SK * NH, combo, tile)) return;
+    int sk, n, tile;   // K slice, head and output tile of this workgroup
+    if (!tile_of_block(tiles_n * tiles_m, SK, NH, TMW == TM && D * 2 % 128 != 0, sk, n, tile)) return;
     const int tn = tile % tiles_n, tm = tile / tiles_n;
-    const int sk = combo % SK, n = combo / SK;
     const int K = T * B;
     const int kchunk = ((K + SK - 1) / SK + TK - 1) / TK * TK;
     const int kbeg = sk * kchunk, kend = min(K, kbeg + kchunk);

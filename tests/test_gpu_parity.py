@@ -564,6 +564,15 @@ def test_weight_gradient_gemm_with_few_heads(cell, NH, D, T, B, slices):
     _check(w, with_dlast=True)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("cell,NH,D,T,B", [(CELL_LSTM, 3, 48, 69, 16), (CELL_GRU, 5, 80, 75, 15), (CELL_ELMAN, 2, 112, 161, 13)])
+def test_weight_gradient_gemm_with_heads_that_share_cache_lines(dtype, cell, NH, D, T, B):
+    """Heads whose rows are no multiple of 128 bytes with eight and more slices: each XCD takes every eighth slice of all heads."""
+    w = Workload(f"shared_{cell}_{dtype}_NH{NH}_D{D}", cell, T, B, NH, D, dtype, True, bias="uniform0.1", init="uniform0.1", seed=D + T)
+    assert api.flashrnn_workspace_bytes(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16 if dtype == "bf16" else api.FLASHRNN_F32)) >= 8 * NH * D * w.G * D * 4
+    _check(w, with_dlast=True)
+
+
 @pytest.mark.parametrize("cell", [CELL_LSTM, CELL_GRU])
 @pytest.mark.parametrize("D,bt", [(192, 4), (160, 4), (192, 8), (128, 8), (32, 4), (16, 8)])
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 6, 7, 9])
