@@ -64,16 +64,21 @@ struct TileLds {
     uint32_t total_fwd;
 };
 __host__ __device__ inline uint32_t div_up(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
+// k_bytes_fwd: operand row of the kernel's contraction length.  In 8-row tiles the image rows of a shorter head have the pitches of a full one:
+// compile-time constants, so that a lane's places in an image are one address with immediate offsets instead of a register each (the GRU's
+// kernel of 80 to 128 units 141 -> 128 registers, two workgroups per CU again: 12 x 80, 64 steps without saved values, 200 rows 71 -> 47 us).  4-row
+// kernels have the registers and gain nothing by it (GRU of up to 128 units +1 to +2 %), and heads of 16 units would take half as much LDS again.
 __host__ __device__ inline TileLds tile_lds(int BT, int G, int S, int D, int NT, int k_bytes_fwd) {
     TileLds L;
     const uint32_t nt16 = (uint32_t)NT * 16;
-    L.rp_io = lds_row_pitch((uint32_t)D * 2);
-    L.rp_st = lds_row_pitch((uint32_t)D * 4);
+    const uint32_t row = BT == 8 && k_bytes_fwd > 64 ? (uint32_t)k_bytes_fwd : (uint32_t)D * 2;   // bytes of a bf16 image row
+    L.hp = lds_row_pitch((uint32_t)k_bytes_fwd);
+    L.rp_io = lds_row_pitch(row);
+    L.rp_st = lds_row_pitch(row * 2);
     L.in_bytes = (uint32_t)BT * G * L.rp_io;
     L.in_pitch = L.in_bytes + div_up((uint32_t)BT * G * (D / 8), NT) * nt16;
     L.st_bytes = (uint32_t)BT * S * L.rp_st;
     L.st_pitch = L.st_bytes + div_up((uint32_t)BT * S * (D / 4), NT) * nt16;
-    L.hp = lds_row_pitch((uint32_t)k_bytes_fwd);
     L.total_fwd = 2 * BT * L.hp + 2 * L.in_pitch + 2 * L.st_pitch;
     return L;
 }
