@@ -187,14 +187,28 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
                 if (nw <= 2 && rounds < 0.77 * per_cu) rounds = 0.77 * per_cu;
             }
             // (8-row staged tiles, measured at 12 x 64 with 96 to 256 rows: backward 1.3 of a 4-row step, forward 1.65 --
-            // 1.25 when the call saves nothing and writes a third of the bytes: 1.48 in one round, 1.12 per round in two --, the
-            // sLSTM's forward step, whose point-wise function is the longest, 2.7.  Heads of 16 and 32 units 1.5 without saved values
+            // 1.25 when the call saves nothing and writes a third of the bytes: 1.48 in one round, 1.12 per round in two.  Heads of 16 and 32 units 1.5 without saved values
             // and backward: 48 x 16 with 24 rows 175 and 258 us against 115 and 208 in 4-row tiles, 48 x 32 with 32 rows 181 and 293 against 162 and 270)
-            const double rel8 = nw <= 2 && mode != 0 && !(d->cell == FLASHRNN_SLSTM && !bwd) ? 1.5 : bwd ? 1.3 : (d->cell == FLASHRNN_SLSTM ? 2.7 : (mode == 2 ? 1.25 : 1.65));
+            double rel8 = bwd ? 1.3 : (mode == 2 ? 1.25 : 1.65);
+            if (nw <= 2 && mode != 0) rel8 = 1.5;
+            // The sLSTM's forward step, whose point-wise function is the longest, 1.5: better than a second 4-row round from 80 units on (12 x 80, 64 steps,
+            // 96 rows 57 us against 71 with and without saved values, 12 x 112 without them 59 and 75), until the call streams so much that many small
+            // workgroups, with more requests in flight, win again (12 x 80, 256 steps, 100 rows with saved values 313 us against 291,
+            // 12 x 112, 128 steps without them 154 and 140).  Heads of 48 and 64 units share a CU in 4-row tiles: with saved values these are slower from 1.05
+            // to 1.1 workgroups per CU on (12 x 64, 64 steps, 96 rows 41.4 us against 36.7, 12 x 48 38.2 and 35.8), but for the shortest sequences (12 x 48, 16 steps,
+            // 100 rows 13.5 and 15.0), and always better without them (12 x 64, 64 steps, 128 rows 33.8 and 36.8).
+            if (d->cell == FLASHRNN_SLSTM && !bwd) {
+                const double mb = (double)(G * 2 + 4 * 4 + (mode == 0 ? record_slots(d->cell) * 2 : 0)) * d->T * d->B * d->NH * d->D / 1e6;
+                rel8 = 2.7;
+                if (nw > 4 && (mode == 0 ? mb < 320 : nw <= 6 || mb < 300)) rel8 = 1.52;
+                else if (nw > 2 && nw <= 4 && mode == 0 && mb > 140 && mb < 320) rel8 = nw == 3 ? 1.38 : 1.33;
+            }
             // (float32: the 4-row kernels run on the 4 x 4 matrix instruction.  Two workgroups of 4 rows on a CU beat one of 8 -- LSTM 16 x 64
             // with 128 rows 283 us per 64 steps against 349, GRU 8 x 96 with 256 rows 452 against 600 --, four of 4 rows lose to one of 16: LSTM
-            // 16 x 64 with 256 rows 565 against 522, Elman 16 x 128 438 against 391)
-            const double rel4 = bf ? 1.8 : 1.45, rel16 = bf ? 6.0 : 5.5;
+            // 16 x 64 with 256 rows 565 against 522, Elman 16 x 128 438 against 391.  Of 128 units the backward passes of the sLSTM and the
+            // four-gate GRU are the exception: sLSTM 8 x 128 with 200 rows, 48 steps 389 us in two rounds of 4 rows and 368 in one of 8, four-gate GRU 348 and 334)
+            const bool two4 = bwd && d->D > 112 && (d->cell == FLASHRNN_SLSTM || d->cell == FLASHRNN_GRU4);
+            const double rel4 = bf ? 1.8 : two4 ? 1.55 : 1.45, rel16 = bf ? 6.0 : 5.5;
             double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? rel4 : e.BT == 8 ? 3.0 : rel16);
             if (e.tile == 0) rel *= 1.0 + 0.05 * (e.eb - 1);       // thin waves overlap better
             rel *= 1.0 + 0.02 * (dk - kdim) / (double)kstep;       // padded k-steps are wasted MFMAs

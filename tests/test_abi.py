@@ -113,3 +113,18 @@ def test_sizes_and_plans_of_the_benchmark_configurations():
 ])
 def test_plans_of_many_small_heads(cell, T, B, NH, D, mode, staged, bt):
     assert api.flashrnn_plan_kernel(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16), mode) == (staged, bt, 1)
+
+
+@pytest.mark.parametrize("T,B,NH,D,mode,bt", [
+    # more 4-row groups than CUs: one round of 8-row tiles instead of a second one of 4 rows from 80 units on ...
+    (64, 96, 12, 80, 0, 8), (64, 96, 12, 96, 2, 8), (64, 96, 12, 128, 2, 8), (64, 170, 12, 96, 2, 4),
+    # ... until the memory bounds the call; heads of 48 and 64 units share a CU in 4-row tiles
+    (256, 100, 12, 80, 0, 4), (256, 100, 12, 80, 2, 8), (256, 100, 12, 112, 2, 4), (64, 96, 12, 64, 0, 8), (64, 96, 12, 64, 2, 4), (16, 100, 12, 48, 0, 4), (64, 64, 12, 80, 0, 4),
+])
+def test_forward_plans_of_the_slstm_with_many_groups(T, B, NH, D, mode, bt):
+    assert api.flashrnn_plan_kernel(api.make_desc(2, T, B, NH, D, api.FLASHRNN_BF16), mode) == (1, bt, 1)
+
+
+@pytest.mark.parametrize("cell,D,bt", [(2, 128, 8), (4, 128, 8), (0, 128, 4), (2, 112, 4)])
+def test_backward_plans_of_float32_heads_of_128_units(cell, D, bt):
+    assert api.flashrnn_plan_kernel(api.make_desc(cell, 48, 200, 8, D, api.FLASHRNN_F32), True) == (0, bt, 1)
