@@ -83,12 +83,12 @@ __host__ __device__ inline TileLds tile_lds(int BT, int G, int S, int D, int NT,
     return L;
 }
 
-// LDS layout of the backward tile kernel (bf16 I/O, one workgroup per group, BT < 16, NT = 4 * D threads).
-// The input images are filled by loads that write LDS directly: a wave's 64 chunks of 16 bytes land
-// back to back, so these images are plain arrays of chunks (no row padding), each rounded up to whole waves.
 // elements between the operand rows of the kernels with plain rows, beyond the contraction length: 16 bytes, or 32 where the sparse
 // instruction's lanes read two 16-byte pieces of each of 4 or 8 rows at once (all in different banks then)
 __host__ __device__ constexpr int operand_pad(bool bf16, bool sparse) { return sparse ? 16 : bf16 ? 8 : 4; }
+// LDS layout of the backward tile kernel (bf16 I/O, one workgroup per group, BT < 16, NT = 4 * D threads).
+// The input images are filled by loads that write LDS directly: a wave's 64 chunks of 16 bytes land
+// back to back, so these images are plain arrays of chunks (no row padding), each rounded up to whole waves.
 struct TileLdsBwd {
     uint32_t hp;                 // operand (gate-gradient) row pitch, buf = BT * hp, two buffers
     uint32_t rp_io;              // row pitch of the output image (bf16 rows)
@@ -230,8 +230,8 @@ __device__ __forceinline__ float sum_quad_slices(const f32x4& a, int c) {
     return odd ? down : up;
 }
 
-// The inverse of compact_tile for one value per pair: the lanes c < BT of a row collect the four consecutive
-// units 4q..4q+3 of their batch slot from the lanes that computed them (valid in those lanes only).
+// The inverse of compact_tile (SPARSE: of sparse_pairs) for one value per pair: the lanes whose first unit is a multiple of four collect
+// that unit and the three behind it of their batch slot from the lanes that computed them (valid in those lanes only).
 template <int BT, int PP, bool SPARSE = false> __device__ __forceinline__ void expand_tile(const float (&v)[PP], float (&out)[4]) {
     auto shl = [](float x, auto n) {   // lane i takes the value of lane i + n of its row
         constexpr int N = decltype(n)::value;
@@ -249,11 +249,8 @@ template <int BT, int PP, bool SPARSE = false> __device__ __forceinline__ void e
         out[1] = shl(v[0], std::integral_constant<int, 1>{});
         out[2] = shl(v[0], std::integral_constant<int, 2>{});
         out[3] = shl(v[0], std::integral_constant<int, 3>{});
-    } else if constexpr (BT == 8) {
-        out[0] = v[0]; out[1] = v[1];
-        out[2] = shl(v[0], std::integral_constant<int, 8>{});
-        out[3] = shl(v[1], std::integral_constant<int, 8>{});
     } else {
+        static_assert(BT == 4, "8-row tiles whose groups are split run on the sparse instruction");
         out[0] = v[0];
         out[1] = shl(v[0], std::integral_constant<int, 4>{});
         out[2] = shl(v[0], std::integral_constant<int, 8>{});

@@ -14,6 +14,14 @@
 
 namespace flashrnn {
 
+// staged 8-row kernels of heads of more than 128 units (a cell whose kernel does not fit the 168 registers of twelve waves defines 0)
+#ifndef FRNN_LONG8_FWD
+#define FRNN_LONG8_FWD 1
+#endif
+#ifndef FRNN_LONG8_BWD
+#define FRNN_LONG8_BWD 1
+#endif
+
 #define FRNN_F(KT, KS, BT, MULTI, MAXW, EB) \
     {FRNN_CELL, FRNN_BF16, 0, KT, KS, BT, MULTI, MAXW, EB, 0, 0, (const void*)&fwd_kernel<FRNN_CELL, (FRNN_BF16 != 0), KT, KS, BT, (MULTI != 0), MAXW, EB>},
 #define FRNN_B(KT, KS, BT, MULTI, MAXW, EB) \
@@ -46,7 +54,13 @@ static const KernelEntry kEntries[] = {
     FRNN_FB(1, 1, 16, 0, 4) FRNN_TILE(1, 8, 4) FRNN_TILE(1, 4, 4) FRNN_BTLD(1, 8, 4) FRNN_BTLD(1, 4, 4)
     FRNN_FB(2, 1, 16, 0, 4) FRNN_TILE(2, 8, 4) FRNN_TILE(2, 4, 4) FRNN_BTLD(2, 8, 4) FRNN_BTLD(2, 4, 4)
     FRNN_FB(4, 1, 16, 0, 8) FRNN_TILE(4, 8, 8) FRNN_TILE(4, 4, 8) FRNN_BTLD(4, 8, 8) FRNN_BTLD(4, 4, 8)
-    FRNN_FB(6, 1, 16, 0, 12) FRNN_TILE(6, 8, 12) FRNN_TILE(6, 4, 12)
+    FRNN_FB(6, 1, 16, 0, 12) FRNN_B(6, 1, 8, 0, 12, 1) FRNN_TILE(6, 4, 12)
+#if FRNN_LONG8_FWD
+    FRNN_FT(6, 8, 12)
+#endif
+#if FRNN_LONG8_BWD
+    FRNN_BTL(6, 8, 12)
+#endif
     FRNN_FBE(4, 16, 4, 2) FRNN_FBE(4, 8, 4, 2) FRNN_FBE(4, 4, 4, 2)
     FRNN_FBE(6, 16, 4, 3) FRNN_FBE(6, 8, 4, 3) FRNN_FBE(6, 4, 4, 3)
 #define FRNN_MULTI_SHAPES(BT) \

@@ -2,6 +2,7 @@
 #define FRNN_CELL flashrnn::CELL_LSTM
 #define FRNN_G 4
 #define FRNN_BF16 1
+#define FRNN_LONG8_BWD 0
 #include "flashrnn_inst.h"
 
 namespace flashrnn {

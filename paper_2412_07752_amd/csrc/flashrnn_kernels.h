@@ -422,26 +422,10 @@ template <bool BF16, int BT, int G> struct Clearer {
     }
 };
 
-// KC consecutive k-steps (64 bytes apart) of the B operand, read by the lanes of the valid batch columns only, under one
-// execution mask.  The other lanes' registers keep whatever they held: a column of the B operand only reaches the same
-// column of the result, and the columns c >= BT of a result are never used (the empty asm statements stand for "any
-// value": without them the compiler would give the idle lanes a defined value, one move per register).  An LDS read costs
-// bandwidth per active lane, and the backward step of a split group, whose waves read all G * D gate gradients, is bound by the LDS.
-template <int BT, int KC, bool MASKED> __device__ __forceinline__ void lds_operand_chunk(const char* p, int c, bf16x8 (&out)[KC]) {
-    if constexpr (BT == 16 || !MASKED) {
+// KC consecutive k-steps (64 bytes apart) of the B operand
+template <int KC> __device__ __forceinline__ void lds_operand_chunk(const char* p, bf16x8 (&out)[KC]) {
 #pragma unroll
-        for (int j = 0; j < KC; ++j) out[j] = *(const bf16x8*)(p + j * 64);
-    } else {
-        i32x4 raw[KC];
-#pragma unroll
-        for (int j = 0; j < KC; ++j) asm volatile("" : "=v"(raw[j]));
-        if (c < BT) {
-#pragma unroll
-            for (int j = 0; j < KC; ++j) raw[j] = *(const i32x4*)(p + j * 64);
-        }
-#pragma unroll
-        for (int j = 0; j < KC; ++j) out[j] = __builtin_bit_cast(bf16x8, raw[j]);
-    }
+    for (int j = 0; j < KC; ++j) out[j] = *(const bf16x8*)(p + j * 64);
 }
 
 // Split groups with bf16 batch tiles of 4 or 8 rows run the recurrent products on the sparse matrix instruction (SparseLane), like the
@@ -460,7 +444,10 @@ template <int KT> __device__ __forceinline__ bf16x16 load_sparse_dense(const uin
     return sparse_dense(piece[0], piece[1]);
 }
 // N consecutive 64-index steps (from kc on, of NK; the last one holds 32 indices if HALF) of the h / dg operand.  With 4 rows the
-// rows j = 1 of the operand need no values (their results are never used): their lanes read nothing, as in lds_operand_chunk.
+// rows j = 1 of the operand need no values (a row only reaches the same row of the result, and theirs are never used): MASKED, their lanes
+// read nothing, all reads under one execution mask, and their registers keep whatever they held (the empty asm statements stand for "any
+// value": without them the compiler would give the idle lanes a defined value, one move per register).  An LDS read costs
+// bandwidth per active lane, and the backward step of a split group, whose waves read all G * D gate gradients, is bound by the LDS.
 template <int BT, int N, int NK, bool HALF, bool MASKED>
 __device__ __forceinline__ void lds_sparse_chunk(const char* p, const SparseLane<BT>& sl, int kc, bf16x8 (&out)[N]) {
     i32x4 raw[N];
@@ -540,20 +527,18 @@ template <bool BF16, int PP> __device__ __forceinline__ void write_operand_lds(c
     }
 }
 
-// partial sums of the KS contraction slices meet in LDS: slices 1.. write, slice 0 adds.  A lane's four values of a tile
+// partial sums of the KS contraction slices of a 16-row tile meet in LDS: slices 1.. write, slice 0 adds.  A lane's four values of a tile
 // travel as one 16-byte access (64 lanes x 16 bytes back to back: no bank conflicts, a quarter of the LDS instructions).
-// Only the lanes of the BT valid batch columns take part (the others' sums are never used, and LDS traffic costs per active lane).
-template <int NT, int KS, int BT>
+template <int NT, int KS>
 __device__ __forceinline__ void reduce_slices(float* red, int parity, int ks, int wu, int NWU, int lane, f32x4 (&acc)[NT]) {
     if constexpr (KS > 1) {
-        const bool valid = BT == 16 || (lane & 15) < BT;
-        if (ks > 0 && valid) {
+        if (ks > 0) {
 #pragma unroll
             for (int g = 0; g < NT; ++g)
                 *(f32x4*)(red + (((((size_t)(parity * (KS - 1) + ks - 1) * NWU + wu) * NT + g) * 64 + lane) * 4)) = acc[g];
         }
         __syncthreads();
-        if (ks == 0 && valid) {
+        if (ks == 0) {
 #pragma unroll
             for (int s = 1; s < KS; ++s)
 #pragma unroll
@@ -625,7 +610,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
-    static_assert(KS == 1 || !kQuadTiles<BF16, BT>, "the sums of contraction slices assume 16 x 16 tiles");
+    static_assert(KS == 1 || SP || BT == 16, "the sums of contraction slices are those of 16-row tiles or of sparse pairs");
 
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, MULTI);
@@ -789,6 +774,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
 #pragma unroll
                     for (int kc = 0; kc < NKS; kc += KCS) {
                         bf16x8 hS[KCS];
+                        // (masked: worth it from 8 k-steps per wave on; with shorter rows the LDS is not what bounds the forward step)
                         lds_sparse_chunk<BT, KCS, NKS, (KT & 1) != 0, (KT >= 8)>(hbuf + (uint32_t)sl.rslot * HP * ESZ + (uint32_t)k0 * ESZ, sl, kc, hS);
 #pragma unroll
                         for (int j = 0; j < KCS; ++j)
@@ -801,8 +787,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                 for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
                     op_t hB[KC];
                     if constexpr (BF16) {
-                        // (forward: worth it from 8 k-steps per wave on; with shorter rows the LDS is not what bounds the step)
-                        lds_operand_chunk<BT, KC, (KT >= 8)>(hbuf + lds_rd + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, lm.c, hB);
+                        lds_operand_chunk<KC>(hbuf + lds_rd + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, hB);
                     } else {
 #pragma unroll
                         for (int j = 0; j < KC; ++j) hB[j] = *(const float*)(hbuf + lds_rd + (size_t)(k0 + kq * KT + kc + j) * 4);
@@ -818,7 +803,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                 for (int g = 0; g < G; ++g) sparse_pairs<BT>(acc[g], lm.c);
                 reduce_pairs<G, KS, PP>(red, t & 1, ks, wu, p.NWU, lane, acc);
             } else {
-                reduce_slices<G, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, acc);
+                reduce_slices<G, KS>(red, t & 1, ks, wu, p.NWU, lane, acc);
             }
 #ifdef FLASHRNN_TRACE
             if constexpr (MULTI) { asm volatile("" : "+v"(acc[0]), "+v"(acc[G - 1]) : : "memory"); FRNN_TRACE_MARK(4); }
@@ -915,7 +900,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
-    static_assert(KS == 1 || !kQuadTiles<BF16, BT>, "the sums of contraction slices assume 16 x 16 tiles");
+    static_assert(KS == 1 || SP || BT == 16, "the sums of contraction slices are those of 16-row tiles or of sparse pairs");
 
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, MULTI);
@@ -1181,7 +1166,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                 for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
                     op_t gB[KC];
                     if constexpr (BF16) {
-                        lds_operand_chunk<BT, KC, true>(gbuf + lds_row + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, lm.c, gB);
+                        lds_operand_chunk<KC>(gbuf + lds_row + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, gB);
                     } else {
 #pragma unroll
                         for (int j = 0; j < KC; ++j) gB[j] = *(const float*)(gbuf + lds_row + (size_t)(k0 + kq * KT + kc + j) * 4);
@@ -1205,7 +1190,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                 sparse_pairs<BT>(accs[0][0], lm.c);
                 reduce_pairs<1, KS, PP>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
             } else {
-                reduce_slices<1, KS, BT>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
+                reduce_slices<1, KS>(red, t & 1, ks, wu, p.NWU, lane, accs[0]);
             }
 #ifdef FLASHRNN_TRACE
             if constexpr (MULTI) { asm volatile("" : "+v"(accs[0][0]) : : "memory"); FRNN_TRACE_MARK(4); }
