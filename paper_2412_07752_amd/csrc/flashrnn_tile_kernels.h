@@ -569,12 +569,12 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     bf16x16 Rf[NF > 0 ? NF : 1];
     i32x4 Rh;   // (KT odd)
     {
-        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK;
+        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK + sparse_k(lm.quad);
         i32x4 piece[NF > 0 ? 2 * NF : 1];
 #pragma unroll
-        for (int kt = 0; kt < 2 * NF; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32 + sparse_k(lm.quad)), *(const i32x2*)(rrow + kt * 32 + sparse_k(lm.quad) + 8));
+        for (int kt = 0; kt < 2 * NF; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32), *(const i32x2*)(rrow + kt * 32 + 8));
         if constexpr (KT & 1) {
-            const i32x4 v = *(const i32x4*)(rrow + 2 * NF * 32 + 8 * lm.quad);
+            const i32x4 v = *(const i32x4*)(rrow + 2 * NF * 32 + 8 * lm.quad - sparse_k(lm.quad));
             Rh = sparse_piece(i32x2{v[0], v[1]}, i32x2{v[2], v[3]});
         }
 #pragma unroll
