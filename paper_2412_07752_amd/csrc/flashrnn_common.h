@@ -71,14 +71,14 @@ __host__ __device__ inline uint32_t div_up(uint32_t a, uint32_t b) { return (a +
 __host__ __device__ inline TileLds tile_lds(int BT, int G, int S, int D, int NT, int k_bytes_fwd) {
     TileLds L;
     const uint32_t nt16 = (uint32_t)NT * 16;
-    const uint32_t row = BT == 8 && k_bytes_fwd > 64 ? (uint32_t)k_bytes_fwd : (uint32_t)D * 2;   // bytes of a bf16 image row
-    L.hp = lds_row_pitch((uint32_t)k_bytes_fwd);
-    L.rp_io = lds_row_pitch(row);
-    L.rp_st = lds_row_pitch(row * 2);
+    const bool full = BT == 8 && k_bytes_fwd > 64;
+    L.rp_io = lds_row_pitch(full ? (uint32_t)k_bytes_fwd : (uint32_t)D * 2);
+    L.rp_st = lds_row_pitch(full ? (uint32_t)k_bytes_fwd * 2 : (uint32_t)D * 4);
     L.in_bytes = (uint32_t)BT * G * L.rp_io;
     L.in_pitch = L.in_bytes + div_up((uint32_t)BT * G * (D / 8), NT) * nt16;
     L.st_bytes = (uint32_t)BT * S * L.rp_st;
     L.st_pitch = L.st_bytes + div_up((uint32_t)BT * S * (D / 4), NT) * nt16;
+    L.hp = lds_row_pitch((uint32_t)k_bytes_fwd);
     L.total_fwd = 2 * BT * L.hp + 2 * L.in_pitch + 2 * L.st_pitch;
     return L;
 }

@@ -105,7 +105,7 @@ __device__ __forceinline__ void fwd_tile_body(const KernelParams& p) {
                 *(i32x4*)(tile + wr) = raw[g][kt];
                 asm volatile("" ::: "memory");
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (half ? rd32 : rd)));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (half ? rd32 + 4 * 32 : rd + 8 * 32)));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + (half ? rd32 : rd) + (half ? 4 : 8) * 32));
                 piece[kt] = sparse_piece(__builtin_bit_cast(i32x2, lo), __builtin_bit_cast(i32x2, hi));
             }
 #pragma unroll
@@ -1045,10 +1045,10 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
         for (int t = T; t >= 1; --t) step(ph0{}, t);
     }
     // ---- gradients w.r.t. the initial states
-    // (kernels of twelve waves, 168 registers per lane: the lane's places are formed anew from the lane index of the hardware.  Kept from
+    // (8-row kernels of twelve waves, 168 registers per lane: the lane's places are formed anew from the lane index of the hardware.  Kept from
     // the prologue they hold registers through the time loop, and the 8-row kernel of the four-gate GRU's heads of 144 to 176 units
     // spills: 16 x 144 with 256 rows, 128 steps backward 936 us in 4-row tiles instead of 760.)
-    constexpr bool kAnew = MAXW > 8;
+    constexpr bool kAnew = MAXW > 8 && BT == 8;
     const SparseLane<BT> lm_end(kAnew ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane);
 #pragma unroll
     for (int i = 0; i < PP; ++i) {
