@@ -161,7 +161,7 @@ int flashrnn_bwd_recompute(const flashrnn_desc_t* desc, const void* Wx, const vo
  * never wait across CUs (one workgroup per group) cannot time out: the call then only synchronizes the stream.
  * Test hooks: with FLASHRNN_PLAN_OVERRIDES=1 in the environment when the library is first called, the variables
  * FLASHRNN_SPIN_LIMIT (a negative value makes every wait give up at once, which exercises this error path without
- * hanging anything), FLASHRNN_MULTI, _BT, _NWU, _KS, _GPAR, _EB, _KIND (single choices of the launch planner,
+ * hanging anything), FLASHRNN_MULTI, _BT, _NWU, _KS, _GPAR, _EB, _DEEP_FETCH, _KIND (single choices of the launch planner,
  * to force every kernel family onto small shapes) and FLASHRNN_RECOMPUTE_STEPS (window length of flashrnn_bwd_recompute)
  * are read on every call; without it the environment is never read.
  */

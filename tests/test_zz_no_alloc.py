@@ -46,7 +46,7 @@ def test_two_calls_in_a_row_second_one_smaller():
     d = api.make_desc(big.cell, big.T, big.B, big.NH, big.D, api.FLASHRNN_BF16)
     assert api.flashrnn_plan_kernel(d)[2] > 1
     _both(big)
-    # smaller in every direction, same kind of plan: it must not see the first call's stamps or packed weights
+    # smaller in every direction, same kind of plan: it must not see the first call's exchange words or packed weights
     small = Workload("static_small", CELL_SLSTM, 5, 3, 1, 208, "bf16", False, bias="forget3", init="uniform0.1", seed=12)
     _both(small)
     # and a one-workgroup plan in the other dtype
