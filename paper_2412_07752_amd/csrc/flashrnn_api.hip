@@ -14,6 +14,7 @@
 #include "flashrnn_common.h"
 #include "flashrnn_host.h"
 #include "flashrnn_recompute.h"
+#include "flashrnn_split_kernels.h"
 
 using namespace flashrnn;
 
@@ -106,6 +107,38 @@ bool kernel_spills(const void* fn) {
     return spills;
 }
 
+// A plan whose groups are split over the CUs of one XCD takes the kernel with wave roles (flashrnn_split_kernels.h) for its batch tile, where
+// there is one that needs no more rounds over the groups.
+void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab, int cus, Plan* pl) {
+    const int units16 = d->D / 16, cap = cus / kXcds, force_ub = env_int("FLASHRNN_NWU", 0), force_gpar = env_int("FLASHRNN_GPAR", 0);
+    auto in_flight = [&](int P) {
+        int gpar = kXcds * (cap / P);
+        if (gpar > pl->NG) gpar = pl->NG;
+        return force_gpar > 0 && force_gpar < gpar ? force_gpar : gpar;
+    };
+    const int rounds = (pl->NG + pl->GPAR - 1) / pl->GPAR;
+    const KernelEntry* best = nullptr;
+    for (int i = 0; i < tab.count; ++i) {
+        const KernelEntry& e = tab.entries[i];
+        if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && e.ub != force_ub)) continue;
+        const int P = units16 / e.ub;
+        if (P > cap || (e.direct ? P != e.nb : units16 > 8 * e.nb) || e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
+        if ((pl->NG + in_flight(P) - 1) / in_flight(P) > rounds) continue;
+        // the wave-direct kernels first, then the most units per workgroup, then the smallest kernel that holds the head
+        if (!best || e.direct > best->direct || (e.direct == best->direct && (e.ub > best->ub || (e.ub == best->ub && e.nb < best->nb)))) best = &e;
+    }
+    if (!best) return;
+    pl->e = best;
+    pl->NWU = best->ub;
+    pl->P = units16 / best->ub;
+    pl->GPAR = in_flight(pl->P);
+    pl->grid = (pl->GPAR + kXcds - 1) / kXcds * pl->P * kXcds;
+    pl->block = 64 * best->maxw;
+    pl->DK = 0;
+    pl->smem = best->smem;
+    pl->exch_bytes = (size_t)best->nbuf * ((size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash);   // a partial sum of every unit from every member
+}
+
 // Launch plan.  One workgroup per group whenever the head's R fits one CU's registers with 16 units
 // per wave (no cross-CU traffic at all); then small batch tiles spread the point-wise work over more
 // CUs.  Otherwise a group is split over P workgroups of one XCD that exchange h / dg every step.
@@ -147,7 +180,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
         size_t best_smem = 0;
         for (int i = 0; i < tab.count; ++i) {
             const KernelEntry& e = tab.entries[i];
-            if (e.bwd != bwd || e.multi || e.KS != 1) continue;
+            if (e.bwd != bwd || e.multi || e.ub || e.KS != 1) continue;
             if (force_bt && e.BT != force_bt) continue;
             if (e.KT * kstep < kdim || units16 % e.eb != 0 || e.maxw * e.eb < units16) continue;
             if (force_eb ? e.eb != force_eb : false) continue;
@@ -241,7 +274,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             for (int i = 0; i < tab.count; ++i) {
                 const KernelEntry& e = tab.entries[i];
                 const int dk = e.KT * e.KS * kstep;
-                if (e.bwd != bwd || !e.multi || e.BT != BT || dk < kdim) continue;
+                if (e.bwd != bwd || !e.multi || e.ub || e.BT != BT || dk < kdim) continue;
                 if (e.maxw == 4 && e.KS == 4 && e.KT * (bwd ? 1 : G) >= 40) continue;   // the shapes of the spread placement
                 if (!spills_ok && kernel_spills(e.fn)) continue;
                 // least padding of the contraction axis first, then the wanted number of slices, then the most waves
@@ -334,6 +367,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             }
         }
     }
+    if (pl.e && pl.e->multi && bf && bwd && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
     if (!pl.e && force_multi != 0 && bf) {
         // Heads beyond what the CUs of one XCD can hold (D > 1024): the group is spread over the CUs of all XCDs, one
         // block of 16 units and 4 contraction slices per workgroup (one wave per SIMD, up to 336 registers of R each),
@@ -350,7 +384,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             for (int i = 0; i < tab.count; ++i) {
                 const KernelEntry& e = tab.entries[i];
                 const int dk = e.KT * e.KS * kstep;
-                if (e.bwd != bwd || !e.multi || e.BT != BT || e.KS != 4 || e.maxw != 4 || dk < kdim) continue;
+                if (e.bwd != bwd || !e.multi || e.ub || e.BT != BT || e.KS != 4 || e.maxw != 4 || dk < kdim) continue;
                 if (!best || dk < best->KT * best->KS * kstep) best = &e;
             }
             if (!best || units16 > budget) continue;
@@ -375,13 +409,13 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
         }
     }
     if (!pl.e) return FLASHRNN_ERR_UNSUPPORTED;
-    pl.rpack_bytes = (bwd ? (size_t)d->NH * d->D * pl.DK : (size_t)d->NH * G * d->D * pl.DK) * io_size(d->io_dtype);
+    pl.rpack_bytes = pl.e->ub && bwd ? 0 : (bwd ? (size_t)d->NH * d->D * pl.DK : (size_t)d->NH * G * d->D * pl.DK) * io_size(d->io_dtype);
     *out = pl;
     return FLASHRNN_OK;
 }
 
 struct Workspace {
-    size_t err_off, exch_off, rpack_off, dgn_off, dbpart_off, drpart_off, trace_off, total;
+    size_t err_off, exch_off, rpack_off[2] /* forward, backward */, dgn_off, dbpart_off, drpart_off, trace_off, total;
     size_t fwd_total;   // bytes a forward call touches: error words, exchange buffers, the forward copy of R
 };
 
@@ -396,9 +430,13 @@ int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, P
     const int G = num_gates(d->cell);
     size_t off = 0;
     w->err_off = off; off += kAlign;   // word 0: forward kernels, word 1: backward kernels
-    w->exch_off = off; off += align_up(pf->exch_bytes > pb->exch_bytes ? pf->exch_bytes : pb->exch_bytes);
-    w->rpack_off = off; off += align_up(pf->rpack_bytes > pb->rpack_bytes ? pf->rpack_bytes : pb->rpack_bytes);
-    w->fwd_total = w->rpack_off + align_up(pf->rpack_bytes);
+    // exchange buffers and packed R of a call: the two directions use the same memory, each with a split of its own
+    w->exch_off = off;
+    w->rpack_off[0] = off + align_up(pf->exch_bytes);
+    w->rpack_off[1] = off + align_up(pb->exch_bytes);
+    w->fwd_total = w->rpack_off[0] + align_up(pf->rpack_bytes);
+    const size_t bwd_total = w->rpack_off[1] + align_up(pb->rpack_bytes);
+    off = w->fwd_total > bwd_total ? w->fwd_total : bwd_total;
     w->dgn_off = off; off += align_up(d->cell == FLASHRNN_GRU ? (size_t)d->T * d->B * d->NH * d->D * io_size(d->io_dtype) : 0);
     const int sk = dr_split_k(d->io_dtype == FLASHRNN_BF16, d->T, d->B, d->NH, d->D, G);
     // partial sums of db: one row per batch row (from the persistent kernel) or per contraction slice (from the dR GEMM)
@@ -537,11 +575,11 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     if (pf.exch_bytes && launch_fill(ws + w.exch_off, align_up(pf.exch_bytes), kNoWord, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
     // (the staged forward kernels read R as it is and clear the error words themselves)
     const bool r_in_place = pf.e->tile != 0;
-    if (!r_in_place && launch_pack_r(d->io_dtype == FLASHRNN_BF16, false, R, ws + w.rpack_off, d->NH, d->D, G, pf.DK, (int*)(ws + w.err_off), stream) != hipSuccess)
+    if (!r_in_place && launch_pack_r(d->io_dtype == FLASHRNN_BF16, false, R, ws + w.rpack_off[0], d->NH, d->D, G, pf.DK, (int*)(ws + w.err_off), stream) != hipSuccess)
         return FLASHRNN_ERR_LAUNCH;
     KernelParams kp;
     memset(&kp, 0, sizeof(kp));
-    kp.Wx = Wx; kp.R = r_in_place ? R : (const void*)(ws + w.rpack_off); kp.bias = b; kp.states0 = (const float*)states0; kp.states = (float*)states;
+    kp.Wx = Wx; kp.R = r_in_place ? R : (const void*)(ws + w.rpack_off[0]); kp.bias = b; kp.states0 = (const float*)states0; kp.states = (float*)states;
     kp.cache = gate_cache;
     kp.exch = (uint32_t*)(ws + w.exch_off);
     kp.err = (int*)(ws + w.err_off);
@@ -600,8 +638,8 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     const size_t esz = io_size(d->io_dtype);
     // The backward copy of R is R itself, padded along (gate, unit) to the kernel's contraction length: without padding
     // and without cross-CU waits (whose error word the packing kernel clears) the kernel reads R where it is.
-    const bool r_in_place = !pb.e->multi && pb.DK == G * d->D;
-    if (!r_in_place && launch_pack_r(bf, true, R, ws + w.rpack_off, d->NH, d->D, G, pb.DK, (int*)(ws + w.err_off) + 1, stream) != hipSuccess)
+    const bool r_in_place = pb.e->ub || (!pb.e->multi && pb.DK == G * d->D);
+    if (!r_in_place && launch_pack_r(bf, true, R, ws + w.rpack_off[1], d->NH, d->D, G, pb.DK, (int*)(ws + w.err_off) + 1, stream) != hipSuccess)
         return FLASHRNN_ERR_LAUNCH;
     const size_t units = (size_t)d->B * d->NH * d->D;
     const size_t st_step = (size_t)S * units * 4, io_step = units * esz, rec_step = units * record_slots(d->cell) * esz;
@@ -624,10 +662,12 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
         } else if (!recompute) {
             cache = gate_cache;
         }
-        if (pb.exch_bytes && launch_fill(ws + w.exch_off, align_up(pb.exch_bytes), kNoWord, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
+        // (where no packing kernel ran, the first fill clears the error word of the waits)
+        if (pb.exch_bytes && launch_fill(ws + w.exch_off, align_up(pb.exch_bytes), kNoWord, stream, r_in_place && first ? (int*)(ws + w.err_off) + 1 : nullptr) != hipSuccess)
+            return FLASHRNN_ERR_LAUNCH;
         KernelParams kp;
         memset(&kp, 0, sizeof(kp));
-        kp.R = r_in_place ? R : (const void*)(ws + w.rpack_off);
+        kp.R = r_in_place ? R : (const void*)(ws + w.rpack_off[1]);
         kp.states = (float*)((char*)const_cast<void*>(states) + (size_t)r0 * st_step);
         kp.cache = const_cast<void*>(cache);
         kp.dH = (const char*)dH + (size_t)r0 * io_step;

@@ -333,13 +333,16 @@ template <bool BF16, int PP> __device__ __forceinline__ void load_io_r(rsrc_t r,
         }
     }
 }
+// Stores of 16 bytes carry no scalar offset.  With one the compiler takes the data registers for free behind the store; a value written to
+// the first of them by the very next instruction was stored instead in the last four lanes of each row of 16 (seen in the
+// partial sums of the split backward kernel; without the scalar offset the compiler keeps two instructions between).
 template <bool BF16, int PP> __device__ __forceinline__ void store_io_r(rsrc_t r, uint32_t voff, uint32_t soff, const float (&v)[PP]) {
     if constexpr (BF16) {
         if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)pack_bf16x2(v[0], v[1]), (int)pack_bf16x2(v[2], v[3])}, r, voff, soff, 0);
         else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(v[0], v[1]), r, voff, soff, 0);
         else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)f32_to_bf16_bits(v[0]), r, voff, soff, 0);
     } else {
-        if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, f32x4{v[0], v[1], v[2], v[3]}), r, voff, soff, 0);
+        if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, f32x4{v[0], v[1], v[2], v[3]}), r, voff + soff, 0, 0);
         else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{__builtin_bit_cast(int, v[0]), __builtin_bit_cast(int, v[1])}, r, voff, soff, 0);
         else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[0]), r, voff, soff, 0);
     }

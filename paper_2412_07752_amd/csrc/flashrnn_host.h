@@ -20,6 +20,12 @@ struct KernelEntry {
     int exact;  // 1: only for heads of exactly the kernel's contraction length (compile-time LDS layout); 2: such a kernel that
                 // fetches its inputs six steps ahead (for inputs that come from HBM); 3: the same for the sizes below
     const void* fn;
+    // kernels with wave roles (heads split over the CUs of one XCD, flashrnn_split_kernels.h); ub = 0: none of them
+    int ub;      // blocks of 16 units per workgroup
+    int nb;      // output blocks per compute wave
+    int direct;  // each compute wave waits for the words of its own lanes: at most nb workgroups per group
+    int nbuf;    // exchange buffers
+    int smem;    // bytes of dynamic LDS
 };
 
 struct KernelTable {
@@ -44,7 +50,7 @@ int dr_split_k(bool bf16, int T, int B, int NH, int D, int G);
 hipError_t launch_dr_gemm(bool bf16, const float* states, const void* dWx, const void* dgn, float* part, float* dR, int T, int B,
                           int NH, int D, int G, int S, bool gru, float* db_part, bool db_from_gemm, float* db, hipStream_t stream);
 hipError_t launch_sum_slices(const float* part, float* out, size_t count, int NS, size_t stride, hipStream_t stream);
-hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t stream);   // 32-bit words
+hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t stream, int* err = nullptr);   // 32-bit words; clears *err as well
 inline hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) { return launch_fill(p, bytes, 0u, stream); }
 hipError_t launch_pack_r(bool bf16, bool bwd, const void* R, void* out, int NH, int D, int G, int DK, int* err, hipStream_t stream);
 

@@ -10,6 +10,7 @@
 #include "flashrnn_host.h"
 #include "flashrnn_kernels.h"
 #include "flashrnn_tile_kernels.h"
+#include "flashrnn_split_kernels.h"
 #include "flashrnn_recompute.h"
 
 namespace flashrnn {
@@ -23,31 +24,36 @@ namespace flashrnn {
 #endif
 
 #define FRNN_F(KT, KS, BT, MULTI, MAXW, EB) \
-    {FRNN_CELL, FRNN_BF16, 0, KT, KS, BT, MULTI, MAXW, EB, 0, 0, (const void*)&fwd_kernel<FRNN_CELL, (FRNN_BF16 != 0), KT, KS, BT, (MULTI != 0), MAXW, EB>},
+    {FRNN_CELL, FRNN_BF16, 0, KT, KS, BT, MULTI, MAXW, EB, 0, 0, (const void*)&fwd_kernel<FRNN_CELL, (FRNN_BF16 != 0), KT, KS, BT, (MULTI != 0), MAXW, EB>, 0, 0, 0, 0, 0},
 #define FRNN_B(KT, KS, BT, MULTI, MAXW, EB) \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, KS, BT, MULTI, MAXW, EB, 0, 0, (const void*)&bwd_kernel<FRNN_CELL, (FRNN_BF16 != 0), (KT) * FRNN_G, KS, BT, (MULTI != 0), MAXW, EB>},
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, KS, BT, MULTI, MAXW, EB, 0, 0, (const void*)&bwd_kernel<FRNN_CELL, (FRNN_BF16 != 0), (KT) * FRNN_G, KS, BT, (MULTI != 0), MAXW, EB>, 0, 0, 0, 0, 0},
 // forward and backward share the shape list: the backward contraction axis is G times longer
 #define FRNN_FB(KT, KS, BT, MULTI, MAXW) FRNN_F(KT, KS, BT, MULTI, MAXW, 1) FRNN_B(KT, KS, BT, MULTI, MAXW, 1)
 // small batch tiles (bf16, one workgroup per group): forward from the dedicated tile kernel
 #define FRNN_FT(KT, BT, MAXW) \
-    {FRNN_CELL, FRNN_BF16, 0, KT, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&fwd_tile_kernel<FRNN_CELL, KT, BT, MAXW>},
+    {FRNN_CELL, FRNN_BF16, 0, KT, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&fwd_tile_kernel<FRNN_CELL, KT, BT, MAXW>, 0, 0, 0, 0, 0},
 // ... backward: one kernel for heads of exactly KT * 32 units (compile-time LDS layout) and one for the sizes below (two
 // kernels, not two paths in one: the backward kernel sits near the register limit of its launch bound, and a spill in either
 // path would disqualify both)
 #define FRNN_BTL(KT, BT, MAXW) \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 1, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true>}, \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false>},
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 1, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true>, 0, 0, 0, 0, 0}, \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 0, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false>, 0, 0, 0, 0, 0},
 // ... and, for heads of up to 128 units, two more that request their inputs six steps ahead through registers
 // (taken when they will come from HBM; KernelEntry::exact = 2: heads of exactly 32, 64 or 128 units, 3: the sizes below)
 #define FRNN_BTLD(KT, BT, MAXW) \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 2, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true, true>}, \
-    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 3, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false, true>},
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 2, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, true, true>, 0, 0, 0, 0, 0}, \
+    {FRNN_CELL, FRNN_BF16, 1, (KT) * FRNN_G, 1, BT, 0, MAXW, 1, 1, 3, (const void*)&bwd_tile_kernel<FRNN_CELL, (KT) * FRNN_G, BT, MAXW, false, true>, 0, 0, 0, 0, 0},
 #define FRNN_TILE(KT, BT, MAXW) FRNN_FT(KT, BT, MAXW) FRNN_B(KT, 1, BT, 0, MAXW, 1) FRNN_BTL(KT, BT, MAXW)
 // the largest heads: one block of 16 units per workgroup, 4 contraction slices, one wave per SIMD
 #define FRNN_FL(KT, BT) FRNN_F(KT, 4, BT, 1, 4, 1)
 #define FRNN_BL(KT, BT) FRNN_B(KT, 4, BT, 1, 4, 1)
 // EB blocks of 16 units per wave (fewer, fatter waves: the operand is read from LDS once per wave)
 #define FRNN_FBE(KT, BT, MAXW, EB) FRNN_F(KT, 1, BT, 0, MAXW, EB) FRNN_B(KT, 1, BT, 0, MAXW, EB)
+
+// heads split over the CUs of an XCD, backward with wave roles: UB blocks of 16 units per workgroup, NB output blocks per compute wave
+#define FRNN_SB(UB, NB, BT, DIRECT) \
+    {FRNN_CELL, FRNN_BF16, 1, 0, 1, BT, 1, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NW, 1, 0, 0, \
+     (const void*)&split_bwd_kernel<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>, UB, NB, DIRECT, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NBUF, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::SMEM},
 
 static const KernelEntry kEntries[] = {
 #if FRNN_BF16
@@ -70,6 +76,10 @@ static const KernelEntry kEntries[] = {
     // a head split over workgroups, for batch tiles of 16, 8 and 4 rows (small tiles: more groups, less to exchange)
     FRNN_MULTI_SHAPES(16) FRNN_MULTI_SHAPES(8) FRNN_MULTI_SHAPES(4)
 #undef FRNN_MULTI_SHAPES
+#define FRNN_SPLIT_SHAPES(BT) FRNN_SB(1, 4, BT, 0) FRNN_SB(2, 4, BT, 0) FRNN_SB(2, 6, BT, 0)
+    FRNN_SPLIT_SHAPES(16) FRNN_SPLIT_SHAPES(8) FRNN_SPLIT_SHAPES(4)
+    FRNN_SB(4, 4, 8, 1) FRNN_SB(4, 5, 8, 1) FRNN_SB(4, 4, 4, 1) FRNN_SB(4, 5, 4, 1) FRNN_SB(4, 6, 4, 1)
+#undef FRNN_SPLIT_SHAPES
     // heads of 1040 .. 2688 units: contraction lengths 1280, 1536, 2048, 2560, 2688.  Forward with all 16 rows of a
     // batch tile where the registers allow, backward (whose point-wise phase holds more values per row) with 8 or 4;
     // the planner takes the largest tile whose kernel neither spills nor overflows the LDS.
@@ -97,6 +107,7 @@ inline KernelTable make_table() {
 #undef FRNN_FB
 #undef FRNN_FBE
 #undef FRNN_FL
+#undef FRNN_SB
 #undef FRNN_BL
 #undef FRNN_FT
 #undef FRNN_BTL

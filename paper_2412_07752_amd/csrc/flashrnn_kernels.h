@@ -372,8 +372,8 @@ __device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t rs, uint32_t 
     else __builtin_amdgcn_raw_buffer_store_b64(w, rs, lane_off, off, 0);
 }
 __device__ __forceinline__ void store_words(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t off, i32x4 w, bool far) {
-    if (far) __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, kAuxAgent);
-    else __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off, off, 0);
+    if (far) __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off + off, 0, kAuxAgent);   // (no scalar offset: see store_io_r)
+    else __builtin_amdgcn_raw_buffer_store_b128(w, rs, lane_off + off, 0, 0);
 }
 // A wave publishes its 16 units (from k_wave on) of the group's BT rows: with BT < 16 the lanes whose first unit is a multiple of four
 // collect it and the three units behind it first (every lane holds fewer values there), the other lanes' stores are dropped.

@@ -415,9 +415,11 @@ __global__ void sum_slices2_kernel(const float* __restrict__ part1, float* __res
     *(f32x4*)(out + j) = a;
 }
 
-__global__ void fill_kernel(uint32_t* __restrict__ p, size_t count, uint32_t word) {
+// (16 bytes per thread: the sizes and addresses of all sections of the workspace are multiples of 256, those of db and dR of 16)
+__global__ void fill_kernel(i32x4* __restrict__ p, size_t count, int word, int* __restrict__ err) {
     const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < count) p[j] = word;
+    if (j == 0 && err != nullptr) *err = 0;
+    if (j < count) p[j] = i32x4{word, word, word, word};
 }
 
 // Packed copies of R for the persistent kernels (made once per call, R is read once per launch):
@@ -541,10 +543,10 @@ hipError_t launch_sum_slices(const float* part, float* out, size_t count, int NS
     return hipGetLastError();
 }
 
-hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t stream) {
-    const size_t count = bytes / 4;
+hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t stream, int* err) {
+    const size_t count = bytes / 16;
     if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, (uint32_t*)p, count, word);
+    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, (i32x4*)p, count, (int)word, err);
     return hipGetLastError();
 }
 

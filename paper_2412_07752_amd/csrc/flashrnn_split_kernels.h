@@ -1,0 +1,607 @@
+// Persistent kernels for heads split over the CUs of one XCD (bf16 I/O, heads of up to 1024 units).
+//
+// Backward: every member of a group keeps the gate gradients dg_t of its own units to itself and multiplies them with the columns of R
+// that belong to them: a partial dh_{t-1} of the WHOLE head.  What crosses the CUs are these partial sums (float32, added in a fixed
+// order by the unit's owner), not the gate gradients: 4 D bytes per row out and in instead of 2 G D bytes in, the matrix
+// product needs one CU's 16 UB G contraction elements in LDS instead of all G D, and the hand-over follows the product instead of preceding it.
+//
+// The waves of a workgroup have roles.  A wave's vector memory operations return in order, so a wave that waits for another CU's words must not
+// have a load from HBM in its queue:
+//   compute waves   point-wise function, matrix product, exchange; nothing else of theirs touches memory
+//   load waves      the inputs of the next steps, straight into a ring of LDS slots, several steps ahead
+//   store waves     the outputs of the step, from the LDS rows that the compute waves leave
+// They meet at the barriers of a step only.
+// (Backward kernels, against the exchange of gate gradients by bwd_kernel: sLSTM 8 x 256, 32 rows, 2048 steps 3.27 -> 2.19 ms, 3 x 256, 16 rows, 1024
+// steps 1.59 -> 0.97 ms, LSTM 1 x 768, 128 rows, 1024 steps 6.77 -> 3.37 ms.)
+#pragma once
+#include "flashrnn_kernels.h"
+
+namespace flashrnn {
+
+// All waves of the workgroup; LDS writes in front of it are visible behind it.  (Not __syncthreads(): nothing else is waited for.)
+__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// ---------------------------------------------------------------------------------------------
+// The Jacobian of a step in two parts: factors that do not depend on dh_t, formed while the exchange is on its way, and the few
+// multiply-adds behind it.
+// ---------------------------------------------------------------------------------------------
+template <int CELL> struct PointGrad;
+template <> struct PointGrad<CELL_LSTM> {   // k = {o (1 - tanh^2 c), z i (1 - i), c_prev f (1 - f), i (1 - z^2), tanh(c) o (1 - o)}
+    static constexpr int NK = 6;
+    static __device__ __forceinline__ void factors(const float (&cv)[4], const float (&sc)[2], const float (&sp)[2], float (&k)[NK]) {
+        const float i = cv[0], f = cv[1], z = cv[2], o = cv[3], tc = tanh_<true>(sc[1]);
+        k[0] = o * (1.0f - tc * tc);
+        k[1] = z * i * (1.0f - i);
+        k[2] = sp[1] * f * (1.0f - f);
+        k[3] = i * (1.0f - z * z);
+        k[4] = tc * o * (1.0f - o);
+        k[5] = f;
+    }
+    static __device__ __forceinline__ void apply(const float (&k)[NK], float (&ds)[2], float (&dwx)[4], float (&dg)[4]) {
+        const float dh = ds[0], dc = fmaf(dh, k[0], ds[1]);
+        dg[0] = dc * k[1]; dg[1] = dc * k[2]; dg[2] = dc * k[3]; dg[3] = dh * k[4];
+        dwx[0] = dg[0]; dwx[1] = dg[1]; dwx[2] = dg[2]; dwx[3] = dg[3];
+        ds[0] = 0.0f; ds[1] = dc * k[5];
+    }
+};
+template <> struct PointGrad<CELL_SLSTM> {   // k = {o/n, o c/n^2, z, i, c_prev, n_prev, f sig(-f), i (1 - z^2), (c/n) o (1 - o), f}
+    static constexpr int NK = 10;
+    static __device__ __forceinline__ void factors(const float (&cv)[5], const float (&sc)[4], const float (&sp)[4], float (&k)[NK]) {
+        const float inv = fast_rcp(sc[2]), q = sc[1] * inv, o = cv[3], z = cv[2], oi = o * inv;
+        k[0] = oi;
+        k[1] = oi * q;
+        k[2] = z;
+        k[3] = cv[0];
+        k[4] = sp[1];
+        k[5] = sp[2];
+        k[6] = cv[1] * cv[4];
+        k[7] = cv[0] * (1.0f - z * z);
+        k[8] = q * o * (1.0f - o);
+        k[9] = cv[1];
+    }
+    static __device__ __forceinline__ void apply(const float (&k)[NK], float (&ds)[4], float (&dwx)[4], float (&dg)[4]) {
+        const float dh = ds[0], dc = fmaf(dh, k[0], ds[1]), dn = fmaf(-dh, k[1], ds[2]);
+        dg[0] = fmaf(dc, k[2], dn) * k[3];
+        dg[1] = fmaf(dc, k[4], dn * k[5]) * k[6];
+        dg[2] = dc * k[7];
+        dg[3] = dh * k[8];
+        dwx[0] = dg[0]; dwx[1] = dg[1]; dwx[2] = dg[2]; dwx[3] = dg[3];
+        ds[0] = 0.0f; ds[1] = dc * k[9]; ds[2] = dn * k[9]; ds[3] = 0.0f;
+    }
+};
+template <> struct PointGrad<CELL_GRU> {   // k = {(1 - z)(1 - cand^2), (h_prev - cand) z (1 - z), k0 yn r (1 - r), k0 r, z}
+    static constexpr int NK = 5;
+    static __device__ __forceinline__ void factors(const float (&cv)[4], const float (&)[1], const float (&sp)[1], float (&k)[NK]) {
+        const float r = cv[0], z = cv[1], cand = cv[2], yn = cv[3];
+        k[0] = (1.0f - z) * (1.0f - cand * cand);
+        k[1] = (sp[0] - cand) * z * (1.0f - z);
+        k[2] = k[0] * yn * r * (1.0f - r);
+        k[3] = k[0] * r;
+        k[4] = z;
+    }
+    static __device__ __forceinline__ void apply(const float (&k)[NK], float (&ds)[1], float (&dwx)[3], float (&dg)[3]) {
+        const float dh = ds[0];
+        dg[0] = dh * k[2]; dg[1] = dh * k[1]; dg[2] = dh * k[3];
+        dwx[0] = dg[0]; dwx[1] = dg[1]; dwx[2] = dh * k[0];
+        ds[0] = dh * k[4];
+    }
+};
+template <> struct PointGrad<CELL_GRU4> {
+    static constexpr int NK = 5;
+    static __device__ __forceinline__ void factors(const float (&cv)[4], const float (&)[1], const float (&sp)[1], float (&k)[NK]) {
+        const float z = cv[0], r = cv[1], cand = cv[2], tg = cv[3];
+        const float pre = (1.0f - z) * (1.0f - cand * cand);
+        k[0] = (sp[0] - cand) * z * (1.0f - z);
+        k[1] = pre * tg * r * (1.0f - r);
+        k[2] = pre;
+        k[3] = pre * r * (1.0f - tg * tg);
+        k[4] = z;
+    }
+    static __device__ __forceinline__ void apply(const float (&k)[NK], float (&ds)[1], float (&dwx)[4], float (&dg)[4]) {
+        const float dh = ds[0];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) { dg[g] = dh * k[g]; dwx[g] = dg[g]; }
+        ds[0] = dh * k[4];
+    }
+};
+template <> struct PointGrad<CELL_ELMAN> {
+    static constexpr int NK = 1;
+    static __device__ __forceinline__ void factors(const float (&cv)[1], const float (&)[1], const float (&)[1], float (&k)[NK]) { k[0] = 1.0f - cv[0] * cv[0]; }
+    static __device__ __forceinline__ void apply(const float (&k)[NK], float (&ds)[1], float (&dwx)[1], float (&dg)[1]) {
+        dg[0] = ds[0] * k[0];
+        dwx[0] = dg[0];
+        ds[0] = 0.0f;
+    }
+};
+
+// partial sums of one [16 units] x [BT rows] block: BT / 4 floats per lane (lane (c, quad): unit c; rows quad (+ 4), with 16 rows 4 quad ..)
+template <int PP> __device__ __forceinline__ void store_part(rsrc_t rs, uint32_t voff, uint32_t soff, const float (&v)[PP]) {
+    int x[PP];
+#pragma unroll
+    for (int i = 0; i < PP; ++i) x[i] = exch_word(__builtin_bit_cast(uint32_t, v[i]));
+    // (16 bytes: no scalar offset, see store_io_r)
+    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{x[0], x[1], x[2], x[3]}, rs, voff + soff, 0, 0);
+    else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{x[0], x[1]}, rs, voff, soff, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(x[0], rs, voff, soff, 0);
+}
+template <int PP> __device__ __forceinline__ void clear_part(rsrc_t rs, uint32_t voff, uint32_t soff) {
+    constexpr int none = (int)kNoWord;
+    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{none, none, none, none}, rs, voff, soff, 0);
+    else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{none, none}, rs, voff, soff, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(none, rs, voff, soff, 0);
+}
+constexpr uint32_t kTrash = 1024;   // bytes at the end of an exchange buffer: blocks that nobody waits for
+constexpr int kAuxPoll = (int)(0x80000000u | (unsigned)kAuxAgent);   // (volatile: every round goes to memory again)
+template <int PP> __device__ __forceinline__ void poll_part(rsrc_t rs, uint32_t voff, uint32_t soff, uint32_t (&v)[PP]) {
+    if constexpr (PP == 4) {
+        const i32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, kAuxPoll);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (uint32_t)x[i];
+    } else if constexpr (PP == 2) {
+        const i32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, kAuxPoll);
+        v[0] = (uint32_t)x[0]; v[1] = (uint32_t)x[1];
+    } else {
+        v[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, kAuxPoll);
+    }
+}
+// One more look at the words failed: give up?  (spin limit, or another workgroup has given up)
+__device__ __forceinline__ bool poll_gives_up(int spins, int spin_limit, int* err) {
+    if (spins > spin_limit) {
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+    return (spins & 255) == 255 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Backward
+// ---------------------------------------------------------------------------------------------
+// UB blocks of 16 units per workgroup, NB output blocks of 16 units per compute wave.
+// DIRECT (few members): compute wave w owns unit block w and forms, for every member of the group, the partial sums of that member's
+// block w: the words it waits for are those of its own lanes, and the step has one barrier.  Otherwise the D / 16 output blocks are dealt out
+// over eight compute waves, the arriving partial sums are added up by all of them (each thread one place of the segment and a fixed subset of the
+// producers) and meet in LDS.
+template <int CELL, int UB, int NB, int BT, bool DIRECT> struct SplitBwd {
+    using CT = CellTraits<CELL>;
+    static constexpr int G = CT::G, S = CT::S, NC = CT::NC;
+    static constexpr bool SP = BT < 16;
+    static constexpr int U = 16 * UB, K = G * U;
+    static constexpr int NCW = DIRECT ? UB : 8, NLD = DIRECT ? 3 : 2, NST = DIRECT ? 1 : 2, NW = NCW + NLD + NST;
+    static constexpr int NKS = (K + 63) / 64, KTD = (K + 31) / 32;     // steps of the sparse / dense matrix instruction
+    static constexpr int HPB = ((SP ? NKS * 64 : KTD * 32) + operand_pad(true, SP)) * 2;   // bytes of an operand row
+    static constexpr int NDG = DIRECT ? 2 : 1;                          // operand buffers
+    static constexpr int PPV = BT / 4;                                  // floats per lane of a block
+    static constexpr int SEG = UB * BT * 64;                            // bytes one member sends another per step
+    static constexpr int NPT = UB * BT / 4, PT = DIRECT ? BT / 4 : (NPT + 7) / 8;   // tiles of 16 units x 4 rows: in all, per wave
+    static constexpr int SEGC = SEG / 16, NSUB = 512 / SEGC < 8 ? 512 / SEGC : 8, NPC = (NB * 8 / UB + NSUB - 1) / NSUB;
+    static constexpr int NBUF = DIRECT ? 4 : 2;
+    // inputs of a step in chunks of 16 bytes, each stream rounded up to whole pieces of 64 chunks
+    static constexpr int REC = CT::RS * 2, SB0 = cell_uses_h_prev(CELL) ? 0 : 1, NSB = CELL == CELL_SLSTM ? 2 : CELL == CELL_ELMAN ? 0 : 1;
+    static constexpr int CR = BT * UB * REC, CS = NSB * BT * 4 * UB, CD = BT * 2 * UB;
+    static constexpr int GR = (CR + 63) / 64, GS = (CS + 63) / 64, GD = (CD + 63) / 64, NLJ = (GR + GS + GD + NLD - 1) / NLD;
+    static constexpr int SLOT = NLD * NLJ * 1024, RD = 49152 / SLOT < 3 ? 3 : 49152 / SLOT > 6 ? 6 : 49152 / SLOT;
+    static constexpr int GO = CELL == CELL_GRU ? G + 1 : G, COUT = BT * GO * 2 * UB, NSJ = (COUT + NST * 64 - 1) / (NST * 64);
+    static constexpr int DG_BYTES = BT * HPB, IMG_BYTES = CELL == CELL_GRU ? BT * U * 2 : 0;
+    static constexpr int IMG_OFF = NDG * DG_BYTES, RING_OFF = (IMG_OFF + NDG * IMG_BYTES + 127) / 128 * 128;
+    static constexpr int RED_OFF = RING_OFF + RD * SLOT, SMEM = RED_OFF + (DIRECT ? 0 : NSUB * SEG);
+    static_assert((RD - 1) * NLJ < 63, "the wait counts of the load waves");
+};
+
+// position of (row, unit block ub) in an input row of the ring: the blocks of row r are stored r places on, modulo UB, so that the
+// rows that one instruction reads lie in different banks
+template <int UB> __device__ __forceinline__ uint32_t ring_block(uint32_t ub, uint32_t row) { return (ub + row) % UB; }
+
+template <int CELL, int UB, int NB, int BT, bool DIRECT>
+__device__ __forceinline__ void split_bwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int wl) {
+    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    char* ring = smem + C::RING_OFF + wl * 1024;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
+        // piece j of this wave: which stream, and this lane's chunk of it
+        uint32_t voff[C::NLJ];
+#pragma unroll
+        for (int j = 0; j < C::NLJ; ++j) {
+            const int piece = j * C::NLD + wl;
+            voff[j] = kDrop;
+            auto place = [&](uint32_t idx, uint32_t rows, uint32_t cpb, uint32_t esz, uint32_t plane) {   // rows of UB blocks of cpb chunks
+                const uint32_t cpr = UB * cpb, r = idx / cpr, pos = idx % cpr, row = r % BT;
+                const uint32_t blk = (pos / cpb + UB * BT - row) % UB, brow = q * BT + row;
+                if (r < rows && brow < B) voff[j] = (r / BT) * plane + (brow * HD + n * D + e0 + blk * 16) * esz + (pos % cpb) * 16;
+            };
+            if (piece < C::GR) place(piece * 64 + lane, BT, C::REC, C::REC, 0);
+            else if (piece < C::GR + C::GS) place((piece - C::GR) * 64 + lane, C::NSB * BT, 4, 4, B * HD * 4);
+            else if (piece < C::GR + C::GS + C::GD) place((piece - C::GR - C::GS) * 64 + lane, BT, 2, 2, 0);
+        }
+        const size_t c_step = (size_t)B * HD * C::REC, st_step = (size_t)C::S * B * HD * 4, dh_step = (size_t)B * HD * 2;
+        auto fetch = [&](int s, int slot) {   // inputs of the step s places before the last one
+            const int t = p.T - 1 - s;
+            const bool real = t >= 0;         // (beyond the first step: nothing is fetched, but as many operations are counted)
+            const size_t at = real ? t : 0;
+            const rsrc_t rc = make_rsrc((const char*)p.cache + at * c_step);
+            const rsrc_t rst = make_rsrc((const char*)p.states + at * st_step + (size_t)C::SB0 * B * HD * 4);
+            const rsrc_t rdh = make_rsrc((const char*)p.dH + at * dh_step);
+#pragma unroll
+            for (int j = 0; j < C::NLJ; ++j) {
+                const int piece = j * C::NLD + wl;
+                load_chunk_to_lds(piece < C::GR ? rc : piece < C::GR + C::GS ? rst : rdh, ring + slot * C::SLOT + j * C::NLD * 1024, voff[j] | (real ? 0u : kDrop));
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < C::RD; ++s) fetch(s, s);
+        wait_vmem<(C::RD - 1) * C::NLJ>();
+        wg_barrier();
+        int slot = 0;
+        for (int s = 0; s < p.T; ++s) {
+            wait_vmem<(C::RD - 2) * C::NLJ>();   // step s + 1 is there
+            wg_barrier();
+            fetch(s + C::RD, slot);              // into the slot of step s, which everybody has read
+            slot = slot + 1 == C::RD ? 0 : slot + 1;
+            if constexpr (!DIRECT) wg_barrier();
+        }
+        wait_vmem<0>();
+    }
+}
+
+template <int CELL, int UB, int NB, int BT, bool DIRECT>
+__device__ __forceinline__ void split_bwd_store(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int ws) {
+    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
+        uint32_t voff[C::NSJ], vofn[C::NSJ], loff[C::NSJ];
+        bool img[C::NSJ];
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) {
+            const uint32_t idx = (j * C::NST + ws) * 64 + lane, cpr = 2 * UB, r = idx / cpr, ch = idx % cpr, g = r % C::GO, row = r / C::GO, brow = q * BT + row;
+            const bool in = row < BT && brow < B;
+            // (the rows of the matrix operand are dWx_t, but for the GRU's candidate: its input-side gradient has an image of its own, and
+            // what the operand holds goes to the buffer of recurrent-side gradients)
+            voff[j] = in && g < (uint32_t)C::G ? ((brow * C::G + g) * HD + n * D + e0) * 2 + ch * 16 : kDrop;
+            vofn[j] = in && g == (uint32_t)C::G ? (brow * HD + n * D + e0) * 2 + ch * 16 : kDrop;
+            img[j] = CELL == CELL_GRU && g == 2;
+            loff[j] = row >= BT ? 0u : img[j] ? C::IMG_OFF + row * C::U * 2 + ch * 16 : row * C::HPB + (g == (uint32_t)C::G ? 2u : g) * C::U * 2 + ch * 16;
+        }
+        const size_t wx_step = (size_t)B * C::G * HD * 2, dh_step = (size_t)B * HD * 2;
+        char* dwx = (char*)p.dWx + (size_t)(p.T > 0 ? p.T - 1 : 0) * wx_step;
+        char* dgn = (char*)p.dgn + (size_t)(p.T > 0 ? p.T - 1 : 0) * dh_step;
+        wg_barrier();
+        for (int s = 0; s < p.T; ++s) {
+            wg_barrier();
+            const uint32_t buf = C::NDG == 2 ? (uint32_t)(s & 1) : 0u;
+            i32x4 v[C::NSJ];
+#pragma unroll
+            for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + buf * (CELL == CELL_GRU && img[j] ? C::IMG_BYTES : C::DG_BYTES));
+#pragma unroll
+            for (int j = 0; j < C::NSJ; ++j) {
+                __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(dwx), voff[j], 0, 0);
+                if constexpr (CELL == CELL_GRU) __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(dgn), vofn[j], 0, 0);
+            }
+            dwx -= wx_step;
+            dgn -= dh_step;
+            if constexpr (!DIRECT) wg_barrier();
+        }
+    }
+}
+
+template <int CELL, int UB, int NB, int BT, bool DIRECT>
+__device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int w) {
+    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
+    using PG = PointGrad<CELL>;
+    constexpr int G = C::G, S = C::S, NC = C::NC, PT = C::PT, PPV = C::PPV, U = C::U;
+    constexpr bool SP = C::SP;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const int T = p.T, P = p.P, me = bm.member;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D, m = D / 16;
+    const SparseLane<BT == 8 ? 8 : 4> sl(lane);
+    const uint32_t c = sl.c, quad = sl.quad;
+    const rsrc_t xr = make_rsrc(p.exch);
+    const uint32_t xbuf = (uint32_t)p.GPAR * P * P * C::SEG + kTrash, xgroup = (uint32_t)bm.gpar * P * P * C::SEG;
+    char* ring = smem + C::RING_OFF;
+    char* red = smem + C::RED_OFF;
+    bool failed = false;
+    FRNN_TRACE_BEGIN();
+
+    // ---- this lane's (unit, row) pairs: tile k covers 16 units x 4 rows.  Via LDS, rows are dealt out so that the lanes of a tile read
+    // their words of a block (PPV consecutive floats per lane) from different banks.
+    const bool pairs = DIRECT || w < C::NPT;
+    uint32_t ub[PT], word[PT], row[PT];
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        const int id = DIRECT ? w * (BT / 4) + k : (pairs ? w : 0) + 8 * k, rr = id % (BT / 4);
+        ub[k] = id / (BT / 4);
+        word[k] = DIRECT || BT == 4 ? rr : BT == 8 ? (rr + (quad >> 1)) & 1 : (rr + quad) & 3;
+        row[k] = BT == 16 ? 4 * quad + word[k] : quad + 4 * word[k];
+    }
+    // ---- the output blocks of this wave (b = 0 is its own block if DIRECT) and where their partial sums go: segment [receiver][sender], UB blocks.
+    // (A wave without a last block forms one all the same and leaves it at the end of the buffer, where nobody looks: no condition in the step.)
+    uint32_t out_off[NB], out_blk[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const uint32_t idx = b * 8 + w;
+        const bool none = !DIRECT && idx >= m;
+        out_blk[b] = DIRECT ? ((uint32_t)(me + b) % NB) * UB + w : none ? 0 : ((uint32_t)me * UB + UB + idx) % m;
+        out_off[b] = none ? xbuf - kTrash : xgroup + ((out_blk[b] / UB) * P + me) * C::SEG + (out_blk[b] % UB) * (64 * BT);
+    }
+    // ---- what this thread waits for.  DIRECT: the words of its own lane from every other member.  Else the 16 bytes at `pos` of the segments
+    // of nv senders from sub * npc on: the waves add up what arrives, each thread a fixed run of senders.
+    constexpr int NIN = DIRECT ? NB - 1 : C::NPC, IW = DIRECT ? PPV : 4;
+    const uint32_t xmine = xgroup + (uint32_t)me * P * C::SEG;
+    const uint32_t pos = (uint32_t)(w * 64 + lane) % C::SEGC, sub = (uint32_t)(w * 64 + lane) / C::SEGC;
+    const int npc = (P + C::NSUB - 1) / C::NSUB;
+    int nv = sub < C::NSUB ? P - (int)sub * npc : 0;
+    nv = nv > npc ? npc : nv;
+    const uint32_t in_lane = DIRECT ? (uint32_t)(lane * BT) : sub * npc * C::SEG + pos * 16;
+    uint32_t in_off[NIN > 0 ? NIN : 1];
+#pragma unroll
+    for (int j = 0; j < NIN; ++j) in_off[j] = xmine + (DIRECT ? ((uint32_t)(me + NB - 1 - j) % NB) * C::SEG + w * (64 * BT) : j * C::SEG);
+    // (the lane offset of sender j, formed anew where it is used: kept from step to step they would take a register each)
+    auto in_voff = [&](int j) {
+        if constexpr (DIRECT) return in_lane;
+        else {
+            asm volatile("" : "+v"(nv));
+            return j < nv ? in_lane : kDrop;
+        }
+    };
+
+    for (uint32_t j = w * 64 + lane; j < (uint32_t)(C::NDG * C::DG_BYTES) / 4; j += C::NCW * 64) ((uint32_t*)smem)[j] = 0u;   // (padding of the operand rows)
+
+    int iter = 0;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = me * U;
+        // ---- R: column c = unit of the output block, contraction over this workgroup's gate gradients k = g * U + u, in registers for all steps
+        bf16x16 Rs[SP ? NB : 1][SP ? C::NKS : 1];
+        bf16x8 Rd[SP ? 1 : NB][SP ? 1 : C::KTD];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + out_blk[b] * 16 + c) * G * D + e0;
+            auto quads = [&](uint32_t kk) {   // four elements of R from k = kk on (zeros beyond the last gate)
+                if constexpr (C::K % (SP ? 64 : 32) == 0) {
+                    return *(const i32x2*)(rrow + (kk / U) * D + kk % U);
+                } else {
+                    const bool in = kk < (uint32_t)C::K;
+                    const i32x2 v = *(const i32x2*)(rrow + (in ? (kk / U) * D + kk % U : 0));
+                    return in ? v : i32x2{0, 0};
+                }
+            };
+            if constexpr (SP) {
+#pragma unroll
+                for (int kc = 0; kc < C::NKS; ++kc) {
+                    i32x4 piece[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t kk = (2 * kc + h) * 32 + sparse_k(quad);
+                        piece[h] = sparse_piece(quads(kk), quads(kk + 8));
+                    }
+                    Rs[b][kc] = sparse_dense(piece[0], piece[1]);
+                }
+            } else {
+#pragma unroll
+                for (int kt = 0; kt < C::KTD; ++kt) {
+                    const uint32_t kk = kt * 32 + quad * 8;
+                    const i32x2 lo = quads(kk), hi = quads(kk + 4);
+                    Rd[b][kt] = __builtin_bit_cast(bf16x8, i32x4{lo[0], lo[1], hi[0], hi[1]});
+                }
+            }
+        }
+        // ---- pairs: places, carried gradients, states after the last step
+        bool ok[PT];
+        uint32_t l_rec[PT], l_st[PT], l_dh[PT], l_dg[PT], g_st[PT];
+        float ds[PT][S], sc[PT][S], sp[PT][S], kf[PT][PG::NK], dh_ext[PT], dbacc[PT][G];
+        const size_t st_step = (size_t)S * B * HD * 4;
+        const uint32_t st_state = B * HD * 4;
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const uint32_t brow = q * BT + row[k];
+            ok[k] = pairs && brow < B;
+            g_st[k] = ((ok[k] ? brow : B - 1) * HD + n * D + e0 + ub[k] * 16 + c) * 4;
+            const uint32_t rb = row[k] * UB + ring_block<UB>(ub[k], row[k]);
+            l_rec[k] = (rb * 16 + c) * C::REC;
+            l_st[k] = C::GR * 1024 + (rb * 16 + c) * 4;
+            l_dh[k] = (C::GR + C::GS) * 1024 + (rb * 16 + c) * 2;
+            l_dg[k] = row[k] * C::HPB + (ub[k] * 16 + c) * 2;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                float v[1] = {0.0f};
+                if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3)) load_io_r<false, 1>(make_rsrc(p.dlast), g_st[k], s * st_state, v);
+                ds[k][s] = v[0];
+                sp[k][s] = 1.0f;
+                float x[1] = {1.0f};
+                if (!cell_uses_h_prev(CELL) && s >= C::SB0 && s < C::SB0 + C::NSB) load_io_r<false, 1>(make_rsrc((const char*)p.states + (size_t)T * st_step), g_st[k], s * st_state, x);
+                sc[k][s] = x[0];
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) dbacc[k][g] = 0.0f;
+        }
+        auto take = [&](uint32_t slot) {   // this lane's inputs of a step, and what follows from them alone
+            const char* in = ring + slot * C::SLOT;
+#pragma unroll
+            for (int k = 0; k < PT; ++k) {
+                float cv[NC];
+                take_record_lds<C::CT::RS, NC>(in + l_rec[k], cv);
+#pragma unroll
+                for (int s = C::SB0; s < C::SB0 + C::NSB; ++s) sp[k][s] = *(const float*)(in + l_st[k] + (s - C::SB0) * BT * U * 4);
+                dh_ext[k] = bf16_bits_to_f32(*(const uint16_t*)(in + l_dh[k]));
+                PG::factors(cv, sc[k], sp[k], kf[k]);
+                if constexpr (!cell_uses_h_prev(CELL)) {
+#pragma unroll
+                    for (int s = C::SB0; s < C::SB0 + C::NSB; ++s) sc[k][s] = sp[k][s];
+                }
+            }
+        };
+        wg_barrier();   // the first inputs are there, the operand rows are zero
+        if (T > 0 && pairs) take(0);
+        // (what the prologue has loaded is complete here: the waits of the time loop are for its own operations only)
+        pin(ds);
+        pin(sc);
+        pin(kf);
+        pin(dh_ext);
+
+        FRNN_TRACE_RESET();
+        uint32_t slot = 0;
+        for (int s = 0; s < T; ++s) {
+            const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)s;
+            const uint32_t buf = cnt % C::NBUF * xbuf;
+            char* dg_rows = smem + (C::NDG == 2 ? (s & 1) * C::DG_BYTES : 0);
+            // ---- gate gradients of the step into the operand rows
+            if (pairs) {
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+                    float dwx[G], dg[G];
+                    ds[k][0] += dh_ext[k];
+                    PG::apply(kf[k], ds[k], dwx, dg);
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        *(uint16_t*)(dg_rows + l_dg[k] + g * U * 2) = (uint16_t)f32_to_bf16_bits(dg[g]);
+                        dbacc[k][g] += dg[g];
+                    }
+                    if constexpr (CELL == CELL_GRU)
+                        *(uint16_t*)(smem + C::IMG_OFF + (C::NDG == 2 ? (s & 1) * C::IMG_BYTES : 0) + row[k] * U * 2 + (ub[k] * 16 + c) * 2) = (uint16_t)f32_to_bf16_bits(dwx[2]);
+                }
+            }
+            // (DIRECT: the accumulators are cleared ahead of the barrier, where the wave waits for its LDS writes anyway)
+            constexpr int CH = DIRECT ? (NB % 2 == 0 ? NB / 2 : 2) : 2;
+            f32x4 a[CH];
+#pragma unroll
+            for (int x = 0; x < CH; ++x) {
+                a[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (DIRECT) asm volatile("" : "+v"(a[x]));
+            }
+            // (two exchange buffers: the words taken back behind the last poll must be gone before anything of this step is published)
+            if constexpr (!DIRECT) wait_vmem<0>();
+            FRNN_TRACE_MARK(0);
+            wg_barrier();
+            FRNN_TRACE_MARK(1);
+            // ---- partial sums of dh_{t-1}: this workgroup's gate gradients times their columns of R
+            bf16x8 gS[SP ? C::NKS : C::KTD];
+            if constexpr (SP) {
+                lds_sparse_chunk<BT, C::NKS, C::NKS, false, true>(dg_rows + sl.rslot * C::HPB, sl, 0, gS);
+            } else {
+#pragma unroll
+                for (int kt = 0; kt < C::KTD; ++kt) gS[kt] = *(const bf16x8*)(dg_rows + c * C::HPB + kt * 64 + quad * 16);
+            }
+            // (CH blocks at a time: the matrix instructions of one block depend on each other)
+            float own[PPV];
+#pragma unroll
+            for (int bi = 0; bi < NB; bi += CH) {
+                if (bi > 0) {
+#pragma unroll
+                    for (int x = 0; x < CH; ++x) a[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+                for (int kc = 0; kc < (SP ? C::NKS : C::KTD); ++kc)
+#pragma unroll
+                    for (int x = 0; x < CH; ++x)
+                        if (bi + x < NB) {
+                            const int b = DIRECT ? (bi + x + 1) % NB : bi + x;
+                            if constexpr (SP) a[x] = smfmac(gS[kc], Rs[b][kc], a[x], sl.idx);
+                            else a[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gS[kc], Rd[b][kc], a[x], 0, 0, 0);
+                        }
+#pragma unroll
+                for (int x = 0; x < CH; ++x)
+                    if (bi + x < NB) {
+                        const int b = DIRECT ? (bi + x + 1) % NB : bi + x;
+                        float v[PPV];
+#pragma unroll
+                        for (int i = 0; i < PPV; ++i) v[i] = SP ? a[x][(2 * i) & 3] + a[x][(2 * i + 1) & 3] : a[x][i];
+                        if (DIRECT && b == 0) {
+#pragma unroll
+                            for (int i = 0; i < PPV; ++i) own[i] = v[i];
+                        } else {
+                            store_part<PPV>(xr, lane * BT, buf + out_off[b], v);
+                        }
+                    }
+            }
+            FRNN_TRACE_MARK(2);
+            // ---- the inputs of the next step, while the partial sums travel
+            slot = slot + 1 == (uint32_t)C::RD ? 0 : slot + 1;
+            if (pairs) take(slot);
+            pin(kf);   // (here, not behind the poll)
+            pin(dh_ext);
+            FRNN_TRACE_MARK(3);
+            // ---- the partial sums of this workgroup's units from the other members
+            uint32_t got[NIN > 0 ? NIN : 1][IW];
+            if (p.spin_limit < 0 && !failed) {   // host-forced failure (tests of the error path): give up without looking
+                __hip_atomic_store(p.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                failed = true;
+            }
+            for (int spins = 0;; ++spins) {
+#pragma unroll
+                for (int j = 0; j < NIN; ++j) poll_part<IW>(xr, in_voff(j), buf + in_off[j], got[j]);
+                uint32_t top = 0u;   // (a word out of range reads as zero)
+#pragma unroll
+                for (int j = 0; j < NIN; ++j)
+#pragma unroll
+                    for (int i = 0; i < IW; ++i) top = max(top, got[j][i]);
+                if (__all((int)(top != kNoWord)) || failed) break;
+                if (poll_gives_up(spins, p.spin_limit, p.err)) { failed = true; break; }
+            }
+            // (taken back for the round NBUF later: this workgroup is the only one that looks at these words)
+#pragma unroll
+            for (int j = 0; j < NIN; ++j) clear_part<IW>(xr, in_voff(j), buf + in_off[j]);
+            FRNN_TRACE_MARK(4);
+            if constexpr (DIRECT) {
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+                    float rec = own[k];
+#pragma unroll
+                    for (int j = 0; j < NIN; ++j) rec += __builtin_bit_cast(float, got[j][k]);
+                    ds[k][0] += fminf(fmaxf(rec, -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
+                }
+            } else {
+                f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < NIN; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[i] += __builtin_bit_cast(float, got[j][i]);
+                if (sub < C::NSUB) *(f32x4*)(red + sub * C::SEG + pos * 16) = sum;
+                wg_barrier();
+                FRNN_TRACE_MARK(5);
+                if (pairs) {
+#pragma unroll
+                    for (int k = 0; k < PT; ++k) {
+                        const float* r0 = (const float*)(red + ub[k] * (64 * BT)) + lane * PPV + word[k];
+                        float part[C::NSUB];
+#pragma unroll
+                        for (int j = 0; j < C::NSUB; ++j) part[j] = r0[j * (C::SEG / 4)];
+                        float rec = part[0];
+#pragma unroll
+                        for (int j = 1; j < C::NSUB; ++j) rec += part[j];
+                        ds[k][0] += fminf(fmaxf(rec, -p.clip), p.clip);
+                    }
+                }
+            }
+        }
+        // ---- gradients of the initial states, per-row partial sums of db
+#pragma unroll
+        for (int k = 0; k < PT; ++k)
+            if (ok[k]) {
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const float v[1] = {ds[k][s]};
+                    store_io_r<false, 1>(make_rsrc(p.dstates0), g_st[k], s * st_state, v);
+                }
+                float* db = p.db_part + (((size_t)(q * BT + row[k]) * NH + n) * G) * D + e0 + ub[k] * 16 + c;
+#pragma unroll
+                for (int g = 0; g < G; ++g) db[(size_t)g * D] = dbacc[k][g] + (p.db_accumulate ? db[(size_t)g * D] : 0.0f);
+            }
+    }
+    FRNN_TRACE_END(p);
+}
+
+template <int CELL, int UB, int NB, int BT, bool DIRECT>
+__global__ __launch_bounds__((SplitBwd<CELL, UB, NB, BT, DIRECT>::NW * 64)) void split_bwd_kernel(const KernelParams p) {
+    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
+    extern __shared__ __align__(16) char smem[];
+    const BlockMap bm(p, true);
+    if (!bm.active) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w < C::NCW) split_bwd_compute<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w);
+    else if (w < C::NCW + C::NLD) split_bwd_load<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW);
+    else split_bwd_store<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW - C::NLD);
+}
+
+}  // namespace flashrnn

@@ -264,6 +264,22 @@ def test_backward_groups_in_rounds_of_smaller_tiles(cell, NH, D, B, bt, split):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,bt,B,T", [
+    (2, 256, 4, 7, 13), (1, 256, 8, 9, 1), (1, 320, 4, 5, 3), (3, 320, 8, 8, 2), (1, 384, 4, 6, 7),   # each compute wave waits for its own lanes' words
+    (2, 208, 4, 5, 8), (1, 272, 8, 11, 7), (1, 448, 4, 6, 13), (1, 640, 8, 9, 5), (1, 768, 4, 5, 2), (1, 208, 16, 17, 6),   # sums via LDS; 13, 17, 28 output blocks over 8 waves
+    (2, 64, 8, 40, 3),   # a small head, groups in rounds
+])
+def test_backward_of_split_heads_exchanges_partial_sums(cell, NH, D, bt, B, T):
+    """Kernels with wave roles: sequences shorter and longer than the ring of inputs, ragged batches, output blocks that do not fill the waves."""
+    w = Workload(f"partial_{cell}_D{D}", cell, T, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + bt)
+    env = {"FLASHRNN_MULTI": "1", "FLASHRNN_BT": str(bt)}
+    if D == 64:
+        env["FLASHRNN_GPAR"] = "8"
+    _check(w, env, with_dlast=True)
+    assert api.flashrnn_plan(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16), True)[2] in ((8, 12) if D in (256, 320, 384) else (12,))
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
     """The staged kernels look two steps ahead: the shortest sequences take every clamped branch of that."""
