@@ -122,10 +122,16 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
         const KernelEntry& e = tab.entries[i];
         if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && e.ub != force_ub)) continue;
         const int P = units16 / e.ub;
-        if (P > cap || (e.direct ? P != e.nb : units16 > 8 * e.nb) || e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
+        if (P > cap || (bwd ? (e.direct ? P != e.nb : units16 > 8 * e.nb) : e.KT * e.KS * 32 < d->D) || e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
+        if (!bwd && env_int("FLASHRNN_NCW", 0) && e.KS != env_int("FLASHRNN_NCW", 0)) continue;
         if ((pl->NG + in_flight(P) - 1) / in_flight(P) > rounds) continue;
-        // the wave-direct kernels first, then the most units per workgroup, then the smallest kernel that holds the head
-        if (!best || e.direct > best->direct || (e.direct == best->direct && (e.ub > best->ub || (e.ub == best->ub && e.nb < best->nb)))) best = &e;
+        if (!best) { best = &e; continue; }
+        // backward the wave-direct kernels first, then the most units per workgroup, then the smallest kernel that holds the head; forward
+        // the fewest units per workgroup (a step's matrix product and point-wise function shrink with them: sLSTM 3 x 256, 16 rows, 1024 steps 900 / 785 /
+        // 733 us with 64 / 32 / 16), then the least padding
+        const bool better = bwd ? (e.direct != best->direct ? e.direct > best->direct : e.ub != best->ub ? e.ub > best->ub : e.nb < best->nb)
+                                : (e.ub != best->ub ? e.ub < best->ub : e.KT * e.KS != best->KT * best->KS ? e.KT * e.KS < best->KT * best->KS : e.KS < best->KS);
+        if (better) best = &e;
     }
     if (!best) return;
     pl->e = best;
@@ -134,9 +140,10 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
     pl->GPAR = in_flight(pl->P);
     pl->grid = (pl->GPAR + kXcds - 1) / kXcds * pl->P * kXcds;
     pl->block = 64 * best->maxw;
-    pl->DK = 0;
+    pl->DK = d->D;   // (the packed copy of R has no padding)
     pl->smem = best->smem;
-    pl->exch_bytes = (size_t)best->nbuf * ((size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash);   // a partial sum of every unit from every member
+    // backward a partial sum of every unit from every member, forward the rows of h
+    pl->exch_bytes = (size_t)best->nbuf * (bwd ? (size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash : (size_t)pl->GPAR * best->BT * best->KT * best->KS * 32 * 2);
 }
 
 // Launch plan.  One workgroup per group whenever the head's R fits one CU's registers with 16 units
@@ -367,7 +374,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             }
         }
     }
-    if (pl.e && pl.e->multi && bf && bwd && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
+    if (pl.e && pl.e->multi && bf && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
     if (!pl.e && force_multi != 0 && bf) {
         // Heads beyond what the CUs of one XCD can hold (D > 1024): the group is spread over the CUs of all XCDs, one
         // block of 16 units and 4 contraction slices per workgroup (one wave per SIMD, up to 336 registers of R each),

@@ -54,6 +54,10 @@ namespace flashrnn {
 #define FRNN_SB(UB, NB, BT, DIRECT) \
     {FRNN_CELL, FRNN_BF16, 1, 0, 1, BT, 1, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NW, 1, 0, 0, \
      (const void*)&split_bwd_kernel<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>, UB, NB, DIRECT, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NBUF, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::SMEM},
+// ... and forward: KTW k-steps for each of NCW compute waves
+#define FRNN_SF(UB, KTW, NCW, BT) \
+    {FRNN_CELL, FRNN_BF16, 0, KTW, NCW, BT, 1, SplitFwd<FRNN_CELL, UB, KTW, NCW, BT>::NW, 1, 0, 0, \
+     (const void*)&split_fwd_kernel<FRNN_CELL, UB, KTW, NCW, BT>, UB, 0, 0, 4, SplitFwd<FRNN_CELL, UB, KTW, NCW, BT>::SMEM},
 
 static const KernelEntry kEntries[] = {
 #if FRNN_BF16
@@ -79,6 +83,12 @@ static const KernelEntry kEntries[] = {
 #define FRNN_SPLIT_SHAPES(BT) FRNN_SB(1, 4, BT, 0) FRNN_SB(2, 4, BT, 0) FRNN_SB(2, 6, BT, 0)
     FRNN_SPLIT_SHAPES(16) FRNN_SPLIT_SHAPES(8) FRNN_SPLIT_SHAPES(4)
     FRNN_SB(4, 4, 8, 1) FRNN_SB(4, 5, 8, 1) FRNN_SB(4, 4, 4, 1) FRNN_SB(4, 5, 4, 1) FRNN_SB(4, 6, 4, 1)
+#undef FRNN_SPLIT_SHAPES
+#define FRNN_SPLIT_SHAPES(BT) FRNN_SF(1, 2, 4, BT) FRNN_SF(1, 3, 4, BT) FRNN_SF(1, 4, 4, BT) \
+    FRNN_SF(2, 2, 4, BT) FRNN_SF(2, 3, 4, BT) FRNN_SF(2, 4, 4, BT) FRNN_SF(2, 4, 6, BT)
+    FRNN_SPLIT_SHAPES(16) FRNN_SPLIT_SHAPES(8) FRNN_SPLIT_SHAPES(4)
+    FRNN_SF(2, 6, 6, 8) FRNN_SF(2, 6, 6, 4)
+    FRNN_SF(4, 2, 4, 8) FRNN_SF(4, 3, 4, 8) FRNN_SF(4, 2, 4, 4) FRNN_SF(4, 3, 4, 4)
 #undef FRNN_SPLIT_SHAPES
     // heads of 1040 .. 2688 units: contraction lengths 1280, 1536, 2048, 2560, 2688.  Forward with all 16 rows of a
     // batch tile where the registers allow, backward (whose point-wise phase holds more values per row) with 8 or 4;
@@ -108,6 +118,7 @@ inline KernelTable make_table() {
 #undef FRNN_FBE
 #undef FRNN_FL
 #undef FRNN_SB
+#undef FRNN_SF
 #undef FRNN_BL
 #undef FRNN_FT
 #undef FRNN_BTL

@@ -8,11 +8,13 @@
 // The waves of a workgroup have roles.  A wave's vector memory operations return in order, so a wave that waits for another CU's words must not
 // have a load from HBM in its queue:
 //   compute waves   point-wise function, matrix product, exchange; nothing else of theirs touches memory
-//   load waves      the inputs of the next steps, straight into a ring of LDS slots, several steps ahead
+//   load waves      the inputs of the next steps, straight into LDS, in bursts of several steps: a CU's vector memory path returns all its waves'
+//                   loads in order, so a poll behind loads from HBM waits for those whoever issued them; once every few steps that costs little
+//                   (sLSTM 8 x 256, 32 rows forward, 2048 steps: loads every step 2.96 ms, every 2 / 4 / 8 / 16 steps 2.41 / 2.19 / 2.11 / 2.05, none at all 1.77)
 //   store waves     the outputs of the step, from the LDS rows that the compute waves leave
 // They meet at the barriers of a step only.
-// (Backward kernels, against the exchange of gate gradients by bwd_kernel: sLSTM 8 x 256, 32 rows, 2048 steps 3.27 -> 2.19 ms, 3 x 256, 16 rows, 1024
-// steps 1.59 -> 0.97 ms, LSTM 1 x 768, 128 rows, 1024 steps 6.77 -> 3.37 ms.)
+// (Backward kernels, against the exchange of gate gradients by bwd_kernel: sLSTM 8 x 256, 32 rows, 2048 steps 3.27 -> 1.79 ms, 3 x 256, 16 rows, 1024
+// steps 1.59 -> 0.84 ms, LSTM 1 x 768, 128 rows, 1024 steps 6.77 -> 3.25 ms.  Forward kernels, against fwd_kernel: 2.31 -> 1.98 ms, 1.00 -> 0.76, 3.30 -> 2.29.)
 #pragma once
 #include "flashrnn_kernels.h"
 
@@ -131,6 +133,11 @@ template <int PP> __device__ __forceinline__ void clear_part(rsrc_t rs, uint32_t
     else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{none, none}, rs, voff, soff, 0);
     else __builtin_amdgcn_raw_buffer_store_b32(none, rs, voff, soff, 0);
 }
+// The lane index, formed anew: what a group's prologue and epilogue derive from it is not kept in registers through the time loop.
+__device__ __forceinline__ int fresh_lane(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 constexpr uint32_t kTrash = 1024;   // bytes at the end of an exchange buffer: blocks that nobody waits for
 constexpr int kAuxPoll = (int)(0x80000000u | (unsigned)kAuxAgent);   // (volatile: every round goes to memory again)
 template <int PP> __device__ __forceinline__ void poll_part(rsrc_t rs, uint32_t voff, uint32_t soff, uint32_t (&v)[PP]) {
@@ -153,6 +160,9 @@ __device__ __forceinline__ bool poll_gives_up(int spins, int spin_limit, int* er
     }
     return (spins & 255) == 255 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
+
+// steps whose inputs are fetched in one burst: two bursts of up to 16 steps fit `room` bytes
+constexpr int burst_steps(int slot, int room) { return room >= 32 * slot ? 16 : room >= 16 * slot ? 8 : room >= 8 * slot ? 4 : 2; }
 
 // ---------------------------------------------------------------------------------------------
 // Backward
@@ -180,12 +190,11 @@ template <int CELL, int UB, int NB, int BT, bool DIRECT> struct SplitBwd {
     static constexpr int REC = CT::RS * 2, SB0 = cell_uses_h_prev(CELL) ? 0 : 1, NSB = CELL == CELL_SLSTM ? 2 : CELL == CELL_ELMAN ? 0 : 1;
     static constexpr int CR = BT * UB * REC, CS = NSB * BT * 4 * UB, CD = BT * 2 * UB;
     static constexpr int GR = (CR + 63) / 64, GS = (CS + 63) / 64, GD = (CD + 63) / 64, NLJ = (GR + GS + GD + NLD - 1) / NLD;
-    static constexpr int SLOT = NLD * NLJ * 1024, RD = 49152 / SLOT < 3 ? 3 : 49152 / SLOT > 6 ? 6 : 49152 / SLOT;
+    static constexpr int SLOT = (GR + GS + GD) * 1024, KB = burst_steps(SLOT, 112 * 1024), RD = 2 * KB;   // steps per burst, slots
     static constexpr int GO = CELL == CELL_GRU ? G + 1 : G, COUT = BT * GO * 2 * UB, NSJ = (COUT + NST * 64 - 1) / (NST * 64);
     static constexpr int DG_BYTES = BT * HPB, IMG_BYTES = CELL == CELL_GRU ? BT * U * 2 : 0;
     static constexpr int IMG_OFF = NDG * DG_BYTES, RING_OFF = (IMG_OFF + NDG * IMG_BYTES + 127) / 128 * 128;
     static constexpr int RED_OFF = RING_OFF + RD * SLOT, SMEM = RED_OFF + (DIRECT ? 0 : NSUB * SEG);
-    static_assert((RD - 1) * NLJ < 63, "the wait counts of the load waves");
 };
 
 // position of (row, unit block ub) in an input row of the ring: the blocks of row r are stored r places on, modulo UB, so that the
@@ -216,29 +225,31 @@ __device__ __forceinline__ void split_bwd_load(const KernelParams& p, const Bloc
             else if (piece < C::GR + C::GS + C::GD) place((piece - C::GR - C::GS) * 64 + lane, BT, 2, 2, 0);
         }
         const size_t c_step = (size_t)B * HD * C::REC, st_step = (size_t)C::S * B * HD * 4, dh_step = (size_t)B * HD * 2;
-        auto fetch = [&](int s, int slot) {   // inputs of the step s places before the last one
-            const int t = p.T - 1 - s;
-            const bool real = t >= 0;         // (beyond the first step: nothing is fetched, but as many operations are counted)
-            const size_t at = real ? t : 0;
-            const rsrc_t rc = make_rsrc((const char*)p.cache + at * c_step);
-            const rsrc_t rst = make_rsrc((const char*)p.states + at * st_step + (size_t)C::SB0 * B * HD * 4);
-            const rsrc_t rdh = make_rsrc((const char*)p.dH + at * dh_step);
+        auto burst = [&](int s0) {   // inputs of the steps s0 .. s0 + KB - 1 (counted from the last one)
+#pragma unroll 1
+            for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
+                const size_t t = p.T - 1 - s;
+                const rsrc_t rc = make_rsrc((const char*)p.cache + t * c_step);
+                const rsrc_t rst = make_rsrc((const char*)p.states + t * st_step + (size_t)C::SB0 * B * HD * 4);
+                const rsrc_t rdh = make_rsrc((const char*)p.dH + t * dh_step);
+                char* to = ring + s % C::RD * C::SLOT;
 #pragma unroll
-            for (int j = 0; j < C::NLJ; ++j) {
-                const int piece = j * C::NLD + wl;
-                load_chunk_to_lds(piece < C::GR ? rc : piece < C::GR + C::GS ? rst : rdh, ring + slot * C::SLOT + j * C::NLD * 1024, voff[j] | (real ? 0u : kDrop));
+                for (int j = 0; j < C::NLJ; ++j) {
+                    const int piece = j * C::NLD + wl;
+                    if (piece < C::GR + C::GS + C::GD) load_chunk_to_lds(piece < C::GR ? rc : piece < C::GR + C::GS ? rst : rdh, to + j * C::NLD * 1024, voff[j]);
+                }
             }
         };
-#pragma unroll
-        for (int s = 0; s < C::RD; ++s) fetch(s, s);
-        wait_vmem<(C::RD - 1) * C::NLJ>();
+        burst(0);
+        wait_vmem<0>();
         wg_barrier();
-        int slot = 0;
+        burst(C::KB);
         for (int s = 0; s < p.T; ++s) {
-            wait_vmem<(C::RD - 2) * C::NLJ>();   // step s + 1 is there
+            // step s + 1 begins a burst: it must be there, and the slots of the burst before are free behind the barrier
+            const bool next = (s + 1) % C::KB == 0;
+            if (next) wait_vmem<0>();
             wg_barrier();
-            fetch(s + C::RD, slot);              // into the slot of step s, which everybody has read
-            slot = slot + 1 == C::RD ? 0 : slot + 1;
+            if (next) burst(s + 1 + C::KB);
             if constexpr (!DIRECT) wg_barrier();
         }
         wait_vmem<0>();
@@ -352,12 +363,13 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
     int iter = 0;
     for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
         const uint32_t n = gid % NH, q = gid / NH, e0 = me * U;
+        const uint32_t pl = fresh_lane(lane), pc = pl & 15, pquad = pl >> 4;
         // ---- R: column c = unit of the output block, contraction over this workgroup's gate gradients k = g * U + u, in registers for all steps
         bf16x16 Rs[SP ? NB : 1][SP ? C::NKS : 1];
         bf16x8 Rd[SP ? 1 : NB][SP ? 1 : C::KTD];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + out_blk[b] * 16 + c) * G * D + e0;
+            const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + out_blk[b] * 16 + pc) * G * D + e0;
             auto quads = [&](uint32_t kk) {   // four elements of R from k = kk on (zeros beyond the last gate)
                 if constexpr (C::K % (SP ? 64 : 32) == 0) {
                     return *(const i32x2*)(rrow + (kk / U) * D + kk % U);
@@ -373,7 +385,7 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
                     i32x4 piece[2];
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const uint32_t kk = (2 * kc + h) * 32 + sparse_k(quad);
+                        const uint32_t kk = (2 * kc + h) * 32 + sparse_k(pquad);
                         piece[h] = sparse_piece(quads(kk), quads(kk + 8));
                     }
                     Rs[b][kc] = sparse_dense(piece[0], piece[1]);
@@ -381,23 +393,30 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
             } else {
 #pragma unroll
                 for (int kt = 0; kt < C::KTD; ++kt) {
-                    const uint32_t kk = kt * 32 + quad * 8;
+                    const uint32_t kk = kt * 32 + pquad * 8;
                     const i32x2 lo = quads(kk), hi = quads(kk + 4);
                     Rd[b][kt] = __builtin_bit_cast(bf16x8, i32x4{lo[0], lo[1], hi[0], hi[1]});
                 }
             }
         }
         // ---- pairs: places, carried gradients, states after the last step
-        bool ok[PT];
-        uint32_t l_rec[PT], l_st[PT], l_dh[PT], l_dg[PT], g_st[PT];
+        uint32_t l_rec[PT], l_st[PT], l_dh[PT], l_dg[PT];
+        // this lane's batch row of tile k, and the place of its value in a plane of states
+        auto batch_row = [&](int k, uint32_t ln) {
+            const uint32_t qd = ln >> 4, rr = (DIRECT ? w * (BT / 4) + k : (pairs ? w : 0) + 8 * k) % (BT / 4);
+            const uint32_t wd = DIRECT || BT == 4 ? rr : BT == 8 ? (rr + (qd >> 1)) & 1 : (rr + qd) & 3;
+            return q * BT + (BT == 16 ? 4 * qd + wd : qd + 4 * wd);
+        };
+        auto state_at = [&](int k, uint32_t ln) {
+            const uint32_t brow = batch_row(k, ln);
+            return ((brow < B ? brow : B - 1) * HD + n * D + e0 + ub[k] * 16 + (ln & 15)) * 4;
+        };
         float ds[PT][S], sc[PT][S], sp[PT][S], kf[PT][PG::NK], dh_ext[PT], dbacc[PT][G];
         const size_t st_step = (size_t)S * B * HD * 4;
         const uint32_t st_state = B * HD * 4;
 #pragma unroll
         for (int k = 0; k < PT; ++k) {
-            const uint32_t brow = q * BT + row[k];
-            ok[k] = pairs && brow < B;
-            g_st[k] = ((ok[k] ? brow : B - 1) * HD + n * D + e0 + ub[k] * 16 + c) * 4;
+            const uint32_t g_st = state_at(k, pl);
             const uint32_t rb = row[k] * UB + ring_block<UB>(ub[k], row[k]);
             l_rec[k] = (rb * 16 + c) * C::REC;
             l_st[k] = C::GR * 1024 + (rb * 16 + c) * 4;
@@ -406,11 +425,11 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 float v[1] = {0.0f};
-                if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3)) load_io_r<false, 1>(make_rsrc(p.dlast), g_st[k], s * st_state, v);
+                if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3)) load_io_r<false, 1>(make_rsrc(p.dlast), g_st, s * st_state, v);
                 ds[k][s] = v[0];
                 sp[k][s] = 1.0f;
                 float x[1] = {1.0f};
-                if (!cell_uses_h_prev(CELL) && s >= C::SB0 && s < C::SB0 + C::NSB) load_io_r<false, 1>(make_rsrc((const char*)p.states + (size_t)T * st_step), g_st[k], s * st_state, x);
+                if (!cell_uses_h_prev(CELL) && s >= C::SB0 && s < C::SB0 + C::NSB) load_io_r<false, 1>(make_rsrc((const char*)p.states + (size_t)T * st_step), g_st, s * st_state, x);
                 sc[k][s] = x[0];
             }
 #pragma unroll
@@ -507,6 +526,7 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
                         float v[PPV];
 #pragma unroll
                         for (int i = 0; i < PPV; ++i) v[i] = SP ? a[x][(2 * i) & 3] + a[x][(2 * i + 1) & 3] : a[x][i];
+                        asm volatile("" : : "v"(a[x]));   // (4-row tiles: nobody gets the two unused registers of an accumulator before the sums are formed)
                         if (DIRECT && b == 0) {
 #pragma unroll
                             for (int i = 0; i < PPV; ++i) own[i] = v[i];
@@ -576,18 +596,21 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
             }
         }
         // ---- gradients of the initial states, per-row partial sums of db
+        const uint32_t el = fresh_lane(lane);
 #pragma unroll
-        for (int k = 0; k < PT; ++k)
-            if (ok[k]) {
+        for (int k = 0; k < PT; ++k) {
+            const uint32_t brow = batch_row(k, el);
+            if (pairs && brow < B) {
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
                     const float v[1] = {ds[k][s]};
-                    store_io_r<false, 1>(make_rsrc(p.dstates0), g_st[k], s * st_state, v);
+                    store_io_r<false, 1>(make_rsrc(p.dstates0), state_at(k, el), s * st_state, v);
                 }
-                float* db = p.db_part + (((size_t)(q * BT + row[k]) * NH + n) * G) * D + e0 + ub[k] * 16 + c;
+                float* db = p.db_part + (((size_t)brow * NH + n) * G) * D + e0 + ub[k] * 16 + (el & 15);
 #pragma unroll
                 for (int g = 0; g < G; ++g) db[(size_t)g * D] = dbacc[k][g] + (p.db_accumulate ? db[(size_t)g * D] : 0.0f);
             }
+        }
     }
     FRNN_TRACE_END(p);
 }
@@ -602,6 +625,444 @@ __global__ __launch_bounds__((SplitBwd<CELL, UB, NB, BT, DIRECT>::NW * 64)) void
     if (w < C::NCW) split_bwd_compute<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w);
     else if (w < C::NCW + C::NLD) split_bwd_load<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW);
     else split_bwd_store<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW - C::NLD);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Forward
+// ---------------------------------------------------------------------------------------------
+// UB blocks of 16 units per workgroup.  NCW compute waves share the contraction: wave w takes the k-steps w * KTW .. of h_{t-1} for ALL
+// outputs of the workgroup, so it polls its own slice of the exchanged rows straight into the operand registers of its matrix instructions (no LDS
+// rows, no barrier between the poll and the product, each word polled once per workgroup); the slices' sums meet in LDS, where the point-wise
+// function takes them up.  h is exchanged as in fwd_kernel: rows of bf16 words, four buffers, taken back one round later.
+// p.R is the packed forward copy of R: Rt[n][g][e][k], k < D.
+template <int CELL, int UB, int KTW, int NCW, int BT> struct SplitFwd {
+    using CT = CellTraits<CELL>;
+    static constexpr int G = CT::G, S = CT::S, NC = CT::NC;
+    static constexpr bool SP = BT < 16;
+    static constexpr int U = 16 * UB, NLD = 1, NST = NCW == 4 ? 3 : 1, NW = NCW + NLD + NST;
+    static constexpr int DK = NCW * KTW * 32, XROW = DK * 2;
+    static constexpr int NKF = KTW / 2, HALF = KTW & 1;                // sparse steps of 64, of 32
+    static constexpr int NPT = UB * BT / 4, PW = NPT <= NCW ? NPT : NPT / 2, PT = NPT / PW;   // tiles of 16 units x 4 rows, the waves that take them, tiles each
+    static constexpr int GP = G == 3 ? 4 : G;                           // floats per pair of the slices' sums
+    // inputs of a step: rows (gate, row) in the ring; outputs: state rows, records
+    static constexpr int CW = G * BT * 2 * UB, NLJ = (CW + 64 * NLD - 1) / (64 * NLD), SLOT = NLD * NLJ * 1024;
+    static constexpr int REC = CT::RS * 2, CST = S * BT * 4 * UB, CRC = BT * REC * UB;
+    static constexpr int GST = (CST + 63) / 64, GRC = (CRC + 63) / 64, NSJ = (GST + GRC + NST - 1) / NST;
+    // (row pitches of the output image: the four rows that one instruction writes -- consecutive ones, or with 16 rows every fourth -- lie 64 bytes
+    // apart modulo the banks)
+    static constexpr int PST = U * 4 + (BT == 16 ? 16 : UB == 1 ? 0 : 64), PRC = U * REC + (BT == 16 ? 16 : UB == 1 ? 0 : 64);
+    static constexpr int OUT = S * BT * PST + BT * PRC, RED = NCW * NPT * 64 * GP * 4;
+    // (two buffers of the slices' sums where they fit; with one a second barrier per step)
+    static constexpr int ROOM = 160 * 1024 - U * GP * 4 - 2 * OUT - 16, NRED = 2 * RED + 8 * SLOT <= ROOM ? 2 : 1;
+    static constexpr int KB = burst_steps(SLOT, ROOM - NRED * RED < 64 * 1024 ? ROOM - NRED * RED : 64 * 1024), RD = 2 * KB;   // steps per burst, slots
+    static constexpr int BIAS_OFF = RD * SLOT, OUT_OFF = BIAS_OFF + U * GP * 4, RED_OFF = (OUT_OFF + 2 * OUT + 15) / 16 * 16, SMEM = RED_OFF + NRED * RED;
+    // unit blocks of a ring row are rotated by the number of the row among those that one instruction reads
+    static __host__ __device__ constexpr uint32_t rot(uint32_t row) { return BT == 16 ? row / 4 : row; }
+};
+
+template <int CELL, int UB, int KTW, int NCW, int BT>
+__device__ __forceinline__ void split_fwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane) {
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    const size_t wx_step = (size_t)B * C::G * HD * 2;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
+        uint32_t voff[C::NLJ];
+#pragma unroll
+        for (int j = 0; j < C::NLJ; ++j) {
+            const uint32_t idx = j * 64 + lane, cpr = 2 * UB, r = idx / cpr, pos = idx % cpr, g = r / BT, row = r % BT, brow = q * BT + row;
+            const uint32_t blk = (pos / 2 + UB * BT - C::rot(row)) % UB;
+            voff[j] = g < (uint32_t)C::G && brow < B ? ((brow * C::G + g) * HD + n * D + e0 + blk * 16) * 2 + (pos & 1) * 16 : kDrop;
+        }
+        auto burst = [&](int s0) {   // inputs of the steps s0 .. s0 + KB - 1
+#pragma unroll 1
+            for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
+                const rsrc_t rs = make_rsrc((const char*)p.Wx + s * wx_step);
+#pragma unroll
+                for (int j = 0; j < C::NLJ; ++j) load_chunk_to_lds(rs, smem + s % C::RD * C::SLOT + j * 1024, voff[j]);
+            }
+        };
+        burst(0);
+        wg_barrier();
+        wg_barrier();
+        for (int s = 0; s < p.T; ++s) {
+            const bool next = s % C::KB == 0;    // step s begins a burst: it must be there, and the slots of the burst before are free behind the barrier
+            if (next) wait_vmem<0>();
+            wg_barrier();
+            if (next) burst(s + C::KB);
+            if constexpr (C::NRED == 1) wg_barrier();
+        }
+        wait_vmem<0>();
+        wg_barrier();
+    }
+}
+
+template <int CELL, int UB, int KTW, int NCW, int BT>
+__device__ __forceinline__ void split_fwd_store(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int ws) {
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    const size_t st_step = (size_t)C::S * B * HD * 4, c_step = (size_t)B * HD * C::REC;
+    const bool saves = p.cache != nullptr;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
+        uint32_t voff[C::NSJ], loff[C::NSJ];
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) {
+            const int piece = j * C::NST + ws;
+            voff[j] = kDrop;
+            loff[j] = C::OUT_OFF;
+            auto place = [&](uint32_t idx, uint32_t rows, uint32_t esz, uint32_t plane, uint32_t base, uint32_t pitch) {   // rows of U elements of esz bytes
+                const uint32_t cpr = UB * esz, r = idx / cpr, ch = idx % cpr, brow = q * BT + r % BT;
+                if (r < rows) {
+                    loff[j] = C::OUT_OFF + base + r * pitch + ch * 16;
+                    if (brow < B) voff[j] = (r / BT) * plane + (brow * HD + n * D + e0) * esz + ch * 16;
+                }
+            };
+            if (piece < C::GST) place(piece * 64 + lane, C::S * BT, 4, B * HD * 4, 0, C::PST);
+            else if (saves && piece < C::GST + C::GRC) place((piece - C::GST) * 64 + lane, BT, C::REC, 0, C::S * BT * C::PST, C::PRC);
+        }
+        char* st = (char*)p.states + st_step;
+        char* ca = (char*)p.cache;
+        wg_barrier();
+        wg_barrier();
+        for (int s = 0; s <= p.T; ++s) {
+            wg_barrier();
+            if (s > 0) {   // the outputs of step s - 1
+                i32x4 v[C::NSJ];
+#pragma unroll
+                for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + ((s - 1) & 1) * C::OUT);
+#pragma unroll
+                for (int j = 0; j < C::NSJ; ++j) {
+                    const bool state = j * C::NST + ws < C::GST;
+                    if (state || saves) __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(state ? st : ca), voff[j], 0, 0);
+                }
+                st += st_step;
+                ca += saves ? c_step : 0;
+            }
+            if constexpr (C::NRED == 1) if (s < p.T) wg_barrier();
+        }
+    }
+}
+
+template <int CELL, int UB, int KTW, int NCW, int BT>
+__device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int w) {
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+    constexpr int G = C::G, S = C::S, NC = C::NC, PT = C::PT, U = C::U, NKF = C::NKF, HALF = C::HALF, GP = C::GP;
+    constexpr bool SP = C::SP;
+    constexpr uint32_t kDrop = 0x80000000u;
+    typedef __attribute__((__vector_size__(GP * sizeof(float)))) float sums_t;
+    const int T = p.T, me = bm.member;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    const SparseLane<BT == 8 ? 8 : 4> sl(lane);
+    const uint32_t c = sl.c, quad = sl.quad, k0 = w * KTW * 32;
+    const rsrc_t xr = make_rsrc(p.exch);
+    const uint32_t xbuf = (uint32_t)p.GPAR * BT * C::XROW, xgroup = (uint32_t)bm.gpar * BT * C::XROW;
+    bool failed = false;
+    FRNN_TRACE_BEGIN();
+
+    // ---- this lane's (unit, row) pairs: the same row and unit in PT blocks of units UBK apart
+    constexpr uint32_t UBK = UB / PT;
+    static_assert(C::PW <= NCW && C::PW % (BT / 4) == 0, "one or two tiles per wave, the second UBK blocks further on");
+    const bool pairs = w < C::PW;
+    const uint32_t tile = pairs ? w : 0, ub = tile / (BT / 4);
+    struct Places { uint32_t xlane, wx, bias, st, rec; };
+    auto places_of = [&](uint32_t ln) {
+        const uint32_t cc = ln & 15, qd = ln >> 4, row = BT == 16 ? 4 * qd + tile % (BT / 4) : qd + 4 * (tile % (BT / 4));
+        Places pl;
+        pl.xlane = (cc & 3) == 0 ? row * C::XROW + (me * U + ub * 16 + cc) * 2 : kDrop;   // (the lanes of every fourth unit publish it and the three behind it)
+        pl.wx = ((row * UB + (ub + C::rot(row)) % UB) * 16 + cc) * 2;
+        pl.bias = C::BIAS_OFF + (ub * 16 + cc) * (GP * 4);
+        pl.st = C::OUT_OFF + row * C::PST + (ub * 16 + cc) * 4;
+        pl.rec = C::OUT_OFF + S * BT * C::PST + row * C::PRC + (ub * 16 + cc) * C::REC;
+        return pl;
+    };
+    // (kernels whose R leaves few registers form them anew every step)
+    constexpr bool kTight = G * UB * KTW >= 44;
+    const Places at_once = places_of(lane);
+    // ---- this lane's operand pieces inside the exchanged rows.  Out of range read as zeros: beyond the head's units; with 4 rows the operand rows
+    // that repeat others (they only reach result registers that nobody uses).
+    constexpr int NPC = SP ? NKF + HALF : KTW;
+    const uint32_t xrow = (SP ? sl.rslot : c) * C::XROW + k0 * 2 + (SP ? sl.rbyte : quad * 16);
+    const bool reads = !(BT == 4 && (c & 2));
+    // (the offset of piece j is formed anew where it is used: kept from step to step they would take a register each)
+    uint32_t k_lane = k0 + (SP ? sl.rbyte / 2 : quad * 8);   // first contraction element of the lane's piece 0
+    if (!reads) k_lane = D;
+    auto piece_voff = [&](int j) {
+        asm volatile("" : "+v"(k_lane));
+        return k_lane + j * (SP ? 64 : 32) < D ? xrow + j * (SP ? 128 : 64) : kDrop;
+    };
+    uint32_t half_off = kDrop;   // (the last half step, of 32 elements)
+    if (SP && HALF && reads && k0 + NKF * 64 + sl.rbyte32 / 2 < D) half_off = sl.rslot * C::XROW + (k0 + NKF * 64) * 2 + sl.rbyte32;
+
+    int iter = 0;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
+        const uint32_t n = gid % NH, q = gid / NH, e0 = me * U;
+        // ---- bias into LDS, initial states
+        wg_barrier();   // (the group before is done with its bias)
+        const uint32_t pl = fresh_lane(lane), pc = pl & 15, pquad = pl >> 4;
+        for (uint32_t j = w * 64 + pl; j < (uint32_t)U * G; j += NCW * 64) {
+            float v[1];
+            load_io<true, 1>(p.bias, ((size_t)n * G + j / U) * D + e0 + j % U, v);
+            *(float*)(smem + C::BIAS_OFF + (j % U) * (GP * 4) + (j / U) * 4) = v[0];
+        }
+        float st[PT][S];
+        {
+            const uint32_t brow = q * BT + (BT == 16 ? 4 * pquad + tile % (BT / 4) : pquad + 4 * (tile % (BT / 4)));
+            const uint32_t g_st = ((brow < B ? brow : B - 1) * HD + n * D + e0 + ub * 16 + pc) * 4;
+#pragma unroll
+            for (int k = 0; k < PT; ++k)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    float v[1] = {0.0f};
+                    if (p.states0 != nullptr) load_io_r<false, 1>(make_rsrc(p.states0), g_st + k * UBK * 64, s * (B * HD * 4), v);
+                    st[k][s] = v[0];
+                    store_io_r<false, 1>(make_rsrc(p.states), pairs && brow < B ? g_st + k * UBK * 64 : kDrop, s * (B * HD * 4), v);
+                }
+        }
+        auto publish = [&](const Places& pl, int k, uint32_t off, bool real) {
+            const float h[1] = {st[k][0]};
+            float v4[4];
+            expand_tile<4, 1, true>(h, v4);
+            store_words(xr, pl.xlane | (real ? 0u : kDrop), off + k * UBK * 32, i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, false);
+        };
+        if (pairs && T > 0) {
+#pragma unroll
+            for (int k = 0; k < PT; ++k) publish(kTight ? places_of(pl) : at_once, k, ((uint32_t)iter * (uint32_t)T & 3u) * xbuf + xgroup, true);
+        }
+        pin(st);
+        // ---- R in registers for all steps (last here: everything above needs registers too): column c = unit of a block, this wave's slice of the contraction
+        bf16x16 Rs[SP && NKF ? G * UB : 1][SP && NKF ? NKF : 1];
+        i32x4 Rh[SP && HALF ? G * UB : 1];
+        bf16x8 Rd[SP ? 1 : G * UB][SP ? 1 : KTW];
+        const rsrc_t r_head = make_rsrc((const uint16_t*)p.R + (size_t)n * G * D * D);
+#pragma unroll
+        for (int x = 0; x < G * UB; ++x) {
+            const uint32_t rrow = (((x / UB) * D + e0 + (x % UB) * 16 + pc) * D + k0) * 2;
+            auto four = [&](uint32_t k) {   // four elements from k on of this wave's slice (beyond the head's units out of range: zeros)
+                return __builtin_amdgcn_raw_buffer_load_b64(r_head, k0 + k < D ? rrow + k * 2 : kDrop, 0, 0);
+            };
+            if constexpr (SP) {
+#pragma unroll
+                for (int kc = 0; kc < NKF; ++kc) {
+                    i32x4 piece[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t k = (2 * kc + h) * 32 + sparse_k(pquad);
+                        piece[h] = sparse_piece(four(k), four(k + 8));
+                    }
+                    Rs[x][kc] = sparse_dense(piece[0], piece[1]);
+                }
+                if constexpr (HALF) Rh[x] = sparse_piece(four(NKF * 64 + 8 * pquad), four(NKF * 64 + 8 * pquad + 4));
+            } else {
+#pragma unroll
+                for (int kt = 0; kt < KTW; ++kt) {
+                    const i32x2 lo = four(kt * 32 + pquad * 8), hi = four(kt * 32 + pquad * 8 + 4);
+                    Rd[x][kt] = __builtin_bit_cast(bf16x8, i32x4{lo[0], lo[1], hi[0], hi[1]});
+                }
+            }
+        }
+        wg_barrier();
+
+        FRNN_TRACE_RESET();
+        uint32_t slot = 0;
+        for (int s = 0; s < T; ++s) {
+            const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)s;
+            FRNN_TRACE_MARK(0);
+            // (the matrix instructions add to their result registers in place: cleared here, while the words travel, where there are registers for it)
+            constexpr bool kEarly = NPC <= 4 && G * UB * (KTW + 4) <= 96;
+            f32x4 acc[kEarly ? UB : 1][G];
+            if constexpr (kEarly) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        acc[u][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        asm volatile("" : "+v"(acc[u][g]));
+                    }
+            }
+            // ---- this wave's slice of h_{t-1}
+            const uint32_t xin = (cnt & 3u) * xbuf + xgroup;
+            i32x4 raw[NPC];
+            if (p.spin_limit < 0 && !failed) {   // host-forced failure (tests of the error path): give up without looking
+                __hip_atomic_store(p.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                failed = true;
+            }
+            auto look = [&](int j) {
+                if (SP && HALF && j == NKF) {
+                    const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(xr, half_off, xin, kAuxPoll);
+                    raw[j] = i32x4{v[0], v[1], 0, 0};
+                } else {
+                    raw[j] = __builtin_amdgcn_raw_buffer_load_b128(xr, piece_voff(j), xin, kAuxPoll);
+                }
+            };
+            // piece `from` (and with `all` the ones behind it too) is there; until then it and the ones behind it are looked at again
+            auto wait_for = [&](auto from_c, bool all) {
+                constexpr int from = decltype(from_c)::value;
+                for (int spins = 0;; ++spins) {
+                    if (from == 0 || spins > 0) {
+#pragma unroll
+                        for (int j = from; j < NPC; ++j) look(j);
+                    }
+                    uint32_t top = 0u;   // (a word out of range reads as zero)
+#pragma unroll
+                    for (int j = from; j < NPC; ++j)
+                        if (all || j == from) top = max(top, max(max((uint32_t)raw[j][0], (uint32_t)raw[j][1]), max((uint32_t)raw[j][2], (uint32_t)raw[j][3])));
+                    if (__all((int)(top != kNoWord)) || failed) break;
+                    if (poll_gives_up(spins, p.spin_limit, p.err)) { failed = true; break; }
+                }
+            };
+            auto product = [&](int j, int u, f32x4 (&a)[G], f32x4& ah) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    if constexpr (!SP) a[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw[j]), Rd[g * UB + u][j], a[g], 0, 0, 0);
+                    else if (HALF && G == 1 && j == NKF) ah = smfmac32(i32x2{raw[j][0], raw[j][1]}, Rh[u], ah, sl.idx);
+                    else if (HALF && j == NKF) a[g] = smfmac32(i32x2{raw[j][0], raw[j][1]}, Rh[HALF ? g * UB + u : 0], a[g], sl.idx);
+                    else a[g] = smfmac(__builtin_bit_cast(bf16x8, raw[j]), Rs[NKF ? g * UB + u : 0][NKF ? j : 0], a[g], sl.idx);
+                }
+            };
+            const uint32_t rl = kTight ? fresh_lane(lane) : lane;
+            char* red = smem + C::RED_OFF + (C::NRED == 2 ? (s & 1) * C::RED : 0);
+            auto leave = [&](int u, f32x4 (&a)[G], f32x4& ah) {   // this wave's sums of unit block u
+#pragma unroll
+                for (int r = 0; r < BT / 4; ++r) {
+                    if constexpr (SP && HALF && G == 1) {
+                        a[0][(2 * r) & 3] += ah[(2 * r) & 3];
+                        a[0][(2 * r + 1) & 3] += ah[(2 * r + 1) & 3];
+                    }
+                    sums_t v;
+#pragma unroll
+                    for (int g = 0; g < GP; ++g) v[g] = g >= G ? 0.0f : SP ? a[g < G ? g : 0][(2 * r) & 3] + a[g < G ? g : 0][(2 * r + 1) & 3] : a[g < G ? g : 0][r];
+                    *(sums_t*)(red + ((w * C::NPT + u * (BT / 4) + r) * 64 + rl) * (GP * 4)) = v;
+                }
+                // (4-row tiles use two of an accumulator's registers: nobody else gets the other two before the sums are formed)
+#pragma unroll
+                for (int g = 0; g < G; ++g) asm volatile("" : : "v"(a[g]));
+                if constexpr (SP && HALF && G == 1) asm volatile("" : : "v"(ah));
+            };
+            // (The half step adds to its accumulator two and more other matrix instructions behind the step of 64 before it.  Elman has one gate and
+            // an accumulator of its own for it: a half step right behind a step of 64 on the same registers gave wrong sums.)
+            f32x4 ah[UB];
+#pragma unroll
+            for (int u = 0; u < UB; ++u) ah[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (kEarly) {
+                // each piece is multiplied as soon as it is there
+                auto piece = [&](auto j_c) {
+                    constexpr int j = decltype(j_c)::value;
+                    if constexpr (j < NPC) {
+                        wait_for(j_c, false);
+                        if constexpr (j == NPC - 1) wait_vmem<0>();   // (also what this wave has taken back, if it had nothing to poll)
+                        if constexpr (j == 0) FRNN_TRACE_MARK(2);
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) product(j, u, acc[u], ah[u]);
+                    }
+                };
+                piece(std::integral_constant<int, 0>{});
+                piece(std::integral_constant<int, 1>{});
+                piece(std::integral_constant<int, 2>{});
+                piece(std::integral_constant<int, 3>{});
+                static_assert(NPC <= 4);
+#pragma unroll
+                for (int u = 0; u < UB; ++u) leave(u, acc[u], ah[u]);
+            } else {
+                wait_for(std::integral_constant<int, 0>{}, true);
+                wait_vmem<0>();   // (also what this wave has taken back, if it had nothing to poll)
+                FRNN_TRACE_MARK(2);
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    f32x4 a[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) a[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < NPC; ++j) product(j, u, a, ah[u]);
+                    leave(u, a, ah[u]);
+                    if constexpr (G * UB * KTW >= 44) __builtin_amdgcn_sched_barrier(0);   // (one block's accumulators at a time where R leaves no more registers)
+                }
+            }
+            FRNN_TRACE_MARK(4);
+            wg_barrier();
+            FRNN_TRACE_MARK(1);
+            if (pairs) {
+                const Places here = kTight ? places_of(fresh_lane(lane)) : at_once;
+                // (every member has this round, so every member is done with the one before: its words are taken back)
+#pragma unroll
+                for (int k = 0; k < PT; ++k) clear_tile<true>(xr, here.xlane, ((cnt + 3u) & 3u) * xbuf + xgroup + k * UBK * 32, false);
+                float yb[PT][G], wx[PT][G], cv[PT][NC];
+                auto sums = [&](int k) {
+                    sums_t v[4];
+                    auto slices = [&](int x0) {
+#pragma unroll
+                        for (int x = 0; x < 4; ++x)
+                            if (x0 + x < NCW) v[x] = *(const sums_t*)(red + (((x0 + x) * C::NPT + w + C::PW * k) * 64 + rl) * (GP * 4));
+                    };
+                    slices(0);
+                    const sums_t b = *(const sums_t*)(smem + here.bias + k * UBK * (16 * GP * 4));
+#pragma unroll
+                    for (int g = 0; g < G; ++g) wx[k][g] = bf16_bits_to_f32(*(const uint16_t*)(smem + slot * C::SLOT + g * (BT * U * 2) + (here.wx ^ (k * UBK * 32))));
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        yb[k][g] = b[g];
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) yb[k][g] += v[x][g];
+                    }
+                    if constexpr (NCW > 4) {
+                        slices(4);
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+#pragma unroll
+                            for (int x = 0; x < NCW - 4; ++x) yb[k][g] += v[x][g];
+                    }
+                };
+                if constexpr (C::NRED == 1) {
+#pragma unroll
+                    for (int k = 0; k < PT; ++k) sums(k);
+                    wg_barrier();
+                }
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+                    if constexpr (C::NRED == 2) sums(k);
+                    Cell<CELL, true>::fwd(wx[k], yb[k], st[k], cv[k]);
+                    publish(here, k, ((cnt + 1u) & 3u) * xbuf + xgroup, s + 1 < T);
+                    if constexpr (kTight && PT > 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                FRNN_TRACE_MARK(5);
+                // ---- states and saved values into the output image: the store waves move them behind the next barrier
+                char* out = smem + (s & 1) * C::OUT;
+#pragma unroll
+                for (int k = 0; k < PT; ++k) {
+#pragma unroll
+                    for (int x = 0; x < S; ++x) *(float*)(out + here.st + k * UBK * 64 + x * (BT * C::PST)) = st[k][x];
+                    if (p.cache != nullptr) {
+                        constexpr int NWD = (C::CT::RS + 1) / 2;
+                        uint32_t wd[NWD];
+                        pack_record<true, C::CT::RS, NC>(cv[k], wd);
+                        if constexpr (C::CT::RS == 1) *(uint16_t*)(out + here.rec + k * UBK * 16 * C::REC) = (uint16_t)(wd[0] & 0xFFFFu);
+                        else if constexpr (NWD == 2) *(i32x2*)(out + here.rec + k * UBK * 16 * C::REC) = i32x2{(int)wd[0], (int)wd[1]};
+                        else *(i32x4*)(out + here.rec + k * UBK * 16 * C::REC) = i32x4{(int)wd[0], (int)wd[1], (int)wd[2], (int)wd[3]};
+                    }
+                }
+            } else if constexpr (C::NRED == 1) {
+                wg_barrier();
+            }
+            slot = slot + 1 == (uint32_t)C::RD ? 0 : slot + 1;
+            FRNN_TRACE_MARK(6);
+        }
+        wg_barrier();   // the last outputs are in their image
+    }
+    FRNN_TRACE_END(p);
+}
+
+template <int CELL, int UB, int KTW, int NCW, int BT>
+__global__ __launch_bounds__((SplitFwd<CELL, UB, KTW, NCW, BT>::NW * 64)) void split_fwd_kernel(const KernelParams p) {
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+    extern __shared__ __align__(16) char smem[];
+    const BlockMap bm(p, true);
+    if (!bm.active) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w < NCW) split_fwd_compute<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane, w);
+    else if (w < NCW + C::NLD) split_fwd_load<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane);
+    else split_fwd_store<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane, w - NCW - C::NLD);
 }
 
 }  // namespace flashrnn

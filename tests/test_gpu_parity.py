@@ -280,6 +280,18 @@ def test_backward_of_split_heads_exchanges_partial_sums(cell, NH, D, bt, B, T):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,bt,B,T,split", [
+    (1, 256, 4, 5, 75, 16), (8, 256, 4, 32, 37, 4), (1, 512, 8, 7, 41, 32), (1, 736, 16, 17, 34, 23), (1, 1024, 4, 3, 35, 32), (2, 384, 16, 30, 50, 24),
+])
+def test_split_heads_over_many_steps(cell, NH, D, bt, B, T, split):
+    """Sequences longer than the rings of inputs in LDS (the slots are used again), few and many members per group, contraction slices that the head
+    does not fill, half steps."""
+    w = Workload(f"ring_{cell}_D{D}", cell, T, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + T)
+    _check(w, {"FLASHRNN_BT": str(bt)}, with_dlast=True)
+    assert api.flashrnn_plan_kernel(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16))[2] == split
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
     """The staged kernels look two steps ahead: the shortest sequences take every clamped branch of that."""
