@@ -112,24 +112,36 @@ bool kernel_spills(const void* fn) {
 void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab, int cus, Plan* pl) {
     const int units16 = d->D / 16, cap = cus / kXcds, force_ub = env_int("FLASHRNN_NWU", 0), force_gpar = env_int("FLASHRNN_GPAR", 0);
     auto in_flight = [&](int P) {
-        int gpar = kXcds * (cap / P);
+        int gpar = pl->spread ? cus / P : kXcds * (cap / P);
         if (gpar > pl->NG) gpar = pl->NG;
         return force_gpar > 0 && force_gpar < gpar ? force_gpar : gpar;
     };
     const int rounds = (pl->NG + pl->GPAR - 1) / pl->GPAR;
+    const int mesh = env_int("FLASHRNN_MESH", 0);   // (test hook: 1 prefers the kernels with two hand-overs)
+    // Backward: where the members' words fit the lanes of the waves that wait for them, that kernel; then one hand-over of partial sums from
+    // everybody to everybody; then (more than 768 units, where R leaves that kernel no registers) two hand-overs over a mesh: us per step of LSTM 1 x 1024
+    // with 16 / 64 / 128 rows 1.69 / 2.07 / 4.10, and 2.61 / 4.81 / 10.4 with exchanged gate gradients; 1 x 768 1.58 / 2.00 / 3.49 and 1.56 / 1.84 / 3.17
+    // in one hand-over.
+    auto kind_rank = [&](const KernelEntry& e) { return e.direct == 1 ? 2 : e.direct == 2 ? (mesh == 1 ? 3 : 0) : 1; };
     const KernelEntry* best = nullptr;
     for (int i = 0; i < tab.count; ++i) {
         const KernelEntry& e = tab.entries[i];
-        if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && e.ub != force_ub)) continue;
+        if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && !pl->spread && e.ub != force_ub)) continue;
         const int P = units16 / e.ub;
-        if (P > cap || (bwd ? (e.direct ? P != e.nb : units16 > 8 * e.nb) : e.KT * e.KS * 32 < d->D) || e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
-        if (!bwd && env_int("FLASHRNN_NCW", 0) && e.KS != env_int("FLASHRNN_NCW", 0)) continue;
+        if (e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
+        if (bwd && e.direct == 2) {
+            // (a mesh of 8 / ub subgroups; spread over the chip each XCD is one of its eight)
+            if (units16 % 8 || num_gates(d->cell) * d->D * e.ub / 8 > e.KT * e.KS * 32 || (e.ub == 1) != (pl->spread != 0)) continue;
+            if (!pl->spread && (d->D > 1024 || P > cap)) continue;
+        } else if (pl->spread || P > cap || (bwd ? (e.direct ? P != e.nb : units16 > 8 * e.nb) : e.KT * e.KS * 32 < d->D)) {
+            continue;
+        }
         if ((pl->NG + in_flight(P) - 1) / in_flight(P) > rounds) continue;
-        if (!best) { best = &e; continue; }
         // backward the wave-direct kernels first, then the most units per workgroup, then the smallest kernel that holds the head; forward
         // the fewest units per workgroup (a step's matrix product and point-wise function shrink with them: sLSTM 3 x 256, 16 rows, 1024 steps 900 / 785 /
         // 733 us with 64 / 32 / 16), then the least padding
-        const bool better = bwd ? (e.direct != best->direct ? e.direct > best->direct : e.ub != best->ub ? e.ub > best->ub : e.nb < best->nb)
+        const int rank = kind_rank(e), brank = best ? kind_rank(*best) : 0;
+        const bool better = !best ? true : bwd ? (rank != brank ? rank > brank : e.ub != best->ub ? e.ub > best->ub : e.direct == 2 ? e.KT < best->KT : e.nb < best->nb)
                                 : (e.ub != best->ub ? e.ub < best->ub : e.KT * e.KS != best->KT * best->KS ? e.KT * e.KS < best->KT * best->KS : e.KS < best->KS);
         if (better) best = &e;
     }
@@ -138,12 +150,14 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
     pl->NWU = best->ub;
     pl->P = units16 / best->ub;
     pl->GPAR = in_flight(pl->P);
-    pl->grid = (pl->GPAR + kXcds - 1) / kXcds * pl->P * kXcds;
+    pl->grid = (pl->spread ? pl->GPAR : (pl->GPAR + kXcds - 1) / kXcds * kXcds) * pl->P;
     pl->block = 64 * best->maxw;
     pl->DK = d->D;   // (the packed copy of R has no padding)
     pl->smem = best->smem;
     // backward a partial sum of every unit from every member, forward the rows of h
-    pl->exch_bytes = (size_t)best->nbuf * (bwd ? (size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash : (size_t)pl->GPAR * best->BT * best->KT * best->KS * 32 * 2);
+    const size_t xrow = (size_t)best->KT * best->KS * 64;   // bytes of an exchanged row
+    if (best->direct == 2) pl->exch_bytes = (size_t)best->nbuf * pl->GPAR * (8 / best->ub) * (best->BT * xrow + (size_t)pl->P * best->ub * best->BT * 64);
+    else pl->exch_bytes = (size_t)best->nbuf * (bwd ? (size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash : (size_t)pl->GPAR * best->BT * xrow);
 }
 
 // Launch plan.  One workgroup per group whenever the head's R fits one CU's registers with 16 units
@@ -415,6 +429,7 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             pl.spread = 1;
         }
     }
+    if (pl.spread && bwd && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
     if (!pl.e) return FLASHRNN_ERR_UNSUPPORTED;
     pl.rpack_bytes = pl.e->ub && bwd ? 0 : (bwd ? (size_t)d->NH * d->D * pl.DK : (size_t)d->NH * G * d->D * pl.DK) * io_size(d->io_dtype);
     *out = pl;

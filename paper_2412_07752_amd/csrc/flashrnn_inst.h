@@ -54,6 +54,10 @@ namespace flashrnn {
 #define FRNN_SB(UB, NB, BT, DIRECT) \
     {FRNN_CELL, FRNN_BF16, 1, 0, 1, BT, 1, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NW, 1, 0, 0, \
      (const void*)&split_bwd_kernel<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>, UB, NB, DIRECT, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::NBUF, SplitBwd<FRNN_CELL, UB, NB, BT, (DIRECT != 0)>::SMEM},
+// ... backward in two hand-overs, KTW k-steps for each of eight compute waves
+#define FRNN_SM(UB, KTW, BT) \
+    {FRNN_CELL, FRNN_BF16, 1, KTW, 8, BT, 1, MeshBwd<FRNN_CELL, UB, KTW, BT>::NW, 1, 0, 0, \
+     (const void*)&mesh_bwd_kernel<FRNN_CELL, UB, KTW, BT>, UB, 0, 2, 4, MeshBwd<FRNN_CELL, UB, KTW, BT>::SMEM},
 // ... and forward: KTW k-steps for each of NCW compute waves
 #define FRNN_SF(UB, KTW, NCW, BT) \
     {FRNN_CELL, FRNN_BF16, 0, KTW, NCW, BT, 1, SplitFwd<FRNN_CELL, UB, KTW, NCW, BT>::NW, 1, 0, 0, \
@@ -90,6 +94,8 @@ static const KernelEntry kEntries[] = {
     FRNN_SF(2, 6, 6, 8) FRNN_SF(2, 6, 6, 4)
     FRNN_SF(4, 2, 4, 8) FRNN_SF(4, 3, 4, 8) FRNN_SF(4, 2, 4, 4) FRNN_SF(4, 3, 4, 4)
 #undef FRNN_SPLIT_SHAPES
+    FRNN_SM(2, 4, 16) FRNN_SM(2, 4, 8) FRNN_SM(2, 4, 4)
+    FRNN_SM(1, 3, 8) FRNN_SM(1, 4, 8) FRNN_SM(1, 3, 4) FRNN_SM(1, 4, 4)
     // heads of 1040 .. 2688 units: contraction lengths 1280, 1536, 2048, 2560, 2688.  Forward with all 16 rows of a
     // batch tile where the registers allow, backward (whose point-wise phase holds more values per row) with 8 or 4;
     // the planner takes the largest tile whose kernel neither spills nor overflows the LDS.
@@ -119,6 +125,7 @@ inline KernelTable make_table() {
 #undef FRNN_FL
 #undef FRNN_SB
 #undef FRNN_SF
+#undef FRNN_SM
 #undef FRNN_BL
 #undef FRNN_FT
 #undef FRNN_BTL

@@ -118,14 +118,14 @@ template <> struct PointGrad<CELL_ELMAN> {
 };
 
 // partial sums of one [16 units] x [BT rows] block: BT / 4 floats per lane (lane (c, quad): unit c; rows quad (+ 4), with 16 rows 4 quad ..)
-template <int PP> __device__ __forceinline__ void store_part(rsrc_t rs, uint32_t voff, uint32_t soff, const float (&v)[PP]) {
+template <int PP, int AUX = 0> __device__ __forceinline__ void store_part(rsrc_t rs, uint32_t voff, uint32_t soff, const float (&v)[PP]) {
     int x[PP];
 #pragma unroll
     for (int i = 0; i < PP; ++i) x[i] = exch_word(__builtin_bit_cast(uint32_t, v[i]));
     // (16 bytes: no scalar offset, see store_io_r)
-    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{x[0], x[1], x[2], x[3]}, rs, voff + soff, 0, 0);
-    else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{x[0], x[1]}, rs, voff, soff, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(x[0], rs, voff, soff, 0);
+    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{x[0], x[1], x[2], x[3]}, rs, voff + soff, 0, AUX);
+    else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{x[0], x[1]}, rs, voff, soff, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b32(x[0], rs, voff, soff, AUX);
 }
 template <int PP> __device__ __forceinline__ void clear_part(rsrc_t rs, uint32_t voff, uint32_t soff) {
     constexpr int none = (int)kNoWord;
@@ -195,26 +195,24 @@ template <int CELL, int UB, int NB, int BT, bool DIRECT> struct SplitBwd {
     static constexpr int DG_BYTES = BT * HPB, IMG_BYTES = CELL == CELL_GRU ? BT * U * 2 : 0;
     static constexpr int IMG_OFF = NDG * DG_BYTES, RING_OFF = (IMG_OFF + NDG * IMG_BYTES + 127) / 128 * 128;
     static constexpr int RED_OFF = RING_OFF + RD * SLOT, SMEM = RED_OFF + (DIRECT ? 0 : NSUB * SEG);
+    static constexpr int kCell = CELL, kUB = UB, kBT = BT, kBarriers = DIRECT ? 1 : 2;   // barriers per step
+    static __device__ __forceinline__ uint32_t unit0(const KernelParams&, uint32_t member) { return member * U; }   // first unit of a member
 };
 
 // position of (row, unit block ub) in an input row of the ring: the blocks of row r are stored r places on, modulo UB, so that the
 // rows that one instruction reads lie in different banks
 template <int UB> __device__ __forceinline__ uint32_t ring_block(uint32_t ub, uint32_t row) { return (ub + row) % UB; }
 
-template <int CELL, int UB, int NB, int BT, bool DIRECT>
-__device__ __forceinline__ void split_bwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int wl) {
-    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
-    constexpr uint32_t kDrop = 0x80000000u;
-    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
-    char* ring = smem + C::RING_OFF + wl * 1024;
-    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
-        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
-        // piece j of this wave: which stream, and this lane's chunk of it
-        uint32_t voff[C::NLJ];
+// The inputs of a group's steps, by C::NLD waves (wl = 0 ..): piece by piece of 64 chunks of 16 bytes into the ring.
+template <class C> struct BwdLoader {
+    uint32_t voff[C::NLJ];   // this lane's chunk of piece j of the wave
+    __device__ __forceinline__ BwdLoader(const KernelParams& p, uint32_t n, uint32_t q, uint32_t e0, int lane, int wl) {
+        constexpr int UB = C::kUB, BT = C::kBT;
+        const uint32_t B = p.B, D = p.D, HD = p.NH * D;
 #pragma unroll
         for (int j = 0; j < C::NLJ; ++j) {
             const int piece = j * C::NLD + wl;
-            voff[j] = kDrop;
+            voff[j] = 0x80000000u;
             auto place = [&](uint32_t idx, uint32_t rows, uint32_t cpb, uint32_t esz, uint32_t plane) {   // rows of UB blocks of cpb chunks
                 const uint32_t cpr = UB * cpb, r = idx / cpr, pos = idx % cpr, row = r % BT;
                 const uint32_t blk = (pos / cpb + UB * BT - row) % UB, brow = q * BT + row;
@@ -224,47 +222,33 @@ __device__ __forceinline__ void split_bwd_load(const KernelParams& p, const Bloc
             else if (piece < C::GR + C::GS) place((piece - C::GR) * 64 + lane, C::NSB * BT, 4, 4, B * HD * 4);
             else if (piece < C::GR + C::GS + C::GD) place((piece - C::GR - C::GS) * 64 + lane, BT, 2, 2, 0);
         }
-        const size_t c_step = (size_t)B * HD * C::REC, st_step = (size_t)C::S * B * HD * 4, dh_step = (size_t)B * HD * 2;
-        auto burst = [&](int s0) {   // inputs of the steps s0 .. s0 + KB - 1 (counted from the last one)
-#pragma unroll 1
-            for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
-                const size_t t = p.T - 1 - s;
-                const rsrc_t rc = make_rsrc((const char*)p.cache + t * c_step);
-                const rsrc_t rst = make_rsrc((const char*)p.states + t * st_step + (size_t)C::SB0 * B * HD * 4);
-                const rsrc_t rdh = make_rsrc((const char*)p.dH + t * dh_step);
-                char* to = ring + s % C::RD * C::SLOT;
-#pragma unroll
-                for (int j = 0; j < C::NLJ; ++j) {
-                    const int piece = j * C::NLD + wl;
-                    if (piece < C::GR + C::GS + C::GD) load_chunk_to_lds(piece < C::GR ? rc : piece < C::GR + C::GS ? rst : rdh, to + j * C::NLD * 1024, voff[j]);
-                }
-            }
-        };
-        burst(0);
-        wait_vmem<0>();
-        wg_barrier();
-        burst(C::KB);
-        for (int s = 0; s < p.T; ++s) {
-            // step s + 1 begins a burst: it must be there, and the slots of the burst before are free behind the barrier
-            const bool next = (s + 1) % C::KB == 0;
-            if (next) wait_vmem<0>();
-            wg_barrier();
-            if (next) burst(s + 1 + C::KB);
-            if constexpr (!DIRECT) wg_barrier();
-        }
-        wait_vmem<0>();
     }
-}
-
-template <int CELL, int UB, int NB, int BT, bool DIRECT>
-__device__ __forceinline__ void split_bwd_store(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int ws) {
-    using C = SplitBwd<CELL, UB, NB, BT, DIRECT>;
-    constexpr uint32_t kDrop = 0x80000000u;
-    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
-    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
-        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
-        uint32_t voff[C::NSJ], vofn[C::NSJ], loff[C::NSJ];
-        bool img[C::NSJ];
+    // inputs of the steps s0 .. s0 + KB - 1 (counted from the last one)
+    __device__ __forceinline__ void burst(const KernelParams& p, char* smem, int wl, int s0) const {
+        const size_t units = (size_t)p.B * p.NH * p.D;
+#pragma unroll 1
+        for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
+            const size_t t = p.T - 1 - s;
+            const rsrc_t rc = make_rsrc((const char*)p.cache + t * (units * C::REC));
+            const rsrc_t rst = make_rsrc((const char*)p.states + (t * C::S + C::SB0) * (units * 4));
+            const rsrc_t rdh = make_rsrc((const char*)p.dH + t * (units * 2));
+            char* to = smem + C::RING_OFF + s % C::RD * C::SLOT + wl * 1024;
+#pragma unroll
+            for (int j = 0; j < C::NLJ; ++j) {
+                const int piece = j * C::NLD + wl;
+                if (piece < C::GR + C::GS + C::GD) load_chunk_to_lds(piece < C::GR ? rc : piece < C::GR + C::GS ? rst : rdh, to + j * C::NLD * 1024, voff[j]);
+            }
+        }
+    }
+};
+// The outputs of a step, by C::NST waves (ws = 0 ..), from the rows of gate gradients in LDS.
+template <class C> struct BwdStorer {
+    uint32_t voff[C::NSJ], vofn[C::NSJ], loff[C::NSJ];
+    bool img[C::NSJ];
+    __device__ __forceinline__ BwdStorer(const KernelParams& p, uint32_t n, uint32_t q, uint32_t e0, int lane, int ws) {
+        constexpr int CELL = C::kCell, UB = C::kUB, BT = C::kBT;
+        constexpr uint32_t kDrop = 0x80000000u;
+        const uint32_t B = p.B, D = p.D, HD = p.NH * D;
 #pragma unroll
         for (int j = 0; j < C::NSJ; ++j) {
             const uint32_t idx = (j * C::NST + ws) * 64 + lane, cpr = 2 * UB, r = idx / cpr, ch = idx % cpr, g = r % C::GO, row = r / C::GO, brow = q * BT + row;
@@ -276,24 +260,51 @@ __device__ __forceinline__ void split_bwd_store(const KernelParams& p, const Blo
             img[j] = CELL == CELL_GRU && g == 2;
             loff[j] = row >= BT ? 0u : img[j] ? C::IMG_OFF + row * C::U * 2 + ch * 16 : row * C::HPB + (g == (uint32_t)C::G ? 2u : g) * C::U * 2 + ch * 16;
         }
-        const size_t wx_step = (size_t)B * C::G * HD * 2, dh_step = (size_t)B * HD * 2;
-        char* dwx = (char*)p.dWx + (size_t)(p.T > 0 ? p.T - 1 : 0) * wx_step;
-        char* dgn = (char*)p.dgn + (size_t)(p.T > 0 ? p.T - 1 : 0) * dh_step;
+    }
+    // step s (counted from the last one), from operand buffer buf
+    __device__ __forceinline__ void store(const KernelParams& p, const char* smem, int s, uint32_t buf) const {
+        const size_t units = (size_t)p.B * p.NH * p.D, t = p.T - 1 - s;
+        const rsrc_t dwx = make_rsrc((char*)p.dWx + t * (units * (C::G * 2)));
+        i32x4 v[C::NSJ];
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + buf * (C::kCell == CELL_GRU && img[j] ? C::IMG_BYTES : C::DG_BYTES));
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) {
+            __builtin_amdgcn_raw_buffer_store_b128(v[j], dwx, voff[j], 0, 0);
+            if constexpr (C::kCell == CELL_GRU) __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc((char*)p.dgn + t * (units * 2)), vofn[j], 0, 0);
+        }
+    }
+};
+
+template <class C>
+__device__ __forceinline__ void split_bwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int wl) {
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const BwdLoader<C> in(p, gid % p.NH, gid / p.NH, C::unit0(p, bm.member), lane, wl);
+        in.burst(p, smem, wl, 0);
+        wait_vmem<0>();
+        wg_barrier();
+        in.burst(p, smem, wl, C::KB);
+        for (int s = 0; s < p.T; ++s) {
+            // step s + 1 begins a burst: it must be there, and the slots of the burst before are free behind the barrier
+            const bool next = (s + 1) % C::KB == 0;
+            if (next) wait_vmem<0>();
+            wg_barrier();
+            if (next) in.burst(p, smem, wl, s + 1 + C::KB);
+            if constexpr (C::kBarriers == 2) wg_barrier();
+        }
+        wait_vmem<0>();
+    }
+}
+
+template <class C>
+__device__ __forceinline__ void split_bwd_store(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int ws) {
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const BwdStorer<C> out(p, gid % p.NH, gid / p.NH, C::unit0(p, bm.member), lane, ws);
         wg_barrier();
         for (int s = 0; s < p.T; ++s) {
             wg_barrier();
-            const uint32_t buf = C::NDG == 2 ? (uint32_t)(s & 1) : 0u;
-            i32x4 v[C::NSJ];
-#pragma unroll
-            for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + buf * (CELL == CELL_GRU && img[j] ? C::IMG_BYTES : C::DG_BYTES));
-#pragma unroll
-            for (int j = 0; j < C::NSJ; ++j) {
-                __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(dwx), voff[j], 0, 0);
-                if constexpr (CELL == CELL_GRU) __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(dgn), vofn[j], 0, 0);
-            }
-            dwx -= wx_step;
-            dgn -= dh_step;
-            if constexpr (!DIRECT) wg_barrier();
+            out.store(p, smem, s, C::NDG == 2 ? (uint32_t)(s & 1) : 0u);
+            if constexpr (C::kBarriers == 2) wg_barrier();
         }
     }
 }
@@ -623,8 +634,341 @@ __global__ __launch_bounds__((SplitBwd<CELL, UB, NB, BT, DIRECT>::NW * 64)) void
     if (!bm.active) return;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w < C::NCW) split_bwd_compute<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w);
-    else if (w < C::NCW + C::NLD) split_bwd_load<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW);
-    else split_bwd_store<CELL, UB, NB, BT, DIRECT>(p, bm, smem, lane, w - C::NCW - C::NLD);
+    else if (w < C::NCW + C::NLD) split_bwd_load<C>(p, bm, smem, lane, w - C::NCW);
+    else split_bwd_store<C>(p, bm, smem, lane, w - C::NCW - C::NLD);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Backward in two hand-overs: many members
+// ---------------------------------------------------------------------------------------------
+// With P members each partial sum of every unit has to reach its owner from all of them: 4 D bytes per row out of and into every CU, most of a
+// step's time with 16 rows or hundreds of CUs.  Here the members form a mesh of PB = 8 / UB subgroups (s = member % PB) of PA = P / PB members
+// (a = member / PB).  A subgroup's members gather each other's gate gradients (bf16 rows of G * U * PA elements) and each forms the partial sums of eight of the
+// D / 16 output blocks, those owned by the members with its own a in all subgroups: PB segments of UB blocks, added up by their owners.
+// A head spread over the chip has one subgroup per XCD (UB = 1): gate gradients stay inside an XCD's L2, only partial sums of eight blocks
+// per member cross the XCDs.
+// NCW = 8 compute waves share the subgroup's contraction like those of split_fwd_kernel (wave w polls its KTW k-steps straight into operand registers);
+// their sums meet in LDS, where wave w takes up block w.  Kernels that hold 128 registers of R per lane have no waves beside them (OWN_IO): the four
+// waves without point-wise work, at least, move inputs and outputs.
+// (LSTM 1 x 2048, 16 rows, per step 7.68 -> 2.70 us against the exchange of gate gradients through memory, 1 x 1024 with 16 / 64 / 128 rows 2.61 / 4.81 / 10.4
+// -> 1.69 / 2.07 / 4.10.  Bound by the two hand-overs: 22 % and 39 % of a step of 1 x 2048, matrix product and the waves' sums a quarter.)
+template <int CELL, int UB, int KTW, int BT> struct MeshBwd {
+    static constexpr bool OWN_IO = KTW >= 4;
+    using CT = CellTraits<CELL>;
+    static constexpr int G = CT::G, S = CT::S, NC = CT::NC;
+    static constexpr bool SP = BT < 16;
+    static constexpr int U = 16 * UB, GU = G * U, PB = 8 / UB, NBUF = 4;
+    static constexpr int NCW = 8, NLD = OWN_IO ? 4 : 2, NST = NLD, NW = OWN_IO ? NCW : NCW + NLD + NST, OB = 8;
+    static constexpr int DK = NCW * KTW * 32, XROW = DK * 2;           // exchanged rows of gate gradients
+    static constexpr int NKF = KTW / 2, HALF = KTW & 1;
+    static constexpr int PPV = BT / 4, SEG = UB * BT * 64;             // floats per lane of a block; bytes one member sends another
+    static constexpr int NPT = UB * BT / 4;                            // tiles of 16 units x 4 rows, one per wave
+    static_assert(NPT <= NCW);
+    static constexpr int REC = CT::RS * 2, SB0 = cell_uses_h_prev(CELL) ? 0 : 1, NSB = CELL == CELL_SLSTM ? 2 : CELL == CELL_ELMAN ? 0 : 1;
+    static constexpr int CR = BT * UB * REC, CS = NSB * BT * 4 * UB, CD = BT * 2 * UB;
+    static constexpr int GR = (CR + 63) / 64, GS = (CS + 63) / 64, GD = (CD + 63) / 64, NLJ = (GR + GS + GD + NLD - 1) / NLD;
+    static constexpr int SLOT = (GR + GS + GD) * 1024;
+    static constexpr int GO = CELL == CELL_GRU ? G + 1 : G, COUT = BT * GO * 2 * UB, NSJ = (COUT + NST * 64 - 1) / (NST * 64);
+    static constexpr int NDG = 2, HPB = (GU + 16) * 2, DG_BYTES = BT * HPB, IMG_BYTES = CELL == CELL_GRU ? BT * U * 2 : 0;   // dWx on its way out
+    static constexpr int IMG_OFF = NDG * DG_BYTES, RING_OFF = (IMG_OFF + NDG * IMG_BYTES + 127) / 128 * 128;
+    static constexpr int RED = NCW * OB * 64 * PPV * 4;                // the waves' sums; two buffers, or one and a second barrier per step
+    static constexpr int ROOM = 160 * 1024 - RING_OFF, NRED = 2 * RED + 8 * SLOT <= ROOM ? 2 : 1, kBarriers = NRED == 2 ? 1 : 2;
+    static constexpr int KB = burst_steps(SLOT, ROOM - NRED * RED < 96 * 1024 ? ROOM - NRED * RED : 96 * 1024), RD = 2 * KB;
+    static constexpr int RED_OFF = RING_OFF + RD * SLOT, SMEM = RED_OFF + NRED * RED;
+    static constexpr int kCell = CELL, kUB = UB, kBT = BT;
+    // the units of a subgroup are consecutive
+    static __device__ __forceinline__ uint32_t unit0(const KernelParams& p, uint32_t member) { return ((member % PB) * (p.P / PB) + member / PB) * U; }
+    static constexpr size_t exch_bytes(int groups, int P) { return (size_t)NBUF * groups * ((size_t)PB * BT * XROW + (size_t)P * PB * SEG); }
+};
+
+template <int CELL, int UB, int KTW, int BT>
+__device__ __forceinline__ void mesh_bwd_compute(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int w) {
+    using C = MeshBwd<CELL, UB, KTW, BT>;
+    using PG = PointGrad<CELL>;
+    constexpr int G = C::G, S = C::S, NC = C::NC, PPV = C::PPV, U = C::U, GU = C::GU, PB = C::PB, NKF = C::NKF, HALF = C::HALF;
+    constexpr bool SP = C::SP;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const int T = p.T;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D, PA = p.P / PB, a_me = bm.member / PB, s_me = bm.member % PB, e0 = C::unit0(p, bm.member);
+    const uint32_t K2 = GU * PA, k0 = w * KTW * 32;
+    const SparseLane<BT == 8 ? 8 : 4> sl(lane);
+    const rsrc_t xr = make_rsrc(p.exch);
+    // exchange buffers: [round & 3] of the subgroups' rows of gate gradients, then [round & 3] of the segments [receiver][sending subgroup]
+    const uint32_t xbuf1 = (uint32_t)p.GPAR * PB * BT * C::XROW, xgroup1 = ((uint32_t)bm.gpar * PB + s_me) * BT * C::XROW;
+    const uint32_t xbuf2 = (uint32_t)p.GPAR * p.P * PB * C::SEG, xgroup2 = C::NBUF * xbuf1 + (uint32_t)bm.gpar * p.P * PB * C::SEG;
+    char* ring = smem + C::RING_OFF;
+    bool failed = false;
+    FRNN_TRACE_BEGIN();
+
+    // ---- this lane's (unit, row) pair, if the wave has a tile
+    const bool pairs = w < C::NPT;
+    const uint32_t ub = pairs ? w / (BT / 4) : 0, rr = pairs ? w % (BT / 4) : 0;
+    auto row_of = [&](uint32_t ln) { return BT == 16 ? 4 * (ln >> 4) + rr : (ln >> 4) + 4 * rr; };
+    const uint32_t row = row_of(lane), c = lane & 15;
+    const uint32_t x1lane = (c & 3) == 0 ? row * C::XROW + (a_me * GU + ub * 16 + c) * 2 : kDrop;   // (the lanes of every fourth unit publish it and the three behind it)
+    const uint32_t rb = row * UB + ring_block<UB>(ub, row);
+    const uint32_t l_rec = (rb * 16 + c) * C::REC, l_st = C::GR * 1024 + (rb * 16 + c) * 4, l_dh = (C::GR + C::GS) * 1024 + (rb * 16 + c) * 2;
+    const uint32_t l_dg = row * C::HPB + (ub * 16 + c) * 2;
+    // ---- this lane's operand pieces of the subgroup's rows (as in split_fwd_kernel)
+    constexpr int NPC = SP ? NKF + HALF : KTW;
+    const uint32_t xrow = (SP ? sl.rslot : c) * C::XROW + k0 * 2 + (SP ? sl.rbyte : sl.quad * 16);
+    const bool reads = !(BT == 4 && (c & 2));
+    uint32_t k_lane = reads ? k0 + (SP ? sl.rbyte / 2 : sl.quad * 8) : K2;
+    auto piece_voff = [&](int j) {
+        asm volatile("" : "+v"(k_lane));
+        return k_lane + j * (SP ? 64 : 32) < K2 ? xrow + j * (SP ? 128 : 64) : kDrop;
+    };
+    uint32_t half_off = kDrop;
+    if (SP && HALF && reads && k0 + NKF * 64 + sl.rbyte32 / 2 < K2) half_off = sl.rslot * C::XROW + (k0 + NKF * 64) * 2 + sl.rbyte32;
+    // ---- block w goes to the member with this a in subgroup w / UB; the words of this wave's tile come from all subgroups
+    const uint32_t x2out = xgroup2 + ((a_me * PB + w / UB) * PB + s_me) * C::SEG + (w % UB) * (64 * BT);
+    const uint32_t x2in = xgroup2 + (uint32_t)bm.member * PB * C::SEG + ub * (64 * BT) + rr * 4;
+
+    int iter = 0;
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
+        const uint32_t n = gid % NH, q = gid / NH;
+        const uint32_t pl = fresh_lane(lane), pc = pl & 15, pquad = pl >> 4;
+        const size_t st_step = (size_t)S * B * HD * 4;
+        const uint32_t st_state = B * HD * 4;
+        auto state_at = [&](uint32_t ln) {
+            const uint32_t brow = q * BT + row_of(ln);
+            return ((brow < B ? brow : B - 1) * HD + n * D + e0 + ub * 16 + (ln & 15)) * 4;
+        };
+        float ds[S], sc[S], sp[S], kf[PG::NK], dh_ext = 0.0f, dbacc[G];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            float v[1] = {0.0f}, x[1] = {1.0f};
+            if (p.dlast != nullptr && !(CELL == CELL_SLSTM && s == 3)) load_io_r<false, 1>(make_rsrc(p.dlast), state_at(pl), s * st_state, v);
+            if (!cell_uses_h_prev(CELL) && s >= C::SB0 && s < C::SB0 + C::NSB) load_io_r<false, 1>(make_rsrc((const char*)p.states + (size_t)T * st_step), state_at(pl), s * st_state, x);
+            ds[s] = v[0];
+            sc[s] = x[0];
+            sp[s] = 1.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < PG::NK; ++k) kf[k] = 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) dbacc[g] = 0.0f;
+        pin(ds);
+        pin(sc);
+        // ---- R: eight output blocks (block b: member a_me of subgroup b / UB), this wave's slice of the subgroup's contraction
+        bf16x16 Rs[SP && NKF ? 8 : 1][SP && NKF ? NKF : 1];
+        i32x4 Rh[SP && HALF ? 8 : 1];
+        bf16x8 Rd[SP ? 1 : 8][SP ? 1 : KTW];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint32_t d = ((b / UB) * PA + a_me) * U + (b % UB) * 16 + pc;
+            const rsrc_t r_row = make_rsrc((const uint16_t*)p.R + (size_t)n * D * G * D);
+            auto four = [&](uint32_t k) {   // four elements of column d from k on of this wave's slice (beyond the subgroup's gate gradients out of range: zeros)
+                const uint32_t kk = k0 + k, am = kk / GU, rem = kk % GU;
+                return __builtin_amdgcn_raw_buffer_load_b64(r_row, kk < K2 ? (d * (G * D) + (rem / U) * D + (s_me * PA + am) * U + rem % U) * 2 : kDrop, 0, 0);
+            };
+            if constexpr (SP) {
+#pragma unroll
+                for (int kc = 0; kc < NKF; ++kc) {
+                    i32x4 piece[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t k = (2 * kc + h) * 32 + sparse_k(pquad);
+                        piece[h] = sparse_piece(four(k), four(k + 8));
+                    }
+                    Rs[b][kc] = sparse_dense(piece[0], piece[1]);
+                }
+                if constexpr (HALF) Rh[b] = sparse_piece(four(NKF * 64 + 8 * pquad), four(NKF * 64 + 8 * pquad + 4));
+            } else {
+#pragma unroll
+                for (int kt = 0; kt < KTW; ++kt) {
+                    const i32x2 lo = four(kt * 32 + pquad * 8), hi = four(kt * 32 + pquad * 8 + 4);
+                    Rd[b][kt] = __builtin_bit_cast(bf16x8, i32x4{lo[0], lo[1], hi[0], hi[1]});
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        auto take = [&](uint32_t slot) {   // this lane's inputs of a step, and what follows from them alone
+            const char* in = ring + slot * C::SLOT;
+            float cv[NC];
+            take_record_lds<C::CT::RS, NC>(in + l_rec, cv);
+#pragma unroll
+            for (int s = C::SB0; s < C::SB0 + C::NSB; ++s) sp[s] = *(const float*)(in + l_st + (s - C::SB0) * BT * U * 4);
+            dh_ext = bf16_bits_to_f32(*(const uint16_t*)(in + l_dh));
+            PG::factors(cv, sc, sp, kf);
+            if constexpr (!cell_uses_h_prev(CELL)) {
+#pragma unroll
+                for (int s = C::SB0; s < C::SB0 + C::NSB; ++s) sc[s] = sp[s];
+            }
+            pin(kf);
+        };
+        const int wio = w - 4;   // (OWN_IO) this wave among those that move inputs and outputs
+        const BwdLoader<C> in(p, n, q, e0, fresh_lane(lane), wio < 0 ? 0 : wio);
+        const BwdStorer<C> out_waves(p, n, q, e0, fresh_lane(lane), wio < 0 ? 0 : wio);
+        if constexpr (C::OWN_IO) {
+            if (wio >= 0) in.burst(p, smem, wio, 0);
+            wait_vmem<0>();
+        }
+        wg_barrier();   // the first inputs are there
+        if constexpr (C::OWN_IO) {
+            if (wio >= 0) in.burst(p, smem, wio, C::KB);
+        }
+        if (T > 0 && pairs) take(0);
+
+        FRNN_TRACE_RESET();
+        uint32_t slot = 0;
+        for (int s = 0; s < T; ++s) {
+            const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)s, x1 = (cnt & 3u) * xbuf1 + xgroup1, x2 = (cnt & 3u) * xbuf2;
+            // ---- gate gradients of the step: to the subgroup, and into the image of dWx
+            if (pairs) {
+                float dwx[G], dg[G];
+                ds[0] += dh_ext;
+                PG::apply(kf, ds, dwx, dg);
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float v[1] = {dg[g]};
+                    float v4[4];
+                    expand_tile<4, 1, true>(v, v4);
+                    store_words(xr, x1lane, x1 + g * (U * 2), i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, false);
+                }
+                char* out = smem + (s & 1) * C::DG_BYTES;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    *(uint16_t*)(out + l_dg + g * U * 2) = (uint16_t)f32_to_bf16_bits(dg[g]);
+                    dbacc[g] += dg[g];
+                }
+                if constexpr (CELL == CELL_GRU) *(uint16_t*)(smem + C::IMG_OFF + (s & 1) * C::IMG_BYTES + row * U * 2 + (ub * 16 + c) * 2) = (uint16_t)f32_to_bf16_bits(dwx[2]);
+            }
+            FRNN_TRACE_MARK(0);
+            // ---- this wave's slice of the subgroup's gate gradients
+            i32x4 raw[NPC];
+            if (p.spin_limit < 0 && !failed) {   // host-forced failure (tests of the error path): give up without looking
+                __hip_atomic_store(p.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                failed = true;
+            }
+            for (int spins = 0;; ++spins) {
+#pragma unroll
+                for (int j = 0; j < NPC; ++j) {
+                    if (SP && HALF && j == NKF) {
+                        const i32x2 v = __builtin_amdgcn_raw_buffer_load_b64(xr, half_off, x1, kAuxPoll);
+                        raw[j] = i32x4{v[0], v[1], 0, 0};
+                    } else {
+                        raw[j] = __builtin_amdgcn_raw_buffer_load_b128(xr, piece_voff(j), x1, kAuxPoll);
+                    }
+                }
+                uint32_t top = 0u;   // (a word out of range reads as zero)
+#pragma unroll
+                for (int j = 0; j < NPC; ++j) top = max(top, max(max((uint32_t)raw[j][0], (uint32_t)raw[j][1]), max((uint32_t)raw[j][2], (uint32_t)raw[j][3])));
+                if (__all((int)(top != kNoWord)) || failed) break;
+                if (poll_gives_up(spins, p.spin_limit, p.err)) { failed = true; break; }
+            }
+            wait_vmem<0>();   // (also what this wave has taken back, if it had nothing to poll)
+            FRNN_TRACE_MARK(2);
+            char* red = smem + C::RED_OFF + (C::NRED == 2 ? (s & 1) * C::RED : 0);
+            constexpr int CH = KTW >= 4 ? 2 : 4;   // blocks at a time: R leaves no registers for more accumulators
+#pragma unroll
+            for (int b0 = 0; b0 < 8; b0 += CH) {
+                f32x4 a[CH];
+#pragma unroll
+                for (int x = 0; x < CH; ++x) a[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                // (a half step comes first: behind a step of 64 on the same registers it would need more instructions between)
+                if constexpr (SP && HALF) {
+#pragma unroll
+                    for (int x = 0; x < CH; ++x) a[x] = smfmac32(i32x2{raw[NPC - 1][0], raw[NPC - 1][1]}, Rh[b0 + x], a[x], sl.idx);
+                }
+#pragma unroll
+                for (int j = 0; j < (SP ? NKF : KTW); ++j)
+#pragma unroll
+                    for (int x = 0; x < CH; ++x) {
+                        if constexpr (SP) a[x] = smfmac(__builtin_bit_cast(bf16x8, raw[j]), Rs[b0 + x][j], a[x], sl.idx);
+                        else a[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw[j]), Rd[b0 + x][j], a[x], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int x = 0; x < CH; ++x) {
+                    float* o = (float*)(red + ((w * 8 + b0 + x) * 64 + lane) * (PPV * 4));
+                    typedef __attribute__((__vector_size__(PPV * sizeof(float)))) float part_t;
+                    part_t v;
+#pragma unroll
+                    for (int i = 0; i < PPV; ++i) v[i] = SP ? a[x][(2 * i) & 3] + a[x][(2 * i + 1) & 3] : a[x][i];
+                    *(part_t*)o = v;
+                    asm volatile("" : : "v"(a[x]));   // (4-row tiles: nobody gets the two unused registers of an accumulator before the sums are formed)
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            FRNN_TRACE_MARK(3);
+            wg_barrier();
+            FRNN_TRACE_MARK(1);
+            if (pairs) {   // (every member of the subgroup has this round, so all are done with the one before: its words are taken back)
+#pragma unroll
+                for (int g = 0; g < G; ++g) clear_tile<true>(xr, x1lane, ((cnt + 3u) & 3u) * xbuf1 + xgroup1 + g * (U * 2), false);
+            }
+            // ---- block w of the eight: the waves' sums, to its owner
+            {
+                typedef __attribute__((__vector_size__(PPV * sizeof(float)))) float part_t;
+                part_t v[8];
+#pragma unroll
+                for (int x = 0; x < 8; ++x) v[x] = *(const part_t*)(red + ((x * 8 + w) * 64 + lane) * (PPV * 4));
+                float sum[PPV];
+#pragma unroll
+                for (int i = 0; i < PPV; ++i) sum[i] = ((v[0][i] + v[1][i]) + (v[2][i] + v[3][i])) + ((v[4][i] + v[5][i]) + (v[6][i] + v[7][i]));
+                if (p.spread) store_part<PPV, kAuxAgent>(xr, lane * BT, x2 + x2out, sum);
+                else store_part<PPV>(xr, lane * BT, x2 + x2out, sum);
+            }
+            if constexpr (C::OWN_IO) {   // (the burst before is complete: every wave has waited for all of its own ahead of the barrier)
+                if (wio >= 0) {
+                    out_waves.store(p, smem, s, (uint32_t)(s & 1));
+                    if ((s + 1) % C::KB == 0) in.burst(p, smem, wio, s + 1 + C::KB);
+                }
+            }
+            if constexpr (C::NRED == 1) wg_barrier();
+            FRNN_TRACE_MARK(5);
+            slot = slot + 1 == (uint32_t)C::RD ? 0 : slot + 1;
+            if (pairs) {
+                take(slot);   // the inputs of the next step, while the partial sums travel
+                uint32_t got[PB];
+                for (int spins = 0;; ++spins) {
+#pragma unroll
+                    for (int j = 0; j < PB; ++j) got[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xr, lane * BT, x2 + x2in + j * C::SEG, kAuxPoll);
+                    uint32_t top = 0u;
+#pragma unroll
+                    for (int j = 0; j < PB; ++j) top = max(top, got[j]);
+                    if (__all((int)(top != kNoWord)) || failed) break;
+                    if (poll_gives_up(spins, p.spin_limit, p.err)) { failed = true; break; }
+                }
+                // (taken back for the round after the next three: nobody else looks at these words)
+#pragma unroll
+                for (int j = 0; j < PB; ++j) {
+                    if (p.spread) __builtin_amdgcn_raw_buffer_store_b32((int)kNoWord, xr, lane * BT, x2 + x2in + j * C::SEG, kAuxAgent);
+                    else __builtin_amdgcn_raw_buffer_store_b32((int)kNoWord, xr, lane * BT, x2 + x2in + j * C::SEG, 0);
+                }
+                float rec = __builtin_bit_cast(float, got[0]);
+#pragma unroll
+                for (int j = 1; j < PB; ++j) rec += __builtin_bit_cast(float, got[j]);
+                ds[0] += fminf(fmaxf(rec, -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
+            }
+            FRNN_TRACE_MARK(4);
+        }
+        // ---- gradients of the initial states, per-row partial sums of db
+        const uint32_t el = fresh_lane(lane), brow = q * BT + row_of(el);
+        if (pairs && brow < B) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const float v[1] = {ds[s]};
+                store_io_r<false, 1>(make_rsrc(p.dstates0), state_at(el), s * st_state, v);
+            }
+            float* db = p.db_part + (((size_t)brow * NH + n) * G) * D + e0 + ub * 16 + (el & 15);
+#pragma unroll
+            for (int g = 0; g < G; ++g) db[(size_t)g * D] = dbacc[g] + (p.db_accumulate ? db[(size_t)g * D] : 0.0f);
+        }
+    }
+    FRNN_TRACE_END(p);
+}
+
+template <int CELL, int UB, int KTW, int BT>
+__global__ __launch_bounds__((MeshBwd<CELL, UB, KTW, BT>::NW * 64)) void mesh_bwd_kernel(const KernelParams p) {
+    using C = MeshBwd<CELL, UB, KTW, BT>;
+    extern __shared__ __align__(16) char smem[];
+    const BlockMap bm(p, true);
+    if (!bm.active) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (C::OWN_IO || w < C::NCW) mesh_bwd_compute<CELL, UB, KTW, BT>(p, bm, smem, lane, w);
+    else if (w < C::NCW + C::NLD) split_bwd_load<C>(p, bm, smem, lane, w - C::NCW);
+    else split_bwd_store<C>(p, bm, smem, lane, w - C::NCW - C::NLD);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -14,7 +14,7 @@ from paper_2412_07752_amd.synth import CELL_ELMAN, CELL_GRU, CELL_GRU4, CELL_LST
 pytestmark = pytest.mark.gpu
 CELLS = [CELL_LSTM, CELL_GRU, CELL_SLSTM, CELL_ELMAN, CELL_GRU4]
 PLAN_ENV = ("FLASHRNN_MULTI", "FLASHRNN_BT", "FLASHRNN_NWU", "FLASHRNN_KS", "FLASHRNN_GPAR", "FLASHRNN_SPIN_LIMIT", "FLASHRNN_DEEP_FETCH",
-            "FLASHRNN_KIND", "FLASHRNN_RECOMPUTE_STEPS")
+            "FLASHRNN_KIND", "FLASHRNN_RECOMPUTE_STEPS", "FLASHRNN_MESH")
 
 
 @pytest.fixture(autouse=True)
@@ -277,6 +277,21 @@ def test_backward_of_split_heads_exchanges_partial_sums(cell, NH, D, bt, B, T):
         env["FLASHRNN_GPAR"] = "8"
     _check(w, env, with_dlast=True)
     assert api.flashrnn_plan(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16), True)[2] in ((8, 12) if D in (256, 320, 384) else (12,))
+
+
+@pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,B,T,env", [
+    (2, 256, 9, 19, {"FLASHRNN_MULTI": "1", "FLASHRNN_MESH": "1", "FLASHRNN_BT": "8"}), (1, 384, 5, 3, {"FLASHRNN_MULTI": "1", "FLASHRNN_MESH": "1", "FLASHRNN_BT": "4"}),
+    (1, 768, 20, 5, {"FLASHRNN_MESH": "1", "FLASHRNN_BT": "16"}), (1, 896, 11, 37, {"FLASHRNN_BT": "8"}), (1, 1024, 17, 4, {"FLASHRNN_BT": "16"}),
+    (3, 128, 13, 7, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "8", "FLASHRNN_GPAR": "3"}), (1, 256, 3, 41, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "4"}), (1, 2048, 7, 1, {}),
+])
+def test_backward_of_split_heads_in_two_hand_overs(cell, NH, D, B, T, env):
+    """Subgroups of 1 to 16 members, inside one XCD (two blocks of 16 units per member) and one subgroup per XCD; contractions that do not fill the
+    waves' k-steps, ragged batches, groups in rounds, sequences shorter and longer than the ring of inputs."""
+    w = Workload(f"mesh_{cell}_D{D}", cell, T, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D + B)
+    _check(w, env, with_dlast=True)
+    wgs, _, waves = api.flashrnn_plan(api.make_desc(cell, T, B, NH, D, api.FLASHRNN_BF16), True)
+    assert waves in (8, 12)   # (the kernel that exchanges gate gradients has 4 waves on the spread heads)
 
 
 @pytest.mark.parametrize("cell", CELLS)
