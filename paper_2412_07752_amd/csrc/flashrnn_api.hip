@@ -128,7 +128,7 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
         const KernelEntry& e = tab.entries[i];
         if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && !pl->spread && e.ub != force_ub)) continue;
         const int P = units16 / e.ub;
-        if (e.smem > (int)kLdsBytes || kernel_spills(e.fn)) continue;
+        if (e.smem > (int)kLdsBytes || e.direct == 3 || kernel_spills(e.fn)) continue;
         if (bwd && e.direct == 2) {
             // (a mesh of 8 / ub subgroups; spread over the chip each XCD is one of its eight)
             if (units16 % 8 || num_gates(d->cell) * d->D * e.ub / 8 > e.KT * e.KS * 32 || (e.ub == 1) != (pl->spread != 0)) continue;
@@ -158,6 +158,36 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
     const size_t xrow = (size_t)best->KT * best->KS * 64;   // bytes of an exchanged row
     if (best->direct == 2) pl->exch_bytes = (size_t)best->nbuf * pl->GPAR * (8 / best->ub) * (best->BT * xrow + (size_t)pl->P * best->ub * best->BT * 64);
     else pl->exch_bytes = (size_t)best->nbuf * (bwd ? (size_t)pl->GPAR * pl->P * units16 * best->BT * 64 + kTrash : (size_t)pl->GPAR * best->BT * xrow);
+}
+
+// The forward pass of a head spread over the chip: the kernel whose members fetch h from memory once per XCD, with the smallest batch tile whose groups
+// all run at once.  (Groups in rounds, and 16-row tiles, stay with fwd_kernel: LSTM 1 x 2048, 32 rows 4.66 us per step in 16-row tiles there, 6.5 here.)
+void take_spread_fwd_kernel(const flashrnn_desc_t* d, const KernelTable& tab, int cus, Plan* pl) {
+    const int units16 = d->D / 16, force_bt = env_int("FLASHRNN_BT", 0), force_gpar = env_int("FLASHRNN_GPAR", 0);
+    if (units16 % kXcds) return;
+    const size_t rpack = (size_t)d->NH * num_gates(d->cell) * d->D * 2;
+    for (int BT = 4; BT <= 8; BT *= 2) {
+        const KernelEntry* best = nullptr;
+        for (int i = 0; i < tab.count; ++i) {
+            const KernelEntry& e = tab.entries[i];
+            if (e.ub && !e.bwd && e.direct == 3 && e.BT == BT && e.KT * e.KS * 32 >= d->D && e.smem <= (int)kLdsBytes && !kernel_spills(e.fn) && (!best || e.KT < best->KT)) best = &e;
+        }
+        if (!best || (force_bt && BT != force_bt)) continue;
+        const int NG = d->NH * ((d->B + BT - 1) / BT);
+        int gpar = cus / units16 < NG ? cus / units16 : NG;
+        if (force_gpar > 0 && force_gpar < gpar) gpar = force_gpar;
+        else if (gpar < NG) continue;
+        // (per step with 4 / 8 / 16 rows, here and with every member polling all rows in memory: LSTM 1 x 1152 2.46 / 2.56 / 2.87 us and 3.31 / 3.30 / 3.32, 1 x 2048
+        // 2.68 / 2.95 / 3.38 and 4.72; GRU 1 x 1280 2.40 / 2.51 / 2.93 and 2.85, Elman 2.03 / 2.16 / 2.51 and 2.37: two groups of the smaller cells stay)
+        if (num_gates(d->cell) < 4 && d->D <= 1280 && NG > 1 && !force_gpar) continue;
+        const size_t exch = (size_t)best->nbuf * gpar * BT * best->KT * best->KS * 64 * (1 + kXcds);   // rows of h: common ones, and each XCD's own
+        // (a call that the library's own scratch array can hold stays within it)
+        const size_t scratch = FLASHRNN_STATIC_SCRATCH_BYTES, fixed = rpack * d->D + kAlign;
+        if (fixed + align_up(exch) > scratch && kAlign + align_up(pl->exch_bytes) + rpack * pl->DK <= scratch) continue;
+        pl->e = best; pl->NWU = 1; pl->P = units16; pl->NG = NG; pl->GPAR = gpar; pl->grid = gpar * units16; pl->block = 64 * best->maxw; pl->DK = d->D; pl->smem = best->smem;
+        pl->exch_bytes = exch;
+        return;
+    }
 }
 
 // Launch plan.  One workgroup per group whenever the head's R fits one CU's registers with 16 units
@@ -429,7 +459,10 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             pl.spread = 1;
         }
     }
-    if (pl.spread && bwd && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
+    if (pl.spread && env_int("FLASHRNN_SPLIT", 1) != 0) {
+        if (bwd) take_split_kernel(d, bwd, tab, cus, &pl);
+        else take_spread_fwd_kernel(d, tab, cus, &pl);
+    }
     if (!pl.e) return FLASHRNN_ERR_UNSUPPORTED;
     pl.rpack_bytes = pl.e->ub && bwd ? 0 : (bwd ? (size_t)d->NH * d->D * pl.DK : (size_t)d->NH * G * d->D * pl.DK) * io_size(d->io_dtype);
     *out = pl;

@@ -23,7 +23,7 @@ struct KernelEntry {
     // kernels with wave roles (heads split over the CUs of one XCD, flashrnn_split_kernels.h); ub = 0: none of them
     int ub;      // blocks of 16 units per workgroup
     int nb;      // output blocks per compute wave
-    int direct;  // backward: 0 partial sums of all members through LDS, 1 each compute wave waits for the words of its own lanes (nb workgroups per group), 2 two hand-overs (mesh_bwd_kernel)
+    int direct;  // backward: 0 partial sums of all members through LDS, 1 each compute wave waits for the words of its own lanes (nb workgroups per group), 2 two hand-overs (mesh_bwd_kernel); forward: 3 members on all XCDs
     int nbuf;    // exchange buffers
     int smem;    // bytes of dynamic LDS
 };

@@ -62,6 +62,9 @@ namespace flashrnn {
 #define FRNN_SF(UB, KTW, NCW, BT) \
     {FRNN_CELL, FRNN_BF16, 0, KTW, NCW, BT, 1, SplitFwd<FRNN_CELL, UB, KTW, NCW, BT>::NW, 1, 0, 0, \
      (const void*)&split_fwd_kernel<FRNN_CELL, UB, KTW, NCW, BT>, UB, 0, 0, 4, SplitFwd<FRNN_CELL, UB, KTW, NCW, BT>::SMEM},
+// ... spread over the XCDs
+#define FRNN_SX(KTW, BT) \
+    {FRNN_CELL, FRNN_BF16, 0, KTW, 8, BT, 1, 8, 1, 0, 0, (const void*)&split_fwd_kernel<FRNN_CELL, 1, KTW, 8, BT, true>, 1, 0, 3, 4, SplitFwd<FRNN_CELL, 1, KTW, 8, BT, true>::SMEM},
 
 static const KernelEntry kEntries[] = {
 #if FRNN_BF16
@@ -96,6 +99,7 @@ static const KernelEntry kEntries[] = {
 #undef FRNN_SPLIT_SHAPES
     FRNN_SM(2, 4, 16) FRNN_SM(2, 4, 8) FRNN_SM(2, 4, 4)
     FRNN_SM(1, 3, 8) FRNN_SM(1, 4, 8) FRNN_SM(1, 3, 4) FRNN_SM(1, 4, 4)
+    FRNN_SX(5, 4) FRNN_SX(6, 4) FRNN_SX(8, 4) FRNN_SX(5, 8) FRNN_SX(6, 8) FRNN_SX(8, 8)
     // heads of 1040 .. 2688 units: contraction lengths 1280, 1536, 2048, 2560, 2688.  Forward with all 16 rows of a
     // batch tile where the registers allow, backward (whose point-wise phase holds more values per row) with 8 or 4;
     // the planner takes the largest tile whose kernel neither spills nor overflows the LDS.
@@ -126,6 +130,7 @@ inline KernelTable make_table() {
 #undef FRNN_SB
 #undef FRNN_SF
 #undef FRNN_SM
+#undef FRNN_SX
 #undef FRNN_BL
 #undef FRNN_FT
 #undef FRNN_BTL

@@ -979,11 +979,17 @@ __global__ __launch_bounds__((MeshBwd<CELL, UB, KTW, BT>::NW * 64)) void mesh_bw
 // rows, no barrier between the poll and the product, each word polled once per workgroup); the slices' sums meet in LDS, where the point-wise
 // function takes them up.  h is exchanged as in fwd_kernel: rows of bf16 words, four buffers, taken back one round later.
 // p.R is the packed forward copy of R: Rt[n][g][e][k], k < D.
-template <int CELL, int UB, int KTW, int NCW, int BT> struct SplitFwd {
+// SPREAD: the group's members sit on all XCDs (member % 8 is the XCD).  h goes to memory once; in each XCD every member fetches an equal share of the
+// group's rows from there (16 bytes per row and member and lane: BT / 4 waves of the upper four, "relays") and leaves it in a buffer of the XCD's own, which
+// all members of that XCD poll in their L2.  (LSTM 1 x 2048, 16 rows 4.57 -> 3.2 us per step, 4 rows 2.5; of a step the way through memory takes a third, the
+// XCD's own hand-over a quarter.  An XCD's members own consecutive units: with consecutive units on all XCDs 3.64.)  There are no waves beside the
+// eight compute waves, whose upper four move inputs and outputs too.
+template <int CELL, int UB, int KTW, int NCW, int BT, bool SPREAD = false> struct SplitFwd {
     using CT = CellTraits<CELL>;
     static constexpr int G = CT::G, S = CT::S, NC = CT::NC;
     static constexpr bool SP = BT < 16;
-    static constexpr int U = 16 * UB, NLD = 1, NST = NCW == 4 ? 3 : 1, NW = NCW + NLD + NST;
+    static constexpr int U = 16 * UB, NLD = 1, NST = SPREAD ? 4 : NCW == 4 ? 3 : 1, NW = SPREAD ? NCW : NCW + NLD + NST;
+    static_assert(!SPREAD || (UB == 1 && NCW == 8));
     static constexpr int DK = NCW * KTW * 32, XROW = DK * 2;
     static constexpr int NKF = KTW / 2, HALF = KTW & 1;                // sparse steps of 64, of 32
     static constexpr int NPT = UB * BT / 4, PW = NPT <= NCW ? NPT : NPT / 2, PT = NPT / PW;   // tiles of 16 units x 4 rows, the waves that take them, tiles each
@@ -1002,39 +1008,82 @@ template <int CELL, int UB, int KTW, int NCW, int BT> struct SplitFwd {
     static constexpr int BIAS_OFF = RD * SLOT, OUT_OFF = BIAS_OFF + U * GP * 4, RED_OFF = (OUT_OFF + 2 * OUT + 15) / 16 * 16, SMEM = RED_OFF + NRED * RED;
     // unit blocks of a ring row are rotated by the number of the row among those that one instruction reads
     static __host__ __device__ constexpr uint32_t rot(uint32_t row) { return BT == 16 ? row / 4 : row; }
+    static constexpr int kUB = UB, kBT = BT;
+    // (spread: the units of an XCD's members are consecutive -- a cache line of h is written from one XCD)
+    static __device__ __forceinline__ uint32_t unit0(const KernelParams& p, uint32_t member) { return SPREAD ? ((member % 8) * (p.P / 8) + member / 8) * U : member * U; }
 };
 
-template <int CELL, int UB, int KTW, int NCW, int BT>
-__device__ __forceinline__ void split_fwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane) {
-    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
-    constexpr uint32_t kDrop = 0x80000000u;
-    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
-    const size_t wx_step = (size_t)B * C::G * HD * 2;
-    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
-        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
-        uint32_t voff[C::NLJ];
+// The inputs of a group's steps, by one wave, into the ring.
+template <class C> struct FwdLoader {
+    uint32_t voff[C::NLJ];
+    __device__ __forceinline__ FwdLoader(const KernelParams& p, uint32_t n, uint32_t q, uint32_t e0, int lane) {
+        constexpr int UB = C::kUB, BT = C::kBT;
 #pragma unroll
         for (int j = 0; j < C::NLJ; ++j) {
             const uint32_t idx = j * 64 + lane, cpr = 2 * UB, r = idx / cpr, pos = idx % cpr, g = r / BT, row = r % BT, brow = q * BT + row;
             const uint32_t blk = (pos / 2 + UB * BT - C::rot(row)) % UB;
-            voff[j] = g < (uint32_t)C::G && brow < B ? ((brow * C::G + g) * HD + n * D + e0 + blk * 16) * 2 + (pos & 1) * 16 : kDrop;
+            voff[j] = g < (uint32_t)C::G && brow < (uint32_t)p.B ? ((brow * C::G + g) * (uint32_t)(p.NH * p.D) + n * p.D + e0 + blk * 16) * 2 + (pos & 1) * 16 : 0x80000000u;
         }
-        auto burst = [&](int s0) {   // inputs of the steps s0 .. s0 + KB - 1
+    }
+    __device__ __forceinline__ void burst(const KernelParams& p, char* smem, int s0) const {   // inputs of the steps s0 .. s0 + KB - 1
+        const size_t wx_step = (size_t)p.B * C::G * p.NH * p.D * 2;
 #pragma unroll 1
-            for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
-                const rsrc_t rs = make_rsrc((const char*)p.Wx + s * wx_step);
+        for (int s = s0; s < s0 + C::KB && s < p.T; ++s) {
+            const rsrc_t rs = make_rsrc((const char*)p.Wx + s * wx_step);
 #pragma unroll
-                for (int j = 0; j < C::NLJ; ++j) load_chunk_to_lds(rs, smem + s % C::RD * C::SLOT + j * 1024, voff[j]);
-            }
-        };
-        burst(0);
+            for (int j = 0; j < C::NLJ; ++j) load_chunk_to_lds(rs, smem + s % C::RD * C::SLOT + j * 1024, voff[j]);
+        }
+    }
+};
+// The outputs of a step, by C::NST waves (ws = 0 ..), from their image in LDS.
+template <class C> struct FwdStorer {
+    uint32_t voff[C::NSJ], loff[C::NSJ];
+    __device__ __forceinline__ FwdStorer(const KernelParams& p, uint32_t n, uint32_t q, uint32_t e0, int lane, int ws) {
+        constexpr int UB = C::kUB, BT = C::kBT;
+        const uint32_t B = p.B, HD = p.NH * p.D;
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) {
+            const int piece = j * C::NST + ws;
+            voff[j] = 0x80000000u;
+            loff[j] = C::OUT_OFF;
+            auto place = [&](uint32_t idx, uint32_t rows, uint32_t esz, uint32_t plane, uint32_t base, uint32_t pitch) {   // rows of U elements of esz bytes
+                const uint32_t cpr = UB * esz, r = idx / cpr, ch = idx % cpr, brow = q * BT + r % BT;
+                if (r < rows) {
+                    loff[j] = C::OUT_OFF + base + r * pitch + ch * 16;
+                    if (brow < B) voff[j] = (r / BT) * plane + (brow * HD + n * p.D + e0) * esz + ch * 16;
+                }
+            };
+            if (piece < C::GST) place(piece * 64 + lane, C::S * BT, 4, B * HD * 4, 0, C::PST);
+            else if (p.cache != nullptr && piece < C::GST + C::GRC) place((piece - C::GST) * 64 + lane, BT, C::REC, 0, C::S * BT * C::PST, C::PRC);
+        }
+    }
+    __device__ __forceinline__ void store(const KernelParams& p, const char* smem, int ws, int s) const {   // the outputs of step s
+        const size_t units = (size_t)p.B * p.NH * p.D;
+        const bool saves = p.cache != nullptr;
+        const rsrc_t st = make_rsrc((char*)p.states + (size_t)(s + 1) * C::S * units * 4), ca = make_rsrc((char*)p.cache + (saves ? s : 0) * (units * C::REC));
+        i32x4 v[C::NSJ];
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + (s & 1) * C::OUT);
+#pragma unroll
+        for (int j = 0; j < C::NSJ; ++j) {
+            const bool state = j * C::NST + ws < C::GST;
+            if (state || saves) __builtin_amdgcn_raw_buffer_store_b128(v[j], state ? st : ca, voff[j], 0, 0);
+        }
+    }
+};
+
+template <class C>
+__device__ __forceinline__ void split_fwd_load(const KernelParams& p, const BlockMap& bm, char* smem, int lane) {
+    for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
+        const FwdLoader<C> in(p, gid % p.NH, gid / p.NH, C::unit0(p, bm.member), lane);
+        in.burst(p, smem, 0);
         wg_barrier();
         wg_barrier();
         for (int s = 0; s < p.T; ++s) {
             const bool next = s % C::KB == 0;    // step s begins a burst: it must be there, and the slots of the burst before are free behind the barrier
             if (next) wait_vmem<0>();
             wg_barrier();
-            if (next) burst(s + C::KB);
+            if (next) in.burst(p, smem, s + C::KB);
             if constexpr (C::NRED == 1) wg_barrier();
         }
         wait_vmem<0>();
@@ -1042,67 +1091,34 @@ __device__ __forceinline__ void split_fwd_load(const KernelParams& p, const Bloc
     }
 }
 
-template <int CELL, int UB, int KTW, int NCW, int BT>
+template <class C>
 __device__ __forceinline__ void split_fwd_store(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int ws) {
-    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
-    constexpr uint32_t kDrop = 0x80000000u;
-    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
-    const size_t st_step = (size_t)C::S * B * HD * 4, c_step = (size_t)B * HD * C::REC;
-    const bool saves = p.cache != nullptr;
     for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR) {
-        const uint32_t n = gid % NH, q = gid / NH, e0 = bm.member * C::U;
-        uint32_t voff[C::NSJ], loff[C::NSJ];
-#pragma unroll
-        for (int j = 0; j < C::NSJ; ++j) {
-            const int piece = j * C::NST + ws;
-            voff[j] = kDrop;
-            loff[j] = C::OUT_OFF;
-            auto place = [&](uint32_t idx, uint32_t rows, uint32_t esz, uint32_t plane, uint32_t base, uint32_t pitch) {   // rows of U elements of esz bytes
-                const uint32_t cpr = UB * esz, r = idx / cpr, ch = idx % cpr, brow = q * BT + r % BT;
-                if (r < rows) {
-                    loff[j] = C::OUT_OFF + base + r * pitch + ch * 16;
-                    if (brow < B) voff[j] = (r / BT) * plane + (brow * HD + n * D + e0) * esz + ch * 16;
-                }
-            };
-            if (piece < C::GST) place(piece * 64 + lane, C::S * BT, 4, B * HD * 4, 0, C::PST);
-            else if (saves && piece < C::GST + C::GRC) place((piece - C::GST) * 64 + lane, BT, C::REC, 0, C::S * BT * C::PST, C::PRC);
-        }
-        char* st = (char*)p.states + st_step;
-        char* ca = (char*)p.cache;
+        const FwdStorer<C> out(p, gid % p.NH, gid / p.NH, C::unit0(p, bm.member), lane, ws);
         wg_barrier();
         wg_barrier();
         for (int s = 0; s <= p.T; ++s) {
             wg_barrier();
-            if (s > 0) {   // the outputs of step s - 1
-                i32x4 v[C::NSJ];
-#pragma unroll
-                for (int j = 0; j < C::NSJ; ++j) v[j] = *(const i32x4*)(smem + loff[j] + ((s - 1) & 1) * C::OUT);
-#pragma unroll
-                for (int j = 0; j < C::NSJ; ++j) {
-                    const bool state = j * C::NST + ws < C::GST;
-                    if (state || saves) __builtin_amdgcn_raw_buffer_store_b128(v[j], make_rsrc(state ? st : ca), voff[j], 0, 0);
-                }
-                st += st_step;
-                ca += saves ? c_step : 0;
-            }
+            if (s > 0) out.store(p, smem, ws, s - 1);
             if constexpr (C::NRED == 1) if (s < p.T) wg_barrier();
         }
     }
 }
 
-template <int CELL, int UB, int KTW, int NCW, int BT>
+template <int CELL, int UB, int KTW, int NCW, int BT, bool SPREAD>
 __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const BlockMap& bm, char* smem, int lane, int w) {
-    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT, SPREAD>;
     constexpr int G = C::G, S = C::S, NC = C::NC, PT = C::PT, U = C::U, NKF = C::NKF, HALF = C::HALF, GP = C::GP;
     constexpr bool SP = C::SP;
     constexpr uint32_t kDrop = 0x80000000u;
     typedef __attribute__((__vector_size__(GP * sizeof(float)))) float sums_t;
     const int T = p.T, me = bm.member;
-    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D;
+    const uint32_t B = p.B, NH = p.NH, D = p.D, HD = NH * D, e0 = C::unit0(p, me);
     const SparseLane<BT == 8 ? 8 : 4> sl(lane);
     const uint32_t c = sl.c, quad = sl.quad, k0 = w * KTW * 32;
     const rsrc_t xr = make_rsrc(p.exch);
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * C::XROW, xgroup = (uint32_t)bm.gpar * BT * C::XROW;
+    const uint32_t xnear = SPREAD ? (4u + 4u * (me % 8)) * xbuf : 0u;   // this XCD's own four buffers, behind the common ones
     bool failed = false;
     FRNN_TRACE_BEGIN();
 
@@ -1115,7 +1131,7 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
     auto places_of = [&](uint32_t ln) {
         const uint32_t cc = ln & 15, qd = ln >> 4, row = BT == 16 ? 4 * qd + tile % (BT / 4) : qd + 4 * (tile % (BT / 4));
         Places pl;
-        pl.xlane = (cc & 3) == 0 ? row * C::XROW + (me * U + ub * 16 + cc) * 2 : kDrop;   // (the lanes of every fourth unit publish it and the three behind it)
+        pl.xlane = (cc & 3) == 0 ? row * C::XROW + (e0 + ub * 16 + cc) * 2 : kDrop;   // (the lanes of every fourth unit publish it and the three behind it)
         pl.wx = ((row * UB + (ub + C::rot(row)) % UB) * 16 + cc) * 2;
         pl.bias = C::BIAS_OFF + (ub * 16 + cc) * (GP * 4);
         pl.st = C::OUT_OFF + row * C::PST + (ub * 16 + cc) * 4;
@@ -1142,7 +1158,7 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
 
     int iter = 0;
     for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
-        const uint32_t n = gid % NH, q = gid / NH, e0 = me * U;
+        const uint32_t n = gid % NH, q = gid / NH;
         // ---- bias into LDS, initial states
         wg_barrier();   // (the group before is done with its bias)
         const uint32_t pl = fresh_lane(lane), pc = pl & 15, pquad = pl >> 4;
@@ -1169,7 +1185,7 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
             const float h[1] = {st[k][0]};
             float v4[4];
             expand_tile<4, 1, true>(h, v4);
-            store_words(xr, pl.xlane | (real ? 0u : kDrop), off + k * UBK * 32, i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, false);
+            store_words(xr, pl.xlane | (real ? 0u : kDrop), off + k * UBK * 32, i32x2{exch_word(pack_bf16x2(v4[0], v4[1])), exch_word(pack_bf16x2(v4[2], v4[3]))}, SPREAD);
         };
         if (pairs && T > 0) {
 #pragma unroll
@@ -1207,6 +1223,17 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
                 }
             }
         }
+        // (SPREAD) what the upper four waves do beside their part of the products
+        const int wio = SPREAD ? w - 4 : -1;
+        const FwdLoader<C> in(p, n, q, e0, pl);
+        const FwdStorer<C> out_waves(p, n, q, e0, pl, wio < 0 ? 0 : wio);
+        const bool relay = SPREAD && wio >= 0 && wio < BT / 4;
+        uint32_t relay_off = 0;
+        if constexpr (SPREAD) {
+            const uint32_t id = (me / 8) * (BT * 16) + (wio < 0 ? 0 : wio) * 64 + pl, cpr = D / 8;   // chunk of 16 bytes among the group's BT rows of D / 8
+            relay_off = id / cpr * C::XROW + id % cpr * 16;
+            if (wio == 3) in.burst(p, smem, 0);
+        }
         wg_barrier();
 
         FRNN_TRACE_RESET();
@@ -1227,7 +1254,19 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
                     }
             }
             // ---- this wave's slice of h_{t-1}
-            const uint32_t xin = (cnt & 3u) * xbuf + xgroup;
+            const uint32_t xin = xnear + (cnt & 3u) * xbuf + xgroup;
+            if constexpr (SPREAD) {   // the relays: their share of h_{t-1} from memory into the XCD's buffer
+                if (relay) {
+                    i32x4 v;
+                    for (int spins = 0;; ++spins) {
+                        v = __builtin_amdgcn_raw_buffer_load_b128(xr, relay_off, (cnt & 3u) * xbuf + xgroup, kAuxPoll);
+                        const uint32_t top = max(max((uint32_t)v[0], (uint32_t)v[1]), max((uint32_t)v[2], (uint32_t)v[3]));
+                        if (__all((int)(top != kNoWord)) || failed || p.spin_limit < 0) break;
+                        if (poll_gives_up(spins, p.spin_limit, p.err)) { failed = true; break; }
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(v, xr, relay_off + xin, 0, 0);
+                }
+            }
             i32x4 raw[NPC];
             if (p.spin_limit < 0 && !failed) {   // host-forced failure (tests of the error path): give up without looking
                 __hip_atomic_store(p.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1327,11 +1366,18 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
             FRNN_TRACE_MARK(4);
             wg_barrier();
             FRNN_TRACE_MARK(1);
+            if constexpr (SPREAD) {
+                // (this workgroup has round cnt from every member, so all members of its XCD are done with the round before: the relay takes its words back.
+                // The burst before is complete: its wave has waited for everything ahead of the barrier.)
+                if (relay) __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)kNoWord, (int)kNoWord, (int)kNoWord, (int)kNoWord}, xr, relay_off + xnear + ((cnt + 3u) & 3u) * xbuf + xgroup, 0, 0);
+                if (wio >= 0 && s > 0) out_waves.store(p, smem, wio, s - 1);
+                if (wio == 3 && s % C::KB == 0) in.burst(p, smem, s + C::KB);
+            }
             if (pairs) {
                 const Places here = kTight ? places_of(fresh_lane(lane)) : at_once;
                 // (every member has this round, so every member is done with the one before: its words are taken back)
 #pragma unroll
-                for (int k = 0; k < PT; ++k) clear_tile<true>(xr, here.xlane, ((cnt + 3u) & 3u) * xbuf + xgroup + k * UBK * 32, false);
+                for (int k = 0; k < PT; ++k) clear_tile<true>(xr, here.xlane, ((cnt + 3u) & 3u) * xbuf + xgroup + k * UBK * 32, SPREAD);
                 float yb[PT][G], wx[PT][G], cv[PT][NC];
                 auto sums = [&](int k) {
                     sums_t v[4];
@@ -1393,20 +1439,23 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
             FRNN_TRACE_MARK(6);
         }
         wg_barrier();   // the last outputs are in their image
+        if constexpr (SPREAD) {
+            if (wio >= 0 && T > 0) out_waves.store(p, smem, wio, T - 1);
+        }
     }
     FRNN_TRACE_END(p);
 }
 
-template <int CELL, int UB, int KTW, int NCW, int BT>
-__global__ __launch_bounds__((SplitFwd<CELL, UB, KTW, NCW, BT>::NW * 64)) void split_fwd_kernel(const KernelParams p) {
-    using C = SplitFwd<CELL, UB, KTW, NCW, BT>;
+template <int CELL, int UB, int KTW, int NCW, int BT, bool SPREAD = false>
+__global__ __launch_bounds__((SplitFwd<CELL, UB, KTW, NCW, BT, SPREAD>::NW * 64)) void split_fwd_kernel(const KernelParams p) {
+    using C = SplitFwd<CELL, UB, KTW, NCW, BT, SPREAD>;
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, true);
     if (!bm.active) return;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w < NCW) split_fwd_compute<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane, w);
-    else if (w < NCW + C::NLD) split_fwd_load<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane);
-    else split_fwd_store<CELL, UB, KTW, NCW, BT>(p, bm, smem, lane, w - NCW - C::NLD);
+    if (SPREAD || w < NCW) split_fwd_compute<CELL, UB, KTW, NCW, BT, SPREAD>(p, bm, smem, lane, w);
+    else if (w < NCW + C::NLD) split_fwd_load<C>(p, bm, smem, lane);
+    else split_fwd_store<C>(p, bm, smem, lane, w - NCW - C::NLD);
 }
 
 }  // namespace flashrnn

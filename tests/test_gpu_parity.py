@@ -283,7 +283,7 @@ def test_backward_of_split_heads_exchanges_partial_sums(cell, NH, D, bt, B, T):
 @pytest.mark.parametrize("NH,D,B,T,env", [
     (2, 256, 9, 19, {"FLASHRNN_MULTI": "1", "FLASHRNN_MESH": "1", "FLASHRNN_BT": "8"}), (1, 384, 5, 3, {"FLASHRNN_MULTI": "1", "FLASHRNN_MESH": "1", "FLASHRNN_BT": "4"}),
     (1, 768, 20, 5, {"FLASHRNN_MESH": "1", "FLASHRNN_BT": "16"}), (1, 896, 11, 37, {"FLASHRNN_BT": "8"}), (1, 1024, 17, 4, {"FLASHRNN_BT": "16"}),
-    (3, 128, 13, 7, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "8", "FLASHRNN_GPAR": "3"}), (1, 256, 3, 41, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "4"}), (1, 2048, 7, 1, {}),
+    (1, 1536, 16, 35, {}), (3, 128, 13, 7, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "8", "FLASHRNN_GPAR": "3"}), (1, 256, 3, 41, {"FLASHRNN_MULTI": "2", "FLASHRNN_BT": "4"}), (1, 2048, 7, 1, {}),
 ])
 def test_backward_of_split_heads_in_two_hand_overs(cell, NH, D, B, T, env):
     """Subgroups of 1 to 16 members, inside one XCD (two blocks of 16 units per member) and one subgroup per XCD; contractions that do not fill the
