@@ -469,6 +469,23 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
     return FLASHRNN_OK;
 }
 
+// Calls of one time step in bf16 run on a kernel of their own, but for small heads with more than one row and for the larger batches, whose rows share
+// what the persistent kernels read of R (us per call, persistent and step: 12 x 64 with 1 / 16 rows 3.7 / 3.8 and 3.1 / 4.4; 8 x 128 with 16 rows 4.9 and 4.3;
+// 4 x 192 with 1 / 32 / 128 rows 8.6 / 8.5 / 9.9 and 4.1 / 6.5 / 13.4; 1 x 768 with 1 / 64 / 256 rows 30 / 31 / 46 and 6.9 / 17 / 54).
+bool make_step_plan(const flashrnn_desc_t* d, Plan* pl) {
+    const KernelEntry* step = table_for(d->cell, d->io_dtype).step;
+    if (d->T != 1 || !step || env_int("FLASHRNN_KIND", -1) >= 0) return false;   // (a forced kernel family: tests)
+    const KernelEntry& e = step[d->B == 1 ? 0 : 1];
+    const long long tiles = (d->B + e.BT - 1) / e.BT, grid = tiles * d->NH * (d->D / 16);
+    if (d->B > 1 && tiles > (d->D <= 64 ? 0 : d->D <= 128 ? 4 : d->D <= 192 ? 8 : 16)) return false;
+    if (grid > 1 << 20) return false;
+    Plan s;
+    s.e = &e;
+    s.NWU = 1; s.P = d->D / 16; s.NG = (int)(tiles * d->NH); s.GPAR = s.NG; s.grid = (int)grid; s.block = 256;
+    *pl = s;
+    return true;
+}
+
 struct Workspace {
     size_t err_off, exch_off, rpack_off[2] /* forward, backward */, dgn_off, dbpart_off, drpart_off, trace_off, total;
     size_t fwd_total;   // bytes a forward call touches: error words, exchange buffers, the forward copy of R
@@ -503,6 +520,9 @@ int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, P
     off += 2 * kTraceBytes;   // forward, backward
 #endif
     w->total = off;
+    // (a call of one step: the layout stays that of the persistent kernels' plans, of which it uses the error words only)
+    Plan step;
+    if (make_step_plan(d, &step)) { *pf = step; *pfn = step; }
     return FLASHRNN_OK;
 }
 

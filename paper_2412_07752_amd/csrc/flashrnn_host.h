@@ -32,6 +32,7 @@ struct KernelTable {
     const KernelEntry* entries;
     int count;
     const void* recompute;   // recompute_records_kernel of this (cell, I/O dtype)
+    const KernelEntry* step;   // step_kernel with 1 and 4 rows per workgroup (bf16), or null
 };
 
 // tables defined in flashrnn_inst_*.hip

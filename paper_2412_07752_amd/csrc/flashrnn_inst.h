@@ -12,6 +12,7 @@
 #include "flashrnn_tile_kernels.h"
 #include "flashrnn_split_kernels.h"
 #include "flashrnn_recompute.h"
+#include "flashrnn_step.h"
 
 namespace flashrnn {
 
@@ -118,8 +119,17 @@ static const KernelEntry kEntries[] = {
 #endif
 };
 
+#if FRNN_BF16
+// one time step on its own: 1 and 4 rows per workgroup
+#define FRNN_ST(RB) {FRNN_CELL, FRNN_BF16, 0, 0, 1, RB, 0, 4, 1, 1, 0, (const void*)&step_kernel<FRNN_CELL, RB>, 0, 0, 0, 0, 0},
+static const KernelEntry kStep[] = {FRNN_ST(1) FRNN_ST(4)};
+#undef FRNN_ST
+#else
+static const KernelEntry* const kStep = nullptr;
+#endif
+
 inline KernelTable make_table() {
-    return KernelTable{kEntries, (int)(sizeof(kEntries) / sizeof(kEntries[0])), (const void*)&recompute_records_kernel<FRNN_CELL, (FRNN_BF16 != 0)>};
+    return KernelTable{kEntries, (int)(sizeof(kEntries) / sizeof(kEntries[0])), (const void*)&recompute_records_kernel<FRNN_CELL, (FRNN_BF16 != 0)>, kStep};
 }
 
 #undef FRNN_F

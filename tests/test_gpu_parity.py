@@ -307,6 +307,18 @@ def test_split_heads_over_many_steps(cell, NH, D, bt, B, T, split):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,B", [(2, 16, 1), (3, 48, 1), (1, 112, 5), (2, 192, 13), (1, 272, 1), (1, 768, 33), (1, 1024, 2)])
+def test_one_step_calls(cell, NH, D, B):
+    """T = 1 on the kernel of its own: contractions that are no multiple of the threads' rounds, ragged batch tiles, with and without saved values
+    and initial states, and the backward call behind it."""
+    d = api.make_desc(cell, 1, B, NH, D, api.FLASHRNN_BF16)
+    assert api.flashrnn_plan(d) == ((B + 3) // 4 * NH * (D // 16) if B > 1 else NH * (D // 16), (B + 3) // 4 * (D // 16) if B > 1 else D // 16, 4)
+    for init in ("uniform0.1", "zero"):
+        _check(Workload(f"step_{cell}_D{D}_{init}", cell, 1, B, NH, D, "bf16", True, bias="uniform0.1", init=init, seed=D + B), with_dlast=True)
+    _check(Workload(f"step_{cell}_D{D}_infer", cell, 1, B, NH, D, "bf16", False, bias="uniform0.1", init="uniform0.1", seed=D))
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
     """The staged kernels look two steps ahead: the shortest sequences take every clamped branch of that."""
