@@ -5,6 +5,7 @@ the computation runs inside the library's kernels.  There is no fallback: if the
 been built (python -m paper_2412_07752_amd.build) every call raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -93,10 +94,12 @@ def status_string(status):
     return lib().flashrnn_status_string(int(status)).decode()
 
 
+@functools.lru_cache(maxsize=None)
 def flashrnn_num_states(cell):
     return lib().flashrnn_num_states(int(cell))
 
 
+@functools.lru_cache(maxsize=None)
 def flashrnn_num_gates(cell):
     return lib().flashrnn_num_gates(int(cell))
 
@@ -104,6 +107,12 @@ def flashrnn_num_gates(cell):
 def make_desc(cell, T, B, NH, D, io_dtype, recurrent_grad_clip=0.0):
     """recurrent_grad_clip: 0 = off, c > 0 clips R^T dg_t to [-c, c] per step, negative cuts it (backward only)."""
     return flashrnn_desc_t(int(cell), int(T), int(B), int(NH), int(D), int(io_dtype), float(recurrent_grad_clip))
+
+
+@functools.lru_cache(maxsize=256)
+def _desc_of(cell, T, B, NH, D, io_dtype, recurrent_grad_clip=0.0):
+    """The descriptor of a call; the binding's own, never handed out, so that one serves all calls of a shape."""
+    return make_desc(cell, T, B, NH, D, io_dtype, recurrent_grad_clip)
 
 
 def flashrnn_gate_cache_bytes(desc):
@@ -160,7 +169,7 @@ def flashrnn_trace_phases(desc, workspace, backward, stream=None):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _io_dtype(t):
@@ -172,6 +181,8 @@ def _io_dtype(t):
 
 
 def _chk(t, shape, dtype, name, optional=False):
+    if t is not None and t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous():
+        return
     if t is None:
         if optional:
             return
@@ -183,8 +194,9 @@ def _chk(t, shape, dtype, name, optional=False):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:   # the current stream's handle, without a stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def alloc_workspace(desc, device):
@@ -203,7 +215,7 @@ def flashrnn_fwd_static_scratch(cell, Wx, R, b, states0=None, save_for_backward=
     if G != flashrnn_num_gates(cell):
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = make_desc(cell, T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -228,7 +240,7 @@ def flashrnn_fwd(cell, Wx, R, b, states0=None, save_for_backward=True, workspace
     if G != flashrnn_num_gates(cell):
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = make_desc(cell, T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -256,7 +268,7 @@ def flashrnn_bwd(cell, R, b, states, gate_cache, dH, dstates_last=None, workspac
     T, B, NH, D = dH.shape
     S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
     dt = dH.dtype
-    desc = make_desc(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
     _chk(states, (T + 1, S, B, NH, D), torch.float32, "states")
@@ -287,7 +299,7 @@ def flashrnn_bwd_recompute(cell, Wx, R, b, states, dH, dstates_last=None, worksp
     T, B, NH, D = dH.shape
     S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
     dt = dH.dtype
-    desc = make_desc(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
