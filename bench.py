@@ -255,10 +255,9 @@ def main():
     ms_per_step, fwd_ms, bwd_ms, launches = runner.run(args.steps, args.warmup)
     value = B * T / (ms_per_step * 1e-3)
     if args.trace_phases:
-        names = {False: ["prefetch_issue", "barrier_rows_read", "wait_exchange_and_lds_fill", "barrier_rows_ready", "lds_reads_mfma_slice_sums",
-                         "pointwise_publish", "stores_and_input_wait", "poll_first_round_trip"],
-                 True: ["loads_pointwise_publish_dwx", "barrier_rows_read", "wait_exchange_and_lds_fill", "barrier_rows_ready",
-                        "lds_reads_mfma_slice_sums", "input_wait", "-", "poll_first_round_trip"]}
+        # (what each phase holds differs between the kernels: comment at FRNN_TRACE_BEGIN in csrc/flashrnn_kernels.h)
+        names = {False: ["loop_head", "barrier", "wait_exchange", "barrier_rows_ready", "products_and_slice_sums", "pointwise_publish", "outputs_and_input_wait", "poll_first_round_trip"],
+                 True: ["pointwise", "barrier", "wait_exchange", "second_barrier", "products", "sums_publish_or_input_wait", "next_inputs", "second_wait_or_poll_first_round_trip"]}
         res = {"workload": w.name, "plan_signature": plan_signature(api, desc, w.backward), "unit": "shader clocks per time step, mean over waves",
                "fwd_kernel_ms": round(fwd_ms, 4), "bwd_kernel_ms": round(bwd_ms, 4)}
         for bwd in ([False, True] if w.backward else [False]):

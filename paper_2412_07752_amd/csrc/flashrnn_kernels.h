@@ -180,6 +180,11 @@ template <int N> __device__ __forceinline__ void pin(float (&v)[N]) {
 //   backward  0 issue of the loads of step t-1, point-wise Jacobians of step t, publish dg_t, dWx stores | 1 barrier | 7 first
 //             round trip of the poll | 2 further rounds until the partners' dg_t is complete, payloads into LDS | 3 barrier | 4 operand reads + MFMA chain + slice sums | 5 wait for
 //             the prefetched inputs
+// Kernels with wave roles (flashrnn_split_kernels.h; compute waves only):
+//   forward   2 poll of the wave's first piece of h_{t-1} | 4 further pieces, products, sums into LDS | 1 barrier | 5 slices' sums, point-wise, publish | 6 outputs
+//             into their image
+//   backward  0 point-wise, operand rows (mesh: publish dg) | mesh: 2 poll of dg | 4 products (one hand-over: publish) | 1 barrier | mesh: 5 waves' sums, publish | 6 inputs
+//             of the next step | 2 (mesh: 7, with 6) poll of the partial sums | 3 second barrier
 #ifdef FLASHRNN_TRACE
 #define FRNN_TRACE_BEGIN() unsigned long long tr_acc[kTracePhases] = {0, 0, 0, 0, 0, 0, 0, 0}; unsigned long long tr_t = __builtin_amdgcn_s_memtime(), tr_first = 0;
 #define FRNN_TRACE_MARK(i) { __builtin_amdgcn_sched_barrier(0); const unsigned long long tr_n = __builtin_amdgcn_s_memtime(); \

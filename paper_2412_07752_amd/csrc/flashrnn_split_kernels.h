@@ -546,13 +546,13 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
                         }
                     }
             }
-            FRNN_TRACE_MARK(2);
+            FRNN_TRACE_MARK(4);
             // ---- the inputs of the next step, while the partial sums travel
             slot = slot + 1 == (uint32_t)C::RD ? 0 : slot + 1;
             if (pairs) take(slot);
             pin(kf);   // (here, not behind the poll)
             pin(dh_ext);
-            FRNN_TRACE_MARK(3);
+            FRNN_TRACE_MARK(6);
             // ---- the partial sums of this workgroup's units from the other members
             uint32_t got[NIN > 0 ? NIN : 1][IW];
             if (p.spin_limit < 0 && !failed) {   // host-forced failure (tests of the error path): give up without looking
@@ -573,7 +573,7 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
             // (taken back for the round NBUF later: this workgroup is the only one that looks at these words)
 #pragma unroll
             for (int j = 0; j < NIN; ++j) clear_part<IW>(xr, in_voff(j), buf + in_off[j]);
-            FRNN_TRACE_MARK(4);
+            FRNN_TRACE_MARK(2);
             if constexpr (DIRECT) {
 #pragma unroll
                 for (int k = 0; k < PT; ++k) {
@@ -590,7 +590,7 @@ __device__ __forceinline__ void split_bwd_compute(const KernelParams& p, const B
                     for (int i = 0; i < 4; ++i) sum[i] += __builtin_bit_cast(float, got[j][i]);
                 if (sub < C::NSUB) *(f32x4*)(red + sub * C::SEG + pos * 16) = sum;
                 wg_barrier();
-                FRNN_TRACE_MARK(5);
+                FRNN_TRACE_MARK(3);
                 if (pairs) {
 #pragma unroll
                     for (int k = 0; k < PT; ++k) {
@@ -890,7 +890,7 @@ __device__ __forceinline__ void mesh_bwd_compute(const KernelParams& p, const Bl
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            FRNN_TRACE_MARK(3);
+            FRNN_TRACE_MARK(4);
             wg_barrier();
             FRNN_TRACE_MARK(1);
             if (pairs) {   // (every member of the subgroup has this round, so all are done with the one before: its words are taken back)
@@ -941,7 +941,7 @@ __device__ __forceinline__ void mesh_bwd_compute(const KernelParams& p, const Bl
                 for (int j = 1; j < PB; ++j) rec += __builtin_bit_cast(float, got[j]);
                 ds[0] += fminf(fmaxf(rec, -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
             }
-            FRNN_TRACE_MARK(4);
+            FRNN_TRACE_MARK(7);
         }
         // ---- gradients of the initial states, per-row partial sums of db
         const uint32_t el = fresh_lane(lane), brow = q * BT + row_of(el);
