@@ -128,7 +128,7 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
         const KernelEntry& e = tab.entries[i];
         if (!e.ub || e.bwd != bwd || e.BT != pl->e->BT || units16 % e.ub || (force_ub && !pl->spread && e.ub != force_ub)) continue;
         const int P = units16 / e.ub;
-        if (e.smem > (int)kLdsBytes || e.direct == 3 || kernel_spills(e.fn)) continue;
+        if (e.smem > (int)kLdsBytes || e.direct == 3) continue;
         if (bwd && e.direct == 2) {
             // (a mesh of 8 / ub subgroups; spread over the chip each XCD is one of its eight)
             if (units16 % 8 || num_gates(d->cell) * d->D * e.ub / 8 > e.KT * e.KS * 32 || (e.ub == 1) != (pl->spread != 0)) continue;
@@ -143,7 +143,7 @@ void take_split_kernel(const flashrnn_desc_t* d, int bwd, const KernelTable& tab
         const int rank = kind_rank(e), brank = best ? kind_rank(*best) : 0;
         const bool better = !best ? true : bwd ? (rank != brank ? rank > brank : e.ub != best->ub ? e.ub > best->ub : e.direct == 2 ? e.KT < best->KT : e.nb < best->nb)
                                 : (e.ub != best->ub ? e.ub < best->ub : e.KT * e.KS != best->KT * best->KS ? e.KT * e.KS < best->KT * best->KS : e.KS < best->KS);
-        if (better) best = &e;
+        if (better && !kernel_spills(e.fn)) best = &e;
     }
     if (!best) return;
     pl->e = best;
