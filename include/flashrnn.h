@@ -87,6 +87,8 @@ size_t flashrnn_workspace_bytes(const flashrnn_desc_t* desc);
  *   b        [NH,G,D]     io_dtype  bias
  *   states0  [S,B,NH,D]   f32       initial states, or NULL for zeros
  *   states   [T+1,S,B,NH,D] f32     OUT: slot 0 = initial states, slot t = states after step t
+ *            (states0 may be any one slot of `states`, e.g. slot 1 of a one-step call whose results the next call starts from; any
+ *            other overlap of an output with an input or another output is undefined)
  *   gate_cache  flashrnn_gate_cache_bytes() bytes, OUT, or NULL for a forward-only call
  *   workspace   flashrnn_workspace_bytes() bytes (may be NULL when that size is 0)
  */

@@ -233,7 +233,8 @@ def flashrnn_fwd_static_scratch(cell, Wx, R, b, states0=None, save_for_backward=
 
 
 def flashrnn_fwd(cell, Wx, R, b, states0=None, save_for_backward=True, workspace=None, stream=None, states=None, gate_cache=None):
-    """Forward pass.  Wx[T,B,G,NH,D], R[NH,D,G,D], b[NH,G,D] (bf16 or f32), states0[S,B,NH,D] f32 or None.
+    """Forward pass.  Wx[T,B,G,NH,D], R[NH,D,G,D], b[NH,G,D] (bf16 or f32), states0[S,B,NH,D] f32 or None.  states0 may be
+    a slot of `states`.
     Returns (states[T+1,S,B,NH,D] f32, gate_cache or None, workspace)."""
     T, B, G, NH, D = Wx.shape
     S = flashrnn_num_states(cell)

@@ -491,7 +491,14 @@ struct Workspace {
     size_t fwd_total;   // bytes a forward call touches: error words, exchange buffers, the forward copy of R
 };
 
-int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, Plan* pfn) {
+// The plans of a descriptor's calls.
+struct Plans {
+    Plan fwd, bwd, infer;   // forward call that saves its values, backward call, forward call that saves nothing
+    Plan step;              // forward calls of one step whose states do not overlap the initial ones (e == nullptr: they run the plans above)
+};
+
+int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plans* pl) {
+    Plan *const pf = &pl->fwd, *const pb = &pl->bwd, *const pfn = &pl->infer;
     int rc = make_plan(d, 0, pf);
     if (rc != FLASHRNN_OK) return rc;
     rc = make_plan(d, 1, pb);
@@ -499,6 +506,8 @@ int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, P
     // A forward call that saves nothing may take another batch tile of the staged kernels (they use no workspace beyond the
     // error words, so the layout below does not depend on it); everywhere else it runs the plan of the saving call.
     if (make_plan(d, 2, pfn) != FLASHRNN_OK || pfn->e->tile == 0 || pf->e->tile == 0) *pfn = *pf;
+    // (a call of one step uses nothing of the layout below but the error words)
+    make_step_plan(d, &pl->step);
     const int G = num_gates(d->cell);
     size_t off = 0;
     w->err_off = off; off += kAlign;   // word 0: forward kernels, word 1: backward kernels
@@ -520,31 +529,27 @@ int carve_uncached(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, P
     off += 2 * kTraceBytes;   // forward, backward
 #endif
     w->total = off;
-    // (a call of one step: the layout stays that of the persistent kernels' plans, of which it uses the error words only)
-    Plan step;
-    if (make_step_plan(d, &step)) { *pf = step; *pfn = step; }
     return FLASHRNN_OK;
 }
 
 // Plans and workspace layout of a descriptor.  A thread that calls with the same descriptor again (the usual case:
 // forward, backward, forward, ...) gets the last answer back instead of planning anew; the answer depends on the
 // descriptor and the device only (and on the override variables, which switch this memo off).
-int carve(const flashrnn_desc_t* d, Workspace* w, Plan* pf, Plan* pb, Plan* pfn = nullptr) {
-    struct Memo { bool valid = false; flashrnn_desc_t d; int dev; int rc; Workspace w; Plan pf, pb, pfn; };
+int carve(const flashrnn_desc_t* d, Workspace* w, Plans* pl) {
+    struct Memo { bool valid = false; flashrnn_desc_t d; int dev; int rc; Workspace w; Plans pl; };
     static thread_local Memo memo;
     int dev = -1;
     (void)hipGetDevice(&dev);
     flashrnn_desc_t key = *d;
     key.recurrent_grad_clip = 0.0f;   // does not enter the plan
     if (!overrides_enabled() && memo.valid && memo.dev == dev && memcmp(&memo.d, &key, sizeof(key)) == 0) {
-        *w = memo.w; *pf = memo.pf; *pb = memo.pb;
-        if (pfn) *pfn = memo.pfn;
+        *w = memo.w;
+        *pl = memo.pl;
         return memo.rc;
     }
-    Plan nosave;
-    const int rc = carve_uncached(d, w, pf, pb, &nosave);
-    memo.valid = true; memo.d = key; memo.dev = dev; memo.rc = rc; memo.w = *w; memo.pf = *pf; memo.pb = *pb; memo.pfn = nosave;
-    if (pfn) *pfn = nosave;
+    *pl = Plans();
+    const int rc = carve_uncached(d, w, pl);
+    memo.valid = true; memo.d = key; memo.dev = dev; memo.rc = rc; memo.w = *w; memo.pl = *pl;
     return rc;
 }
 
@@ -636,10 +641,15 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     if (!aligned16(Wx) || !aligned16(R) || !aligned16(b) || !aligned16(states0) || !aligned16(states) || !aligned16(gate_cache))
         return FLASHRNN_ERR_UNSUPPORTED;
     Workspace w;
-    Plan pf, pb, pfn;
-    rc = carve(d, &w, &pf, &pb, &pfn);
+    Plans pl;
+    rc = carve(d, &w, &pl);
     if (rc != FLASHRNN_OK) return rc;
-    if (!gate_cache) pf = pfn;
+    // The one-step kernel's workgroups read h_0 of a whole head while others write states: initial states that lie in `states` itself (but as its
+    // slot 0, which gets the same values) go the way of longer sequences, where units that others own come through the exchange or were read before.
+    const size_t slab = (size_t)num_states(d->cell) * d->B * d->NH * d->D * 4;
+    const uintptr_t s0 = (uintptr_t)states0, out = (uintptr_t)states;
+    const bool overlap = states0 && s0 != out && s0 < out + 2 * slab && out < s0 + slab;
+    const Plan& pf = pl.step.e && !overlap ? pl.step : gate_cache ? pl.fwd : pl.infer;
     if (!workspace || ((uintptr_t)workspace & (kAlign - 1))) return FLASHRNN_ERR_WORKSPACE;
     if (ws_limit && w.fwd_total > ws_limit) return FLASHRNN_ERR_SCRATCH;
     hipStream_t stream = (hipStream_t)hip_stream;
@@ -702,9 +712,10 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
         !aligned16(dWx) || !aligned16(dR) || !aligned16(db) || !aligned16(dstates0) || !aligned16(Wx) || !aligned16(b))
         return FLASHRNN_ERR_UNSUPPORTED;
     Workspace w;
-    Plan pf, pb;
-    rc = carve(d, &w, &pf, &pb);
+    Plans pl;
+    rc = carve(d, &w, &pl);
     if (rc != FLASHRNN_OK) return rc;
+    const Plan& pb = pl.bwd;
     if (!workspace || ((uintptr_t)workspace & (kAlign - 1))) return FLASHRNN_ERR_WORKSPACE;
     hipStream_t stream = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
@@ -804,8 +815,8 @@ size_t flashrnn_gate_cache_bytes(const flashrnn_desc_t* d) {
 size_t flashrnn_workspace_bytes(const flashrnn_desc_t* d) {
     if (validate(d) != FLASHRNN_OK) return 0;
     Workspace w;
-    Plan pf, pb;
-    if (carve(d, &w, &pf, &pb) != FLASHRNN_OK) return 0;
+    Plans pl;
+    if (carve(d, &w, &pl) != FLASHRNN_OK) return 0;
     return w.total;
 }
 
@@ -814,10 +825,10 @@ namespace {
 int plan_of_call(const flashrnn_desc_t* d, int which, Plan* pl) {
     if (which < 0 || which > 2) return FLASHRNN_ERR_SHAPE;
     Workspace w;
-    Plan pf, pb, pfn;
-    const int rc = carve(d, &w, &pf, &pb, &pfn);
+    Plans all;
+    const int rc = carve(d, &w, &all);
     if (rc != FLASHRNN_OK) return rc;
-    *pl = which == 0 ? pf : (which == 1 ? pb : pfn);
+    *pl = which == 1 ? all.bwd : all.step.e ? all.step : which == 0 ? all.fwd : all.infer;
     return FLASHRNN_OK;
 }
 }  // namespace
@@ -877,8 +888,8 @@ int flashrnn_bwd_recompute(const flashrnn_desc_t* d, const void* Wx, const void*
 size_t flashrnn_recompute_workspace_bytes(const flashrnn_desc_t* d) {
     if (validate(d) != FLASHRNN_OK) return 0;
     Workspace w;
-    Plan pf, pb;
-    if (carve(d, &w, &pf, &pb) != FLASHRNN_OK) return 0;
+    Plans pl;
+    if (carve(d, &w, &pl) != FLASHRNN_OK) return 0;
     return recompute_layout(d, w.total).total;
 }
 
@@ -893,8 +904,8 @@ int flashrnn_check(const flashrnn_desc_t* d, const void* workspace, void* hip_st
     bool fwd_waits = true, bwd_waits = true;
     {   // plans without cross-CU waits cannot time out and do not maintain their error word
         Workspace w;
-        Plan pf, pb;
-        if (d && validate(d) == FLASHRNN_OK && carve(d, &w, &pf, &pb) == FLASHRNN_OK) { fwd_waits = pf.e->multi; bwd_waits = pb.e->multi; }
+        Plans pl;
+        if (d && validate(d) == FLASHRNN_OK && carve(d, &w, &pl) == FLASHRNN_OK) { fwd_waits = pl.fwd.e->multi; bwd_waits = pl.bwd.e->multi; }
         if (!fwd_waits && !bwd_waits) return hipStreamSynchronize(stream) == hipSuccess ? FLASHRNN_OK : FLASHRNN_ERR_LAUNCH;
     }
     if (hipMemcpyAsync(flags, workspace, sizeof(flags), hipMemcpyDeviceToHost, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
@@ -908,8 +919,8 @@ int flashrnn_trace_phases(const flashrnn_desc_t* d, const void* workspace, int b
     if (rc != FLASHRNN_OK) return rc;
     if (!workspace || !clocks) return FLASHRNN_ERR_NULL;
     Workspace w;
-    Plan pf, pb;
-    rc = carve(d, &w, &pf, &pb);
+    Plans pl;
+    rc = carve(d, &w, &pl);
     if (rc != FLASHRNN_OK) return rc;
     static unsigned long long host[kTraceGrid * kTraceWaves * kTracePhases];
     hipStream_t stream = (hipStream_t)hip_stream;

@@ -320,6 +320,53 @@ def test_one_step_calls(cell, NH, D, B):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,B", [(4, 192, 1), (2, 96, 5), (1, 768, 3), (1, 1152, 2)])
+def test_one_step_calls_that_carry_their_states_in_place(cell, NH, D, B):
+    """states0 = states[1] of the same buffer, call after call: every unit's new state must come from the old h of the whole head."""
+    w = Workload(f"carry_{cell}_D{D}", cell, 6, B, NH, D, "bf16", False, bias="uniform0.1", init="uniform0.1", seed=D + B)
+    inp = synth.make_inputs(w)
+    print(f"case {w.name}", flush=True)
+    ref = pu.run_oracle(w, inp)
+    Wx, R, b = (pu.to_device(inp[k], "bf16") for k in ("Wx", "R", "b"))
+    d = api.make_desc(cell, 1, B, NH, D, api.FLASHRNN_BF16)
+    ws = api.alloc_workspace(d, "cuda")
+    states = torch.empty((2, w.S, B, NH, D), dtype=torch.float32, device="cuda")
+    for scratch in (False, True):
+        states[1].copy_(pu.to_device(inp["states0"], "f32"))
+        steps = [states[1].clone()]
+        for t in range(w.T):
+            if scratch:
+                api.flashrnn_fwd_static_scratch(cell, Wx[t:t + 1], R, b, states[1], save_for_backward=False, states=states)
+                api.flashrnn_check(d, api.STATIC_SCRATCH)
+            else:
+                api.flashrnn_fwd(cell, Wx[t:t + 1], R, b, states[1], save_for_backward=t % 2 == 1, workspace=ws, states=states)
+                api.flashrnn_check(d, ws)
+            assert torch.equal(states[0], steps[-1])   # slot 0 holds what the call started from
+            steps.append(states[1].clone())
+        gpu = {"states": pu.to_host64(torch.stack(steps))}
+        pu.assert_close(w, pu.compare(w, gpu, ref))
+        pu.assert_states_elementwise(w, gpu, ref)
+
+
+@pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("dtype,NH,D,B", [("bf16", 2, 64, 7), ("bf16", 1, 192, 19), ("bf16", 2, 256, 9), ("bf16", 1, 768, 35), ("bf16", 1, 1152, 5), ("f32", 2, 96, 7), ("f32", 1, 208, 5)])
+def test_initial_states_in_a_slot_of_the_output(cell, dtype, NH, D, B):
+    """states0 = any slot of `states`: the same bits as with a buffer of its own, in every kernel family."""
+    w = Workload(f"slot_{cell}_{dtype}_D{D}", cell, 3, B, NH, D, dtype, False, bias="uniform0.1", init="uniform0.1", seed=D + B)
+    inp = synth.make_inputs(w)
+    print(f"case {w.name}", flush=True)
+    Wx, R, b = (pu.to_device(inp[k], dtype) for k in ("Wx", "R", "b"))
+    s0 = pu.to_device(inp["states0"], "f32")
+    ref, _, ws = api.flashrnn_fwd(cell, Wx, R, b, s0, save_for_backward=False)
+    for slot in range(w.T + 1):
+        states = torch.empty_like(ref)
+        states[slot].copy_(s0)
+        api.flashrnn_fwd(cell, Wx, R, b, states[slot], save_for_backward=False, workspace=ws, states=states)
+        api.flashrnn_check(api.make_desc(cell, w.T, B, NH, D, api.FLASHRNN_BF16 if dtype == "bf16" else api.FLASHRNN_F32), ws)
+        assert torch.equal(states, ref), slot
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
     """The staged kernels look two steps ahead: the shortest sequences take every clamped branch of that."""
