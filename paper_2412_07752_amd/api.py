@@ -94,14 +94,17 @@ def status_string(status):
     return lib().flashrnn_status_string(int(status)).decode()
 
 
-@functools.lru_cache(maxsize=None)
+@functools.lru_cache(maxsize=16)
+def _cell_sizes(cell):
+    return lib().flashrnn_num_states(cell), lib().flashrnn_num_gates(cell)
+
+
 def flashrnn_num_states(cell):
-    return lib().flashrnn_num_states(int(cell))
+    return _cell_sizes(int(cell))[0]
 
 
-@functools.lru_cache(maxsize=None)
 def flashrnn_num_gates(cell):
-    return lib().flashrnn_num_gates(int(cell))
+    return _cell_sizes(int(cell))[1]
 
 
 def make_desc(cell, T, B, NH, D, io_dtype, recurrent_grad_clip=0.0):
@@ -111,7 +114,8 @@ def make_desc(cell, T, B, NH, D, io_dtype, recurrent_grad_clip=0.0):
 
 @functools.lru_cache(maxsize=256)
 def _desc_of(cell, T, B, NH, D, io_dtype, recurrent_grad_clip=0.0):
-    """The descriptor of a call; the binding's own, never handed out, so that one serves all calls of a shape."""
+    """The descriptor of a call; the binding's own, never handed out, so that one serves all calls of a shape.  Plain numbers only: a caller's
+    object (a tensor or an array that holds the clip) would be looked up by what it is, not by its value."""
     return make_desc(cell, T, B, NH, D, io_dtype, recurrent_grad_clip)
 
 
@@ -215,7 +219,7 @@ def flashrnn_fwd_static_scratch(cell, Wx, R, b, states0=None, save_for_backward=
     if G != flashrnn_num_gates(cell):
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -241,7 +245,7 @@ def flashrnn_fwd(cell, Wx, R, b, states0=None, save_for_backward=True, workspace
     if G != flashrnn_num_gates(cell):
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -269,7 +273,7 @@ def flashrnn_bwd(cell, R, b, states, gate_cache, dH, dstates_last=None, workspac
     T, B, NH, D = dH.shape
     S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
     dt = dH.dtype
-    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
+    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
     _chk(states, (T + 1, S, B, NH, D), torch.float32, "states")
@@ -300,7 +304,7 @@ def flashrnn_bwd_recompute(cell, Wx, R, b, states, dH, dstates_last=None, worksp
     T, B, NH, D = dH.shape
     S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
     dt = dH.dtype
-    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), recurrent_grad_clip)
+    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
