@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void step_kernel(const KernelParams p) {
     for (int r = 0; r < RB; ++r)
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[r][j] = 0.0f;
-    if (p.states0 != nullptr && ks < (uint32_t)KS) {
+    auto contract = [&](auto state_c) {   // (without initial states R meets zeros, as everywhere: an infinite or NaN weight makes a NaN)
         const uint16_t* R = (const uint16_t*)p.R + (size_t)n * D * G * D + g * D + e0 + half * 8;
         const float* h = p.states0 + n * D;
         for (uint32_t d0 = ks; d0 < D; d0 += KS * NI) {
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void step_kernel(const KernelParams p) {
                 const uint32_t d = d0 + i * KS < D ? d0 + i * KS : d0;
                 w[i] = *(const i32x4*)(R + (size_t)d * G * D);
 #pragma unroll
-                for (int r = 0; r < RB; ++r) hv[i][r] = h[(size_t)(b0 + r < B ? b0 + r : B - 1) * HD + d];
+                for (int r = 0; r < RB; ++r) hv[i][r] = decltype(state_c)::value ? h[(size_t)(b0 + r < B ? b0 + r : B - 1) * HD + d] : 0.0f;
             }
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -50,8 +50,10 @@ __global__ __launch_bounds__(256) void step_kernel(const KernelParams p) {
                 }
             }
         }
-    }
+    };
     if (ks < (uint32_t)KS) {
+        if (p.states0 != nullptr) contract(std::true_type{});
+        else contract(std::false_type{});
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll

@@ -367,6 +367,22 @@ def test_initial_states_in_a_slot_of_the_output(cell, dtype, NH, D, B):
 
 
 @pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,B", [(2, 96, 1), (1, 768, 3)])
+def test_one_step_calls_from_zero_states_with_weights_that_are_not_finite(cell, NH, D, B):
+    """No initial states: h_0 is zero, and zero times an infinite or NaN weight is NaN, as on the kernels of longer sequences."""
+    w = Workload(f"zero_{cell}_D{D}", cell, 1, B, NH, D, "bf16", False, bias="uniform0.1", init="zero", seed=D + B)
+    inp = synth.make_inputs(w)
+    inp["R"][0, 3, 0, 5], inp["R"][NH - 1, D - 1, w.G - 1, D - 1] = np.inf, np.nan
+    Wx, R, b = (pu.to_device(inp[k], "bf16") for k in ("Wx", "R", "b"))
+    two = torch.cat([Wx, Wx])
+    got, ref = (pu.to_host64(api.flashrnn_fwd(cell, x, R, b, save_for_backward=False)[0][1]) for x in (Wx, two))
+    assert np.isnan(ref[0, :, 0, 5]).all() and np.isnan(ref).sum() <= 2 * w.S * B
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    fin = np.isfinite(ref)
+    assert np.abs(got[fin] - ref[fin]).max() <= pu.TOL_BF16_REL * np.abs(ref[fin]).max()
+
+
+@pytest.mark.parametrize("cell", CELLS)
 @pytest.mark.parametrize("T", [0, 1, 2, 3])
 def test_degenerate_lengths(cell, T):
     """The staged kernels look two steps ahead: the shortest sequences take every clamped branch of that."""
