@@ -333,7 +333,7 @@ template <bool BF16, int PP> __device__ __forceinline__ void load_io_r(rsrc_t r,
         }
     }
 }
-// Stores of 16 bytes carry no scalar offset.  With one the compiler takes the data registers for free behind the store; a value written to
+// Stores of 12 and 16 bytes carry no scalar offset, here and everywhere else.  With one the compiler takes the data registers for free behind the store; a value written to
 // the first of them by the very next instruction was stored instead in the last four lanes of each row of 16 (seen in the
 // partial sums of the split backward kernel; without the scalar offset the compiler keeps two instructions between).
 template <bool BF16, int PP> __device__ __forceinline__ void store_io_r(rsrc_t r, uint32_t voff, uint32_t soff, const float (&v)[PP]) {
@@ -390,12 +390,12 @@ template <bool BF16, int RS, int NC> __device__ __forceinline__ void store_recor
     if constexpr (BF16 && RS == 1) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(w[0] & 0xFFFFu), r, voff, soff, 0);
     else if constexpr (NW == 1) __builtin_amdgcn_raw_buffer_store_b32(w[0], r, voff, soff, 0);
     else if constexpr (NW == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{(int)w[0], (int)w[1]}, r, voff, soff, 0);
-    else if constexpr (NW == 3) __builtin_amdgcn_raw_buffer_store_b96(i32x3{(int)w[0], (int)w[1], (int)w[2]}, r, voff, soff, 0);
-    else if constexpr (NW == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]}, r, voff, soff, 0);
+    else if constexpr (NW == 3) __builtin_amdgcn_raw_buffer_store_b96(i32x3{(int)w[0], (int)w[1], (int)w[2]}, r, voff + soff, 0, 0);
+    else if constexpr (NW == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]}, r, voff + soff, 0, 0);
     else {
         static_assert(NW == 8, "record sizes: 1, 2, 3, 4 or 8 dwords");
-        __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]}, r, voff, soff, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[4], (int)w[5], (int)w[6], (int)w[7]}, r, voff + 16, soff, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]}, r, voff + soff, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(i32x4{(int)w[4], (int)w[5], (int)w[6], (int)w[7]}, r, voff + soff + 16, 0, 0);
     }
 }
 template <bool BF16, int RS, int NC> __device__ __forceinline__ void load_record(rsrc_t r, uint32_t voff, uint32_t soff, float (&v)[NC]) {

@@ -129,7 +129,7 @@ template <int PP, int AUX = 0> __device__ __forceinline__ void store_part(rsrc_t
 }
 template <int PP> __device__ __forceinline__ void clear_part(rsrc_t rs, uint32_t voff, uint32_t soff) {
     constexpr int none = (int)kNoWord;
-    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{none, none, none, none}, rs, voff, soff, 0);
+    if constexpr (PP == 4) __builtin_amdgcn_raw_buffer_store_b128(i32x4{none, none, none, none}, rs, voff + soff, 0, 0);
     else if constexpr (PP == 2) __builtin_amdgcn_raw_buffer_store_b64(i32x2{none, none}, rs, voff, soff, 0);
     else __builtin_amdgcn_raw_buffer_store_b32(none, rs, voff, soff, 0);
 }
