@@ -866,10 +866,13 @@ __device__ __forceinline__ void mesh_bwd_compute(const KernelParams& p, const Bl
                 f32x4 a[CH];
 #pragma unroll
                 for (int x = 0; x < CH; ++x) a[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-                // (a half step comes first: behind a step of 64 on the same registers it would need more instructions between)
+                // (R leaves no registers for accumulators of the half step's own, as split_fwd_compute has them: it comes first, and the steps of 64 begin when
+                // all its sums are there -- four passes, eight instruction slots)
                 if constexpr (SP && HALF) {
 #pragma unroll
                     for (int x = 0; x < CH; ++x) a[x] = smfmac32(i32x2{raw[NPC - 1][0], raw[NPC - 1][1]}, Rh[b0 + x], a[x], sl.idx);
+                    static_assert(CH == 4);
+                    asm volatile("s_nop 7" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
                 }
 #pragma unroll
                 for (int j = 0; j < (SP ? NKF : KTW); ++j)
@@ -1324,17 +1327,26 @@ __device__ __forceinline__ void split_fwd_compute(const KernelParams& p, const B
                 for (int g = 0; g < G; ++g) asm volatile("" : : "v"(a[g]));
                 if constexpr (SP && HALF && G == 1) asm volatile("" : : "v"(ah));
             };
-            // (The half step adds to its accumulator two and more other matrix instructions behind the step of 64 before it.  Elman has one gate and
-            // an accumulator of its own for it: a half step right behind a step of 64 on the same registers gave wrong sums.)
+            // A half step on registers that a step of 64 is still adding to has given wrong sums, and the compiler keeps no distance between the two.  So the
+            // sums are read between them, behind the wait for the half step's piece: an empty instruction, for which the compiler lets the matrix
+            // instructions finish (they long have: 0.3 % over heads of 288 to 368 and 1280 units; accumulators of its own for the half step 3 %, the same
+            // read ahead of the wait 1.6 %).  Elman, with one matrix instruction per piece, has accumulators of its own.
             f32x4 ah[UB];
 #pragma unroll
             for (int u = 0; u < UB; ++u) ah[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            static_assert(!(SP && HALF) || kEarly, "the half step's distance rests on the wait in front of it");
             if constexpr (kEarly) {
                 // each piece is multiplied as soon as it is there
                 auto piece = [&](auto j_c) {
                     constexpr int j = decltype(j_c)::value;
                     if constexpr (j < NPC) {
                         wait_for(j_c, false);
+                        if constexpr (SP && HALF && G > 1 && j == NKF) {
+#pragma unroll
+                            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                                for (int g = 0; g < G; ++g) asm volatile("" : "+v"(acc[u][g]));
+                        }
                         if constexpr (j == NPC - 1) wait_vmem<0>();   // (also what this wave has taken back, if it had nothing to poll)
                         if constexpr (j == 0) FRNN_TRACE_MARK(2);
 #pragma unroll

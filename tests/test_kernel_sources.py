@@ -1,9 +1,16 @@
-"""CPU-only checks of rules that the kernels' sources keep because a compiler does not."""
+"""CPU-only checks of rules that the kernels keep because a compiler does not."""
 import glob
 import os
 import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2412_07752_amd import api
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2412_07752_amd", "csrc")
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
 def _arguments(text, start):
@@ -31,3 +38,45 @@ def test_wide_stores_carry_no_scalar_offset():
             assert len(args) == 5 and args[3] == "0", f"{os.path.basename(path)}: {args}"
             seen += 1
     assert seen >= 20
+
+
+def _code_objects(library):
+    """The gfx950 code objects of a library: the bundles of its .hip_fatbin section, one per translation unit."""
+    data, magic = open(library, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        count, pos = struct.unpack_from("<Q", data, at + 24)[0], at + 32
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, pos)
+            name = data[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if name.endswith(b"gfx950") and size:
+                yield data[at + offset:at + offset + size]
+        at = data.find(magic, at + 32)
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_sparse_steps_of_two_depths_on_the_same_sums_keep_their_distance(tmp_path):
+    """A step of one depth that adds to registers which a step of the other depth is still adding to has given wrong sums, and the compiler keeps no
+    distance between them: the first one's passes (eight of the deeper step, four of the other) and four instruction slots in every kernel of the
+    built library."""
+    pairs = 0
+    for i, code in enumerate(_code_objects(api.library_path())):
+        path = tmp_path / f"{i}.o"
+        path.write_bytes(code)
+        kernel, last, slot = None, {}, 0
+        for line in subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout.splitlines():
+            if line.endswith(">:"):
+                kernel, last, slot = line, {}, 0
+                continue
+            words = line.split("//")[0].split()
+            if not words or kernel is None:
+                continue
+            slot += int(words[1]) + 1 if words[0] == "s_nop" else 1
+            if words[0].startswith("v_smfmac_f32_16x16x"):
+                depth, sums = words[0].split("x")[2].split("_")[0], words[1]
+                if sums in last and last[sums][0] != depth:
+                    pairs += 1
+                    assert slot - last[sums][1] >= (12 if last[sums][0] == "64" else 8), f"{kernel} {line}"
+                last[sums] = depth, slot
+    assert pairs
