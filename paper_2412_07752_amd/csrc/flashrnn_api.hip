@@ -474,10 +474,19 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
 // 4 x 192 with 1 / 32 / 128 rows 8.6 / 8.5 / 9.9 and 4.1 / 6.5 / 13.4; 1 x 768 with 1 / 64 / 256 rows 30 / 31 / 46 and 6.9 / 17 / 54).
 bool make_step_plan(const flashrnn_desc_t* d, Plan* pl) {
     const KernelEntry* step = table_for(d->cell, d->io_dtype).step;
-    if (d->T != 1 || !step || env_int("FLASHRNN_KIND", -1) >= 0) return false;   // (a forced kernel family: tests)
+    if (d->T != 1 || !step || env_int("FLASHRNN_KIND", -1) >= 0 || env_int("FLASHRNN_STEP", 1) == 0) return false;   // (tests of the other kernels)
     const KernelEntry& e = step[d->B == 1 ? 0 : 1];
     const long long tiles = (d->B + e.BT - 1) / e.BT, grid = tiles * d->NH * (d->D / 16);
     if (d->B > 1 && tiles > (d->D <= 64 ? 0 : d->D <= 128 ? 4 : d->D <= 192 ? 8 : 16)) return false;
+    // (Every batch tile reads R once more, which the persistent kernels do not: with many heads or rows that is what a call takes.  sLSTM, us step / persistent, and
+    // MB that the tiles read: 64 x 80 with 4 / 16 rows 5.5 / 5.6 (3) and 9.7 / 6.0 (13); 24 x 192 with 4 / 32 rows 8.1 / 8.6 (7) and 23.0 / 11.1 (57); 24 x 256 with 8 / 16 / 32
+    // rows 14.1 / 21.8 (25), 26.1 / 29.3 (50) and 48.2 / 31.2 (101); 12 x 512 with 8 / 16 rows 23.6 / 31.8 (50) and 43.9 / 31.7 (101); 4 x 1024 with 8 / 32 / 64 rows 23.5 / 35.1
+    // (67), 79 / 35 (268) and 196 / 51 (537); one row 64 x 128 5.7 / 5.9 (8.4) and 96 x 128 10.3 / 6.0 (13).  Elman, whose persistent kernels have a gate's work only: 24 x 128 with
+    // 2 / 8 rows 3.3 / 3.5 (0.8) and 3.8 / 3.5 (1.6), 32 x 192 3.8 / 4.1 (2.4) and 4.4 / 4.3 (4.7), 24 x 384 with 8 / 12 rows 8.5 / 11.6 (14) and 12.2 / 11.5 (21).)
+    const double mb = (double)tiles * d->NH * num_gates(d->cell) * d->D * d->D * 2 / 1e6;
+    const int size = d->D <= 128 ? 0 : d->D <= 192 ? 1 : d->D <= 256 ? 2 : d->D <= 512 ? 3 : 4;
+    static const double most[3][5] = {{8.5, 9.5, 76, 76, 76}, {4.5, 7.5, 25.2, 50.4, 75.6}, {1.1, 2.5, 16, 18, 26}};   // one row; more; more, one gate
+    if (mb > most[d->B == 1 ? 0 : num_gates(d->cell) > 1 ? 1 : 2][size]) return false;
     if (grid > 1 << 20) return false;
     Plan s;
     s.e = &e;

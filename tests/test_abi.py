@@ -128,3 +128,16 @@ def test_forward_plans_of_the_slstm_with_many_groups(T, B, NH, D, mode, bt):
 @pytest.mark.parametrize("cell,D,bt", [(2, 128, 8), (4, 128, 8), (0, 128, 4), (2, 112, 4)])
 def test_backward_plans_of_float32_heads_of_128_units(cell, D, bt):
     assert api.flashrnn_plan_kernel(api.make_desc(cell, 48, 200, 8, D, api.FLASHRNN_F32), True) == (0, bt, 1)
+
+
+@pytest.mark.parametrize("cell,NH,D,B,step", [
+    # one-step calls: a kernel of their own, but where its batch tiles read R so often that the persistent kernels are faster
+    (2, 4, 192, 1, True), (2, 4, 192, 16, True), (2, 24, 192, 4, True), (2, 24, 192, 32, False), (2, 32, 192, 2, False), (0, 12, 512, 8, True), (0, 12, 512, 16, False),
+    (0, 4, 1024, 8, True), (2, 4, 1024, 64, False), (2, 64, 128, 1, True), (2, 96, 128, 1, False), (1, 64, 80, 2, True), (1, 64, 80, 16, False),
+    (3, 24, 128, 2, True), (3, 24, 128, 8, False), (3, 24, 384, 8, True), (3, 24, 384, 12, False), (3, 96, 64, 2, False),
+])
+def test_one_step_plans_of_many_heads_and_rows(cell, NH, D, B, step):
+    d = api.make_desc(cell, 1, B, NH, D, api.FLASHRNN_BF16)
+    for mode in (0, 2):
+        staged, rows, split = api.flashrnn_plan_kernel(d, mode)
+        assert (staged == 1 and split == D // 16 and rows == (1 if B == 1 else 4)) == step
