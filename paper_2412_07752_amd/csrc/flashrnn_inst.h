@@ -95,15 +95,18 @@ static const KernelEntry kEntries[] = {
     FRNN_SPLIT_SHAPES(16) FRNN_SPLIT_SHAPES(8) FRNN_SPLIT_SHAPES(4)
 #undef FRNN_SPLIT_SHAPES
 #endif
-    FRNN_SB(4, 4, 8, 1) FRNN_SB(4, 5, 8, 1) FRNN_SB(4, 4, 4, 1) FRNN_SB(4, 5, 4, 1) FRNN_SB(4, 6, 4, 1)
+    FRNN_SB(4, 5, 8, 1) FRNN_SB(4, 4, 4, 1) FRNN_SB(4, 5, 4, 1) FRNN_SB(4, 6, 4, 1)
 #define FRNN_SPLIT_SHAPES(BT) FRNN_SF(1, 2, 4, BT) FRNN_SF(1, 3, 4, BT) FRNN_SF(1, 4, 4, BT) \
-    FRNN_SF(2, 2, 4, BT) FRNN_SF(2, 3, 4, BT) FRNN_SF(2, 4, 4, BT) FRNN_SF(2, 4, 6, BT)
+    FRNN_SF(2, 3, 4, BT) FRNN_SF(2, 4, 4, BT) FRNN_SF(2, 4, 6, BT)
     FRNN_SPLIT_SHAPES(16) FRNN_SPLIT_SHAPES(8) FRNN_SPLIT_SHAPES(4)
-    FRNN_SF(2, 6, 6, 8) FRNN_SF(2, 6, 6, 4)
+    FRNN_SF(2, 2, 4, 4) FRNN_SF(2, 6, 6, 8) FRNN_SF(2, 6, 6, 4)
     // (four blocks per workgroup at 256 units only: with 192 registers of R, heads of 320 and 384 units, fwd_kernel is 5 to 30 % faster)
-    FRNN_SF(4, 2, 4, 8) FRNN_SF(4, 2, 4, 4)
+    FRNN_SF(4, 2, 4, 4)
 #undef FRNN_SPLIT_SHAPES
-    FRNN_SM(1, 3, 8) FRNN_SM(1, 4, 8) FRNN_SM(1, 3, 4) FRNN_SM(1, 4, 4)
+    FRNN_SM(1, 3, 8) FRNN_SM(1, 3, 4)
+#if FRNN_G > 1
+    FRNN_SM(1, 4, 8)
+#endif
     FRNN_SX(5, 4) FRNN_SX(6, 4) FRNN_SX(8, 4) FRNN_SX(5, 8) FRNN_SX(6, 8) FRNN_SX(8, 8)
     // heads of 1040 .. 2688 units: contraction lengths 1280, 1536, 2048, 2560, 2688.  Forward with all 16 rows of a
     // batch tile where the registers allow, backward (whose point-wise phase holds more values per row) with 8 or 4;
