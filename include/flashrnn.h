@@ -164,7 +164,9 @@ int flashrnn_bwd_recompute(const flashrnn_desc_t* desc, const void* Wx, const vo
  * Test hooks: with FLASHRNN_PLAN_OVERRIDES=1 in the environment when the library is first called, the variables
  * FLASHRNN_SPIN_LIMIT (a negative value makes every wait give up at once, which exercises this error path without
  * hanging anything), FLASHRNN_MULTI, _BT, _NWU, _KS, _GPAR, _EB, _DEEP_FETCH, _KIND (single choices of the launch planner,
- * to force every kernel family onto small shapes) and FLASHRNN_RECOMPUTE_STEPS (window length of flashrnn_bwd_recompute)
+ * to force every kernel family onto small shapes), FLASHRNN_SPLIT (0: split heads without the kernels that have wave roles, 2 / 3: a
+ * forward / backward plan that would take another kernel is refused), FLASHRNN_MESH (1: backward kernels with two hand-overs first),
+ * FLASHRNN_STEP (0: calls of one step as longer ones) and FLASHRNN_RECOMPUTE_STEPS (window length of flashrnn_bwd_recompute)
  * are read on every call; without it the environment is never read.
  */
 #define FLASHRNN_STATIC_SCRATCH ((const void*)(size_t)1)

@@ -418,7 +418,8 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             }
         }
     }
-    if (pl.e && pl.e->multi && bf && env_int("FLASHRNN_SPLIT", 1) != 0) take_split_kernel(d, bwd, tab, cus, &pl);
+    const int split_mode = env_int("FLASHRNN_SPLIT", 1);   // (test hook: 0 no kernels with wave roles, 2 nothing else forward, 3 nothing else backward)
+    if (pl.e && pl.e->multi && bf && split_mode != 0) take_split_kernel(d, bwd, tab, cus, &pl);
     if (!pl.e && force_multi != 0 && bf) {
         // Heads beyond what the CUs of one XCD can hold (D > 1024): the group is spread over the CUs of all XCDs, one
         // block of 16 units and 4 contraction slices per workgroup (one wave per SIMD, up to 336 registers of R each),
@@ -459,11 +460,11 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             pl.spread = 1;
         }
     }
-    if (pl.spread && env_int("FLASHRNN_SPLIT", 1) != 0) {
+    if (pl.spread && split_mode != 0) {
         if (bwd) take_split_kernel(d, bwd, tab, cus, &pl);
         else take_spread_fwd_kernel(d, tab, cus, &pl);
     }
-    if (!pl.e) return FLASHRNN_ERR_UNSUPPORTED;
+    if (!pl.e || (split_mode == (bwd ? 3 : 2) && !pl.e->ub)) return FLASHRNN_ERR_UNSUPPORTED;
     pl.rpack_bytes = pl.e->ub && bwd ? 0 : (bwd ? (size_t)d->NH * d->D * pl.DK : (size_t)d->NH * G * d->D * pl.DK) * io_size(d->io_dtype);
     *out = pl;
     return FLASHRNN_OK;
