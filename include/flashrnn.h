@@ -2,8 +2,9 @@
  * flashrnn.h -- C ABI of the MI355X (gfx950) FlashRNN time-step loop.
  *
  * One library, two compute entry points: flashrnn_fwd runs the strictly sequential, head-wise
- * block-diagonal recurrence for all T steps in one persistent kernel, flashrnn_bwd runs
- * back-propagation through time and the weight-gradient reduction.
+ * block-diagonal recurrence for all T steps in one persistent kernel (bf16 calls of one step, but for
+ * many rows or heads, on a kernel of their own), flashrnn_bwd runs back-propagation through time and the
+ * weight-gradient reduction.
  *
  * Conventions for every function below
  *   - All tensor pointers are DEVICE pointers owned by the caller; the library never allocates or
@@ -158,6 +159,9 @@ int flashrnn_bwd_recompute(const flashrnn_desc_t* desc, const void* Wx, const vo
  * forward / backward pair at the latest.  The forward call's word survives the backward call that follows it (a new
  * forward call clears both), so one check after the backward call sees a timeout of either.  flashrnn_bwd on a workspace
  * that no flashrnn_fwd call has used yet: zero its first 256 bytes first.
+ * The workgroups of a split head find each other by workgroup index: indices equal modulo 8 are taken to lie on one XCD, which is how the
+ * hardware deals them out; heads of more than 1024 units, whose members sit on all XCDs, rely on it too.  Where something places them
+ * otherwise the waits give up, and this call is what reports it.
  * Returns FLASHRNN_OK, FLASHRNN_ERR_TIMEOUT, or FLASHRNN_ERR_LAUNCH.  workspace may be NULL (returns OK) or
  * FLASHRNN_STATIC_SCRATCH (the array flashrnn_fwd_static_scratch works in, on the current device).  A shape whose plans
  * never wait across CUs (one workgroup per group) cannot time out: the call then only synchronizes the stream.
@@ -187,7 +191,9 @@ int flashrnn_plan(const flashrnn_desc_t* desc, int backward, int* workgroups, in
  * its inputs six steps ahead (backward pass of heads of up to 128 units whose inputs exceed the last-level cache; test
  * hook FLASHRNN_DEEP_FETCH = 1 / 0 allows it whatever the size of the inputs / forbids it, 2 takes it also where the planner's
  * rules on the number of workgroups exclude it), 0 for the kernels whose lanes access global memory themselves; *batch_tile = rows of a batch tile (16, 8 or 4); *split = workgroups per group
- * (> 1: the head is split over CUs that exchange h / dg every step).  Any out pointer may be NULL.
+ * (> 1: the head is split over CUs that exchange h, and gate gradients or partial sums of dh, every step; a call of one step on the
+ * kernel of its own reports *staged = 1, *batch_tile = 1 or 4 and a workgroup for every 16 units, which exchange nothing and never wait).
+ * Any out pointer may be NULL.
  */
 int flashrnn_plan_kernel(const flashrnn_desc_t* desc, int backward, int* staged, int* batch_tile, int* split);
 

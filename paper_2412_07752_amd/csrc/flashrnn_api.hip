@@ -732,8 +732,8 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     const int G = num_gates(d->cell), S = num_states(d->cell);
     const bool bf = d->io_dtype == FLASHRNN_BF16;
     const size_t esz = io_size(d->io_dtype);
-    // The backward copy of R is R itself, padded along (gate, unit) to the kernel's contraction length: without padding
-    // and without cross-CU waits (whose error word the packing kernel clears) the kernel reads R where it is.
+    // The backward copy of R is R itself, padded along (gate, unit) to the kernel's contraction length: without padding the kernel reads R where it
+    // is, and so do the kernels with wave roles, for whose waits the first fill clears the error word (the packing kernel does for the others that wait).
     const bool r_in_place = pb.e->ub || (!pb.e->multi && pb.DK == G * d->D);
     if (!r_in_place && launch_pack_r(bf, true, R, ws + w.rpack_off[1], d->NH, d->D, G, pb.DK, (int*)(ws + w.err_off) + 1, stream) != hipSuccess)
         return FLASHRNN_ERR_LAUNCH;

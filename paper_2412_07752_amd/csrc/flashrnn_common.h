@@ -506,7 +506,7 @@ __device__ __forceinline__ f32x4 smfmac(bf16x8 a, bf16x16 b, f32x4 c, int idx) {
     return c;
 #endif
 }
-// Where only 32 contraction elements are left (an odd number of 32-element blocks): the sparse instruction of that depth, in the staged kernels.  A
+// Where only 32 contraction elements are left (an odd number of 32-element blocks): the sparse instruction of that depth, in the staged and the split kernels.  A
 // lane of the first operand reads the four elements 8 q + 4 hf .. + 3 of its slot's row, the dense operand's lane holds
 // sparse_piece(8 q .. + 3, 8 q + 4 .. + 7).  (Filling a step of 64 with elements that meet weights of zero makes a NaN of an infinite h or dg, and takes
 // twice the registers for R.)

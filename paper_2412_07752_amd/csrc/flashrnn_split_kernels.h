@@ -1,4 +1,4 @@
-// Persistent kernels for heads split over the CUs of one XCD (bf16 I/O, heads of up to 1024 units).
+// Persistent kernels for heads split over the CUs of one XCD (bf16 I/O, heads of up to 1024 units), and for those spread over all XCDs (up to 2048 units).
 //
 // Backward: every member of a group keeps the gate gradients dg_t of its own units to itself and multiplies them with the columns of R
 // that belong to them: a partial dh_{t-1} of the WHOLE head.  What crosses the CUs are these partial sums (float32, added in a fixed
@@ -1012,7 +1012,7 @@ template <int CELL, int UB, int KTW, int NCW, int BT, bool SPREAD = false> struc
     // unit blocks of a ring row are rotated by the number of the row among those that one instruction reads
     static __host__ __device__ constexpr uint32_t rot(uint32_t row) { return BT == 16 ? row / 4 : row; }
     static constexpr int kUB = UB, kBT = BT;
-    // (spread: the units of an XCD's members are consecutive -- a cache line of h is written from one XCD)
+    // (spread: the units of an XCD's members are consecutive -- where D is a multiple of 512 every cache line of h is written from one XCD)
     static __device__ __forceinline__ uint32_t unit0(const KernelParams& p, uint32_t member) { return SPREAD ? ((member % 8) * (p.P / 8) + member / 8) * U : member * U; }
 };
 
