@@ -883,3 +883,42 @@ def test_split_heads_with_an_infinite_gradient(cell, NH, D, env, clip):
         # (a GRU's update gate has the sign of h_{t-1} - candidate, and the candidate is saved with eight bits: one unit in some hundred)
         assert np.count_nonzero(got[k][inf] != ref[k][inf]) <= (np.count_nonzero(inf) // 256 if cell == CELL_GRU else 0)
         assert np.isfinite(got[k][fin]).all() and np.abs(got[k][fin] - ref[k][fin]).max() <= pu.TOL_BF16_REL * np.abs(ref[k][fin]).max()
+
+
+SPLIT_KINDS = [(2, 256, 7, {}), (1, 640, 9, {}), (1, 1024, 5, {}), (1, 1280, 3, {}), (1, 2048, 9, {}), (1, 528, 3, {})]
+
+
+@pytest.mark.parametrize("cell", CELLS)
+@pytest.mark.parametrize("NH,D,B,env", SPLIT_KINDS)
+def test_empty_sequences_of_split_heads(cell, NH, D, B, env):
+    w = Workload(f"T0_{cell}_D{D}", cell, 0, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D)
+    gpu = _check(w, env, with_dlast=True)
+    assert np.all(gpu["dR"] == 0) and np.all(gpu["db"] == 0)
+
+
+@pytest.mark.parametrize("NH,D,B,env", SPLIT_KINDS + [(1, 256, 3, {"FLASHRNN_BT": "4"}), (1, 768, 17, {"FLASHRNN_BT": "16"})])
+def test_waits_that_give_up_are_reported_in_both_directions(NH, D, B, env):
+    """Every kind of split kernel with waits that give up at once: each direction ends, reports its own timeout, and the next calls are right again."""
+    os.environ.update(env)
+    w = Workload(f"giveup_D{D}", CELL_SLSTM, 5, B, NH, D, "bf16", True, bias="uniform0.1", init="uniform0.1", seed=D)
+    print(f"case {w.name}", flush=True)
+    inp = synth.make_inputs(w)
+    Wx, R, b, dH = (pu.to_device(inp[k], "bf16") for k in ("Wx", "R", "b", "dH"))
+    s0, desc = pu.to_device(inp["states0"], "f32"), api.make_desc(w.cell, w.T, B, NH, D, api.FLASHRNN_BF16)
+    states, cache, ws = api.flashrnn_fwd(w.cell, Wx, R, b, s0)
+    grads = api.flashrnn_bwd(w.cell, R, b, states, cache, dH, workspace=ws)
+    api.flashrnn_check(desc, ws)
+    for bwd in (False, True):
+        os.environ["FLASHRNN_SPIN_LIMIT"] = "-1"
+        if bwd:
+            api.flashrnn_bwd(w.cell, R, b, states, cache, dH, workspace=ws)
+        else:
+            api.flashrnn_fwd(w.cell, Wx, R, b, s0, workspace=ws)
+        os.environ["FLASHRNN_SPIN_LIMIT"] = "400000"
+        with pytest.raises(api.FlashRNNError) as ei:
+            api.flashrnn_check(desc, ws)
+        assert ei.value.status == api.FLASHRNN_ERR_TIMEOUT
+        again, cache2, _ = api.flashrnn_fwd(w.cell, Wx, R, b, s0, workspace=ws)
+        grads2 = api.flashrnn_bwd(w.cell, R, b, again, cache2, dH, workspace=ws)
+        api.flashrnn_check(desc, ws)
+        assert torch.equal(again, states) and all(torch.equal(x, y) for x, y in zip(grads, grads2))
