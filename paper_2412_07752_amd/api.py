@@ -215,11 +215,12 @@ def flashrnn_fwd_static_scratch(cell, Wx, R, b, states0=None, save_for_backward=
     """flashrnn_fwd without a workspace: the library works in its own static device array (no allocation in the call
     when `states` and `gate_cache` are passed in).  Returns (states, gate_cache or None)."""
     T, B, G, NH, D = Wx.shape
-    S = flashrnn_num_states(cell)
-    if G != flashrnn_num_gates(cell):
+    cell = int(cell)
+    S, gates = _cell_sizes(cell)
+    if G != gates:
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -241,11 +242,12 @@ def flashrnn_fwd(cell, Wx, R, b, states0=None, save_for_backward=True, workspace
     a slot of `states`.
     Returns (states[T+1,S,B,NH,D] f32, gate_cache or None, workspace)."""
     T, B, G, NH, D = Wx.shape
-    S = flashrnn_num_states(cell)
-    if G != flashrnn_num_gates(cell):
+    cell = int(cell)
+    S, gates = _cell_sizes(cell)
+    if G != gates:
         raise ValueError("gate axis of Wx does not match the cell")
     dt = Wx.dtype
-    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(Wx))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(Wx))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
@@ -271,9 +273,10 @@ def flashrnn_bwd(cell, R, b, states, gate_cache, dH, dstates_last=None, workspac
     dstates0[S,B,NH,D] f32).  `out` may pass preallocated (dWx, dR, db, dstates0).  recurrent_grad_clip as in
     flashrnn_desc_t: 0 off, c > 0 clips R^T dg_t to [-c, c] per step, negative cuts it."""
     T, B, NH, D = dH.shape
-    S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
+    cell = int(cell)
+    S, G = _cell_sizes(cell)
     dt = dH.dtype
-    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
     _chk(states, (T + 1, S, B, NH, D), torch.float32, "states")
@@ -302,9 +305,10 @@ def flashrnn_bwd_recompute(cell, Wx, R, b, states, dH, dstates_last=None, worksp
     results as flashrnn_bwd, with Wx[T,B,G,NH,D] in place of the gate cache; `workspace` needs
     flashrnn_recompute_workspace_bytes() bytes."""
     T, B, NH, D = dH.shape
-    S, G = flashrnn_num_states(cell), flashrnn_num_gates(cell)
+    cell = int(cell)
+    S, G = _cell_sizes(cell)
     dt = dH.dtype
-    desc = _desc_of(int(cell), T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
+    desc = _desc_of(cell, T, B, NH, D, _io_dtype(dH), float(recurrent_grad_clip))
     _chk(Wx, (T, B, G, NH, D), dt, "Wx")
     _chk(R, (NH, D, G, D), dt, "R")
     _chk(b, (NH, G, D), dt, "b")
