@@ -668,8 +668,8 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     // the exchange buffers start empty (a fill kernel, not a memset: the call may be captured into a graph);
     // both error words are cleared by the packing kernel
     if (pf.exch_bytes && launch_fill(ws + w.exch_off, align_up(pf.exch_bytes), kNoWord, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
-    // (the staged forward kernels read R as it is and clear the error words themselves)
-    const bool r_in_place = pf.e->tile != 0;
+    // (the staged forward kernels and the float32 kernels of 4-row tiles on one CU read R as it is and clear the error words themselves)
+    const bool r_in_place = pf.e->tile != 0 || (d->io_dtype == FLASHRNN_F32 && pf.e->BT == 4 && !pf.e->multi);
     if (!r_in_place && launch_pack_r(d->io_dtype == FLASHRNN_BF16, false, R, ws + w.rpack_off[0], d->NH, d->D, G, pf.DK, (int*)(ws + w.err_off), stream) != hipSuccess)
         return FLASHRNN_ERR_LAUNCH;
     KernelParams kp;

@@ -264,29 +264,58 @@ template <int BT> __device__ __forceinline__ void compact_tile(f32x4& a) {
     }
 }
 
-// Recurrent product of a 4-row batch tile in float32.  v_mfma_f32_16x16x4 would spend 32 clocks on a [16 x 4] x [4 x 16] product of
-// which four columns are rows of the tile.  v_mfma_f32_4x4x1 forms 16 independent [4 x 1] x [1 x 4] products in 8 clocks, all
-// of them used here: block b = lane / 4 takes units 4 (b / 4) .. + 3 of the wave and contraction slice b % 4, so that one
-// instruction still covers 16 units and 4 contraction steps.  (GRU 4 x 96, 12 rows: the step was 80 % matrix pipe;
-// forward 3.15 -> 1.19 us, backward 2.99 -> 0.92.  LSTM 1 x 64 forward 1.51 -> 0.96.)  The four slices of a unit quad meet across the lanes
-// of a row (sum_quad_slices), which also leaves lane (c, quad) with unit 4 quad + c / 4 of batch slot c % 4: the
-// places of compact_tile<4>.
-template <bool BF16, int BT> constexpr bool kQuadTiles = !BF16 && BT == 4;
-__device__ __forceinline__ f32x4 mfma_quads(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ float sum_quad_slices(const f32x4& a, int c) {
-    auto ror = [](float x, auto n) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + decltype(n)::value, 0xF, 0xF, false));
-    };
-    // lane bits 3 and 2 (the slice) select the unit that the lane ends up with: halve the register set twice
-    const bool hi = (c & 8) != 0, odd = (c & 4) != 0;
-    const float k0 = hi ? a[2] : a[0], k1 = hi ? a[3] : a[1], s0 = hi ? a[0] : a[2], s1 = hi ? a[1] : a[3];
-    const float f0 = k0 + ror(s0, std::integral_constant<int, 8>{}), f1 = k1 + ror(s1, std::integral_constant<int, 8>{});
-    // (an even slice takes from the lane 4 up, an odd one from the lane 4 down: rotations by 12 and by 4
-    // -- both with all lanes active, a lane outside the execution mask gives nothing)
-    const float up = f0 + ror(f0, std::integral_constant<int, 12>{}), down = f1 + ror(f1, std::integral_constant<int, 4>{});
-    return odd ? down : up;
+// y[i] of lane group g (16 lanes) becomes element g of lane group i
+__device__ __forceinline__ f32x4 transpose_quads(const float (&y)[4]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    auto bits = [](float v) { return __builtin_bit_cast(uint32_t, v); };
+    const u32x2 p02 = __builtin_amdgcn_permlane32_swap(bits(y[0]), bits(y[2]), false, false), p13 = __builtin_amdgcn_permlane32_swap(bits(y[1]), bits(y[3]), false, false);
+    const u32x2 q01 = __builtin_amdgcn_permlane16_swap(p02.x, p13.x, false, false), q23 = __builtin_amdgcn_permlane16_swap(p02.y, p13.y, false, false);
+    const uint32_t z0 = q01.x, z1 = q01.y, z2 = q23.x, z3 = q23.y;
+    return f32x4{__builtin_bit_cast(float, z0), __builtin_bit_cast(float, z1), __builtin_bit_cast(float, z2), __builtin_bit_cast(float, z3)};
+#else
+    return f32x4{y[0], y[1], y[2], y[3]};
+#endif
 }
 
+// Recurrent product of a 4-row batch tile in float32.  v_mfma_f32_16x16x4 would spend 32 clocks on a [16 x 4] x [4 x 16] product of
+// which four columns are rows of the tile.  v_mfma_f32_4x4x1 forms 16 independent [4 x 1] x [1 x 4] products in 8 clocks, all
+// of them used here: block b = lane / 4 takes units 4 (b % 4) .. + 3 of the wave and contraction quarter b / 4, so that one
+// instruction still covers 16 units and 4 contraction steps.  (GRU 4 x 96, 12 rows, against the wide instruction: forward 3.15 -> 1.19 us a step, backward 2.99 -> 0.92.)
+// The rows are the first operand, of which the instruction hands the values of one block to the four of its quarter: a lane reads KT / 4 values, consecutive in its row, instead
+// of KT -- with each lane reading its own four times the LDS was what bound the backward step.  Element m of block 4 g + a is contraction index
+// g KT + a KT / 4 + m.  The quarters of a unit meet after a transposition across the lane groups, which leaves lane (c, quad) with unit c of
+// row quad: the places after the sparse instruction (LaneMap).
+template <bool BF16, int BT> constexpr bool kQuadTiles = !BF16 && BT == 4;
+__device__ __forceinline__ f32x4 mfma_quads(int a, float rows, float r, f32x4 c) {   // block a of each quarter (known when compiled)
+    switch (a) {
+        case 0: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, r, c, 2, 0, 0);
+        case 1: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, r, c, 2, 1, 0);
+        case 2: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, r, c, 2, 2, 0);
+        default: return __builtin_amdgcn_mfma_f32_4x4x1f32(rows, r, c, 2, 3, 0);
+    }
+}
+__device__ __forceinline__ float sum_quad_slices(const f32x4& a) {
+    const float y[4] = {a[0], a[1], a[2], a[3]};
+    const f32x4 z = transpose_quads(y);
+    return (z[0] + z[1]) + (z[2] + z[3]);
+}
+
+// Forward, cells of four gates, heads on one CU: the 16 products of an instruction are the four gates of four unit quads at ONE contraction index.  The 4 rows of h are
+// the first operand, and the instruction hands the same four of them (lanes 4 b .. 4 b + 3 of it) to all 16 blocks: a register holds 16 contraction indices, four
+// registers all of a head of 64 units.  Lane (c, quad) accumulates gate quad of unit c, rows 0 .. 3 in the four registers: no slices to add up across the lanes, only
+// a 4 x 4 transposition of what is left.  (With three gates a quarter of
+// the blocks would be idle, with one three quarters.)
+template <int CELL, bool BF16, int BT, bool MULTI> constexpr bool kGateTiles = kQuadTiles<BF16, BT> && !MULTI && CellTraits<CELL>::G == 4;
+__device__ __forceinline__ f32x4 mfma_block_row(int b, float h, float r, f32x4 c) {   // (b: known when compiled)
+#define FRNN_ROW(I) case I: return __builtin_amdgcn_mfma_f32_4x4x1f32(h, r, c, 4, I, 0);
+    switch (b) {
+        FRNN_ROW(0) FRNN_ROW(1) FRNN_ROW(2) FRNN_ROW(3) FRNN_ROW(4) FRNN_ROW(5) FRNN_ROW(6) FRNN_ROW(7)
+        FRNN_ROW(8) FRNN_ROW(9) FRNN_ROW(10) FRNN_ROW(11) FRNN_ROW(12) FRNN_ROW(13) FRNN_ROW(14) FRNN_ROW(15)
+    }
+#undef FRNN_ROW
+    return c;
+}
 // The inverse of compact_tile (SPARSE: of sparse_pairs) for one value per pair: the lanes whose first unit is a multiple of four collect
 // that unit and the three behind it of their batch slot from the lanes that computed them (valid in those lanes only).
 template <int BT, int PP, bool SPARSE = false> __device__ __forceinline__ void expand_tile(const float (&v)[PP], float (&out)[4]) {

@@ -503,14 +503,75 @@ __device__ __forceinline__ void read_operand_lds(const char* row, int k0, int qu
     }
 }
 
-// one k-step of a tile product, and the tile's (unit, batch slot) pairs from its accumulators
-template <bool BF16, int BT> __device__ __forceinline__ f32x4 mfma_step(typename Operand<BF16>::type a, typename Operand<BF16>::type b, f32x4 c) {
-    if constexpr (kQuadTiles<BF16, BT>) return mfma_quads(a, b, c);
-    else return Operand<BF16>::mfma(a, b, c);
-}
-template <bool BF16, int BT> __device__ __forceinline__ void finish_tile(f32x4& a, int c) {
-    if constexpr (kQuadTiles<BF16, BT>) a[0] = sum_quad_slices(a, c);
+// the tile's (unit, batch slot) pairs from its accumulators
+template <bool BF16, int BT> __device__ __forceinline__ void finish_tile(f32x4& a) {
+    if constexpr (kQuadTiles<BF16, BT>) a[0] = sum_quad_slices(a);
     else compact_tile<BT>(a);
+}
+
+// Recurrent product of a 4-row tile on the 4 x 4 matrix instruction (kQuadTiles in flashrnn_common.h): rows of h or dg, `pitch` floats apart, times the KT elements
+// of R that each lane holds, for G output tiles, or for one whose four chains are left to the caller.
+template <int KT> __device__ __forceinline__ void read_quads(const char* rows, int pitch, int lane, float (&v)[KT / 4]) {
+    constexpr int NV = KT / 4, V = NV % 4 == 0 ? 4 : NV % 2 == 0 ? 2 : 1;
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const float* from = (const float*)rows + (lane & 3) * pitch + (lane >> 2) * NV;
+#pragma unroll
+    for (int j = 0; j < NV / V; ++j) {
+        const vec x = *(const vec*)(from + j * V);
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[j * V + i] = x[i];
+    }
+}
+template <int KT, int G, int NR> __device__ __forceinline__ void quad_product(const char* rows, int pitch, int lane, const float (&R)[G][NR], f32x4 (&acc)[G]) {
+    float v[KT / 4];
+    read_quads<KT>(rows, pitch, lane, v);
+#pragma unroll
+    for (int m = 0; m < KT / 4; ++m)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = mfma_quads(a, v[m], R[g][(a * (KT / 4) + m) % NR], acc[g]);
+}
+template <int KT, int NR, int NA> __device__ __forceinline__ void quad_product(const char* rows, int pitch, int lane, const float (&R)[NR], f32x4 (&acc)[NA]) {
+    static_assert(NA == 4 && NR == KT);
+    float v[KT / 4];
+    read_quads<KT>(rows, pitch, lane, v);
+#pragma unroll
+    for (int m = 0; m < KT / 4; ++m)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a] = mfma_quads(a, v[m], R[a * (KT / 4) + m], acc[a]);
+}
+
+// N elements of a column of R from byte offset off on, `step` bytes apart, zeros from the `valid`-th on.  (The offset runs along and eight loads go out at a time: left to itself
+// the compiler forms all addresses first and holds a register for each.)
+template <int N> __device__ __forceinline__ void load_column(rsrc_t r, uint32_t off, uint32_t step, int valid, float (&out)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        float v[1];
+        load_io_r<false, 1>(r, valid > 0 ? off : 0x80000000u, 0, v);
+        out[k] = v[0];
+        off += step;
+        --valid;
+        asm volatile("" : "+v"(off), "+v"(valid));
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+// All four gates of 16 units and 4 rows at once (gate tiles, kGateTiles in flashrnn_common.h): h[k][row] of the previous step in LDS, four chains over a quarter
+// of the contraction each, their sum, and a transposition across the lane groups: on return lane (c, quad) holds the four pre-activations of unit c, row quad.
+template <int KT, int NR> __device__ __forceinline__ f32x4 gate_product(const char* h_rows, int lane, const float (&Rg)[NR], float bias) {
+    static_assert(KT % 4 == 0 && NR == 4 * KT);
+    float h[KT / 4];   // lane (block b, row i): element 16 m + b
+#pragma unroll
+    for (int m = 0; m < KT / 4; ++m) h[m] = *(const float*)(h_rows + (64 * m + lane) * 4);
+    f32x4 a[4] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[s] = mfma_block_row((s * KT + kt) % 16, h[(s * KT + kt) / 16], Rg[s * KT + kt], a[s]);
+    float y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = ((a[0][i] + a[1][i]) + (a[2][i] + a[3][i])) + bias;   // (the bias last: a chain that begins with it rounds every sum to its size)
+    return transpose_quads(y);
 }
 
 template <bool BF16, int PP> __device__ __forceinline__ void write_operand_lds(char* row, int k, const float (&v)[PP]) {
@@ -587,7 +648,7 @@ __device__ __forceinline__ void reduce_pairs(float* red, int parity, int ks, int
 // =============================================================================================
 // CELL, BF16 (I/O dtype), KT k-steps per wave, KS contraction slices, BT valid batch slots per tile,
 // MULTI several workgroups per group, MAXW launch bound in waves.
-// p.R is the packed forward copy of R: Rt[n][g][e][k], k < DK = KT*KS*KSTEP, zero beyond D.
+// p.R is the packed forward copy of R: Rt[n][g][e][k], k < DK = KT*KS*KSTEP, zero beyond D (R_IN_PLACE: R as the caller has it).
 // The launch guarantees P * NWU * 16 == D and DK >= D (operand rows and packed R are zero beyond D).
 // Global addresses are formed as (uniform base advanced per step on the scalar unit) + (32-bit lane offset).
 template <bool BF16> constexpr int poll_chunk(int KT) {
@@ -611,25 +672,32 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     constexpr int HP = DK + operand_pad(BF16, SP);         // LDS row pitch in elements
     constexpr int BUF = BT * HP * ESZ;              // bytes of one LDS operand buffer
     constexpr int KC = poll_chunk<BF16>(KT);
+    constexpr bool GT = kGateTiles<CELL, BF16, BT, MULTI>, QT = kQuadTiles<BF16, BT>;
+    constexpr bool LM = SP || QT;                   // places of a lane's (unit, row) pairs: after the sparse instruction, of 4 x 4 blocks, or the others
+    // (float32, 4-row tiles on one CU: R is read where it is, 16 or 64 consecutive bytes at a time; a packing kernel in front is 4 us of the call.  Larger tiles, for whose
+    // calls that is little, have no registers for it to spare.)
+    constexpr bool R_IN_PLACE = kQuadTiles<BF16, BT> && !MULTI;
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
     static_assert(KS == 1 || SP || BT == 16, "the sums of contraction slices are those of 16-row tiles or of sparse pairs");
+    static_assert(!GT || EB == 1);
 
     extern __shared__ __align__(16) char smem[];
     const BlockMap bm(p, MULTI);
     if (!bm.active) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wu = w % p.NWU, ks = w / p.NWU;
+    if constexpr (R_IN_PLACE) {   // (no packing kernel has cleared the error words)
+        if (blockIdx.x == 0 && threadIdx.x == 0) { p.err[0] = 0; p.err[1] = 0; }
+    }
     stagger_waves(w);
-    const LaneMap<BT, SP> lm(lane);
+    const LaneMap<BT, LM> lm(lane);
     const SparseLane<BT == 8 ? 8 : 4> sl(lane);
     const int T = p.T, B = p.B, NH = p.NH, D = p.D;
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;  // first unit of this wave
     const int e0 = e_wave + lm.uoff;                    // first unit of this lane's pairs
     const int k0 = ks * KT * OP::KSTEP;
-    constexpr bool QT = kQuadTiles<BF16, BT>;
-    const int kq = QT ? lm.c >> 2 : lm.quad, arow = QT ? 4 * lm.quad + (lm.c & 3) : lm.c;   // contraction quarter, row of R that this lane holds
 
     char* hbuf = smem;                                          // !MULTI: [2][BT][HP] operand rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));            // MULTI: one operand buffer [BT][HP], then (KS > 1) the partial sums
@@ -637,7 +705,7 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     constexpr uint32_t XROW = DK * ESZ;                        // bytes per exchange row
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;     // this group's BT rows inside one buffer
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;        // bytes per buffer
-    const uint32_t xlane = exch_lane_off<BF16, BT, SP>(lm, XROW, e_wave);
+    const uint32_t xlane = exch_lane_off<BF16, BT, LM>(lm, XROW, e_wave);
     bool failed = false;
     const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)p.D * ESZ / 16, XROW, HP * ESZ);
     FRNN_TRACE_BEGIN();
@@ -653,28 +721,44 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
     // LDS lane offsets inside one operand buffer
     const uint32_t lds_rd = (uint32_t)lm.bslot * HP * ESZ;     // row this lane reads as the B operand column
     const uint32_t lds_wr = (uint32_t)lm.bslot * HP * ESZ;     // row this lane writes its new h into
+    auto leave_h = [&](int parity, int eb, const float (&h)[PP]) {   // this lane's h for the next step (gate tiles: h[k][row], else h[row][k])
+        if constexpr (GT) *(float*)(hbuf + parity * BUF + (e0 * 4 + lm.bslot) * 4) = h[0];
+        else write_operand_lds<BF16, PP>(hbuf + parity * BUF + lds_wr, e0 + 16 * eb, h);
+    };
 
     int iter = 0;
     for (int gid = bm.gpar; gid < p.NG; gid += p.GPAR, ++iter) {
         const int n = gid % NH, q = gid / NH;
         // ---- load once per group: R fragments (A operand: row = unit e_wave + c) and bias; they stay
         // in registers for all T steps
-        op_t Rf[EB][G][SP ? 1 : KT];
+        op_t Rf[EB][G][SP || GT ? 1 : KT];
         bf16x16 Rs[G][SP ? NKS : 1];
+        float Rg[GT ? DK : 1], bias_g = 0.0f;   // gate tiles: column (gate quad, unit c) of R, its bias
         float bias[EB][G][PP];
+        if constexpr (GT) {
+            load_column<DK>(make_rsrc((const float*)p.R + (size_t)n * D * G * D), (uint32_t)(lm.quad * D + e_wave + lm.c) * 4, (uint32_t)(G * D * 4), D, Rg);
+            bias_g = ((const float*)p.bias)[((size_t)n * G + lm.quad) * D + e_wave + lm.c];
+        }
 #pragma unroll
-        for (int eb = 0; eb < EB; ++eb)
+        for (int eb = 0; eb < (GT ? 0 : EB); ++eb)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const size_t rrow = (((size_t)n * G + g) * D + e_wave + 16 * eb + arow) * DK;
+            if constexpr (R_IN_PLACE) {
+                const int k = lm.quad * KT;
+                if constexpr (!BF16 && !GT)
+                    load_column<KT>(make_rsrc((const float*)p.R + (size_t)n * D * G * D), (uint32_t)((k * G + g) * D + e_wave + 16 * eb + lm.c) * 4, (uint32_t)(G * D * 4), D - k, Rf[eb][g]);
+                load_io<BF16, PP>(p.bias, ((size_t)n * G + g) * D + e0 + 16 * eb, bias[eb][g]);
+                continue;
+            }
+            const size_t rrow = (((size_t)n * G + g) * D + e_wave + 16 * eb + lm.c) * DK;
             if constexpr (SP) {
 #pragma unroll
                 for (int kc = 0; kc < NKS; ++kc) Rs[g][kc] = load_sparse_dense<KT>((const uint16_t*)p.R + rrow + k0, kc, lm.quad);
             }
 #pragma unroll
             for (int kt = 0; kt < (SP ? 0 : KT); ++kt) {
-                if constexpr (BF16) Rf[eb][g][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
-                else Rf[eb][g][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
+                if constexpr (BF16) Rf[eb][g][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0));
+                else Rf[eb][g][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0)];
             }
             load_io<BF16, PP>(p.bias, ((size_t)n * G + g) * D + e0 + 16 * eb, bias[eb][g]);
         }
@@ -714,12 +798,12 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
             for (int j = threadIdx.x; j < 2 * BUF / 4; j += blockDim.x) ((uint32_t*)hbuf)[j] = 0u;
             __syncthreads();
 #pragma unroll
-            for (int eb = 0; eb < EB; ++eb) write_operand_lds<BF16, PP>(hbuf + lds_wr, e0 + 16 * eb, st[eb][0]);
+            for (int eb = 0; eb < EB; ++eb) leave_h(0, eb, st[eb][0]);
             __syncthreads();
         } else {
             if (ks == 0 && T > 0) {
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T;
-                publish_tile<BF16, BT, PP, SP>(xr, xlane, (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
+                publish_tile<BF16, BT, PP, LM>(xr, xlane, (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
             }
         }
 
@@ -753,15 +837,21 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
 #pragma unroll
             for (int g = 0; g < G; ++g) accs[eb][g] = f32x4{0.f, 0.f, 0.f, 0.f};
             f32x4 (&acc)[G] = accs[0];
-            if constexpr (!MULTI) {
+            if constexpr (GT) {
+                const f32x4 y = gate_product<KT>(hbuf + ((t - 1) & 1) * BUF, lane, Rg, bias_g);
+#pragma unroll
+                for (int g = 0; g < G; ++g) accs[0][g][0] = y[g];
+            } else if constexpr (QT && !MULTI) {
+                quad_product<KT, G>(hbuf + ((t - 1) & 1) * BUF, HP, lane, Rf[0], acc);
+            } else if constexpr (!MULTI) {
                 op_t hB[KT];
-                read_operand_lds<BF16, KT>(hbuf + ((t - 1) & 1) * BUF + lds_rd, k0, kq, hB);
+                read_operand_lds<BF16, KT>(hbuf + ((t - 1) & 1) * BUF + lds_rd, k0, lm.quad, hB);
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int g = 0; g < G; ++g) accs[eb][g] = mfma_step<BF16, BT>(Rf[eb][g][kt], hB[kt], accs[eb][g]);
+                    for (int g = 0; g < G; ++g) accs[eb][g] = OP::mfma(Rf[eb][g][kt], hB[kt], accs[eb][g]);
             } else {
                 // h_{t-1} of the whole group: polled once per workgroup into LDS, then read like in the one-workgroup case
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(t - 1);
@@ -787,19 +877,20 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                                 if (kc + j < NKS) acc[g] = smfmac(hS[j], Rs[g][kc + j], acc[g], sl.idx);
                     }
                 }
+                if constexpr (QT) quad_product<KT, G>(hbuf, HP, lane, Rf[0], acc);
 #pragma unroll
-                for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
+                for (int kc = 0; kc < (SP || QT ? 0 : KT); kc += KC) {
                     op_t hB[KC];
                     if constexpr (BF16) {
                         lds_operand_chunk<KC>(hbuf + lds_rd + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, hB);
                     } else {
 #pragma unroll
-                        for (int j = 0; j < KC; ++j) hB[j] = *(const float*)(hbuf + lds_rd + (size_t)(k0 + kq * KT + kc + j) * 4);
+                        for (int j = 0; j < KC; ++j) hB[j] = *(const float*)(hbuf + lds_rd + (size_t)(k0 + lm.quad * KT + kc + j) * 4);
                     }
 #pragma unroll
                     for (int j = 0; j < KC; ++j)
 #pragma unroll
-                        for (int g = 0; g < G; ++g) acc[g] = mfma_step<BF16, BT>(Rf[0][g][kc + j], hB[j], acc[g]);
+                        for (int g = 0; g < G; ++g) acc[g] = OP::mfma(Rf[0][g][kc + j], hB[j], acc[g]);
                 }
             }
             if constexpr (SP) {
@@ -819,12 +910,12 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                 for (int eb = 0; eb < EB; ++eb) {
 #pragma unroll
                     for (int g = 0; g < G; ++g)
-                        if constexpr (!SP) finish_tile<BF16, BT>(accs[eb][g], lm.c);
+                        if constexpr (!SP && !GT) finish_tile<BF16, BT>(accs[eb][g]);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) {
                         float wxi[G], ybi[G], sti[S], cvi[NC];
 #pragma unroll
-                        for (int g = 0; g < G; ++g) { wxi[g] = wx[eb][g][i]; ybi[g] = accs[eb][g][i] + bias[eb][g][i]; }
+                        for (int g = 0; g < G; ++g) { wxi[g] = wx[eb][g][i]; ybi[g] = GT ? accs[eb][g][i] : accs[eb][g][i] + bias[eb][g][i]; }
 #pragma unroll
                         for (int s = 0; s < S; ++s) sti[s] = st[eb][s][i];
                         Cell<CELL, BF16>::fwd(wxi, ybi, sti, cvi);
@@ -837,13 +928,13 @@ __global__ __launch_bounds__(MAXW * 64) void fwd_kernel(const KernelParams p) {
                     }
                     // ---- hand the new h to the other waves as soon as it exists
                     if constexpr (!MULTI) {
-                        write_operand_lds<BF16, PP>(hbuf + (t & 1) * BUF + lds_wr, e0 + 16 * eb, st[eb][0]);
+                        leave_h(t & 1, eb, st[eb][0]);
                     } else {
                         // (the last step has nobody to hand its h to: its stores are issued all the same, out of range and dropped.
                         // Under a condition the compiler could no longer count this store among the memory operations behind the
                         // input prefetch, and the wait for the prefetched inputs below would wait for its acknowledgement as well.)
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)t;
-                        publish_tile<BF16, BT, PP, SP>(xr, xlane | (t < T ? 0u : 0x80000000u), (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
+                        publish_tile<BF16, BT, PP, LM>(xr, xlane | (t < T ? 0u : 0x80000000u), (cnt & 3u) * xbuf + xgroup, st[0][0], p.spread != 0);
                     }
                 }
                 if constexpr (MULTI) FRNN_TRACE_MARK(5);
@@ -906,6 +997,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     constexpr int HP = DK + operand_pad(BF16, SP);
     constexpr int BUF = BT * HP * ESZ;
     constexpr int KC = poll_chunk<BF16>(KT);
+    constexpr bool QT = kQuadTiles<BF16, BT>, LM = SP || QT;   // (as in the forward kernel)
     static_assert(KS == 1 || MULTI, "contraction slices are only used with several workgroups per group");
     static_assert(!MULTI || KT % KC == 0, "poll chunks must tile the k-steps");
     static_assert(EB == 1 || !MULTI, "several unit blocks per wave only with one workgroup per group");
@@ -917,14 +1009,12 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wu = w % p.NWU, ks = w / p.NWU;
     stagger_waves(w);
-    const LaneMap<BT, SP> lm(lane);
+    const LaneMap<BT, LM> lm(lane);
     const SparseLane<BT == 8 ? 8 : 4> sl(lane);
     const int T = p.T, B = p.B, NH = p.NH, D = p.D;
     const int e_wave = (bm.member * p.NWU + wu) * 16 * EB;
     const int e0 = e_wave + lm.uoff;
     const int k0 = ks * KT * OP::KSTEP;
-    constexpr bool QT = kQuadTiles<BF16, BT>;
-    const int kq = QT ? lm.c >> 2 : lm.quad, arow = QT ? 4 * lm.quad + (lm.c & 3) : lm.c;   // (as in the forward kernel)
 
     char* gbuf = smem;          // !MULTI: [2][BT][HP] gate-gradient rows
     float* red = (float*)(smem + (MULTI ? BUF : 0));  // MULTI: one operand buffer [16][HP], then (KS > 1) the partial sums
@@ -932,7 +1022,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
     constexpr uint32_t XROW = DK * ESZ;
     const uint32_t xgroup = (uint32_t)bm.gpar * BT * XROW;
     const uint32_t xbuf = (uint32_t)p.GPAR * BT * XROW;
-    const uint32_t xlane = exch_lane_off<BF16, BT, SP>(lm, XROW, e_wave);
+    const uint32_t xlane = exch_lane_off<BF16, BT, LM>(lm, XROW, e_wave);
     const Clearer<BF16, BT, G> clearer(threadIdx.x, (uint32_t)p.NWU, (uint32_t)D, (uint32_t)bm.member, XROW);
     bool failed = false;
     const Poller poller(MULTI ? threadIdx.x : 0u, MULTI ? blockDim.x : 64u, MULTI ? BT : 0, (uint32_t)(G * p.D) * ESZ / 16, XROW, HP * ESZ);
@@ -956,15 +1046,15 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
         bf16x16 Rs[SP ? NKS : 1];
 #pragma unroll
         for (int eb = 0; eb < EB; ++eb) {
-            const size_t rrow = ((size_t)n * D + e_wave + 16 * eb + arow) * DK;
+            const size_t rrow = ((size_t)n * D + e_wave + 16 * eb + lm.c) * DK;
             if constexpr (SP) {
 #pragma unroll
                 for (int kc = 0; kc < NKS; ++kc) Rs[kc] = load_sparse_dense<KT>((const uint16_t*)p.R + rrow + k0, kc, lm.quad);
             }
 #pragma unroll
             for (int kt = 0; kt < (SP ? 0 : KT); ++kt) {
-                if constexpr (BF16) Rf[eb][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, kq, 0));
-                else Rf[eb][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, kq, 0)];
+                if constexpr (BF16) Rf[eb][kt] = *(const bf16x8*)((const uint16_t*)p.R + rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0));
+                else Rf[eb][kt] = ((const float*)p.R)[rrow + k_index<BF16, KT>(k0, kt, lm.quad, 0)];
             }
         }
         const int bb_raw = q * BT + lm.bslot;
@@ -1042,7 +1132,9 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
         const char* dh_run = dh_g + (size_t)t_last * dh_step;
         char* dwx_run = dwx_g + (size_t)t_last * wx_step;       // dWx (and the GRU's candidate-gate gradient) of the current step
         char* dgn_run = dgn_g + (size_t)t_last * dh_step;
-        auto load_step = [&](int t, bool more, float (&cv_)[EB][NC][PP], float (&sc_)[EB][S][PP], float (&sp_)[EB][S][PP], float (&dh_)[EB][PP]) {
+        // (the states after a step are those before the one handled ahead of it: loaded once where there are registers to keep them)
+        constexpr bool kKeepStates = !BF16 && !MULTI;
+        auto load_step = [&](int t, bool more, bool after, float (&cv_)[EB][NC][PP], float (&sc_)[EB][S][PP], float (&sp_)[EB][S][PP], float (&dh_)[EB][PP]) {
             const rsrc_t c_t = make_rsrc(kRunning ? c_run : c_g + (size_t)(t - 1) * c_step);
             const rsrc_t st_p = make_rsrc(kRunning ? st_run : st_g + (size_t)(t - 1) * st_step);
             const rsrc_t dh_t = make_rsrc(kRunning ? dh_run : dh_g + (size_t)(t - 1) * dh_step);
@@ -1065,7 +1157,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             }
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                if (!cell_uses_h_prev(CELL) && s > 0 && s < 3) load_io_r<false, PP>(st_t, voff_st + eb * 64, s * st_state + st_after, sc_[eb][s]);
+                if (!cell_uses_h_prev(CELL) && s > 0 && s < 3 && after) load_io_r<false, PP>(st_t, voff_st + eb * 64, s * st_state + st_after, sc_[eb][s]);
                 else
 #pragma unroll
                     for (int i = 0; i < PP; ++i) sc_[eb][s][i] = 1.0f;
@@ -1077,7 +1169,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             load_io_r<BF16, PP>(dh_t, voff_dh + eb * 16 * ESZ, 0, dh_[eb]);
             }
         };
-        if ((KS == 1 || ks == 0) && T > 0) load_step(T, T > 1, cv, sc, sp, dh_ext);
+        if ((KS == 1 || ks == 0) && T > 0) load_step(T, T > 1, true, cv, sc, sp, dh_ext);
 
         FRNN_TRACE_RESET();
         for (int t = T; t >= 1; --t) {
@@ -1085,7 +1177,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             if (KS == 1 || ks == 0) {
                 // ---- prefetch the inputs of the next (earlier) step; they are pinned after the MFMA phase
                 // (with several workgroups per group they are issued behind the poll for dg_t: see the forward kernel)
-                if constexpr (!MULTI) load_step(t > 1 ? t - 1 : 1, t > 2, cvn, scn, spn, dhn);
+                if constexpr (!MULTI) load_step(t > 1 ? t - 1 : 1, t > 2, !kKeepStates, cvn, scn, spn, dhn);
                 // ---- point-wise Jacobians
                 const rsrc_t dwx_t = make_rsrc(kRunning ? dwx_run : dwx_g + (size_t)(t - 1) * wx_step);
 #pragma unroll
@@ -1115,7 +1207,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                         const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(T - t);
 #pragma unroll
                         for (int g2 = 0; g2 < G; ++g2)
-                            publish_tile<BF16, BT, PP, SP>(xr, xlane, (cnt & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, dg[g2], p.spread != 0);
+                            publish_tile<BF16, BT, PP, LM>(xr, xlane, (cnt & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, dg[g2], p.spread != 0);
                     }
                     if constexpr (!kOutRows) {
 #pragma unroll
@@ -1135,11 +1227,12 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             if constexpr (!MULTI) {
                 __syncthreads();
                 op_t gB[KT];
-                read_operand_lds<BF16, KT>(gbuf + (t & 1) * BUF + lds_row, k0, kq, gB);
+                if constexpr (!QT) read_operand_lds<BF16, KT>(gbuf + (t & 1) * BUF + lds_row, k0, lm.quad, gB);
+                else quad_product<KT>(gbuf + (t & 1) * BUF, HP, lane, Rf[0], a4[0]);
 #pragma unroll
-                for (int kt = 0; kt < KT; ++kt)
+                for (int kt = 0; kt < (QT ? 0 : KT); ++kt)
 #pragma unroll
-                    for (int eb = 0; eb < EB; ++eb) a4[eb][kt % NA] = mfma_step<BF16, BT>(Rf[eb][kt], gB[kt], a4[eb][kt % NA]);
+                    for (int eb = 0; eb < EB; ++eb) a4[eb][kt % NA] = OP::mfma(Rf[eb][kt], gB[kt], a4[eb][kt % NA]);
             } else {
                 // dg_t of the whole group: polled once per workgroup into LDS, then read like in the one-workgroup case
                 const uint32_t cnt = (uint32_t)iter * (uint32_t)T + (uint32_t)(T - t);
@@ -1156,7 +1249,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
 #pragma unroll
                     for (int g2 = 0; g2 < G; ++g2) clear_tile<BF16>(xr, xlane, ((cnt + 3u) & 3u) * xbuf + xgroup + (uint32_t)(g2 * D) * ESZ, p.spread != 0);
                 }
-                if (KS == 1 || ks == 0) load_step(t > 1 ? t - 1 : 1, t > 2, cvn, scn, spn, dhn);
+                if (KS == 1 || ks == 0) load_step(t > 1 ? t - 1 : 1, t > 2, !kKeepStates, cvn, scn, spn, dhn);
                 i32x4 out_v[NBO];
                 if constexpr (kOutRows) {
 #pragma unroll
@@ -1172,17 +1265,18 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
                             if (kc + j < NKS) a4[0][(kc + j) % NA] = smfmac(gS[j], Rs[kc + j], a4[0][(kc + j) % NA], sl.idx);
                     }
                 }
+                if constexpr (QT) quad_product<KT>(gbuf, HP, lane, Rf[0], a4[0]);
 #pragma unroll
-                for (int kc = 0; kc < (SP ? 0 : KT); kc += KC) {
+                for (int kc = 0; kc < (SP || QT ? 0 : KT); kc += KC) {
                     op_t gB[KC];
                     if constexpr (BF16) {
                         lds_operand_chunk<KC>(gbuf + lds_row + (size_t)(k0 + kc * 32 + lm.quad * 8) * 2, gB);
                     } else {
 #pragma unroll
-                        for (int j = 0; j < KC; ++j) gB[j] = *(const float*)(gbuf + lds_row + (size_t)(k0 + kq * KT + kc + j) * 4);
+                        for (int j = 0; j < KC; ++j) gB[j] = *(const float*)(gbuf + lds_row + (size_t)(k0 + lm.quad * KT + kc + j) * 4);
                     }
 #pragma unroll
-                    for (int j = 0; j < KC; ++j) a4[0][(kc + j) % NA] = mfma_step<BF16, BT>(Rf[0][kc + j], gB[j], a4[0][(kc + j) % NA]);
+                    for (int j = 0; j < KC; ++j) a4[0][(kc + j) % NA] = OP::mfma(Rf[0][kc + j], gB[j], a4[0][(kc + j) % NA]);
                 }
                 if constexpr (kOutRows) {
                     const rsrc_t dwx_rows = make_rsrc(kRunning ? dwx_run : dwx_g + (size_t)(t - 1) * wx_step);
@@ -1208,13 +1302,18 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
             if (KS == 1 || ks == 0) {
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb) {
-                    if constexpr (!SP) finish_tile<BF16, BT>(accs[eb][0], lm.c);
+                    if constexpr (!SP) finish_tile<BF16, BT>(accs[eb][0]);
 #pragma unroll
                     for (int i = 0; i < PP; ++i) ds[eb][0][i] += fminf(fmaxf(accs[eb][0][i], -p.clip), p.clip);   // (Sec. 4.1 clip; +inf = off)
                 }
                 // wait for the prefetched inputs here, where only this step's stores are younger
 #pragma unroll
-                for (int eb = 0; eb < EB; ++eb) { pin(cvn[eb]); pin(scn[eb]); pin(spn[eb]); pin(dhn[eb]); }
+                for (int eb = 0; eb < EB; ++eb) {
+                    pin(cvn[eb]);
+                    if constexpr (!kKeepStates) pin(scn[eb]);
+                    pin(spn[eb]);
+                    pin(dhn[eb]);
+                }
 #pragma unroll
                 for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
@@ -1222,7 +1321,7 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_kernel(const KernelParams p) {
 #pragma unroll
                     for (int c2 = 0; c2 < NC; ++c2) cv[eb][c2][i] = cvn[eb][c2][i];
 #pragma unroll
-                    for (int s = 0; s < S; ++s) { sc[eb][s][i] = scn[eb][s][i]; sp[eb][s][i] = spn[eb][s][i]; }
+                    for (int s = 0; s < S; ++s) { sc[eb][s][i] = kKeepStates ? sp[eb][s][i] : scn[eb][s][i]; sp[eb][s][i] = spn[eb][s][i]; }
                     dh_ext[eb][i] = dhn[eb][i];
                 }
             }
