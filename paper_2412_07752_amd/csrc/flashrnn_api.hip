@@ -287,15 +287,24 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
                 if (nw > 4 && (mode == 0 ? mb < 320 : nw <= 6 || mb < 300)) rel8 = 1.52;
                 else if (nw > 2 && nw <= 4 && mode == 0 && mb > 140 && mb < 320) rel8 = nw == 3 ? 1.38 : 1.33;
             }
-            // (float32: the 4-row kernels run on the 4 x 4 matrix instruction.  Two workgroups of 4 rows on a CU beat one of 8 -- LSTM 16 x 64
-            // with 128 rows 283 us per 64 steps against 349, GRU 8 x 96 with 256 rows 452 against 600 --, four of 4 rows lose to one of 16: LSTM
-            // 16 x 64 with 256 rows 565 against 522, Elman 16 x 128 438 against 391.  Of 128 units the backward passes of the sLSTM and the
-            // four-gate GRU are the exception: sLSTM 8 x 128 with 200 rows, 48 steps 389 us in two rounds of 4 rows and 368 in one of 8, four-gate GRU 348 and 334)
-            const bool two4 = bwd && d->D > 112 && (d->cell == FLASHRNN_SLSTM || d->cell == FLASHRNN_GRU4);
-            const double rel4 = bf ? 1.8 : two4 ? 1.55 : 1.45, rel16 = bf ? 6.0 : 5.5;
-            double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? rel4 : e.BT == 8 ? 3.0 : rel16);
+            // float32: the 4-row kernels, which waste nothing of the 4 x 4 matrix instruction, beat 8 rows everywhere (16 heads, 24 steps, 64 / 128 / 192 rows: LSTM of 64
+            // units forward 21 / 30 / 41 us in 4-row and 49 / 50 / 77 in 8-row tiles, backward 43 / 63 / 83 and 62 / 74 / 114; sLSTM of 128 units backward 91 / 188 / 276 and 167 / 220 / 369).
+            // Where workgroups share a CU -- up to four waves, or the few registers of one gate -- also one of 16 rows, up to eight to the CU (LSTM 16 x 32 with 256 rows
+            // forward 25 us and 41, 16 x 64 51 and 62, Elman 16 x 128 48 and 57); whole rounds of larger heads lose to it from four on (LSTM 16 x 96 with 256 rows
+            // 151 / 254 us and 143 / 240, 16 x 128 166 / 341 and 163 / 298), but for the sLSTM (16 x 96 179 / 256 and 194 / 283, 16 x 128 202 / 352 and 219 / 388).
+            double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? 1.8 : e.BT == 8 ? 3.0 : 6.0);
+            if (!bf) {
+                const bool shares = nw <= 4 || G == 1;
+                rounds = e.BT == 4 && G == 3 && !bwd && ng > cus ? per_cu : rounds;   // (two workgroups to a CU: the last round need not be a whole one)
+                rel = e.BT == 4 ? 1.0 : e.BT == 8 ? 2.9 : nw <= 2 ? 2.4 : nw <= 4 ? 2.8 : G == 1 ? (bwd ? 2.2 : 3.0) : d->cell == FLASHRNN_SLSTM ? 4.3 : 3.3;
+                if (e.BT == 4 && shares && ng > cus) {
+                    rounds = nw <= 2 ? 0.9 + 0.2 * per_cu : 0.9 + 0.35 * per_cu;
+                    const double full = bwd ? 0.75 * per_cu - 0.25 : 0.66 * per_cu;
+                    if (nw > 2 && G > 1 && rounds < full) rounds = full;
+                }
+            }
             if (e.tile == 0) rel *= 1.0 + 0.05 * (e.eb - 1);       // thin waves overlap better
-            rel *= 1.0 + 0.02 * (dk - kdim) / (double)kstep;       // padded k-steps are wasted MFMAs
+            rel *= bf ? 1.0 + 0.02 * (dk - kdim) / (double)kstep : 1.0 + 0.3 * (dk - kdim) / (double)dk;   // padded k-steps are wasted MFMAs
             if (exact_only) rel *= 0.99;                           // compile-time LDS layout: fewer address instructions
             if (e.exact >= 2) rel *= 0.9;                          // (only a candidate when the inputs come from HBM: -10 % there)
             const double cost = rounds * rel;
