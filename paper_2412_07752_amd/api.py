@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libflashrnn.so (the C ABI of include/flashrnn.h), same entry-point names.
+"""Thin binding over libflashrnn.so (the C ABI of include/flashrnn.h), same entry-point names: ctypes, and for plain forward calls a native module
+(csrc/flashrnn_binding.cpp) that makes the same checks.
 
 Argument marshalling only: torch supplies device memory and the current HIP stream, every step of
 the computation runs inside the library's kernels.  There is no fallback: if the library has not
@@ -22,6 +23,7 @@ STATIC_SCRATCH = "static"   # stands for FLASHRNN_STATIC_SCRATCH in flashrnn_che
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)),
                          "libflashrnn_trace.so" if os.environ.get("FLASHRNN_LIB") == "trace" else "libflashrnn.so")
 _lib = None
+_native = None   # the native module, bound to the loaded library
 
 
 class flashrnn_desc_t(ctypes.Structure):
@@ -41,7 +43,7 @@ def library_path():
 
 def lib():
     """The loaded C-ABI library; raises if it was not built."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2412_07752_amd.build` "
@@ -81,7 +83,13 @@ def lib():
         L.flashrnn_trace_phases.restype = ctypes.c_int
         L.flashrnn_status_string.argtypes = [ctypes.c_int]
         L.flashrnn_status_string.restype = ctypes.c_char_p
-        _lib = L
+        try:
+            from . import _flashrnn_binding as native
+        except ImportError:   # (built against another torch: every call goes through ctypes)
+            native = None
+        if native is not None:
+            native.bind(*(ctypes.cast(f, vp).value for f in (L.flashrnn_fwd, L.flashrnn_fwd_static_scratch, L.flashrnn_num_states, L.flashrnn_num_gates)))
+        _lib, _native = L, native
     return _lib
 
 
@@ -214,6 +222,12 @@ def alloc_workspace(desc, device):
 def flashrnn_fwd_static_scratch(cell, Wx, R, b, states0=None, save_for_backward=True, stream=None, states=None, gate_cache=None):
     """flashrnn_fwd without a workspace: the library works in its own static device array (no allocation in the call
     when `states` and `gate_cache` are passed in).  Returns (states, gate_cache or None)."""
+    if _native is not None and stream is None:
+        rc = _native.fwd(cell, Wx, R, b, states0, save_for_backward, None, states, gate_cache)
+        if rc == FLASHRNN_OK:
+            return states, (gate_cache if save_for_backward else None)
+        if rc < 0:
+            raise FlashRNNError(rc, "flashrnn_fwd_static_scratch")
     T, B, G, NH, D = Wx.shape
     cell = int(cell)
     S, gates = _cell_sizes(cell)
@@ -241,6 +255,12 @@ def flashrnn_fwd(cell, Wx, R, b, states0=None, save_for_backward=True, workspace
     """Forward pass.  Wx[T,B,G,NH,D], R[NH,D,G,D], b[NH,G,D] (bf16 or f32), states0[S,B,NH,D] f32 or None.  states0 may be
     a slot of `states`.
     Returns (states[T+1,S,B,NH,D] f32, gate_cache or None, workspace)."""
+    if _native is not None and stream is None and workspace is not None:
+        rc = _native.fwd(cell, Wx, R, b, states0, save_for_backward, workspace, states, gate_cache)
+        if rc == FLASHRNN_OK:
+            return states, (gate_cache if save_for_backward else None), workspace
+        if rc < 0:
+            raise FlashRNNError(rc, "flashrnn_fwd")
     T, B, G, NH, D = Wx.shape
     cell = int(cell)
     S, gates = _cell_sizes(cell)

@@ -1,4 +1,4 @@
-"""Build libflashrnn.so (HIP, gfx950) in-tree.  `python -m paper_2412_07752_amd.build [--force]`.
+"""Build libflashrnn.so (HIP, gfx950) and the Python binding's native part (g++) in-tree.  `python -m paper_2412_07752_amd.build [--force]`.
 
 Every translation unit is compiled with hipcc for gfx950 only, with the packed-FP32 VALU
 instructions disabled (compiler flag, device side).  Objects land in csrc/_build (git-ignored), the
@@ -38,6 +38,23 @@ def _compile(src, obj, extra=()):
     return log
 
 
+def build_binding(force=False):
+    """_flashrnn_binding.so: the native part of api.py's forward calls (host code, against the installed torch)."""
+    import sysconfig
+    import torch
+    root, src, out = os.path.dirname(torch.__file__), os.path.join(CSRC, "flashrnn_binding.cpp"), os.path.join(HERE, "_flashrnn_binding.so")
+    if not force and os.path.exists(out) and os.path.getmtime(out) >= max(os.path.getmtime(src), os.path.getmtime(os.path.join(INCLUDE, "flashrnn.h"))):
+        return out
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-I", sysconfig.get_paths()["include"], "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), src, "-o", out, "-L", os.path.join(root, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on flashrnn_binding.cpp:\n{r.stdout}")
+    return out
+
+
 def build(force=False, jobs=None, trace=False):
     """trace=True: the same sources with -DFLASHRNN_TRACE (per-phase clock stamps in the split-group kernels), as
     libflashrnn_trace.so; a measurement build, never what the tests or the benchmark's numbers run on."""
@@ -54,9 +71,11 @@ def build(force=False, jobs=None, trace=False):
             todo.append((src, obj))
     jobs = jobs or min(8, os.cpu_count() or 1)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(build_binding, force)
         for log in ex.map(lambda so: _compile(*so, extra=flags_extra), todo):
             if log.strip():
                 print(log)
+        binding.result()
     if todo or not os.path.exists(out):
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out])
     return out

@@ -60,3 +60,64 @@ def test_cells_given_as_arrays_or_tensors(library):
         api.flashrnn_fwd(c, Wx, R, b, save_for_backward=False, workspace=ws)
         api.flashrnn_fwd_static_scratch(c, Wx, R, b, save_for_backward=False)
         assert [s[1] for s in library.seen[-2:]] == [api.FLASHRNN_GRU] * 2
+
+
+def _call(T=1, B=2, cell=None, dev="cpu", dtype=torch.bfloat16):
+    cell = api.FLASHRNN_LSTM if cell is None else cell
+    G, S, NH, D = 4, 2, 1, 16
+    rng = torch.Generator().manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=rng).to(dtype).to(dev)
+    return dict(cell=cell, Wx=r(T, B, G, NH, D), R=r(NH, D, G, D), b=r(NH, G, D), states0=torch.randn((S, B, NH, D), generator=rng).to(dev),
+                save_for_backward=False, workspace=None, states=torch.zeros((T + 1, S, B, NH, D), device=dev), gate_cache=None)
+
+
+def test_native_calls_hand_back_what_is_not_plain():
+    """Nothing but device tensors proper is the native module's business; in particular it touches no host memory."""
+    api.lib()
+    if api._native is None:
+        pytest.skip("the native module was built against another torch")
+    a = _call()
+    assert api._native.fwd(*a.values()) == 1
+    for name, value in (("cell", 0.0), ("cell", np.int64(0)), ("cell", -1), ("cell", 99), ("Wx", None), ("Wx", np.zeros(3)), ("save_for_backward", 1), ("states", None)):
+        assert api._native.fwd(*dict(a, **{name: value}).values()) == 1
+    assert api._native.fwd(1, 2) == 1
+
+
+@pytest.mark.gpu
+def test_native_calls_and_calls_through_python_are_the_same(monkeypatch):
+    """The same buffers, results and refusals with and without the native module, for every argument that it hands back."""
+    api.lib()
+    assert api._native is not None
+    desc = api.make_desc(api.FLASHRNN_LSTM, 3, 2, 1, 16, api.FLASHRNN_BF16)
+    results = {}
+    for native in (True, False):
+        if not native:
+            monkeypatch.setattr(api, "_native", None)
+        a = _call(T=3, dev="cuda")
+        a.pop("workspace")
+        ws, cache = api.alloc_workspace(desc, "cuda"), torch.zeros(api.flashrnn_gate_cache_bytes(desc), dtype=torch.uint8, device="cuda")
+        out = []
+        for change in ({}, {"states0": None}, {"states": None}, {"save_for_backward": True}, {"save_for_backward": True, "gate_cache": cache},
+                       {"Wx": a["Wx"].transpose(0, 1).contiguous().transpose(0, 1)}, {"Wx": a["Wx"][:, :, :3].contiguous()}, {"R": a["R"].float()}, {"R": a["R"].cpu()},
+                       {"b": a["b"][:, :2]}, {"states0": a["states0"].bfloat16()}, {"states": a["states"][:2]}, {"cell": 7}, {"Wx": torch.nn.Parameter(a["Wx"])},
+                       {"R": a["R"].reshape(-1)[1:], }):
+            for kw in (dict(workspace=ws), dict()):
+                fn = api.flashrnn_fwd if kw else api.flashrnn_fwd_static_scratch
+                args = dict(a, **kw)
+                args.update(change)
+                if args.get("states") is not None:
+                    args["states"].zero_()
+                try:
+                    res = fn(**args)
+                    torch.cuda.synchronize()
+                    out.append([x.clone().cpu() if i < 2 and x is not None else x is None for i, x in enumerate(res)])
+                except Exception as e:
+                    out.append((type(e).__name__, str(e)))
+        results[native] = out
+    assert len(results[True]) == len(results[False])
+    for x, y in zip(results[True], results[False]):
+        assert type(x) is type(y)
+        if isinstance(x, tuple):
+            assert x == y
+        else:
+            assert all(torch.equal(p, q) if torch.is_tensor(p) else p == q for p, q in zip(x, y))
