@@ -17,6 +17,21 @@ __global__ __launch_bounds__(256) void step_kernel(const KernelParams p) {
     __shared__ float part[KS][COLS * 8 + 4][RB];   // (the threads' sums: slice, column)
     if (blockIdx.x == 0 && tid == 0) { p.err[0] = 0; p.err[1] = 0; }   // (as the packing kernel of the other plans)
 
+    // ---- what the point-wise function of this thread's (unit, row) pair needs is requested first: behind the contraction it would be a second round of memory latency
+    const uint32_t u = tid % 16, pr = tid / 16, b = b0 + pr, e = e0 + u;
+    const bool pair = tid < 16 * RB && b < B;
+    float st[S];
+    uint32_t wx_bits[G], b_bits[G];
+    if (pair) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) st[s] = p.states0 != nullptr ? p.states0[((size_t)s * B + b) * HD + n * D + e] : 0.0f;
+#pragma unroll
+        for (int g2 = 0; g2 < G; ++g2) {
+            wx_bits[g2] = ((const uint16_t*)p.Wx)[((size_t)b * G + g2) * HD + n * D + e];
+            b_bits[g2] = ((const uint16_t*)p.bias)[((size_t)n * G + g2) * D + e];
+        }
+    }
+
     const uint32_t ks = tid / COLS, col = tid % COLS, g = col / 2, half = col % 2;
     float acc[RB][8];
 #pragma unroll
@@ -72,22 +87,16 @@ __global__ __launch_bounds__(256) void step_kernel(const KernelParams p) {
         sums[sl][v] = a;
     }
     __syncthreads();
-    if (tid >= 16 * RB) return;
-    const uint32_t u = tid % 16, r = tid / 16, b = b0 + r, e = e0 + u;
-    if (b >= B) return;
-    float st[S], wx[G], yb[G], cv[NC];
+    if (!pair) return;
+    float wx[G], yb[G], cv[NC];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const size_t at = ((size_t)s * B + b) * HD + n * D + e;
-        st[s] = p.states0 != nullptr ? p.states0[at] : 0.0f;
-        p.states[at] = st[s];
-    }
+    for (int s = 0; s < S; ++s) p.states[((size_t)s * B + b) * HD + n * D + e] = st[s];
 #pragma unroll
     for (int g2 = 0; g2 < G; ++g2) {
-        wx[g2] = bf16_bits_to_f32(((const uint16_t*)p.Wx)[((size_t)b * G + g2) * HD + n * D + e]);
-        yb[g2] = bf16_bits_to_f32(((const uint16_t*)p.bias)[((size_t)n * G + g2) * D + e]);
+        wx[g2] = bf16_bits_to_f32(wx_bits[g2]);
+        yb[g2] = bf16_bits_to_f32(b_bits[g2]);
 #pragma unroll
-        for (int sl = 0; sl < NSL; ++sl) yb[g2] += sums[sl][(g2 * 16 + u) * RB + r];
+        for (int sl = 0; sl < NSL; ++sl) yb[g2] += sums[sl][(g2 * 16 + u) * RB + pr];
     }
     Cell<CELL, true>::fwd(wx, yb, st, cv);
 #pragma unroll
