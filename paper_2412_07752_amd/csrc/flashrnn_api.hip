@@ -698,14 +698,17 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
 }
 
 // Workspace of flashrnn_bwd_recompute behind the ordinary one: the records of one window of time steps and two buffers
-// for the state gradients carried from window to window.  The window holds as many steps as fit 64 MiB (at least one):
-// small enough to stay in the last-level cache between the kernel that writes it and the one that reads it.
+// for the state gradients carried from window to window.  Windows of equal length, at most 80 MiB of records each (at least one step):
+// small enough to stay in the last-level cache between the kernel that writes them and the one that reads them.  (Every window costs three launches and the
+// backward kernel's prologue, 20 us at 3 x 256: sLSTM 3 x 256, 16 rows, 1024 steps in windows of 341 steps had a fourth one of a single step.)
 struct RecomputeLayout { size_t window_off, carry_off, total; int window; };
 RecomputeLayout recompute_layout(const flashrnn_desc_t* d, size_t base_total) {
     RecomputeLayout rl;
     const size_t units = (size_t)d->B * d->NH * d->D;
     const size_t rec_step = units * record_slots(d->cell) * io_size(d->io_dtype);
-    long long steps = (long long)((64ull << 20) / (rec_step ? rec_step : 1));
+    const size_t whole = rec_step * (size_t)(d->T > 0 ? d->T : 1), limit = (size_t)80 << 20;
+    const long long windows = (long long)((whole + limit - 1) / limit);
+    long long steps = windows > 0 ? (d->T + windows - 1) / windows : 1;
     const int forced = env_int("FLASHRNN_RECOMPUTE_STEPS", 0);   // (test hook: windows of this many steps)
     if (forced > 0) steps = forced;
     if (steps < 1) steps = 1;
@@ -761,7 +764,7 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
             rp.states = (const float*)((const char*)states + (size_t)r0 * st_step);
             rp.cache = ws + rl.window_off; rp.steps = steps; rp.B = d->B; rp.NH = d->NH; rp.D = d->D;
             void* args[] = {&rp};
-            const dim3 grid((unsigned)((steps * d->B + kRecomputeCols - 1) / kRecomputeCols), (unsigned)((d->D + 63) / 64), (unsigned)d->NH);
+            const dim3 grid((unsigned)((steps * d->B + recompute_cols(bf) - 1) / recompute_cols(bf)), (unsigned)((d->D + 63) / 64), (unsigned)d->NH);
             if (hipLaunchKernel(table_for(d->cell, d->io_dtype).recompute, grid, dim3(256), args, 0, stream) != hipSuccess) return FLASHRNN_ERR_LAUNCH;
             cache = ws + rl.window_off;
         } else if (!recompute) {

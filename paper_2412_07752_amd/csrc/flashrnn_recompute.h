@@ -7,7 +7,7 @@
 // The persistent backward kernel then runs over the window as usual, with the gradients of the carried states handed
 // from window to window.
 //
-// Tile of one workgroup (4 waves): 64 units x all G gates x 128 columns (a column = one (step, batch row) pair); a wave owns
+// Tile of one workgroup (4 waves): 64 units x all G gates x 64 columns (f32: 128; a column = one (step, batch row) pair); a wave owns
 // 16 units and, like the forward kernel, all gates of them, so that its G accumulators of a column tile hold the G
 // pre-activations of a (unit, column) pair in the same lane and the point-wise function runs in registers.
 // R[n][d][g][e] has the contraction index d as its slow axis and the units contiguous: its tile goes to LDS as it is and
@@ -18,7 +18,11 @@
 
 namespace flashrnn {
 
-constexpr int kRecomputeCols = 128;   // columns (step, batch row) per workgroup
+// Columns (step, batch row) per workgroup.  The point-wise phase is bound by memory: half the columns of before, so that a window has twice the workgroups (128 columns
+// of 3 x 256, 341 steps of 16 rows: 516 workgroups, four more than fit the chip at once), and the next 16 columns' inputs and states on their way while the present ones are
+// worked on.  Backward with recompute, us, 128 columns without / with that / 64 columns / 32: sLSTM 3 x 256, 16 rows, 1024 steps 1223 / 1178 / 1125 / 1118, 16 x 48, 64 rows, 128 steps
+// 213 / 174 / 161 / 157, LSTM 6 x 112, 33 rows, 200 steps 187 / 186 / 170 / 174, 1 x 768, 40 rows, 200 steps 533 / 564 / 532 / 553 (R once more per workgroup).
+constexpr int recompute_cols(bool bf16) { return bf16 ? 64 : 128; }
 
 struct RecomputeParams {
     const void* Wx;        // [T,B,G,NH,D] io, already advanced to the window's first step
@@ -35,7 +39,7 @@ __global__ __launch_bounds__(256) void recompute_records_kernel(const RecomputeP
     using OP = Operand<BF16>;
     constexpr int G = CT::G, S = CT::S, NC = CT::NC, RS = CT::RS;
     constexpr int ESZ = BF16 ? 2 : 4;
-    constexpr int UB = 64, CB = kRecomputeCols, KR = 32;   // units, columns per workgroup; contraction rows per round
+    constexpr int UB = 64, CB = recompute_cols(BF16), KR = 32;   // units, columns per workgroup; contraction rows per round
     constexpr int NCT = CB / 16;                         // column tiles per wave
     constexpr int PR = G * UB + (BF16 ? 16 : 8);         // LDS row pitch of the R tile (elements): see the dR GEMM for the bf16 choice
     constexpr int PH = KR + (BF16 ? 8 : 4);              // LDS row pitch of the h tile (elements)
@@ -119,12 +123,69 @@ __global__ __launch_bounds__(256) void recompute_records_kernel(const RecomputeP
             else *(f32x4*)(ldsH(buf) + h_lds[x]) = hr[x];
         }
     };
+    const int ul = w * 16 + 4 * quad, e0 = u0 + ul;
+    // chunk roles of the three tiles (fixed per thread; the column advances by 16 per tile)
+    constexpr int CWX = UB * ESZ / 16, NWX = 16 * G * CWX, LWX = (NWX + 255) / 256;   // chunks per (column, gate) row
+    constexpr int CST = UB * 4 / 16, NST = 16 * S * CST, LST = (NST + 255) / 256;
+    constexpr int CRC = UB * REC / 16, NRC = 16 * CRC, LRC = (NRC + 255) / 256;
+    static_assert((UB * REC) % 16 == 0, "record rows are whole chunks");
+    const int adv_q = 16 / B, adv_r = 16 % B;
+    auto col_of = [&](int cc, int& r, int& b) { const int m = col0 + cc; r = m / B; b = m - r * B; };
+    int wx_cc[LWX], st_cc[LST], st_r[LST], st_b[LST], rc_cc[LRC];
+    uint32_t wx_in[LWX], wx_l[LWX], st_in[LST], st_l[LST], rc_in[LRC], rc_l[LRC];   // byte offset inside a column's row / in the tile
+    bool wx_u[LWX], st_u[LST], rc_u[LRC];                                          // the chunk's units exist
+#pragma unroll
+    for (int x = 0; x < LWX; ++x) {
+        const int ch = tid + x * 256, row = ch / CWX, part = ch % CWX, cc = row / G, g = row % G;
+        wx_cc[x] = cc;
+        wx_u[x] = ch < NWX && u0 + part * (16 / ESZ) < D;
+        wx_in[x] = (uint32_t)(((size_t)g * NH * D + u0) * ESZ) + part * 16;   // + ((m * G) * NH + n) * D * ESZ
+        wx_l[x] = cc * PWX + (g * UB) * ESZ + part * 16;
+    }
+#pragma unroll
+    for (int x = 0; x < LST; ++x) {
+        const int ch = tid + x * 256, row = ch / CST, part = ch % CST, cc = row / S, s2 = row % S;
+        st_cc[x] = cc;
+        col_of(cc, st_r[x], st_b[x]);
+        st_u[x] = ch < NST && u0 + part * 4 < D;
+        st_in[x] = (uint32_t)s2;                                              // state index; the address is formed per tile
+        st_l[x] = cc * PST + (s2 * UB) * 4 + part * 16;
+        st_in[x] |= (uint32_t)part << 8;
+    }
+#pragma unroll
+    for (int x = 0; x < LRC; ++x) {
+        const int ch = tid + x * 256, cc = ch / CRC, part = ch % CRC;
+        rc_cc[x] = cc;
+        rc_u[x] = ch < NRC && u0 + (part * 16) / (int)REC < D;
+        rc_in[x] = part * 16;
+        rc_l[x] = cc * PRC + part * 16;
+    }
+    // inputs and states of the next 16 columns on their way: requested while those before them (for the first: the last round of the contraction) are worked on
+    i32x4 wx_r[LWX], st_v[LST];
+    auto load_stage = [&](int mbase) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < LWX; ++x) {
+            const int m = mbase + wx_cc[x];
+            wx_r[x] = i32x4{0, 0, 0, 0};
+            if (wx_u[x] && m < ncols) wx_r[x] = *(const i32x4*)((const char*)p.Wx + (((size_t)m * G) * NH + n) * D * ESZ + wx_in[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < LST; ++x) {
+            const int m = mbase + st_cc[x], s2 = (int)(st_in[x] & 0xFF), part = (int)(st_in[x] >> 8);
+            st_v[x] = i32x4{0, 0, 0, 0};
+            if (st_u[x] && m < ncols)
+                st_v[x] = *(const i32x4*)(p.states + (((size_t)st_r[x] * S + s2) * B + st_b[x]) * HD + (size_t)n * D + u0 + part * 4);
+            st_b[x] += adv_r; st_r[x] += adv_q;                                // the next tile's column: 16 further
+            if (st_b[x] >= B) { st_b[x] -= B; st_r[x] += 1; }
+        }
+    };
     load_round(0);
     int buf = 0;
     for (int kb = 0; kb < D; kb += KR, buf ^= 1) {
         park_round(buf);   // (the buffer was last read two rounds ago: the barrier of the round before lies in between)
         __syncthreads();
         if (kb + KR < D) load_round(kb + KR);
+        else load_stage(col0);
         if (u0 + w * 16 < D) {   // (a wave beyond the head's units only helps loading)
             if constexpr (BF16) {
                 // quad q's 8 contraction elements of a round: rows 4q..4q+3 and 16+4q..16+4q+3, in both operands
@@ -174,70 +235,23 @@ __global__ __launch_bounds__(256) void recompute_records_kernel(const RecomputeP
     char* const wx_t = lds_all;
     char* const st_t = lds_all + 16 * PWX;
     char* const rc_t = st_t + 16 * PST;
-    const int ul = w * 16 + 4 * quad, e0 = u0 + ul;
     float bias[G][4];
     if (e0 < D) {
 #pragma unroll
         for (int g = 0; g < G; ++g) load_io<BF16, 4>(p.bias, ((size_t)n * G + g) * D + e0, bias[g]);
-    }
-    // chunk roles of the three tiles (fixed per thread; the column advances by 16 per tile)
-    constexpr int CWX = UB * ESZ / 16, NWX = 16 * G * CWX, LWX = (NWX + 255) / 256;   // chunks per (column, gate) row
-    constexpr int CST = UB * 4 / 16, NST = 16 * S * CST, LST = (NST + 255) / 256;
-    constexpr int CRC = UB * REC / 16, NRC = 16 * CRC, LRC = (NRC + 255) / 256;
-    static_assert((UB * REC) % 16 == 0, "record rows are whole chunks");
-    const int adv_q = 16 / B, adv_r = 16 % B;
-    auto col_of = [&](int cc, int& r, int& b) { const int m = col0 + cc; r = m / B; b = m - r * B; };
-    int wx_cc[LWX], st_cc[LST], st_r[LST], st_b[LST], rc_cc[LRC];
-    uint32_t wx_in[LWX], wx_l[LWX], st_in[LST], st_l[LST], rc_in[LRC], rc_l[LRC];   // byte offset inside a column's row / in the tile
-    bool wx_u[LWX], st_u[LST], rc_u[LRC];                                          // the chunk's units exist
-#pragma unroll
-    for (int x = 0; x < LWX; ++x) {
-        const int ch = tid + x * 256, row = ch / CWX, part = ch % CWX, cc = row / G, g = row % G;
-        wx_cc[x] = cc;
-        wx_u[x] = ch < NWX && u0 + part * (16 / ESZ) < D;
-        wx_in[x] = (uint32_t)(((size_t)g * NH * D + u0) * ESZ) + part * 16;   // + ((m * G) * NH + n) * D * ESZ
-        wx_l[x] = cc * PWX + (g * UB) * ESZ + part * 16;
-    }
-#pragma unroll
-    for (int x = 0; x < LST; ++x) {
-        const int ch = tid + x * 256, row = ch / CST, part = ch % CST, cc = row / S, s2 = row % S;
-        st_cc[x] = cc;
-        col_of(cc, st_r[x], st_b[x]);
-        st_u[x] = ch < NST && u0 + part * 4 < D;
-        st_in[x] = (uint32_t)s2;                                              // state index; the address is formed per tile
-        st_l[x] = cc * PST + (s2 * UB) * 4 + part * 16;
-        st_in[x] |= (uint32_t)part << 8;
-    }
-#pragma unroll
-    for (int x = 0; x < LRC; ++x) {
-        const int ch = tid + x * 256, cc = ch / CRC, part = ch % CRC;
-        rc_cc[x] = cc;
-        rc_u[x] = ch < NRC && u0 + (part * 16) / (int)REC < D;
-        rc_in[x] = part * 16;
-        rc_l[x] = cc * PRC + part * 16;
     }
 #pragma unroll
     for (int j = 0; j < NCT; ++j) {
         const int mbase = col0 + j * 16;
         // ---- inputs and states of the 16 columns into their tiles
 #pragma unroll
-        for (int x = 0; x < LWX; ++x) {
-            const int m = mbase + wx_cc[x];
-            i32x4 v = i32x4{0, 0, 0, 0};
-            if (wx_u[x] && m < ncols) v = *(const i32x4*)((const char*)p.Wx + (((size_t)m * G) * NH + n) * D * ESZ + wx_in[x]);
-            if (tid + x * 256 < NWX) *(i32x4*)(wx_t + wx_l[x]) = v;
-        }
+        for (int x = 0; x < LWX; ++x)
+            if (tid + x * 256 < NWX) *(i32x4*)(wx_t + wx_l[x]) = wx_r[x];
 #pragma unroll
-        for (int x = 0; x < LST; ++x) {
-            const int m = mbase + st_cc[x], s2 = (int)(st_in[x] & 0xFF), part = (int)(st_in[x] >> 8);
-            i32x4 v = i32x4{0, 0, 0, 0};
-            if (st_u[x] && m < ncols)
-                v = *(const i32x4*)(p.states + (((size_t)st_r[x] * S + s2) * B + st_b[x]) * HD + (size_t)n * D + u0 + part * 4);
-            if (tid + x * 256 < NST) *(i32x4*)(st_t + st_l[x]) = v;
-            st_b[x] += adv_r; st_r[x] += adv_q;                                // the next tile's column: 16 further
-            if (st_b[x] >= B) { st_b[x] -= B; st_r[x] += 1; }
-        }
+        for (int x = 0; x < LST; ++x)
+            if (tid + x * 256 < NST) *(i32x4*)(st_t + st_l[x]) = st_v[x];
         __syncthreads();
+        if (j + 1 < NCT) load_stage(mbase + 16);
         // ---- this lane's four (unit, column) pairs
         if (e0 < D) {
             float wx[G][4], st[S][4];
