@@ -379,6 +379,129 @@ __global__ __launch_bounds__(WM * WN * 64) void dr_gemm_tr_kernel(const float* _
         }
 }
 
+// The 256 x 256 tile (eight waves of 64 x 128) with TWO rounds of global loads in flight.  A round is 1024 clocks of matrix instructions per SIMD and about as much LDS time, a load from HBM
+// takes twice that: with one round in flight (dr_gemm_tr_kernel, whose addresses take the registers of a second one) a round was 2800 clocks, the latency.  Here a load's row
+// is the same for a whole wave (h: one row of 256 floats per wave and load) or its place in the round does not change (gate gradients), so addresses live in scalar registers: buffer loads from
+// bases that move on by a round, out of range -- zeros -- beyond the slice, the head or the gates.  Not for the GRU, whose gate gradients come from two tensors.
+// (Backward call with one / two rounds in flight / these issued first, us: LSTM 1 x 768, 128 rows, 256 steps 1055 / 1025 / 1009, of which the GEMM 204 -> 158; sLSTM 8 x 256, 32 rows, 512 steps 593 / 587 / 574,
+// GEMM 98 -> 79; LSTM 1 x 2048, 16 rows, 256 steps 878 / 859 / 847, GEMM 170 -> 139: 0.97 PFLOP/s.)
+__global__ __launch_bounds__(512) void dr_gemm_square_kernel(const float* __restrict__ states, const uint16_t* __restrict__ dWx, float* __restrict__ out, int T, int B, int NH, int D, int G,
+                                                             int S, int SK) {
+    constexpr int FM = 4, FN = 8, WN = 2, TW = 256, PITCH = TW + 16, LA = 4, LB = 2;
+    constexpr uint32_t kDrop = 0x80000000u;
+    __shared__ __align__(16) uint16_t ldsA[2][TK * PITCH], ldsB[2][TK * PITCH];
+    const int GD = G * D;
+    const int tiles_n = (GD + TW - 1) / TW, tiles_m = (D + TW - 1) / TW;
+    int sk, n, tile;
+    if (!tile_of_block(tiles_n * tiles_m, SK, NH, false, sk, n, tile)) return;
+    const int tn = tile % tiles_n, tm = tile / tiles_n;
+    const int K = T * B, kchunk = ((K + SK - 1) / SK + TK - 1) / TK * TK;
+    const int kbeg = sk * kchunk, kend = min(K, kbeg + kchunk);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, quad = lane >> 4, wm = w / WN, wn = w % WN;
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // ---- h: load x of wave w is row w + 8 x of a round, four floats per lane.  Row k = (tt, bb) lies at (tt S B + bb) HD.
+    const size_t HD = (size_t)NH * D;
+    const int adv_q = TK / B, adv_r = TK % B;
+    const size_t inc0 = (size_t)TK * HD + (size_t)adv_q * (size_t)(S - 1) * B * HD, inc1 = inc0 + (size_t)(S - 1) * B * HD;
+    const uint32_t a_voff = tm * TW + lane * 4 < D ? (uint32_t)lane * 16 : kDrop;
+    const float* a_ptr[LA];
+    int a_bb[LA];
+#pragma unroll
+    for (int x = 0; x < LA; ++x) {
+        const int k = kbeg + w + 8 * x, tt = k / B;
+        a_bb[x] = k - tt * B;
+        a_ptr[x] = states + ((size_t)tt * S * B + a_bb[x]) * HD + (size_t)n * D + tm * TW;
+    }
+    // ---- gate gradients: load x of a thread is row tid / 32 + 16 x of a round, eight columns
+    const uint32_t b_row = tid / 32, b_stride = (uint32_t)GD * NH * 2;   // bytes between contraction rows
+    const int b_col = tn * TW + (tid % 32) * 8;
+    const uint32_t b_voff = b_col < GD ? b_row * b_stride + (uint32_t)((b_col / D * NH + n) * D + b_col % D) * 2 : kDrop;
+    const char* b_ptr = (const char*)dWx + (size_t)kbeg * b_stride;
+    f32x4 ra[2][LA];
+    i32x4 rb[2][LB];
+    int kround = kbeg;
+    auto resource = [](const void* p, bool in) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, in ? 0x7FFFFFFF : 0, 0x00020000); };
+    auto load_tiles = [&](auto set_c) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_c)::value;
+#pragma unroll
+        for (int x = 0; x < LA; ++x) {
+            const bool in = kround + w + 8 * x < kend;
+            ra[SET][x] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(resource(in ? a_ptr[x] : states, in), a_voff, 0, 0));
+            const int bb = a_bb[x] + adv_r;
+            const bool wrap = bb >= B;
+            a_bb[x] = wrap ? bb - B : bb;
+            a_ptr[x] += wrap ? inc1 : inc0;
+        }
+        const auto rs = resource(kround < kend ? b_ptr : (const char*)dWx, kround < kend);
+#pragma unroll
+        for (int x = 0; x < LB; ++x)
+            rb[SET][x] = __builtin_amdgcn_raw_buffer_load_b128(rs, kround + (int)b_row + 16 * x < kend ? b_voff + 16 * x * b_stride : kDrop, 0, 0);
+        b_ptr += (size_t)TK * b_stride;
+        kround += TK;
+    };
+    auto park_tiles = [&](auto set_c, int buf) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_c)::value;
+#pragma unroll
+        for (int x = 0; x < LA; ++x)
+            *(i32x2*)(&ldsA[buf][(w + 8 * x) * PITCH + lane * 4]) =
+                i32x2{(int)pack_bf16x2(ra[SET][x][0], ra[SET][x][1]), (int)pack_bf16x2(ra[SET][x][2], ra[SET][x][3])};
+#pragma unroll
+        for (int x = 0; x < LB; ++x) *(i32x4*)(&ldsB[buf][(b_row + 16 * x) * PITCH + (tid % 32) * 8]) = rb[SET][x];
+    };
+    // (the transposing operand reads are those of dr_gemm_tr_kernel)
+    const int tr = (4 * quad + (c >> 2)) * PITCH + 4 * (c & 3);
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    auto operand = [&](const uint16_t* tile, int col0) __attribute__((always_inline)) -> bf16x8 {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + tr + col0));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + tr + 16 * PITCH + col0));
+        return __builtin_bit_cast(bf16x8, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    };
+    using set0 = std::integral_constant<int, 0>;
+    using set1 = std::integral_constant<int, 1>;
+    auto round = [&](auto set_c, int buf) __attribute__((always_inline)) {
+        park_tiles(set_c, buf);       // (the buffer was last read two rounds ago: the barrier of the previous round lies in between)
+        __syncthreads();
+        load_tiles(set_c);
+        __builtin_amdgcn_sched_barrier(0);   // (the loads first: left alone the compiler issues them behind most of the products, and half of their lead is gone)
+        bf16x8 af[FM];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) af[i] = operand(ldsA[buf], (wm * FM + i) * 16);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const bf16x8 b = operand(ldsB[buf], (wn * FN + j) * 16);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], b, acc[i][j], 0, 0, 0);
+        }
+    };
+    load_tiles(set0{});
+    load_tiles(set1{});
+    for (int kb = kbeg; kb < kend; kb += 2 * TK) {   // (an odd last round is one of zeros)
+        round(set0{}, 0);
+        round(set1{}, 1);
+    }
+    float* dst = out + ((size_t)sk * NH + n) * (size_t)D * GD;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int col = tn * TW + (wn * FN + j) * 16 + c;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = tm * TW + (wm * FM + i) * 16 + quad * 4 + r;
+                if (row < D && col < GD) dst[(size_t)row * GD + col] = acc[i][j][r];
+            }
+        }
+}
+
 // out[j] = sum_{s < NS} part[s * stride + j], added in index order
 __global__ void sum_slices_kernel(const float* __restrict__ part, float* __restrict__ out, size_t count, int NS, size_t stride) {
     const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -535,7 +658,9 @@ hipError_t launch_dr_gemm(bool bf16, const float* states, const void* dWx, const
     const DrTile t = dr_tile(bf16, NH, D, G);
     const int grid = (dr_tiles(t, NH, D, G) * SK + 7) / 8 * 8;
     if (db_from_gemm && (!bf16 || t == kDrSquare)) return hipErrorInvalidValue;
-    if (t == kDrSquare)
+    if (t == kDrSquare && !gru)
+        hipLaunchKernelGGL(dr_gemm_square_kernel, dim3(grid), dim3(512), 0, stream, states, (const uint16_t*)dWx, target, T, B, NH, D, G, S, SK);
+    else if (t == kDrSquare)
         hipLaunchKernelGGL((dr_gemm_tr_kernel<4, 8, 4, 2, false, 1>), dim3(grid), dim3(512), 0, stream, states, dWx, dgn, target, db_part, T, B, NH, D, G, S, SK, gru ? 1 : 0);
     else if (t == kDrWide && db_from_gemm)
         hipLaunchKernelGGL((dr_gemm_tr_kernel<4, 4, 2, 4, true, 2>), dim3(grid), dim3(512), 0, stream, states, dWx, dgn, target, db_part, T, B, NH, D, G, S, SK, gru ? 1 : 0);
