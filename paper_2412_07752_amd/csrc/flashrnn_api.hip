@@ -745,8 +745,8 @@ int bwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
     const bool bf = d->io_dtype == FLASHRNN_BF16;
     const size_t esz = io_size(d->io_dtype);
     // The backward copy of R is R itself, padded along (gate, unit) to the kernel's contraction length: without padding the kernel reads R where it
-    // is, and so do the kernels with wave roles, for whose waits the first fill clears the error word (the packing kernel does for the others that wait).
-    const bool r_in_place = pb.e->ub || (!pb.e->multi && pb.DK == G * d->D);
+    // is, and so do the staged kernels and those with wave roles, for whose waits the first fill clears the error word (the packing kernel does for the others that wait).
+    const bool r_in_place = pb.e->ub || pb.e->tile || (!pb.e->multi && pb.DK == G * d->D);
     if (!r_in_place && launch_pack_r(bf, true, R, ws + w.rpack_off[1], d->NH, d->D, G, pb.DK, (int*)(ws + w.err_off) + 1, stream) != hipSuccess)
         return FLASHRNN_ERR_LAUNCH;
     const size_t units = (size_t)d->B * d->NH * d->D;

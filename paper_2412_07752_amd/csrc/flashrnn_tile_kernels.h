@@ -569,13 +569,26 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
     bf16x16 Rf[NF > 0 ? NF : 1];
     i32x4 Rh;   // (KT odd)
     {
-        const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK + sparse_k(lm.quad);
         i32x4 piece[NF > 0 ? 2 * NF : 1];
+        if constexpr (EXACT) {
+            const uint16_t* rrow = (const uint16_t*)p.R + ((size_t)n * D + w * 16 + lm.c) * DK + sparse_k(lm.quad);
 #pragma unroll
-        for (int kt = 0; kt < 2 * NF; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32), *(const i32x2*)(rrow + kt * 32 + 8));
-        if constexpr (KT & 1) {
-            const i32x4 v = *(const i32x4*)(rrow + 2 * NF * 32 + 8 * lm.quad - sparse_k(lm.quad));
-            Rh = sparse_piece(i32x2{v[0], v[1]}, i32x2{v[2], v[3]});
+            for (int kt = 0; kt < 2 * NF; ++kt) piece[kt] = sparse_piece(*(const i32x2*)(rrow + kt * 32), *(const i32x2*)(rrow + kt * 32 + 8));
+            if constexpr (KT & 1) {
+                const i32x4 v = *(const i32x4*)(rrow + 2 * NF * 32 + 8 * lm.quad - sparse_k(lm.quad));
+                Rh = sparse_piece(i32x2{v[0], v[1]}, i32x2{v[2], v[3]});
+            }
+        } else {   // the caller's R, zeros beyond the last gate (a padded copy of it was a launch of 5 us), one address at a time
+            const rsrc_t r_head = make_rsrc((const uint16_t*)p.R + (size_t)n * D * G * D);
+            const uint32_t r_row = (uint32_t)(w * 16 + lm.c) * G * D;
+            auto four = [&](uint32_t k) { return __builtin_amdgcn_raw_buffer_load_b64(r_head, k < (uint32_t)(G * D) ? (r_row + k) * 2 : 0x80000000u, 0, 0); };
+#pragma unroll
+            for (int kt = 0; kt < 2 * NF; ++kt) {
+                const uint32_t k = kt * 32 + sparse_k(lm.quad);
+                piece[kt] = sparse_piece(four(k), four(k + 8));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (KT & 1) Rh = sparse_piece(four(2 * NF * 32 + 8 * lm.quad), four(2 * NF * 32 + 8 * lm.quad + 4));
         }
 #pragma unroll
         for (int kc = 0; kc < NF; ++kc) Rf[kc] = sparse_dense(piece[2 * kc], piece[2 * kc + 1]);
@@ -1042,6 +1055,9 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             step(ph1{}, t - 1);
         }
     } else {
+        // (the loop's place in the code is worth 1 to 3 %.  At a multiple of 64 bytes, backward calls, us: LSTM 3 x 80 197.7 -> 195, 4 x 144 251 -> 248, 8 x 96 188 -> 185, sLSTM 4 x 176 265 -> 261;
+        // heads of 48 units, with fewer waves, lose: LSTM 12 x 48 182 -> 189)
+        if constexpr (MAXW >= 8) asm volatile(".p2align 6");
         for (int t = T; t >= 1; --t) step(ph0{}, t);
     }
     // ---- gradients w.r.t. the initial states
