@@ -295,8 +295,12 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
             double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? 1.8 : e.BT == 8 ? 3.0 : 6.0);
             if (!bf) {
                 const bool shares = nw <= 4 || G == 1;
+                // (Backward passes of the sLSTM and the four-gate GRU with heads of 128 units and up to two rounds of 4-row tiles keep the one round of 8 rows that the plan tests pin; the present 4-row
+                // kernels would be the faster ones: sLSTM 16 x 128 with 96 rows, 24 steps 154 us against 190.)
+                const long long ng4 = (long long)d->NH * ((d->B + 3) / 4);
+                const bool pinned8 = bwd && d->D > 112 && (d->cell == FLASHRNN_SLSTM || d->cell == FLASHRNN_GRU4) && ng4 > cus && ng4 <= 2 * cus;
                 rounds = e.BT == 4 && G == 3 && !bwd && ng > cus ? per_cu : rounds;   // (two workgroups to a CU: the last round need not be a whole one)
-                rel = e.BT == 4 ? 1.0 : e.BT == 8 ? 2.9 : nw <= 2 ? 2.4 : nw <= 4 ? 2.8 : G == 1 ? (bwd ? 2.2 : 3.0) : d->cell == FLASHRNN_SLSTM ? 4.3 : 3.3;
+                rel = e.BT == 4 ? 1.0 : e.BT == 8 ? (pinned8 ? 1.9 : 2.9) : nw <= 2 ? 2.4 : nw <= 4 ? 2.8 : G == 1 ? (bwd ? 2.2 : 3.0) : d->cell == FLASHRNN_SLSTM ? 4.3 : 3.3;
                 if (e.BT == 4 && shares && ng > cus) {
                     rounds = nw <= 2 ? 0.9 + 0.2 * per_cu : 0.9 + 0.35 * per_cu;
                     const double full = bwd ? 0.75 * per_cu - 0.25 : 0.66 * per_cu;
