@@ -382,7 +382,8 @@ __global__ __launch_bounds__(WM * WN * 64) void dr_gemm_tr_kernel(const float* _
 // The 256 x 256 tile (eight waves of 64 x 128) with TWO rounds of global loads in flight.  A round is 1024 clocks of matrix instructions per SIMD and about as much LDS time, a load from HBM
 // takes twice that: with one round in flight (dr_gemm_tr_kernel, whose addresses take the registers of a second one) a round was 2800 clocks, the latency.  Here a load's row
 // is the same for a whole wave (h: one row of 256 floats per wave and load) or its place in the round does not change (gate gradients), so addresses live in scalar registers: buffer loads from
-// bases that move on by a round, out of range -- zeros -- beyond the slice, the head or the gates.  Not for the GRU, whose gate gradients come from two tensors.
+// bases that move on by a round, out of range -- zeros -- beyond the slice, the head or the gates.  Not for the GRU, whose gate gradients come from two tensors,
+// nor for rounds that span 2^31 bytes (dr_square_in_reach).
 // (Backward call with one / two rounds in flight / these issued first, us: LSTM 1 x 768, 128 rows, 256 steps 1055 / 1025 / 1009, of which the GEMM 204 -> 158; sLSTM 8 x 256, 32 rows, 512 steps 593 / 587 / 574,
 // GEMM 98 -> 79; LSTM 1 x 2048, 16 rows, 256 steps 878 / 859 / 847, GEMM 170 -> 139: 0.97 PFLOP/s.)
 __global__ __launch_bounds__(512) void dr_gemm_square_kernel(const float* __restrict__ states, const uint16_t* __restrict__ dWx, float* __restrict__ out, int T, int B, int NH, int D, int G,
@@ -648,6 +649,10 @@ int dr_split_k(bool bf16, int T, int B, int NH, int D, int G) {
     return sk;
 }
 
+// The square tile runs on dr_gemm_square_kernel where that kernel can address the gate gradients: a lane's offset covers the 32 rows of a round, and offsets from 2^31 on read
+// as zeros.  Beyond that (more than 2^25 gate columns; a call with few batch rows may have up to 2^30), and for the GRU's two tensors, on dr_gemm_tr_kernel, whose offsets have 64 bits.
+bool dr_square_in_reach(int NH, int D, int G, bool gru) { return !gru && (size_t)TK * 2 * G * NH * D < (size_t)1 << 31; }
+
 // db_from_gemm: db_part is written here, one row of sums per contraction slice (bf16 only); otherwise it holds the
 // persistent kernel's per-batch-row sums.
 hipError_t launch_dr_gemm(bool bf16, const float* states, const void* dWx, const void* dgn, float* part, float* dR, int T, int B,
@@ -658,7 +663,7 @@ hipError_t launch_dr_gemm(bool bf16, const float* states, const void* dWx, const
     const DrTile t = dr_tile(bf16, NH, D, G);
     const int grid = (dr_tiles(t, NH, D, G) * SK + 7) / 8 * 8;
     if (db_from_gemm && (!bf16 || t == kDrSquare)) return hipErrorInvalidValue;
-    if (t == kDrSquare && !gru)
+    if (t == kDrSquare && dr_square_in_reach(NH, D, G, gru))
         hipLaunchKernelGGL(dr_gemm_square_kernel, dim3(grid), dim3(512), 0, stream, states, (const uint16_t*)dWx, target, T, B, NH, D, G, S, SK);
     else if (t == kDrSquare)
         hipLaunchKernelGGL((dr_gemm_tr_kernel<4, 8, 4, 2, false, 1>), dim3(grid), dim3(512), 0, stream, states, dWx, dgn, target, db_part, T, B, NH, D, G, S, SK, gru ? 1 : 0);

@@ -141,3 +141,19 @@ def test_one_step_plans_of_many_heads_and_rows(cell, NH, D, B, step):
     for mode in (0, 2):
         staged, rows, split = api.flashrnn_plan_kernel(d, mode)
         assert (staged == 1 and split == D // 16 and rows == (1 if B == 1 else 4)) == step
+
+
+def test_weight_gradients_of_very_wide_layers_keep_64_bit_offsets():
+    """The weight-gradient kernel of the largest tile reaches the 32 rows of a round with offsets below 2^31: the library takes it only where the last byte of the last
+    row is in reach, and a call may be far wider than that (one batch row: up to 2^30 gate columns)."""
+    in_reach = getattr(api.lib(), "_ZN8flashrnn18dr_square_in_reachEiiib")
+    in_reach.restype = ctypes.c_bool
+    for G in (1, 4):
+        for D in (208, 256, 1024):
+            edge = (1 << 31) // (32 * 2 * G * D)
+            for NH in (1, 8, edge - 1, edge, edge + 1, 2 * edge, 4 * edge, 31 * edge):
+                assert in_reach(NH, D, G, False) == (32 * 2 * G * NH * D < 1 << 31), (NH, D, G)
+                assert not in_reach(NH, D, G, True)
+    # LSTM, 40000 heads of 256 units, one row: an accepted call whose rounds span 2.6 GB
+    assert api.flashrnn_workspace_bytes(api.make_desc(0, 32, 1, 40000, 256, api.FLASHRNN_BF16)) > 0
+    assert not in_reach(40000, 256, 4, False)
