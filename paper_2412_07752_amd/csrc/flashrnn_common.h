@@ -169,11 +169,15 @@ __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_lo
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Point-wise math in two flavours: FAST (bf16 I/O: hardware exp2/log2/rcp, ~1e-6 relative) and accurate (f32 I/O, for 1e-5 agreement with the fp64 oracle).
-// The accurate one is branch-free and as exact as the library's functions (root mean square of the relative error over 4 M arguments within +-2, in units of 2^-24:
-// sigmoid 0.66, tanh 0.44, exp 0.44, log sigmoid 0.54, library 0.66, 0.44, 0.44, 0.52; within +-20 0.62, 0.23, 0.45, 0.50 and 0.61, 0.23, 0.44, 0.49) in half the instructions: they bound a
-// step of the float32 kernels, whose waves run alone on their SIMD (sigmoid 13 and 26 vector instructions, tanh 22 and 31, log sigmoid with its
-// complement 27 and more than 250; forward LSTM 1 x 64, 4 rows 0.90 -> 0.71 us a step, sLSTM 2 x 128, 16 rows 2.53 -> 1.85, GRU 4 x 96, 12 rows 1.23 -> 1.00).  e^x = 2^n 2^f: n the whole number nearest to x log2 e -- adding 1.5 * 2^23 leaves
-// it in the low bits of the sum -- and f what is left of the product, whose rounding the two-part constant takes out.  Clamps keep a NaN.
+// The accurate one is branch-free and no further from 64 bits than the library's functions.  Root mean square of the relative error over 4 M arguments within +-0.6 / +-2 / +-20, in units of 2^-24:
+//   sigmoid            0.48 / 0.48 / 0.47, library's exp in 1 / (1 + e^-x) 0.71 / 0.66 / 0.61;  17 vector instructions and 26
+//   sig(-x) beside log sigmoid  the same as sigmoid
+//   tanh               0.43 / 0.44 / 0.23, library 0.43 / 0.44 / 0.23;                              22 and 31
+// (They bound a step of the float32 kernels, whose waves run alone on their SIMD.  Forward, us a step with the library's functions / these: LSTM 1 x 64, 4 rows 0.90 / 0.73, GRU 4 x 96,
+// 12 rows 1.23 / 1.02.  A sigmoid with 1 + e^-x unbounded and rounded took 13 instructions, 0.71 and 1.00 us: three to four hundredths further off than this on either side of the
+// library's, and sig(-x) 0.63 / 0.66 / 0.70.)  Results saturate at exact zeros and ones, and go through the numbers below the smallest normal one on their way.
+// e^x = 2^n 2^f: n the whole number nearest to x log2 e -- adding 1.5 * 2^23 leaves it in the low bits of the sum -- and f what is left of the product, whose rounding the
+// two-part constant takes out (Cody and Waite's range reduction).  Clamps keep a NaN.
 constexpr float kLog2eHi = 1.44269502162933349609375f, kLog2eLo = 1.925963033500011e-8f;   // log2 e = Hi + Lo to 48 bits
 constexpr float kRoundInt = 12582912.0f;
 __device__ __forceinline__ float min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
@@ -184,24 +188,29 @@ template <int S> __device__ __forceinline__ float exp_parts(float x, float& z) {
     const float n = z - kRoundInt;
     return fast_exp2(fmaf(x, S * kLog2eLo, fmaf(x, S * kLog2eHi, -n)));
 }
-__device__ __forceinline__ float pow2_of(float z) { return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, z) << 23) + 0x3F800000u); }   // 2^n, |n| < 127
-__device__ __forceinline__ float accurate_rcp(float d) {   // finite d
-    const float r = fast_rcp(d);
-    return fmaf(fmaf(-d, r, 1.0f), r, r);
+__device__ __forceinline__ float pow2_of(float z) { return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, z) << 23) + 0x3F800000u); }   // 2^n, -127 < n < 128
+__device__ __forceinline__ float times_pow2(float p, float z) {   // p 2^n, any n: also below the smallest normal number, zero and infinity
+    return __builtin_amdgcn_ldexpf(p, __builtin_bit_cast(int, z) - __builtin_bit_cast(int, kRoundInt));
+}
+// num / (1 + u) for num = 1 or num = u, 0 <= u <= 1: what 1 + u loses to rounding is in the correction, whose difference num - q is exact
+__device__ __forceinline__ float over_one_plus(float num, float u) {
+#pragma clang fp contract(off)
+    const float r = fast_rcp(1.0f + u), q = num * r;
+    return fmaf(fmaf(-q, u, num - q), r, q);
 }
 template <bool FAST> __device__ __forceinline__ float sigm(float x) {
     if constexpr (FAST) {
         return fast_rcp(1.0f + fast_exp2(-kLog2e * x));
     } else {
         float z;
-        const float p = exp_parts<-1>(max_nan(min_nan(x, 87.0f), -88.0f), z);
-        return accurate_rcp(fmaf(p, pow2_of(z), 1.0f));
+        const float p = exp_parts<-1>(min_nan(fabsf(x), 110.0f), z), u = times_pow2(p, z);
+        return over_one_plus(x >= 0.0f ? 1.0f : u, u);
     }
 }
 template <bool FAST> __device__ __forceinline__ float tanh_(float x) {
     if constexpr (FAST) {
         return 1.0f - 2.0f * fast_rcp(1.0f + fast_exp2((2.0f * kLog2e) * x));
-    } else {   // 1 - 2 / (1 + e^2x), below 0.625 x + x^3 P(x^2) with P fitted to 4e-9 of tanh
+    } else {   // 1 - 2 / (1 + e^2x), below 0.625 x + x^3 P(x^2) (the two ranges of Moshier's Cephes library; P fitted here, to 4e-9 of tanh)
         const float ax = min_nan(fabsf(x), 20.0f);
         float z;
         const float e = exp_parts<2>(ax, z);
@@ -216,18 +225,17 @@ template <bool FAST> __device__ __forceinline__ float tanh_(float x) {
 template <bool FAST> __device__ __forceinline__ float exp_(float x) {
     if constexpr (FAST) {
         return fast_exp2(kLog2e * x);
-    } else {   // (ldexp: also results below the smallest normal number, and infinity)
+    } else {
         float z;
         const float p = exp_parts<1>(max_nan(min_nan(x, 90.0f), -110.0f), z);
-        return __builtin_amdgcn_ldexpf(p, __builtin_bit_cast(int, z) - __builtin_bit_cast(int, kRoundInt));
+        return times_pow2(p, z);
     }
 }
 // log sig(x) and sig(-x), accurate: with u = e^-|x|, log(1 + u) = u + u^2 P(u), P fitted to 8e-10 of it on [0, 1]
 __device__ __forceinline__ void accurate_log_sigm(float x, float& log_s, float& s_neg) {
     float z;
-    const float e = exp_parts<-1>(min_nan(fabsf(x), 87.0f), z), two_n = pow2_of(z), u = e * two_n, d = fmaf(e, two_n, 1.0f), r = fast_rcp(d);
-    const float num = x >= 0.0f ? u : 1.0f, q = num * r;
-    s_neg = fmaf(fmaf(-d, q, num), r, q);
+    const float e = exp_parts<-1>(min_nan(fabsf(x), 110.0f), z), u = times_pow2(e, z);
+    s_neg = over_one_plus(x >= 0.0f ? u : 1.0f, u);
     float p = fmaf(u, 0.002072942908853292f, -0.013631458394229412f);
     p = fmaf(u, p, 0.04198131337761879f);
     p = fmaf(u, p, -0.08307401090860367f);

@@ -107,3 +107,53 @@ def test_nan_and_infinities(cell):
         assert h[2] == 1.0 and h[5] == -1.0
     else:
         assert abs(h[5]) < 1e-30 and abs(h[2] * float(_sig(np.float64(0.5))) - base) < 1e-5 * abs(base)
+
+
+def _records(cell, Wx, states0):
+    """The values that one step saves for the backward pass [n, values]: every gate by itself, in float64."""
+    n, G = Wx.shape
+    B = n // 16
+    wx = torch.from_numpy(np.ascontiguousarray(Wx.reshape(B, 16, G).transpose(0, 2, 1))[None, :, :, None, :]).cuda()
+    s0 = torch.from_numpy(np.ascontiguousarray(states0.reshape(-1, B, 1, 16))).cuda()
+    R, b = torch.zeros((1, 16, G, 16), device="cuda"), torch.zeros((1, G, 16), device="cuda")
+    states, cache, _ = api.flashrnn_fwd(cell, wx.contiguous(), R, b, s0)
+    torch.cuda.synchronize()
+    return cache.view(torch.float32).reshape(n, -1).cpu().numpy().astype(np.float64), states[1].reshape(-1, n).cpu().numpy().astype(np.float64)
+
+
+def _off(got, ref):
+    """Root mean square of the relative error, in roundings."""
+    return np.sqrt(np.mean(((got - ref) / ref) ** 2)) / ULP
+
+
+@pytest.mark.parametrize("reach", [0.1, 0.6, 2.0, 5.0, 20.0, 80.0])
+def test_sigmoids_are_no_further_off_than_the_plain_formula(reach):
+    """1 / (1 + e^-x) with each of its three steps correctly rounded; two hundredths for the sample."""
+    x = np.random.default_rng(3).uniform(-reach, reach, 1 << 16).astype(np.float32)
+    ones = np.ones((4, x.size), np.float32)
+    lstm, _ = _records(api.FLASHRNN_LSTM, np.stack([x] * 4, axis=1), ones[:2])
+    slstm, _ = _records(api.FLASHRNN_SLSTM, np.stack([np.zeros_like(x), -x, x, x], axis=1), ones)
+    ref = _sig(x.astype(np.float64))
+    plain = (np.float32(1) / (np.float32(1) + np.exp(-x.astype(np.float64)).astype(np.float32))).astype(np.float64)
+    for got in (lstm[:, 0], lstm[:, 1], lstm[:, 3], slstm[:, 3], slstm[:, 4]):   # (the sLSTM's last: sig(-f), f = -x)
+        assert _off(got, ref) <= 1.02 * _off(plain, ref)
+
+
+def test_saturated_gates_are_zero_or_one():
+    """Beyond the reach of float32 a gate is exactly open or shut, as in 1 / (1 + e^-x), and what is masked by an infinite pre-activation is gone."""
+    far = np.float32([105.0, 110.0, 111.0, 200.0, 1e4, 1e30, 3e38, np.inf] * 2)
+    ones = np.ones((4, far.size), np.float32)
+    for x, want in ((far, 1.0), (-far, 0.0)):
+        lstm, _ = _records(api.FLASHRNN_LSTM, np.stack([x] * 4, axis=1), ones[:2])
+        assert (lstm[:, [0, 1, 3]] == want).all()
+        gru, _ = _records(api.FLASHRNN_GRU, np.stack([x] * 3, axis=1), ones[:1])
+        assert (gru[:, :2] == want).all()
+    zeros = np.zeros_like(far)
+    slstm, states = _records(api.FLASHRNN_SLSTM, np.stack([zeros - 5, far, zeros, far], axis=1), np.stack([zeros, zeros + 1, zeros + 1, zeros]))
+    assert (slstm[:, 3] == 1).all() and (slstm[:, 4] == 0).all()   # output gate; what the forget gate still lacks
+    assert (states[3] == 0).all()                                  # m = log sig(f) + m0
+    # below the smallest normal number: what is left of it, to half a unit of the last place there is
+    x = np.linspace(-103.0, -86.0, 1024).astype(np.float32)
+    lstm, _ = _records(api.FLASHRNN_LSTM, np.stack([x] * 4, axis=1), np.ones((2, x.size), np.float32))
+    ref = _sig(x.astype(np.float64))
+    assert np.all(np.abs(lstm[:, 3] - ref) <= 3 * ULP * ref + 1.5 * 2.0 ** -149)
