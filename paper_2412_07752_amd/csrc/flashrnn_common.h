@@ -172,6 +172,8 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 // The accurate one is branch-free and no further from 64 bits than the library's functions.  Root mean square of the relative error over 4 M arguments within +-0.6 / +-2 / +-20, in units of 2^-24:
 //   sigmoid            0.48 / 0.48 / 0.47, library's exp in 1 / (1 + e^-x) 0.71 / 0.66 / 0.61;  17 vector instructions and 26
 //   sig(-x) beside log sigmoid  the same as sigmoid
+//   exp                0.44 / 0.44 / 0.44, library 0.44 / 0.44 / 0.44
+//   log sigmoid        0.50 / 0.51 / 0.49, library's exp and log1p 0.56 / 0.52 / 0.49;              50 with sig(-x), and more than 280
 //   tanh               0.43 / 0.44 / 0.23, library 0.43 / 0.44 / 0.23;                              22 and 31
 // (They bound a step of the float32 kernels, whose waves run alone on their SIMD.  Forward, us a step with the library's functions / these: LSTM 1 x 64, 4 rows 0.90 / 0.73, GRU 4 x 96,
 // 12 rows 1.23 / 1.02.  A sigmoid with 1 + e^-x unbounded and rounded took 13 instructions, 0.71 and 1.00 us: three to four hundredths further off than this on either side of the
@@ -182,11 +184,19 @@ constexpr float kLog2eHi = 1.44269502162933349609375f, kLog2eLo = 1.925963033500
 constexpr float kRoundInt = 12582912.0f;
 __device__ __forceinline__ float min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 __device__ __forceinline__ float max_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-// e^(S x) = 2^f 2^n: returns 2^f, leaves n in the low bits of z
-template <int S> __device__ __forceinline__ float exp_parts(float x, float& z) {
-    z = fmaf(x, S * kLog2eHi, kRoundInt);
-    const float n = z - kRoundInt;
-    return fast_exp2(fmaf(x, S * kLog2eLo, fmaf(x, S * kLog2eHi, -n)));
+// e^(S x) = 2^f 2^n: returns 2^f, leaves n in the low bits of z.  EXACT: f with one rounding instead of two (three instructions more)
+template <int S, bool EXACT = false> __device__ __forceinline__ float exp_parts(float x, float& z) {
+#pragma clang fp contract(off)
+    if constexpr (EXACT) {
+        const float y = x * (S * kLog2eHi);
+        z = y + kRoundInt;
+        const float n = z - kRoundInt;
+        return fast_exp2((y - n) + fmaf(x, S * kLog2eLo, fmaf(x, S * kLog2eHi, -y)));
+    } else {
+        z = fmaf(x, S * kLog2eHi, kRoundInt);
+        const float n = z - kRoundInt;
+        return fast_exp2(fmaf(x, S * kLog2eLo, fmaf(x, S * kLog2eHi, -n)));
+    }
 }
 __device__ __forceinline__ float pow2_of(float z) { return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, z) << 23) + 0x3F800000u); }   // 2^n, -127 < n < 128
 __device__ __forceinline__ float times_pow2(float p, float z) {   // p 2^n, any n: also below the smallest normal number, zero and infinity
@@ -227,25 +237,31 @@ template <bool FAST> __device__ __forceinline__ float exp_(float x) {
         return fast_exp2(kLog2e * x);
     } else {
         float z;
-        const float p = exp_parts<1>(max_nan(min_nan(x, 90.0f), -110.0f), z);
+        const float p = exp_parts<1, true>(max_nan(min_nan(x, 90.0f), -110.0f), z);
         return times_pow2(p, z);
     }
 }
-// log sig(x) and sig(-x), accurate: with u = e^-|x|, log(1 + u) = u + u^2 P(u), P fitted to 8e-10 of it on [0, 1]
+// log sig(x) and sig(-x), accurate.  With u = e^-|x|: log sig(x) = min(x, 0) - k - log(1 + v), where v = u and k = 0 up to u = 1/2, and above it v = (u - 1) / 2, which is
+// exact, and k = log 2; log(1 + v) = v + v^2 P(v), P fitted to 3e-9 of the result.  t + et = min(x, 0) - k and hi + lo = v + v^2 P(v) without their last roundings (Dekker)
+// (|k| is the larger, or zero; hi is within a factor of two of v), and so is the sum of the four.
 __device__ __forceinline__ void accurate_log_sigm(float x, float& log_s, float& s_neg) {
+#pragma clang fp contract(off)
     float z;
-    const float e = exp_parts<-1>(min_nan(fabsf(x), 110.0f), z), u = times_pow2(e, z);
+    const float e = exp_parts<-1, true>(min_nan(fabsf(x), 110.0f), z), u = times_pow2(e, z);
     s_neg = over_one_plus(x >= 0.0f ? u : 1.0f, u);
-    float p = fmaf(u, 0.002072942908853292f, -0.013631458394229412f);
-    p = fmaf(u, p, 0.04198131337761879f);
-    p = fmaf(u, p, -0.08307401090860367f);
-    p = fmaf(u, p, 0.12467118352651596f);
-    p = fmaf(u, p, -0.16129334270954132f);
-    p = fmaf(u, p, 0.19897931814193726f);
-    p = fmaf(u, p, -0.24988578259944916f);
-    p = fmaf(u, p, 0.33332690596580505f);
-    p = fmaf(u, p, -0.49999988079071045f);
-    log_s = min_nan(x, 0.0f) - fmaf(u * u, p, u);
+    const bool upper = u > 0.5f;
+    const float v = upper ? fmaf(u, 0.5f, -0.5f) : u, k = upper ? 0.693147182464599609375f : 0.0f, s = v * v;
+    float p = fmaf(v, -0.04145870357751846f, 0.10075175762176514f);
+    p = fmaf(v, p, -0.13104549050331116f);
+    p = fmaf(v, p, 0.145358145236969f);
+    p = fmaf(v, p, -0.16662335395812988f);
+    p = fmaf(v, p, 0.19988174736499786f);
+    p = fmaf(v, p, -0.2499927580356598f);
+    p = fmaf(v, p, 0.33333489298820496f);
+    p = fmaf(v, p, -0.5000001192092896f);
+    const float hi = fmaf(s, p, v), lo = fmaf(s, p, v - hi), m = min_nan(x, 0.0f), t = m - k, et = m - (t + k);
+    const float r = t - hi, er = (t - r) - hi;
+    log_s = x < -40.0f ? x : r + (er + (et - lo));   // (also minus infinity)
 }
 
 // DPP row shift right by N lanes inside each row of 16 lanes, written only to the lanes of the

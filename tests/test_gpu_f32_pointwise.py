@@ -157,3 +157,28 @@ def test_saturated_gates_are_zero_or_one():
     lstm, _ = _records(api.FLASHRNN_LSTM, np.stack([x] * 4, axis=1), np.ones((2, x.size), np.float32))
     ref = _sig(x.astype(np.float64))
     assert np.all(np.abs(lstm[:, 3] - ref) <= 3 * ULP * ref + 1.5 * 2.0 ** -149)
+
+
+@pytest.mark.parametrize("reach", [0.1, 0.6, 2.0, 5.0, 20.0, 80.0])
+def test_log_sigmoids_and_exponentials_are_no_further_off_than_the_plain_formulas(reach):
+    """min(x, 0) - log(1 + e^-|x|) and e^x with each step correctly rounded, but for the exponential: on the hardware's 2^f the library's comes to 1.02 to 1.04 times the error
+    of correct rounding (two roundings of the exponent's fraction instead of one: 1.06), which log sig(x) -> -e^-x takes over; half a hundredth for the sample."""
+    x = np.random.default_rng(4).uniform(-reach, reach, 1 << 16).astype(np.float32)
+    zeros = np.zeros_like(x)
+    # m = max(log sig(f) + m0, i) with m0 = 0 and i far below
+    _, states = _records(api.FLASHRNN_SLSTM, np.stack([zeros - 1000, x, zeros, zeros], axis=1), np.stack([zeros, zeros, zeros + 1, zeros]))
+    xd = x.astype(np.float64)
+    ref = np.minimum(xd, 0) - np.log1p(np.exp(-np.abs(xd)))
+    log1p = np.log1p(np.exp(-np.abs(xd)).astype(np.float32).astype(np.float64)).astype(np.float32)
+    plain = (np.minimum(x, np.float32(0)) - log1p).astype(np.float64)
+    assert _off(states[3], ref) <= 1.045 * _off(plain, ref)
+    # weights e^(a - m), e^(i - m): f = 1000 (log sig = 0), m0 = 0 and i = +-x
+    for sign in (1, -1):
+        i = sign * x
+        rec, _ = _records(api.FLASHRNN_SLSTM, np.stack([i, zeros + 1000, zeros, zeros], axis=1), np.stack([zeros, zeros, zeros + 1, zeros]))
+        m = np.maximum(i, 0).astype(np.float64)
+        for got, arg in ((rec[:, 0], i - m), (rec[:, 1], -m)):
+            some = arg != 0
+            assert (got[~some] == 1).all()
+            e = np.exp(arg[some])
+            assert _off(got[some], e) <= 1.045 * _off(e.astype(np.float32).astype(np.float64), e)
