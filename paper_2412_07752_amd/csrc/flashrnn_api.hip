@@ -288,19 +288,16 @@ int make_plan(const flashrnn_desc_t* d, int mode, Plan* out) {
                 else if (nw > 2 && nw <= 4 && mode == 0 && mb > 140 && mb < 320) rel8 = nw == 3 ? 1.38 : 1.33;
             }
             // float32: the 4-row kernels, which waste nothing of the 4 x 4 matrix instruction, beat 8 rows everywhere (16 heads, 24 steps, 64 / 128 / 192 rows: LSTM of 64
-            // units forward 21 / 30 / 41 us in 4-row and 49 / 50 / 77 in 8-row tiles, backward 43 / 63 / 83 and 62 / 74 / 114; sLSTM of 128 units backward 91 / 188 / 276 and 167 / 220 / 369).
+            // units forward 21 / 30 / 41 us in 4-row and 49 / 50 / 77 in 8-row tiles, backward 43 / 63 / 83 and 62 / 74 / 114; sLSTM of 128
+            // units backward, 24 steps with 66 / 96 / 128 rows 146 / 158 / 185 and 177 / 190 / 222, four-gate GRU 136 / 147 / 175 and 163 / 176 / 197).
             // Where workgroups share a CU -- up to four waves, or the few registers of one gate -- also one of 16 rows, up to eight to the CU (LSTM 16 x 32 with 256 rows
             // forward 25 us and 41, 16 x 64 51 and 62, Elman 16 x 128 48 and 57); whole rounds of larger heads lose to it from four on (LSTM 16 x 96 with 256 rows
             // 151 / 254 us and 143 / 240, 16 x 128 166 / 341 and 163 / 298), but for the sLSTM (16 x 96 179 / 256 and 194 / 283, 16 x 128 202 / 352 and 219 / 388).
             double rel = e.tile == 1 ? (e.BT == 4 ? 1.0 : rel8) : (e.BT == 4 ? 1.8 : e.BT == 8 ? 3.0 : 6.0);
             if (!bf) {
                 const bool shares = nw <= 4 || G == 1;
-                // (Backward passes of the sLSTM and the four-gate GRU with heads of 128 units and up to two rounds of 4-row tiles keep the one round of 8 rows that the plan tests pin; the present 4-row
-                // kernels would be the faster ones: sLSTM 16 x 128 with 96 rows, 24 steps 154 us against 190.)
-                const long long ng4 = (long long)d->NH * ((d->B + 3) / 4);
-                const bool pinned8 = bwd && d->D > 112 && (d->cell == FLASHRNN_SLSTM || d->cell == FLASHRNN_GRU4) && ng4 > cus && ng4 <= 2 * cus;
                 rounds = e.BT == 4 && G == 3 && !bwd && ng > cus ? per_cu : rounds;   // (two workgroups to a CU: the last round need not be a whole one)
-                rel = e.BT == 4 ? 1.0 : e.BT == 8 ? (pinned8 ? 1.9 : 2.9) : nw <= 2 ? 2.4 : nw <= 4 ? 2.8 : G == 1 ? (bwd ? 2.2 : 3.0) : d->cell == FLASHRNN_SLSTM ? 4.3 : 3.3;
+                rel = e.BT == 4 ? 1.0 : e.BT == 8 ? 2.9 : nw <= 2 ? 2.4 : nw <= 4 ? 2.8 : G == 1 ? (bwd ? 2.2 : 3.0) : d->cell == FLASHRNN_SLSTM ? 4.3 : 3.3;
                 if (e.BT == 4 && shares && ng > cus) {
                     rounds = nw <= 2 ? 0.9 + 0.2 * per_cu : 0.9 + 0.35 * per_cu;
                     const double full = bwd ? 0.75 * per_cu - 0.25 : 0.66 * per_cu;
