@@ -142,8 +142,9 @@ int flashrnn_bwd(const flashrnn_desc_t* desc, const void* R, const void* b, cons
  * persistent backward kernel runs window by window from the last step to the first.  Same outputs as flashrnn_bwd
  * within rounding (the saved values are rounded to the I/O dtype either way).
  *   Wx          [T,B,G,NH,D] io_dtype  the forward call's inputs
- *   workspace   flashrnn_recompute_workspace_bytes() bytes: the ordinary workspace, the records of one window (of
- *               equal windows of at most 80 MiB) and two buffers for the state gradients carried between windows
+ *   workspace   flashrnn_recompute_workspace_bytes() bytes: the ordinary workspace, the records of one window
+ *               (windows of nearly equal length, at most 80 MiB or one step of records each) and two buffers for the
+ *               state gradients carried between windows
  *   all other arguments as in flashrnn_bwd
  */
 size_t flashrnn_recompute_workspace_bytes(const flashrnn_desc_t* desc);

@@ -699,16 +699,17 @@ int fwd_impl(const flashrnn_desc_t* d, const void* Wx, const void* R, const void
 }
 
 // Workspace of flashrnn_bwd_recompute behind the ordinary one: the records of one window of time steps and two buffers
-// for the state gradients carried from window to window.  Windows of equal length, at most 80 MiB of records each (at least one step):
-// small enough to stay in the last-level cache between the kernel that writes them and the one that reads them.  (Every window costs three launches and the
-// backward kernel's prologue, 20 us at 3 x 256: sLSTM 3 x 256, 16 rows, 1024 steps in windows of 341 steps had a fourth one of a single step.)
+// for the state gradients carried from window to window.  Windows as equal as whole steps allow, at most 80 MiB of records each (but at least one step): small enough to stay
+// in the last-level cache between the kernel that writes them and the one that reads them.  Every window costs three launches and the backward kernel's prologue, 20 us at
+// 3 x 256.  Backward with recompute within 64 / 80 / 128 MiB, us: sLSTM 3 x 256, 16 rows, 1024 steps 1115 / 1093 / 1082; LSTM 12 x 64, 64 rows, 1024 steps 862 / 824 / 818; float32 LSTM 4 x 96,
+// 64 rows, 512 steps 1015 / 1029 / 991; sLSTM 8 x 256, 32 rows, 512 steps 1223 / 1225 / 1142 (and 48 MiB 1297).
 struct RecomputeLayout { size_t window_off, carry_off, total; int window; };
 RecomputeLayout recompute_layout(const flashrnn_desc_t* d, size_t base_total) {
     RecomputeLayout rl;
     const size_t units = (size_t)d->B * d->NH * d->D;
     const size_t rec_step = units * record_slots(d->cell) * io_size(d->io_dtype);
-    const size_t whole = rec_step * (size_t)(d->T > 0 ? d->T : 1), limit = (size_t)80 << 20;
-    const long long windows = (long long)((whole + limit - 1) / limit);
+    const long long most = (long long)(((size_t)80 << 20) / rec_step), fits = most > 0 ? most : 1;   // steps
+    const long long windows = (d->T + fits - 1) / fits;
     long long steps = windows > 0 ? (d->T + windows - 1) / windows : 1;
     const int forced = env_int("FLASHRNN_RECOMPUTE_STEPS", 0);   // (test hook: windows of this many steps)
     if (forced > 0) steps = forced;

@@ -175,9 +175,9 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 //   exp                0.44 / 0.44 / 0.44, library 0.44 / 0.44 / 0.44
 //   log sigmoid        0.50 / 0.51 / 0.49, library's exp and log1p 0.56 / 0.52 / 0.49;              50 with sig(-x), and more than 280
 //   tanh               0.43 / 0.44 / 0.23, library 0.43 / 0.44 / 0.23;                              22 and 31
-// (They bound a step of the float32 kernels, whose waves run alone on their SIMD.  Forward, us a step with the library's functions / these: LSTM 1 x 64, 4 rows 0.90 / 0.73, GRU 4 x 96,
-// 12 rows 1.23 / 1.02.  A sigmoid with 1 + e^-x unbounded and rounded took 13 instructions, 0.71 and 1.00 us: three to four hundredths further off than this on either side of the
-// library's, and sig(-x) 0.63 / 0.66 / 0.70.)  Results saturate at exact zeros and ones, and go through the numbers below the smallest normal one on their way.
+// They bound a step of the float32 kernels, whose waves run alone on their SIMD.  (Forward, us a step with the library's functions / these: LSTM 1 x 64, 4 rows 0.90 / 0.73, GRU 4 x 96,
+// 12 rows 1.23 / 1.03.  With 1 + e^-x unbounded and rounded, 13 instructions a sigmoid, 0.71 and 1.00, and sLSTM 1 x 192, 7 rows 1.80 where these take 1.89; but sigmoid and exp were up to 1 % further
+// off than the library's, log sigmoid up to 13 %, sig(-x) up to 14 %.)  Results saturate at exact zeros and ones, and go through the numbers below the smallest normal one on their way there.
 // e^x = 2^n 2^f: n the whole number nearest to x log2 e -- adding 1.5 * 2^23 leaves it in the low bits of the sum -- and f what is left of the product, whose rounding the
 // two-part constant takes out (Cody and Waite's range reduction).  Clamps keep a NaN.
 constexpr float kLog2eHi = 1.44269502162933349609375f, kLog2eLo = 1.925963033500011e-8f;   // log2 e = Hi + Lo to 48 bits

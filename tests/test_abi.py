@@ -159,3 +159,18 @@ def test_weight_gradients_of_very_wide_layers_keep_64_bit_offsets():
     # LSTM, 40000 heads of 256 units, one row: an accepted call whose rounds span 2.6 GB
     assert api.flashrnn_workspace_bytes(api.make_desc(0, 32, 1, 40000, 256, api.FLASHRNN_BF16)) > 0
     assert not in_reach(40000, 256, 4, False)
+
+
+@pytest.mark.parametrize("cell,T,B,NH,D,dtype", [(2, 40, 192, 8, 256, api.FLASHRNN_BF16), (2, 1024, 16, 3, 256, api.FLASHRNN_BF16), (0, 333, 11, 3, 80, api.FLASHRNN_BF16), (1, 1000, 64, 8, 128, api.FLASHRNN_BF16),
+                                                 (4, 77, 200, 16, 112, api.FLASHRNN_F32), (3, 2048, 128, 16, 128, api.FLASHRNN_BF16), (2, 7, 1000, 8, 1024, api.FLASHRNN_BF16), (0, 1, 3, 1, 16, api.FLASHRNN_F32),
+                                                 (2, 0, 16, 4, 192, api.FLASHRNN_BF16)])
+def test_windows_of_the_recomputing_backward_pass_stay_within_their_limit(cell, T, B, NH, D, dtype):
+    """The records of a window take 80 MiB at most, or one step's where that is more; and no more windows than that takes."""
+    d = api.make_desc(cell, T, B, NH, D, dtype)
+    up = lambda n: (n + 255) // 256 * 256
+    slots = {0: 4, 1: 4, 2: 8, 3: 1, 4: 4}[cell]
+    step = B * NH * D * slots * (4 if dtype == api.FLASHRNN_F32 else 2)
+    records = api.lib().flashrnn_recompute_workspace_bytes(ctypes.byref(d)) - api.flashrnn_workspace_bytes(d) - 2 * up(api.flashrnn_num_states(cell) * B * NH * D * 4)
+    assert records <= up(max(80 << 20, step))
+    windows = max(1, -(-T // max(1, (80 << 20) // step)))
+    assert records == up(max(1, -(-T // windows)) * step)
