@@ -7,6 +7,7 @@ library next to the Python binding.
 import os
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -75,9 +76,12 @@ def build(force=False, jobs=None, trace=False):
         for log in ex.map(lambda so: _compile(*so, extra=flags_extra), todo):
             if log.strip():
                 print(log)
-        binding.result()
-    if todo or not os.path.exists(out):
+    if todo or not os.path.exists(out) or os.path.getmtime(out) < max(map(os.path.getmtime, objs)):
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out])
+    try:   # (the library is whole without it: a machine that has hipcc alone builds and uses the C ABI)
+        binding.result()
+    except Exception as e:
+        warnings.warn(f"the native part of the Python binding was not built, forward calls take a few microseconds more through ctypes: {e}", RuntimeWarning)
     return out
 
 
