@@ -8,8 +8,11 @@ been built (python -m paper_2412_07752_amd.build) every call raises.
 import ctypes
 import functools
 import os
+import warnings
 
 import torch
+
+from .build import binding_stamp
 
 FLASHRNN_LSTM, FLASHRNN_GRU, FLASHRNN_SLSTM, FLASHRNN_ELMAN, FLASHRNN_GRU4 = 0, 1, 2, 3, 4
 FLASHRNN_F32, FLASHRNN_BF16 = 0, 1
@@ -39,6 +42,21 @@ class FlashRNNError(RuntimeError):
 
 def library_path():
     return _LIB_PATH
+
+
+def _load_native():
+    """The native module, or None: every call then goes through ctypes."""
+    try:
+        from . import _flashrnn_binding as native
+    except ImportError as e:
+        why = str(e)
+    else:
+        built_for = getattr(native, "built_for", "an unknown torch")
+        if built_for == binding_stamp():
+            return native
+        why = f"built for {built_for}, running {binding_stamp()}"
+    warnings.warn(f"forward calls take a few microseconds more through ctypes, for want of the native binding ({why}): python -m paper_2412_07752_amd.build", RuntimeWarning, stacklevel=3)
+    return None
 
 
 def lib():
@@ -83,10 +101,7 @@ def lib():
         L.flashrnn_trace_phases.restype = ctypes.c_int
         L.flashrnn_status_string.argtypes = [ctypes.c_int]
         L.flashrnn_status_string.restype = ctypes.c_char_p
-        try:
-            from . import _flashrnn_binding as native
-        except ImportError:   # (built against another torch: every call goes through ctypes)
-            native = None
+        native = _load_native()
         if native is not None:
             native.bind(*(ctypes.cast(f, vp).value for f in (L.flashrnn_fwd, L.flashrnn_fwd_static_scratch, L.flashrnn_num_states, L.flashrnn_num_gates)))
         _lib, _native = L, native

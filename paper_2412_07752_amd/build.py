@@ -7,6 +7,7 @@ library next to the Python binding.
 import os
 import subprocess
 import sys
+import sysconfig
 import warnings
 from concurrent.futures import ThreadPoolExecutor
 
@@ -39,14 +40,27 @@ def _compile(src, obj, extra=()):
     return log
 
 
-def build_binding(force=False):
-    """_flashrnn_binding.so: the native part of api.py's forward calls (host code, against the installed torch)."""
-    import sysconfig
+def binding_stamp():
+    """What the native module reads objects and tensors through: the headers of one Python and one torch.  Compiled into it, and compared when it is loaded."""
     import torch
-    root, src, out = os.path.dirname(torch.__file__), os.path.join(CSRC, "flashrnn_binding.cpp"), os.path.join(HERE, "_flashrnn_binding.so")
+    return f"python {sys.version_info[0]}.{sys.version_info[1]}, torch {torch.__version__} {torch.version.git_version}"
+
+
+def build_binding(force=False):
+    """_flashrnn_binding<ABI tag>.so: the native part of api.py's forward calls (host code, against the running Python and its torch)."""
+    import torch
+    root, src, name = os.path.dirname(torch.__file__), os.path.join(CSRC, "flashrnn_binding.cpp"), "_flashrnn_binding"
+    out = os.path.join(HERE, name + sysconfig.get_config_var("EXT_SUFFIX"))
+    if os.path.exists(os.path.join(HERE, name + ".so")):   # (without a tag any Python would load it)
+        os.remove(os.path.join(HERE, name + ".so"))
     if not force and os.path.exists(out) and os.path.getmtime(out) >= max(os.path.getmtime(src), os.path.getmtime(os.path.join(INCLUDE, "flashrnn.h"))):
-        return out
+        with open(out, "rb") as f:
+            if binding_stamp().encode() + b"\0" in f.read():
+                return out
+    if os.path.exists(out):   # (nothing old stays where the new one does not compile)
+        os.remove(out)
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DFLASHRNN_BUILT_FOR="{binding_stamp()}"',
            "-I", INCLUDE, "-I", sysconfig.get_paths()["include"], "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), src, "-o", out, "-L", os.path.join(root, "lib"),
            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

@@ -89,4 +89,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_flashrnn_binding", nullptr, -1, m
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__flashrnn_binding() { return PyModule_Create(&module); }
+// built_for: the Python and the torch whose headers this was compiled with.  The loader binds no other: a layout may change while every symbol still resolves.
+PyMODINIT_FUNC PyInit__flashrnn_binding() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", FLASHRNN_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2412_07752_amd import api
+from paper_2412_07752_amd import api, build
 
 
 class _Library:
@@ -69,6 +69,32 @@ def _call(T=1, B=2, cell=None, dev="cpu", dtype=torch.bfloat16):
     r = lambda *s: torch.randn(s, generator=rng).to(dtype).to(dev)
     return dict(cell=cell, Wx=r(T, B, G, NH, D), R=r(NH, D, G, D), b=r(NH, G, D), states0=torch.randn((S, B, NH, D), generator=rng).to(dev),
                 save_for_backward=False, workspace=None, states=torch.zeros((T + 1, S, B, NH, D), device=dev), gate_cache=None)
+
+
+@pytest.mark.parametrize("built_for", [None, "python 3.10, torch 2.9.1 0000", ""])
+def test_a_native_module_of_another_torch_or_python_is_not_bound(built_for, monkeypatch):
+    """It would read tensors through a layout that need not be theirs; that it loads says nothing."""
+    import sys
+    import types
+    import paper_2412_07752_amd as package
+    module = types.ModuleType("paper_2412_07752_amd._flashrnn_binding")
+    if built_for is not None:
+        module.built_for = built_for
+    monkeypatch.setitem(sys.modules, module.__name__, module)
+    monkeypatch.setattr(package, "_flashrnn_binding", module, raising=False)
+    with pytest.warns(RuntimeWarning, match="built for"):
+        assert api._load_native() is None
+    module.built_for = build.binding_stamp()
+    assert api._load_native() is module
+
+
+def test_a_missing_native_module_is_told_of(monkeypatch):
+    import sys
+    import paper_2412_07752_amd as package
+    monkeypatch.setitem(sys.modules, "paper_2412_07752_amd._flashrnn_binding", None)
+    monkeypatch.delattr(package, "_flashrnn_binding", raising=False)
+    with pytest.warns(RuntimeWarning, match="native binding"):
+        assert api._load_native() is None
 
 
 def test_native_calls_hand_back_what_is_not_plain():

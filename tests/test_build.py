@@ -1,6 +1,7 @@
 """CPU-only checks of the build's bookkeeping: compilers are stand-ins that leave a file behind."""
 import os
 import subprocess
+import sysconfig
 
 import pytest
 
@@ -29,6 +30,36 @@ def tree(monkeypatch, tmp_path):
     monkeypatch.setattr(b, "_compile", compile)
     monkeypatch.setattr(subprocess, "check_call", link)
     return calls
+
+
+def test_the_binding_is_built_anew_for_another_torch(tree, monkeypatch, tmp_path):
+    """The file's time says nothing of the headers it was compiled with; what has no ABI tag, or cannot be built again, does not stay."""
+    import torch
+    made = []
+
+    def compiler(cmd, **kw):
+        made.append(cmd)
+        with open(cmd[cmd.index("-o") + 1], "w") as f:
+            f.write([a for a in cmd if a.startswith("-DFLASHRNN_BUILT_FOR=")][0].split('"')[1] + "\0")
+        return subprocess.CompletedProcess(cmd, 0, "")
+
+    monkeypatch.setattr(b, "HERE", str(tmp_path))
+    monkeypatch.setattr(subprocess, "run", compiler)
+    (tmp_path / "csrc" / "flashrnn_binding.cpp").write_text("")
+    (tmp_path / "_flashrnn_binding.so").write_text("")
+    out = b.build_binding()
+    assert os.path.basename(out) == "_flashrnn_binding" + sysconfig.get_config_var("EXT_SUFFIX") and not (tmp_path / "_flashrnn_binding.so").exists()
+    b.build_binding()
+    assert len(made) == 1
+    monkeypatch.setattr(torch, "__version__", "99.0")
+    b.build_binding()
+    b.build_binding()
+    assert len(made) == 2
+    monkeypatch.setattr(torch, "__version__", "99.1")
+    monkeypatch.setattr(subprocess, "run", lambda cmd, **kw: subprocess.CompletedProcess(cmd, 1, "no Python.h"))
+    with pytest.raises(RuntimeError, match="no Python.h"):
+        b.build_binding()
+    assert not os.path.exists(out)
 
 
 def test_the_library_is_built_without_the_python_binding(tree, monkeypatch):
