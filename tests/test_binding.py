@@ -97,16 +97,72 @@ def test_a_missing_native_module_is_told_of(monkeypatch):
         assert api._load_native() is None
 
 
-def test_native_calls_hand_back_what_is_not_plain():
-    """Nothing but device tensors proper is the native module's business; in particular it touches no host memory."""
+def test_native_calls_hand_back_host_tensors():
+    """Nothing but device tensors is the native module's business."""
     api.lib()
     if api._native is None:
         pytest.skip("the native module was built against another torch")
     a = _call()
     assert api._native.fwd(*a.values()) == 1
-    for name, value in (("cell", 0.0), ("cell", np.int64(0)), ("cell", -1), ("cell", 99), ("Wx", None), ("Wx", np.zeros(3)), ("save_for_backward", 1), ("states", None)):
-        assert api._native.fwd(*dict(a, **{name: value}).values()) == 1
+    assert api._native.fwd(*dict(a, states0=None).values()) == 1
     assert api._native.fwd(1, 2) == 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_native_calls_take_what_is_plain_and_hand_back_the_rest(dtype):
+    """Plain calls are made, not handed back; every single change to one is handed back (or, for a pointer that the library refuses, comes back as its status)."""
+    api.lib()
+    assert api._native is not None
+    desc = api.make_desc(api.FLASHRNN_LSTM, 3, 2, 1, 16, api.FLASHRNN_BF16 if dtype is torch.bfloat16 else api.FLASHRNN_F32)
+    ws, cache = api.alloc_workspace(desc, "cuda"), torch.zeros(api.flashrnn_gate_cache_bytes(desc), dtype=torch.uint8, device="cuda")
+    a = dict(_call(T=3, dev="cuda", dtype=dtype), workspace=ws)
+    native = lambda **change: api._native.fwd(*dict(a, **change).values())
+    for plain in ({}, {"workspace": None}, {"states0": None}, {"save_for_backward": True, "gate_cache": cache}, {"gate_cache": cache}, {"Wx": torch.nn.Parameter(a["Wx"])}):
+        assert native(**plain) == api.FLASHRNN_OK
+    strided = lambda t: t.transpose(0, -1).contiguous().transpose(0, -1)
+    other = torch.float32 if dtype is torch.bfloat16 else torch.bfloat16
+    changes = [("cell", c) for c in (0.0, np.int64(0), True, -1, 5, 99, 10 ** 30, api.FLASHRNN_GRU)]
+    changes += [("save_for_backward", v) for v in (1, None, np.bool_(False))] + [("states", None), ("Wx", None), ("R", None), ("b", None)]
+    changes += [("Wx", np.zeros(3)), ("Wx", a["Wx"][0]), ("Wx", a["Wx"][:, :, :3].contiguous()), ("Wx", a["Wx"][:2].contiguous())]
+    changes += [("R", a["R"][:, :, :, :8].contiguous()), ("b", a["b"][:, :2].contiguous()), ("states", a["states"][:3]), ("states0", a["states0"][:, :1].contiguous())]
+    for name in ("Wx", "R", "b", "states0", "states"):
+        changes += [(name, a[name].cpu()), (name, a[name].double())]
+        if name in ("Wx", "R", "b"):
+            changes.append((name, a[name].to(other)))
+    changes += [(name, strided(a[name])) for name in ("R", "states0", "states")] + [("Wx", a["Wx"].transpose(0, 1).contiguous().transpose(0, 1))]
+    changes += [("workspace", ws.cpu()), ("workspace", 0), ("states0", 0.0)]
+    for name, value in changes:
+        assert native(**{name: value}) == 1, (name, value)
+    assert native(save_for_backward=True) == 1 and native(save_for_backward=True, gate_cache=cache.cpu()) == 1
+    assert native(workspace=ws[1:]) == api.FLASHRNN_ERR_WORKSPACE
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_run_on_the_current_stream(native, static, monkeypatch):
+    """Inputs that another stream is still to write, behind a wait: a call made while that stream is the current one sees them."""
+    api.lib()
+    if not native:
+        monkeypatch.setattr(api, "_native", None)
+    desc = api.make_desc(api.FLASHRNN_LSTM, 3, 2, 1, 16, api.FLASHRNN_BF16)
+    a = _call(T=3, dev="cuda")
+    a.pop("workspace")
+    kw = {} if static else dict(workspace=api.alloc_workspace(desc, "cuda"))
+    fn = api.flashrnn_fwd_static_scratch if static else api.flashrnn_fwd
+    want = fn(**a, **kw)[0].clone()
+    late, stream = a["Wx"].clone(), torch.cuda.Stream()
+    a["Wx"].zero_()
+    a["states"].zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(20_000_000)   # (clocks: ten milliseconds)
+        a["Wx"].copy_(late)
+        fn(**a, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a["states"], want)
 
 
 @pytest.mark.gpu
