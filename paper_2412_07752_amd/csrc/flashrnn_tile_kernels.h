@@ -1055,8 +1055,9 @@ __global__ __launch_bounds__(MAXW * 64) void bwd_tile_kernel(const KernelParams 
             step(ph1{}, t - 1);
         }
     } else {
-        // (the loop's place in the code is worth 1 to 3 %.  At a multiple of 64 bytes, backward calls, us: LSTM 3 x 80 197.7 -> 195, 4 x 144 251 -> 248, 8 x 96 188 -> 185, sLSTM 4 x 176 265 -> 261;
-        // heads of 48 units, with fewer waves, lose: LSTM 12 x 48 182 -> 189)
+        // (The loop's place in the code is worth 1 to 3 %.  Backward calls without / at a multiple of 64 bytes, us, 256 steps: LSTM 3 x 80, 11 rows, 333 steps 197.1 / 194.5, 4 x 144, 16 rows 216.8 / 214.4, 8 x 96
+        // 162.3 / 160.7, sLSTM 4 x 176 229.9 / 226.0, 12 x 80, 30 rows 212.9 / 210.1, Elman 5 x 160, 20 rows 119.0 / 117.4; sLSTM 4 x 192, GRU 6 x 112 and 8 x 128 the same; sLSTM 8 x 112 162.5 / 163.9.
+        // Heads of 48 units, with fewer waves, lose: LSTM 12 x 48 182 / 189.)
         if constexpr (MAXW >= 8) asm volatile(".p2align 6");
         for (int t = T; t >= 1; --t) step(ph0{}, t);
     }
