@@ -385,7 +385,8 @@ __global__ __launch_bounds__(WM * WN * 64) void dr_gemm_tr_kernel(const float* _
 // bases that move on by a round, out of range -- zeros -- beyond the slice, the head or the gates.  Not for the GRU, whose gate gradients come from two tensors,
 // nor for rounds that span 2^31 bytes (dr_square_in_reach).
 // (Backward call with one / two rounds in flight / these issued first, us: LSTM 1 x 768, 128 rows, 256 steps 1055 / 1025 / 1009, of which the GEMM 204 -> 158; sLSTM 8 x 256, 32 rows, 512 steps 593 / 587 / 574,
-// GEMM 98 -> 79; LSTM 1 x 2048, 16 rows, 256 steps 878 / 859 / 847, GEMM 170 -> 139: 0.97 PFLOP/s.)
+// GEMM 98 -> 79; LSTM 1 x 2048, 16 rows, 256 steps 878 / 859 / 847, GEMM 170 -> 139 in repeated
+// backward calls; in whole training passes 158 us there, 328 at 8 x 256, 2048 steps, and 674 at 1 x 768, 128 rows, 1024 steps: 0.87, 0.84 and 0.92 PFLOP/s, the matrix pipe busy 38 to 40 %.)
 __global__ __launch_bounds__(512) void dr_gemm_square_kernel(const float* __restrict__ states, const uint16_t* __restrict__ dWx, float* __restrict__ out, int T, int B, int NH, int D, int G,
                                                              int S, int SK) {
     constexpr int FM = 4, FN = 8, WN = 2, TW = 256, PITCH = TW + 16, LA = 4, LB = 2;
